@@ -271,7 +271,7 @@ typedef struct vorta_attn_io {
 /* softmax(scale * Q K^T) V for every head in one call: route 0 over all N keys (Eq. 2),
  * route 1 over the key tiles of vorta_window_runs plus text keys (Algorithm 1), route 2
  * over the pooled core-set rows.  bf16: MFMA contractions, fp32 softmax statistics, P and
- * the output rounded to bf16.  fp32: fp32 throughout. */
+ * the output rounded to bf16.  fp32: fp64 between fp32 inputs and outputs, rounded once. */
 int vorta_attention_routed(vorta_plan* plan, const uint8_t* routes_host,
                            const vorta_attn_io* io, void* stream);
 
@@ -285,8 +285,9 @@ int vorta_scatter_back(vorta_plan* plan, const uint8_t* routes_host, const void*
 
 /* ---- the whole path ----------------------------------------------------------------------- */
 
-/* Bytes of device scratch the layer call needs for these routes (internal buffers above; with
- * bf16 the four tile-ordered buffers are empty because the layer call does not make them). */
+/* Bytes of device scratch the layer call needs for these routes (internal buffers above; the layer
+ * call makes no tile-ordered copies: those four buffers are empty with bf16, reserved but unused
+ * with fp32). */
 int vorta_workspace_bytes(const vorta_plan* plan, const uint8_t* routes_host, size_t* bytes);
 
 /* Byte offsets of the internal buffers inside the workspace, in the order

@@ -98,10 +98,11 @@ int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io,
   return VORTA_OK;
 }
 
-static int attention(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, void* stream) {
+// staged: the caller's own vorta_attention_routed call, where fp32 takes the tile-ordered copies only
+static int attention(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, void* stream, bool staged) {
   if (!io) return fail(VORTA_EINVAL, "io is null");
   const bool gather = rl.count[1] && !io->q_t && !io->k_t && !io->v_t && !io->o_t;   // window heads read q, k, v directly
-  if (gather && p->d.dtype != VORTA_BF16)
+  if (gather && staged && p->d.dtype != VORTA_BF16)
     return fail(VORTA_EINVAL, "the fp32 path needs the tile-ordered copies io.q_t, k_t, v_t, o_t");
   if (rl.count[0] || gather) {
     VORTA_TRY(check_ptr(io->q, "io.q")); VORTA_TRY(check_ptr(io->k, "io.k"));
@@ -150,10 +151,8 @@ static int layer(vorta_plan* p, const RouteLists& rl, const void* q, const void*
                  const uint8_t* routes, void* out, const Carved& c, void* stream) {
   int32_t* keep_idx = (int32_t*)c.buf[8];
   int32_t* assign = (int32_t*)c.buf[9];
-  // route 1: with bf16 the window kernel gathers token rows through the tile permutation and
-  // scatters its output rows the same way, so the reorder passes and the tile-ordered copies
-  // are only used by the fp32 path
-  const bool gather = p->d.dtype == VORTA_BF16;
+  // route 1: the attention kernels gather token rows through the tile permutation and scatter their
+  // output rows the same way, so the layer call makes no tile-ordered copies
   // routes 0 and 1 with a rotary embedding: attention reads rotated copies of Q and K
   const void *q_att = q, *k_att = k;
   if (p->rope && rl.count[0] + rl.count[1] > 0) {
@@ -162,20 +161,13 @@ static int layer(vorta_plan* p, const RouteLists& rl, const void* q, const void*
     q_att = c.buf[10];
     k_att = c.buf[11];
   }
-  if (!gather) {
-    VORTA_TRY(launch_reorder(p, rl, q_att, c.buf[0], true, stream));
-    VORTA_TRY(launch_reorder(p, rl, k_att, c.buf[1], true, stream));
-    VORTA_TRY(launch_reorder(p, rl, v, c.buf[2], true, stream));
-  }
   VORTA_TRY(select_and_pool(p, rl, q, k, v, keep_idx, assign, c, stream));
   vorta_attn_io io;
   io.q = q_att; io.k = k_att; io.v = v; io.out = out;
   io.q_t = io.k_t = io.v_t = nullptr;
   io.o_t = nullptr;
-  if (!gather) { io.q_t = c.buf[0]; io.k_t = c.buf[1]; io.v_t = c.buf[2]; io.o_t = c.buf[3]; }
   io.q_c = c.buf[4]; io.k_c = c.buf[5]; io.v_c = c.buf[6]; io.o_c = c.buf[7];
-  VORTA_TRY(attention(p, rl, &io, stream));
-  if (!gather) VORTA_TRY(launch_reorder(p, rl, out, c.buf[3], false, stream));
+  VORTA_TRY(attention(p, rl, &io, stream, false));
   VORTA_TRY(launch_unpool(p, rl, c.buf[7], assign, out, stream));
   (void)routes;
   return VORTA_OK;
@@ -264,7 +256,7 @@ int vorta_bcs_pool(vorta_plan* p, const void* src, const uint8_t* routes, const 
 int vorta_attention_routed(vorta_plan* p, const uint8_t* routes, const vorta_attn_io* io, void* stream) {
   RouteLists rl;
   VORTA_TRY(begin(p, routes, &rl));
-  return attention(p, rl, io, stream);
+  return attention(p, rl, io, stream, true);
 }
 
 int vorta_scatter_back(vorta_plan* p, const uint8_t* routes, const void* o_t, const void* o_c,

@@ -99,48 +99,6 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 #define MFMA(a_, b_, c_) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_, b_, c_, 0, 0, 0)
 
-// Run list of a work item.  It is the same for every lane and no kernel writes it, so it is
-// read as constant memory: with a wave-uniform index that is a scalar load, whose result lands
-// in a scalar register and whose wait does not include the vector loads in flight.
-typedef const __attribute__((address_space(4))) int* const_int_ptr;
-struct RunList {
-  const_int_ptr runs;      // (start, length) pairs; null: the single run {0, single_len}
-  int n_runs, single_len;
-  __device__ __forceinline__ explicit RunList(const WorkItem& w)
-      : runs((const_int_ptr)(uintptr_t)w.runs), n_runs(w.n_runs), single_len(w.single_len) {}
-  __device__ __forceinline__ int start(int r) const { return runs ? runs[2 * r] : 0; }
-  __device__ __forceinline__ int len(int r) const { return runs ? runs[2 * r + 1] : single_len; }
-};
-
-// Rows of keys j0 + step i (i < NR) of the bn-key block that begins pos keys into run r, whose
-// first row is s and whose length is len (r, pos, s, len wave-uniform; j0 per lane).  A block
-// that reaches past the end of run r continues in the following runs: they are walked with
-// uniform control flow, each lane keeping the row of the run its key falls in.  Keys past the
-// end of the last run repeat its last row (they are masked out of the softmax).
-template <int NR>
-__device__ __forceinline__ void block_rows(const RunList& rl, int r, int pos, int s, int len, int bn, int j0, int step,
-                                           int (&rows)[NR]) {
-  int k[NR];
-#pragma unroll
-  for (int i = 0; i < NR; ++i) {
-    k[i] = pos + j0 + step * i;
-    rows[i] = s + min(k[i], len - 1);
-  }
-  int end = pos + bn;
-  while (end > len && r + 1 < rl.n_runs) {
-    end -= len;
-#pragma unroll
-    for (int i = 0; i < NR; ++i) k[i] -= len;
-    ++r;
-    s = rl.start(r);
-    len = rl.len(r);
-#pragma unroll
-    for (int i = 0; i < NR; ++i)
-      if (k[i] >= 0) rows[i] = s + min(k[i], len - 1);
-  }
-}
-
-
 // Window segment over tile-ordered copies of Q, K, V (the staged call with q_t, k_t, v_t, o_t
 // given): a tile's key set is a short list of runs of consecutive rows.
 template <int NW>   // NW wavefronts per workgroup: 4 (two workgroups per CU)

@@ -5,117 +5,236 @@
 // output element) carry fp64 rounding only.  (An all-fp32 version of this kernel drifted past
 // 1e-5 from about three thousand keys on: sequential fp32 accumulation over the key stream.)
 //
-// A workgroup of four wavefronts owns 64 query rows; four neighbouring lanes share a row, lane
-// quarter c owning the 16-byte chunks e with e % 4 == c of the query row and of the output
-// accumulator (neighbouring chunks, so the four reads of a K or V row hit different LDS banks
-// while the 16 rows of a wavefront read the same addresses: LDS broadcasts).  Keys stream
-// through LDS 32 rows at a time; a score is the sum over the quad of four partial dot products.
-// Online softmax in fp64 with the running maximum.  Throughput is not a goal of this kernel;
-// the bf16 MFMA kernel is the fast path.
+// Both contractions run on v_mfma_f64_16x16x4_f64 and are computed transposed, as in the bf16
+// kernels:  S^T = K Q^T,  O^T += V^T P^T  -- lane (m = lane & 15, g = lane >> 4) owns query m.
+// The instruction's operands are one double per lane (row or column m, k index g) and its
+// accumulator register v holds row 4 v + g, so with key 4 v + g in register v the probabilities
+// are already the B operand of the second product's step v.  The k index of the first product and
+// the row index of the second one are permutations of the head dimension chosen so that K, V and
+// O move as 16-byte pieces: step (c, i) contracts dim 16 c + 4 g + i, and accumulator row m of
+// tile (h, i) is dim 64 h + 4 m + i.
+//
+// What bounds it: the fp64 matrix instruction (64 cycles, 77.9 TFLOP/s over the chip in a
+// register-only loop) shares its execution unit with the vector ALU -- in the same loop eight
+// fp32 fused multiply-adds behind each matrix instruction cost their full issue time, 32 cycles --
+// so whatever is not a matrix instruction is paid for.  Per 16 keys x 16 queries x 128 dims that is
+// 64 matrix instructions = 4,096 cycles and about 64 widenings of K and V, four exponentials and the
+// addresses.  Hence no LDS staging and no running maximum: a wavefront owns 16 query rows and reads
+// its K and V rows straight from L2 into operand registers (16 B/clk and CU, a quarter of what a CU's
+// cache port moves), K of the next block while the softmax and the second product run, V of this block
+// under the first product.  The row reference is a lagging maximum, raised only when a score exceeds it
+// by more than 2^512: fp64 has the range, and the accumulators are then touched by matrix
+// instructions only.
+//
+// Split: the NW wavefronts of a workgroup share 16 query rows and take every NW-th 16-key block;
+// their (reference, sum, accumulator) triples are merged through LDS at the end, in a fixed order.  A
+// full head of 3,072 tokens is then 192 items of 48 blocks per wavefront instead of one long
+// stream per 64 rows.
+//
+// Measured (attention launch and whole layer; the vector-ALU kernel before it in brackets): eight dense
+// heads of 3,072 tokens x 128 run at 57 TFLOP/s, 73 % of the matrix instruction's rate, without the
+// exponentials at 59; the 3,072-token layer with 2 full, 3 window and 3 core-set heads 484 us
+// [1,701 us], two heads of 256 tokens x 64 22 us [140 us, four of its launches reorder passes].
 #include <hip/hip_runtime.h>
 
 #include "vorta_attn_common.h"
 
 namespace vorta {
 
-template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const AttnArgs a) {
-  constexpr int BM = 64, BN = 32;
-  constexpr int CH = D / 16;                 // 16-byte chunks of a row per lane
-  __shared__ float sK[BN][D];
-  __shared__ float sV[BN][D];
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+#define MFMA64(a_, b_, c_) __builtin_amdgcn_mfma_f64_16x16x4f64(a_, b_, c_, 0, 0, 0)
+
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, 8 / NW) void attn_f32_kernel(const AttnArgs a) {
+  constexpr int BM = 16, KB = 16;            // query rows per item, keys per block
+  constexpr int NC = D / 16;                 // 16-byte pieces of a K row per lane
+  constexpr int NH = D / 64;                 // 16-byte pieces of a V row per lane and k step
+  constexpr int NT = 4 * NH;                 // accumulator tiles of O^T
+  constexpr double REF_SLACK = 512.0;        // log2 units a score may exceed the row reference by
+  __shared__ double s_ref[NW][BM], s_sum[NW][BM];
+  __shared__ f64x4 s_acc[NW / 2][NT][64];
   const WorkItem w = decode_item<BM, D>(a, blockIdx.x);
-  const float* Q = (const float*)(w.seg == 0 ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
-  const float* K = (const float*)(w.seg == 0 ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
-  const float* V = (const float*)(w.seg == 0 ? a.v0 : w.seg == 1 ? a.vc : a.vt) + w.kv_off;
-  float* O = (float*)(w.seg == 0 ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
   if (w.n_rows <= 0) return;       // q-block past the end of a clipped tile
-  const int t = threadIdx.x;
-  const int quarter = t & 3, r_local = t >> 2;
-  const long my_row = w.row(min(r_local, w.n_rows - 1));
+  // window heads without tile-ordered copies: rows of the caller's tensors through the tile permutation
+  const bool gather = w.seg == 2 && a.win_gather;
+  const float* Q = (const float*)(w.seg == 0 || gather ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
+  const float* K = (const float*)(w.seg == 0 || gather ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
+  const float* V = (const float*)(w.seg == 0 || gather ? a.v0 : w.seg == 1 ? a.vc : a.vt) + w.kv_off;
+  float* O = (float*)(w.seg == 0 || gather ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int m = lane & 15, g = lane >> 4;
 
-  float4 q[CH];
-  double o[CH][4];
-#pragma unroll
-  for (int i = 0; i < CH; ++i) {
-    q[i] = ((const float4*)(Q + my_row * w.row_stride))[4 * i + quarter];
-    o[i][0] = o[i][1] = o[i][2] = o[i][3] = 0.0;
+  // rows are addressed by their element offset: row times stride is below 2^31, checked on the host
+  auto row_off = [&](int row) { return (unsigned)row * (unsigned)w.row_stride; };
+  unsigned my_off;
+  {
+    int row = w.row(min(m, w.n_rows - 1));
+    if (gather) row = a.tok_of[row];
+    my_off = row_off(row);
   }
-  double m = -INFINITY, l = 0.0;
-  const double scale = (double)a.scale;
-
-  for (int r = 0; r < w.n_runs; ++r) {
-    const int start = w.runs ? w.runs[2 * r] : 0;
-    const int len = w.runs ? w.runs[2 * r + 1] : w.single_len;
-    for (int pos = 0; pos < len; pos += BN) {
-      const int n_valid = min(BN, len - pos);
-      __syncthreads();
-      for (int c = t; c < BN * D / 4; c += 256) {
-        const int j = c / (D / 4), e = c - j * (D / 4);
-        const long row = start + pos + min(j, n_valid - 1);   // rows past the run repeat its last row
-        ((float4*)&sK[j][0])[e] = ((const float4*)(K + row * w.row_stride))[e];
-        ((float4*)&sV[j][0])[e] = ((const float4*)(V + row * w.row_stride))[e];
-      }
-      __syncthreads();
-      double s[BN];
-      double mt = -INFINITY;
+  // scores come out in log2 units: scale and log2(e) go into Q (fp64: a rounding of 2^-53)
+  double q[4 * NC];
+  {
+    const double qs = (double)a.scale * 1.4426950408889634074;
+    const float* qp = Q + my_off + 4 * g;
 #pragma unroll
-      for (int j = 0; j < BN; ++j) {
-        double dot = 0.0;
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-          const float4 kk = ((const float4*)&sK[j][0])[4 * i + quarter];
-          dot = fma((double)q[i].x, (double)kk.x, dot);
-          dot = fma((double)q[i].y, (double)kk.y, dot);
-          dot = fma((double)q[i].z, (double)kk.z, dot);
-          dot = fma((double)q[i].w, (double)kk.w, dot);
-        }
-        dot += __shfl_xor(dot, 1, 64);
-        dot += __shfl_xor(dot, 2, 64);
-        s[j] = j < n_valid ? dot * scale : -INFINITY;
-        mt = fmax(mt, s[j]);
-      }
-      const double m_new = fmax(m, mt);
-      const double alpha = exp(m - m_new);   // 0 for the first block
-      l *= alpha;
-#pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        o[i][0] *= alpha; o[i][1] *= alpha; o[i][2] *= alpha; o[i][3] *= alpha;
-      }
-#pragma unroll
-      for (int j = 0; j < BN; ++j) {
-        const double pj = exp(s[j] - m_new);
-        l += pj;
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-          const float4 vv = ((const float4*)&sV[j][0])[4 * i + quarter];
-          o[i][0] = fma(pj, (double)vv.x, o[i][0]);
-          o[i][1] = fma(pj, (double)vv.y, o[i][1]);
-          o[i][2] = fma(pj, (double)vv.z, o[i][2]);
-          o[i][3] = fma(pj, (double)vv.w, o[i][3]);
-        }
-      }
-      m = m_new;
+    for (int c = 0; c < NC; ++c) {
+      const float4 x = *(const float4*)(qp + 16 * c);
+      q[4 * c] = (double)x.x * qs; q[4 * c + 1] = (double)x.y * qs;
+      q[4 * c + 2] = (double)x.z * qs; q[4 * c + 3] = (double)x.w * qs;
     }
   }
-  if (r_local < w.n_rows) {
-    const double inv = 1.0 / l;
-    float4* dst = (float4*)(O + my_row * w.row_stride);
+
+  const RunList rl(w);
+  int n_keys = 0;
+  for (int r = 0; r < w.n_runs; ++r) n_keys += rl.len(r);
+  // cursor of this wavefront's next block: run, keys into it, its first row and length
+  int fr = 0, fpos = 0, fstart = rl.start(0), flen = rl.len(0);
+  auto advance = [&](int keys) {
+    fpos += keys;
+    while (fpos >= flen && fr + 1 < w.n_runs) {
+      fpos -= flen;
+      ++fr;
+      fstart = rl.start(fr);
+      flen = rl.len(fr);
+    }
+  };
+  unsigned koff = 0;               // row offset of key m of the block
+  float4 kf[NC];
+  auto load_k = [&]() {            // rows of the block under the cursor, then on to this wavefront's next one
+    int rows[1];
+    block_rows<1>(rl, fr, fpos, fstart, flen, KB, m, 0, rows);
+    koff = row_off(gather ? a.tok_of[rows[0]] : rows[0]);
+    const float* kp = K + koff + 4 * g;
 #pragma unroll
-    for (int i = 0; i < CH; ++i)
-      dst[4 * i + quarter] = make_float4((float)(o[i][0] * inv), (float)(o[i][1] * inv), (float)(o[i][2] * inv),
-                                         (float)(o[i][3] * inv));
+    for (int c = 0; c < NC; ++c) kf[c] = *(const float4*)(kp + 16 * c);
+    advance(NW * KB);
+  };
+
+  f64x4 o[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) o[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+  double ref = -INFINITY, sum = 0.0;         // row reference of query m, this lane's share of the row sum
+
+  int left = n_keys - KB * wave;             // keys from this wavefront's next block on
+  advance(KB * wave);
+  if (left > 0) load_k();
+  for (; left > 0; left -= NW * KB) {
+    float4 vf[4][NH];                        // V rows of keys 4 v + g
+    unsigned voff[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) voff[v] = __shfl(koff, 4 * v + g, 64);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float* vp = V + voff[v] + 4 * m;
+#pragma unroll
+      for (int h = 0; h < NH; ++h) vf[v][h] = *(const float4*)(vp + 64 * h);
+    }
+    f64x4 s = {0.0, 0.0, 0.0, 0.0}, s2 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      s = MFMA64((double)kf[c].x, q[4 * c], s);
+      s2 = MFMA64((double)kf[c].y, q[4 * c + 1], s2);
+      s = MFMA64((double)kf[c].z, q[4 * c + 2], s);
+      s2 = MFMA64((double)kf[c].w, q[4 * c + 3], s2);
+    }
+    s += s2;
+    if (left < KB) {                         // last block: register v is key 4 v + g
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (4 * v + g >= left) s[v] = -INFINITY;
+    }
+    if (left > NW * KB) load_k();            // rows of the next block arrive under the softmax and the second product
+
+    double mx = fmax(fmax(s[0], s[1]), fmax(s[2], s[3]));
+    if (__any(mx - ref > REF_SLACK)) {       // always for the first block
+      mx = fmax(mx, __shfl_xor(mx, 16, 64));
+      mx = fmax(mx, __shfl_xor(mx, 32, 64));
+      const double ref_new = fmax(ref, mx);
+      const double alpha = ref == ref_new ? 1.0 : exp2(ref - ref_new);   // 0 for the first block
+      ref = ref_new;
+      sum *= alpha;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) o[t] *= alpha;
+    }
+    const double base = ref == -INFINITY ? 0.0 : ref;    // only scores of -inf so far: probabilities 0
+    f64x4 p;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      p[v] = exp2(s[v] - base);
+      sum += p[v];
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        o[4 * h] = MFMA64((double)vf[v][h].x, p[v], o[4 * h]);
+        o[4 * h + 1] = MFMA64((double)vf[v][h].y, p[v], o[4 * h + 1]);
+        o[4 * h + 2] = MFMA64((double)vf[v][h].z, p[v], o[4 * h + 2]);
+        o[4 * h + 3] = MFMA64((double)vf[v][h].w, p[v], o[4 * h + 3]);
+      }
+  }
+
+  // ---- merge of the NW shares of the key stream: common reference, then a tree of additions
+  sum += __shfl_xor(sum, 16, 64);
+  sum += __shfl_xor(sum, 32, 64);
+  if (g == 0) {
+    s_ref[wave][m] = ref;
+    s_sum[wave][m] = sum;
+  }
+  __syncthreads();
+  double top = -INFINITY, total = 0.0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) top = fmax(top, s_ref[i][m]);
+  auto weight = [&](double r) { return r == -INFINITY ? 0.0 : exp2(r - top); };
+#pragma unroll
+  for (int i = 0; i < NW; ++i) total += s_sum[i][m] * weight(s_ref[i][m]);
+  const double mine = weight(ref);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) o[t] *= mine;
+#pragma unroll
+  for (int half = NW / 2; half >= 1; half /= 2) {
+    if (wave >= half && wave < 2 * half) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) s_acc[wave - half][t][lane] = o[t];
+    }
+    __syncthreads();
+    if (wave < half) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) o[t] += s_acc[wave][t][lane];
+    }
+    if (half > 1) __syncthreads();
+  }
+  if (wave == 0 && m < w.n_rows) {
+    const double inv = 1.0 / total;
+    float* op = O + my_off + 4 * g;
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        *(float4*)(op + 64 * h + 16 * v) = make_float4((float)(o[4 * h][v] * inv), (float)(o[4 * h + 1][v] * inv),
+                                                       (float)(o[4 * h + 2][v] * inv), (float)(o[4 * h + 3][v] * inv));
   }
 }
 
 int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, void* stream) {
   AttnArgs a;
-  if (int rc = fill_attn_args(p, rl, io, 64, WIN_ALL, &a)) return rc;
+  if (int rc = fill_attn_args(p, rl, io, 16, WIN_ALL, &a)) return rc;
   if (a.end_tile == 0) return VORTA_OK;
-  if (p->d.head_dim == 64)
-    hipLaunchKernelGGL(attn_f32_kernel<64>, dim3(a.end_tile), dim3(256), 0, (hipStream_t)stream, a);
-  else
-    hipLaunchKernelGGL(attn_f32_kernel<128>, dim3(a.end_tile), dim3(256), 0, (hipStream_t)stream, a);
+  const dim3 grid(a.end_tile);
+  hipStream_t st = (hipStream_t)stream;
+  // NW = 4 lets two workgroups share a CU.  With no more items than CUs the second one is missing and
+  // eight wavefronts hide more of the latency, if the key stream is long enough to pay for
+  // the longer merge: one head of 2,048 / 3,072 keys 93 -> 88 / 140 -> 129 us, of 770 keys level,
+  // two of 256 keys 22.2 -> 23.3 us.  With more items than CUs NW = 8 costs 8 % (fp32 layer of 3,072 tokens).
+  const bool few = a.end_tile <= p->n_cus && a.N >= 1024;
+  if (p->d.head_dim == 64) {
+    if (few) hipLaunchKernelGGL((attn_f32_kernel<64, 8>), grid, dim3(512), 0, st, a);
+    else hipLaunchKernelGGL((attn_f32_kernel<64, 4>), grid, dim3(256), 0, st, a);
+  } else {
+    if (few) hipLaunchKernelGGL((attn_f32_kernel<128, 8>), grid, dim3(512), 0, st, a);
+    else hipLaunchKernelGGL((attn_f32_kernel<128, 4>), grid, dim3(256), 0, st, a);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(VORTA_EHIP, "launch of attn_f32_kernel: %s", hipGetErrorString(e));
   return VORTA_OK;

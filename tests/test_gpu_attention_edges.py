@@ -1,0 +1,71 @@
+"""Attention kernels at the sizes where their splits can go wrong: fewer keys than one block, fewer
+blocks than key groups, remainders of rows and keys, run lists that end inside a block, and scores
+that leave the range of the lagging row reference.  Against the fp64 oracle."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_18809_amd as vorta
+from oracle import vorta_oracle as vo
+from synth_inputs import LayerConfig, make_qkv
+from helpers import f64, spec_of
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+def layer_error(cfg, q, k, v, layout, bar):
+    """Runs the layer, holds every head to the oracle within bar(want)."""
+    plan = vorta.plan_for(cfg, layout=layout)
+    out = vorta.vorta_routed_attention_layer(plan, q, k, v, cfg.fixed_routes)
+    torch.cuda.synchronize()
+    hnd = (lambda t: t) if layout == 1 else (lambda t: t.transpose(0, 1))
+    spec = spec_of(cfg)
+    for h, r in enumerate(cfg.fixed_routes):
+        want = vo.head_attention(int(r), f64(hnd(q)[h]), f64(hnd(k)[h]), f64(hnd(v)[h]), spec, None)
+        err = np.abs(f64(hnd(out)[h]) - want)
+        say(f"{cfg.name} head {h} route {r}: max-abs {err.max():.3e}")
+        assert (err <= bar(want)).all(), f"head {h} route {r}: {err.max():.3e}"
+
+
+# fp64 inside, one rounding to fp32: half an ulp of the result, and as much again for the sums
+def fp32_bar(want):
+    return 2.0 ** -23 * np.maximum(1.0, np.abs(want))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("grid,tile,n_text,layout", [
+    ((1, 1, 1), (1, 1, 1), 0, 1),          # one key: three wavefronts without any
+    ((1, 3, 5), (1, 2, 3), 0, 0),          # 15 keys, tiles of 1 to 6 rows
+    ((2, 3, 3), (2, 3, 2), 15, 1),         # 33 keys: two blocks and one key
+    ((3, 7, 7), (2, 3, 5), 3, 0),          # runs that end inside a block
+    ((4, 14, 18), (3, 4, 7), 16, 1),       # 1,024 rows and fewer items than CUs: eight-wavefront workgroups
+    ((8, 16, 20), (3, 4, 7), 17, 1),       # 2,577 rows: more items than CUs
+])
+def test_fp32_attention_at_the_edges_of_its_split(grid, tile, n_text, layout, d):
+    cfg = LayerConfig(f"edge{grid}d{d}", grid, 3, d, "fp32", tile, (3, 1, 3), seed=5, n_text=n_text, fixed_routes=(0, 1, 2))
+    say(cfg.name)
+    q, k, v = make_qkv(cfg, DEV, layout)
+    layer_error(cfg, q, k, v, layout, fp32_bar)
+
+
+def test_fp32_row_reference_follows_scores_far_beyond_its_slack():
+    """Scores that rise by thousands of log2 units along the keys (and fall again): the row reference has
+    to be raised block after block, and shares of the key stream whose reference is far below the
+    largest have to vanish from the merge."""
+    cfg = LayerConfig("far_scores", (4, 6, 8), 3, 64, "fp32", (2, 3, 4), (3, 3, 3), seed=9, fixed_routes=(0, 1, 2))
+    say(cfg.name)
+    q, k, v = make_qkv(cfg, DEV)
+    n = cfg.n_tokens
+    ramp = torch.sin(torch.linspace(0.0, 9.0, n, device=DEV))[:, None] * 3000.0
+    u = torch.zeros(64, device=DEV)
+    u[3] = 1.0
+    k = (k + ramp * u).contiguous()
+    layer_error(cfg, q, k, v, 1, lambda want: 1e-5 * np.maximum(1.0, np.abs(want)))
