@@ -156,8 +156,7 @@ static int layer(vorta_plan* p, const RouteLists& rl, const void* q, const void*
   // routes 0 and 1 with a rotary embedding: attention reads rotated copies of Q and K
   const void *q_att = q, *k_att = k;
   if (p->rope && rl.count[0] + rl.count[1] > 0) {
-    VORTA_TRY(launch_rope_rows(p, rl, q, c.buf[10], stream));
-    VORTA_TRY(launch_rope_rows(p, rl, k, c.buf[11], stream));
+    VORTA_TRY(launch_rope_rows(p, rl, q, c.buf[10], k, c.buf[11], stream));
     q_att = c.buf[10];
     k_att = c.buf[11];
   }
@@ -238,7 +237,7 @@ int vorta_rope_apply(vorta_plan* p, const void* src, const uint8_t* routes, void
   if (!p->rope || rl.count[0] + rl.count[1] == 0) return VORTA_OK;
   VORTA_TRY(check_ptr(src, "src"));
   VORTA_TRY(check_ptr(dst, "dst"));
-  return launch_rope_rows(p, rl, src, dst, stream);
+  return launch_rope_rows(p, rl, src, dst, nullptr, nullptr, stream);
 }
 
 int vorta_bcs_pool(vorta_plan* p, const void* src, const uint8_t* routes, const int32_t* keep_idx,
@@ -327,8 +326,7 @@ int vorta_soft_mixture_layer(vorta_plan* p, const void* q, const void* k, const 
       RouteLists all_full;
       std::memset(routes, VORTA_ROUTE_FULL, sizeof(routes));
       VORTA_TRY(split_routes(p, routes, &all_full));
-      VORTA_TRY(launch_rope_rows(p, all_full, q, q_r, stream));
-      VORTA_TRY(launch_rope_rows(p, all_full, k, k_r, stream));
+      VORTA_TRY(launch_rope_rows(p, all_full, q, q_r, k, k_r, stream));
       q_att = q_r;
       k_att = k_r;
     }

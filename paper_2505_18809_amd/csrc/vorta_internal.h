@@ -84,7 +84,8 @@ int launch_bcs_pool(vorta_plan* p, const RouteLists& rl, const void* src, const 
 bool bcs_fused_applies(const vorta_plan* p);
 int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, const void* k, const void* v,
                            int32_t* keep_idx, int32_t* assign, void* qc, void* kc, void* vc, void* stream);
-int launch_rope_rows(vorta_plan* p, const RouteLists& rl, const void* src, void* dst, void* stream);
+int launch_rope_rows(vorta_plan* p, const RouteLists& rl, const void* src, void* dst, const void* src2, void* dst2,
+                     void* stream);
 int launch_unpool(vorta_plan* p, const RouteLists& rl, const void* o_c, const int32_t* assign, void* out,
                   void* stream);
 int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, void* stream);

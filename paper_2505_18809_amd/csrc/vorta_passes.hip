@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstring>
+#include <type_traits>
 
 #include "vorta_internal.h"
 
@@ -134,29 +135,40 @@ static Rope make_rope(const vorta_plan* p) {
   return r;
 }
 
-// Turns the NP channel pairs x[2i], x[2i+1] that start at channel pair `pair0` of the head,
-// for the video token `tok`.  Pairs past the three spans are left alone.
+// What of the table a lane needs for its NP channel pairs, whatever the token: pair i's entry is
+// base[i] + (the token's coordinate on axis[i]) * stride[i]; base < 0 for a pair past the spans, which
+// is left alone.
 template <int NP>
-__device__ __forceinline__ void rope_turn(const Rope& r, int tok, int pair0, double* x) {
-#pragma clang fp contract(off)
-  const int hw = r.H * r.W;
-  const int f = tok / hw, rem = tok - f * hw;
-  const int h = rem / r.W, w = rem - h * r.W;
+struct RopeLane {
+  int base[NP], stride[NP], axis[NP];
+  __device__ __forceinline__ RopeLane(const Rope& r, int pair0) {
 #pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const int j = pair0 + i;
-    int idx = -1;
-    if (j < r.pF) idx = f * r.pF + j;
-    else if (j < r.pF + r.pH) idx = r.baseH + h * r.pH + (j - r.pF);
-    else if (j < r.pF + r.pH + r.pW) idx = r.baseW + w * r.pW + (j - r.pF - r.pH);
-    if (idx >= 0) {
-      const float2 cs = r.cs[idx];
-      const double a = x[2 * i], b = x[2 * i + 1];
-      x[2 * i] = a * (double)cs.x - b * (double)cs.y;
-      x[2 * i + 1] = a * (double)cs.y + b * (double)cs.x;
+    for (int i = 0; i < NP; ++i) {
+      const int j = pair0 + i, jh = j - r.pF, jw = jh - r.pH;
+      axis[i] = j < r.pF ? 0 : jh < r.pH ? 1 : 2;
+      stride[i] = j < r.pF ? r.pF : jh < r.pH ? r.pH : r.pW;
+      base[i] = j < r.pF ? j : jh < r.pH ? r.baseH + jh : jw < r.pW ? r.baseW + jw : -1;
     }
   }
-}
+  __device__ __forceinline__ void load(const Rope& r, int f, int h, int w, float2 (&cs)[NP]) const {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int x = axis[i] == 0 ? f : axis[i] == 1 ? h : w;
+      cs[i] = r.cs[max(base[i], 0) + (base[i] < 0 ? 0 : x * stride[i])];
+    }
+  }
+  // Turns x[2i], x[2i+1].  fp64; for rows as given (bf16 or fp32 elements times fp32 table entries) the
+  // products are exact, so the fused form changes no bit there.
+  __device__ __forceinline__ void turn(const float2 (&cs)[NP], double* x) const {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const double c = (double)cs[i].x, sn = (double)cs[i].y, u = x[2 * i], v = x[2 * i + 1];
+      const double x0 = __builtin_fma(u, c, -(v * sn)), x1 = __builtin_fma(u, sn, v * c);
+      x[2 * i] = base[i] < 0 ? u : x0;
+      x[2 * i + 1] = base[i] < 0 ? v : x1;
+    }
+  }
+};
 
 // ------------------------------------------------------------------------------------------
 // reorder: one thread per (tile-order row, 16-byte chunk), looping over the heads of route 1
@@ -258,7 +270,8 @@ template <> struct Elem<uint16_t> {   // bf16 bits
 struct Bucket {
   int f0, h0, w0;   // origin
   int df, dh, dw;   // clipped extent
-  int size, centre, prune;
+  int size, centre;
+  float inv_hw, inv_dw;
 };
 
 __device__ __forceinline__ Bucket bucket_of(const Geo& g, int b) {
@@ -270,15 +283,23 @@ __device__ __forceinline__ Bucket bucket_of(const Geo& g, int b) {
   k.df = min(g.bF, g.F - k.f0); k.dh = min(g.bH, g.H - k.h0); k.dw = min(g.bW, g.W - k.w0);
   k.size = k.df * k.dh * k.dw;
   k.centre = ((k.df / 2) * k.dh + k.dh / 2) * k.dw + k.dw / 2;
-  k.prune = min(k.size - 1, (int)(((long)k.size * (g.keep_den - g.keep_num)) / g.keep_den));
+  k.inv_hw = __builtin_amdgcn_rcpf((float)(k.dh * k.dw));
+  k.inv_dw = __builtin_amdgcn_rcpf((float)k.dw);
   return k;
 }
 
-__device__ __forceinline__ int bucket_token(const Geo& g, const Bucket& k, int j) {
-  const int hw = k.dh * k.dw;
-  const int a = j / hw, r = j - a * hw;
-  const int b = r / k.dw, c = r - b * k.dw;
-  return ((k.f0 + a) * g.H + k.h0 + b) * g.W + k.w0 + c;
+// Grid position and raster index of token j (0 <= j < 64) of a bucket.  The quotients are taken in
+// fp32: (j + 1/2) / n is at least 1 / 128 away from an integer, far more than the reciprocal is off.
+struct BucketToken {
+  int f, h, w, tok;
+};
+__device__ __forceinline__ BucketToken bucket_token(const Geo& g, const Bucket& k, int j) {
+  BucketToken t;
+  const int a = (int)(((float)j + 0.5f) * k.inv_hw), r = j - a * (k.dh * k.dw);
+  const int b = (int)(((float)r + 0.5f) * k.inv_dw), c = r - b * k.dw;
+  t.f = k.f0 + a; t.h = k.h0 + b; t.w = k.w0 + c;
+  t.tok = (t.f * g.H + t.h) * g.W + t.w;
+  return t;
 }
 
 // 16-byte chunk of a row (8 bf16 or 4 fp32 elements): raw load, and widening to fp64
@@ -305,61 +326,133 @@ template <> struct Chunk<float> {
   __device__ static void load(const float* p, double* x) { widen(raw(p), x); }
 };
 
-// sum over the 4 lanes of a quad (lanes 4k .. 4k+3)
-__device__ __forceinline__ double quad_sum(double v) {
-  v += __shfl_xor(v, 1, 64);
-  v += __shfl_xor(v, 2, 64);
-  return v;
+// A 16-byte chunk from fp64 values, each rounded to the element type through fp32 (round to nearest even).
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+template <typename T> __device__ __forceinline__ uint4 pack_chunk(const double* x);
+template <> __device__ __forceinline__ uint4 pack_chunk<uint16_t>(const double* x) {
+  unsigned u[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x2_t f = {(float)x[2 * i], (float)x[2 * i + 1]};
+    u[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2_t));
+  }
+  return make_uint4(u[0], u[1], u[2], u[3]);
+}
+template <> __device__ __forceinline__ uint4 pack_chunk<float>(const double* x) {
+  return make_uint4(__float_as_uint((float)x[0]), __float_as_uint((float)x[1]), __float_as_uint((float)x[2]),
+                    __float_as_uint((float)x[3]));
 }
 
-// One wavefront per (bucket, head).  Four lanes share a token: lane 4t + q holds quarter q of
-// token t's feature row (16-byte loads, all rows of a pass in flight at once), so a pass of
-// the wavefront covers 16 tokens; partial dot products and norms are fp64 and are summed
-// over the quad.  Then lane j ranks token j.  The products are formed inside fused
-// multiply-adds: a product of two bf16 (or fp32) values is exact in fp64, so fusing changes
-// no bit and halves the fp64 instruction count; everything after the sums stays unfused.
-// Cosine similarity of this quad's token to the bucket's centre from the lane's quarter rows
-// (craw: centre, xraw: token).  nc, the centre's squared norm, is produced when first is set and
-// reused afterwards.  Returns 0 for an invalid lane, a zero norm or a non-finite result.
-template <typename T, int CH>
-__device__ __forceinline__ double quad_similarity(const uint4 (&craw)[CH], const uint4 (&xraw)[CH], bool valid,
-                                                  bool first, double& nc) {
-#pragma clang fp contract(off)
-  double dot = 0.0, nj = 0.0, ncp = 0.0;
-#pragma unroll
-  for (int ch = 0; ch < CH; ++ch) {
-    double c[Chunk<T>::N], x[Chunk<T>::N];
-    Chunk<T>::widen(craw[ch], c);
-    Chunk<T>::widen(xraw[ch], x);
-#pragma unroll
-    for (int e = 0; e < Chunk<T>::N; ++e) {
-      ncp = __builtin_fma(c[e], c[e], ncp);
-      dot = __builtin_fma(c[e], x[e], dot);
-      nj = __builtin_fma(x[e], x[e], nj);
-    }
+// x / m for a small whole m with r = 1 / m (both correctly rounded): the quotient's error is removed by
+// one residual step, three operations where a division takes ten times that.  A sum that is infinite
+// or NaN has no residual and keeps the plain product.
+__device__ __forceinline__ double div_by(double x, double m, double r) {
+  const double q = x * r, e = __builtin_fma(-q, m, x);
+  return e == e ? __builtin_fma(e, r, q) : q;
+}
+
+// ---- cross-lane sums of fp64 values.  The 16 lanes of a DPP row by rotations, the rows by half-row and
+// half-wavefront swaps: all in the vector ALU, and every lane ends up with the same bits.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const long long u = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)u, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double row16_sum(double v) {
+  v = dpp_add<0x128>(v);      // row_ror:8
+  v = dpp_add<0x124>(v);
+  v = dpp_add<0x122>(v);
+  return dpp_add<0x121>(v);
+}
+template <bool HALF>          // HALF: lanes l and l ^ 32, else l and l ^ 16
+__device__ __forceinline__ double swap_add(double v) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
+  unsigned l0, l1, h0, h1;
+  if constexpr (HALF) {
+    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    l0 = a[0]; l1 = a[1]; h0 = b[0]; h1 = b[1];
+  } else {
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    l0 = a[0]; l1 = a[1]; h0 = b[0]; h1 = b[1];
   }
-  if (first) nc = quad_sum(ncp);
-  dot = quad_sum(dot);
-  nj = quad_sum(nj);
+  return __builtin_bit_cast(double, ((unsigned long long)h0 << 32) | l0) +
+         __builtin_bit_cast(double, ((unsigned long long)h1 << 32) | l1);
+}
+template <int CPR>            // sum over the CPR lanes that hold one row
+__device__ __forceinline__ double row_sum(double v) {
+  v = row16_sum(v);
+  return CPR == 32 ? swap_add<false>(v) : v;
+}
+template <int CPR>            // sum over the 64 / CPR rows of a pass, chunk by chunk
+__device__ __forceinline__ double group_sum(double v) {
+  if (CPR == 16) v = swap_add<false>(v);
+  return swap_add<true>(v);
+}
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  const long long u = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_readlane((int)u, lane), hi = __builtin_amdgcn_readlane((int)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+
+// ---- shared by the index pass, the pool pass and the two in one.  One wavefront per (bucket, head).  A
+// row is CPR 16-byte chunks (16 or 32) and lies across CPR lanes, lane (c = lane % CPR, group =
+// lane / CPR) holding chunk c of token G pass + group (G = 64 / CPR tokens a pass): every load and store
+// instruction moves whole rows, and index and pool read the bucket in the same form.
+
+// Dot product with the centre row (chunk craw) and squared norm of the row whose chunk is xraw, summed over
+// the row's lanes.  fp64; a product of two bf16 (or fp32) values is exact in it, so forming
+// it inside a fused multiply-add changes no bit.
+template <typename T, int CPR>
+__device__ __forceinline__ void row_dots(const uint4& craw, const uint4& xraw, double& dot, double& norm) {
+  double c[Chunk<T>::N], x[Chunk<T>::N];
+  Chunk<T>::widen(craw, c);
+  Chunk<T>::widen(xraw, x);
+  double d = 0.0, n = 0.0;
+#pragma unroll
+  for (int e = 0; e < Chunk<T>::N; ++e) {
+    d = __builtin_fma(c[e], x[e], d);
+    n = __builtin_fma(x[e], x[e], n);
+  }
+  dot = row_sum<CPR>(d);
+  norm = row_sum<CPR>(n);
+}
+
+// Value of token `lane` (lanes below the bucket size), given pass p's value spread over the token's row.
+template <int CPR>
+__device__ __forceinline__ void to_token_lane(double v, int pass, int lane, double& mine) {
+  constexpr int G = 64 / CPR;
+  const double x = __shfl(v, CPR * (lane & (G - 1)), 64);
+  if (lane / G == pass) mine = x;
+}
+
+// Cosine similarity from the sums; 0 for a zero norm or a non-finite result (keeps the ranking a total order).
+__device__ __forceinline__ double similarity(double dot, double nc, double nj) {
+#pragma clang fp contract(off)
   double sim = 0.0;
-  if (valid && nc != 0.0 && nj != 0.0) sim = dot / sqrt(nc * nj);
-  if (!(sim == sim)) sim = 0.0;       // non-finite features: keep the ranking a total order
-  return sim;
+  if (nc != 0.0 && nj != 0.0) sim = dot / sqrt(nc * nj);
+  return sim == sim ? sim : 0.0;
 }
 
 // Lane j holds the similarity of token j.  Ranks the non-centre tokens (larger similarity first,
-// ties by index), prunes the first k.prune of them and numbers the kept tokens in raster order.
+// ties by index), prunes the first `prune` of them and numbers the kept tokens in raster order.
 // Returns the slot token `lane` reads its output from (its own if kept, else the centre's);
-// kept / own_slot say whether the lane's token owns a slot and which.
-__device__ __forceinline__ int rank_and_assign(const Bucket& k, int lane, double my_sim, int base_slot, bool& kept,
-                                               int& centre_slot) {
+// kept / centre_slot say whether the lane's token owns a slot and which slot the centre has.
+__device__ __forceinline__ int rank_and_assign(const Bucket& k, int prune, int lane, double my_sim, int base_slot,
+                                               bool& kept, int& centre_slot) {
   int rank = 0;
   for (int m = 0; m < k.size; ++m) {
-    const double sm = __shfl(my_sim, m, 64);
-    if (m != k.centre && (sm > my_sim || (sm == my_sim && m < lane))) ++rank;
+    if (m == k.centre) continue;
+    const double sm = read_lane(my_sim, m);
+    if (sm > my_sim || (sm == my_sim && m < lane)) ++rank;
   }
   const bool in_bucket = lane < k.size;
-  kept = in_bucket && (lane == k.centre || rank >= k.prune);
+  kept = in_bucket && (lane == k.centre || rank >= prune);
   const unsigned long long kept_mask = __ballot(kept);
   const int my_slot = base_slot + __popcll(kept_mask & ((1ull << lane) - 1ull));
   centre_slot = base_slot + __popcll(kept_mask & ((1ull << k.centre) - 1ull));
@@ -371,44 +464,30 @@ __global__ __launch_bounds__(256) void bcs_index_kernel(const T* __restrict__ fe
                                                         int n_buckets, const int* __restrict__ slot_base,
                                                         long head_stride, long row_stride, int Lc,
                                                         int* __restrict__ keep_idx, int* __restrict__ assign) {
-  constexpr int EP = D / 4;                 // elements per lane
-  constexpr int CH = EP / Chunk<T>::N;      // 16-byte chunks per lane
+  constexpr int CN = Chunk<T>::N, CPR = D / CN, G = 64 / CPR;
   const int lane = threadIdx.x & 63;
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int b = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   const int s = blockIdx.y;
   if (b >= n_buckets) return;
   const Bucket k = bucket_of(g, b);
-  const int quarter = lane & 3, tl = lane >> 2;
-  const T* base = feat + hl.id[s] * head_stride + quarter * EP;
-
-  // The centre row and the rows of the first pass are requested together; rows stay in their
-  // 16-byte form and are widened chunk by chunk as they are used, so a bucket of up to 16
-  // tokens costs one memory round trip.
-  uint4 craw[CH];
-  {
-    const T* row = base + (long)bucket_token(g, k, k.centre) * row_stride;
-#pragma unroll
-    for (int ch = 0; ch < CH; ++ch) craw[ch] = Chunk<T>::raw(row + ch * Chunk<T>::N);
+  const int base_slot = slot_base[b], prune = k.size - (slot_base[b + 1] - base_slot);
+  const int c = lane % CPR, grp = lane / CPR;
+  const T* base = feat + hl.id[s] * head_stride + c * CN;
+  const uint4 craw = Chunk<T>::raw(base + (long)bucket_token(g, k, k.centre).tok * row_stride);
+  double nc, self, my_dot = 0.0, my_norm = 0.0;
+  row_dots<T, CPR>(craw, craw, self, nc);
+  for (int pass = 0; pass * G < k.size; ++pass) {
+    const int j = min(G * pass + grp, k.size - 1);
+    double dot, norm;
+    row_dots<T, CPR>(craw, Chunk<T>::raw(base + (long)bucket_token(g, k, j).tok * row_stride), dot, norm);
+    to_token_lane<CPR>(dot, pass, lane, my_dot);
+    to_token_lane<CPR>(norm, pass, lane, my_norm);
   }
-  double nc = 0.0, my_sim = 0.0;
-  for (int pass = 0; pass * 16 < k.size; ++pass) {
-    const int j = pass * 16 + tl;
-    const bool valid = j < k.size && j != k.centre;
-    const T* row = base + (long)bucket_token(g, k, valid ? j : k.centre) * row_stride;
-    uint4 xraw[CH];
-#pragma unroll
-    for (int ch = 0; ch < CH; ++ch) xraw[ch] = Chunk<T>::raw(row + ch * Chunk<T>::N);
-    const double sim = quad_similarity<T, CH>(craw, xraw, valid, pass == 0, nc);
-    // token 16 pass + t sits in lanes 4t .. 4t+3; hand it to lane 16 pass + t
-    const double mine = __shfl(sim, 4 * (lane & 15), 64);
-    if ((lane >> 4) == pass) my_sim = mine;
-  }
-
   bool kept;
   int centre_slot;
-  const int slot = rank_and_assign(k, lane, my_sim, slot_base[b], kept, centre_slot);
+  const int slot = rank_and_assign(k, prune, lane, similarity(my_dot, nc, my_norm), base_slot, kept, centre_slot);
   if (lane < k.size) {
-    const int tok = bucket_token(g, k, lane);
+    const int tok = bucket_token(g, k, lane).tok;
     if (kept) keep_idx[(long)s * Lc + slot] = tok;
     assign[(long)s * g.L + tok] = slot;
   }
@@ -435,77 +514,67 @@ int launch_bcs_index(vorta_plan* p, const RouteLists& rl, const UserTensor& ut, 
 }
 
 // ------------------------------------------------------------------------------------------
-// pool / merge: one wavefront per (bucket, head).  A row is CPR 16-byte chunks; lane
-// (c = lane % CPR, group = lane / CPR) moves chunk c of the tokens group, group + G, ...
-// (G = 64 / CPR token groups).  A kept token's chunk is copied to its slot; the chunks of the
-// centre and of the tokens pruned into it are summed in fp64, the G partial sums are added
-// across the groups, and group 0 writes the mean to the centre's slot.
-// ------------------------------------------------------------------------------------------
+// pool / merge.  A kept token's chunk is copied to its slot; the chunks of the centre and of the
+// tokens pruned into it are summed in fp64, the G partial sums are added across the groups, and
+// group 0 writes the mean to the centre's slot.
 // ROPE: every pooled row is turned by the rotary embedding at the position of the token that owns
 // its slot (the kept token itself; for a merged row the bucket's centre) before it is stored.
+// ------------------------------------------------------------------------------------------
 template <typename T, int D, bool ROPE>
 __global__ __launch_bounds__(256) void bcs_pool_kernel(const T* __restrict__ src, HeadList hl, Geo g,
                                                        int n_buckets, long head_stride, long row_stride,
                                                        int n_core_rows, const int* __restrict__ assign,
                                                        T* __restrict__ dst, Rope rope) {
-  constexpr int CN = Chunk<T>::N;           // elements per chunk
-  constexpr int CPR = D / CN;               // chunks per row: 16 or 32
-  constexpr int G = 64 / CPR;               // token groups per pass
+  constexpr int CN = Chunk<T>::N, CPR = D / CN, G = 64 / CPR;
   const int lane = threadIdx.x & 63;
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int b = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   const int s = blockIdx.y;
   if (b >= n_buckets) return;
   const Bucket k = bucket_of(g, b);
   const int c = lane % CPR, grp = lane / CPR;
   const T* base = src + hl.id[s] * head_stride + c * CN;
   T* out = dst + (long)s * n_core_rows * D + c * CN;
+  const RopeLane<CN / 2> rl(rope, c * (CN / 2));
 
   int my_slot = 0;
-  if (lane < k.size) my_slot = assign[(long)s * g.L + bucket_token(g, k, lane)];
+  if (lane < k.size) my_slot = assign[(long)s * g.L + bucket_token(g, k, lane).tok];
   const int centre_slot = __shfl(my_slot, k.centre, 64);
+  const int members = __popcll(__ballot(lane < k.size && my_slot == centre_slot));
   double acc[CN];
 #pragma unroll
   for (int e = 0; e < CN; ++e) acc[e] = 0.0;
-  int members = 0;
   for (int j0 = 0; j0 < k.size; j0 += G) {
     const int j = j0 + grp;
     const int slot = __shfl(my_slot, min(j, k.size - 1), 64);
-    // members of the centre's cluster among the G tokens of this pass (same count in every lane)
-#pragma unroll
-    for (int q = 0; q < G; ++q)
-      if (j0 + q < k.size && __shfl(my_slot, min(j0 + q, k.size - 1), 64) == centre_slot) ++members;
     if (j >= k.size) continue;
-    const int tok = bucket_token(g, k, j);
-    const T* row = base + (long)tok * row_stride;
+    const BucketToken t = bucket_token(g, k, j);
+    const uint4 raw = Chunk<T>::raw(base + (long)t.tok * row_stride);
     if (slot == centre_slot) {
       double x[CN];
-      Chunk<T>::load(row, x);
+      Chunk<T>::widen(raw, x);
 #pragma unroll
       for (int e = 0; e < CN; ++e) acc[e] += x[e];
     } else if (ROPE) {
       double x[CN];
-      Chunk<T>::load(row, x);
-      rope_turn<CN / 2>(rope, tok, c * (CN / 2), x);
-      T* o = out + (long)slot * D;
-#pragma unroll
-      for (int e = 0; e < CN; ++e) Elem<T>::store(o + e, x[e]);
+      float2 cs[CN / 2];
+      Chunk<T>::widen(raw, x);
+      rl.load(rope, t.f, t.h, t.w, cs);
+      rl.turn(cs, x);
+      *(uint4*)(out + (long)slot * D) = pack_chunk<T>(x);
     } else {
-      *(uint4*)(out + (long)slot * D) = *(const uint4*)row;
+      *(uint4*)(out + (long)slot * D) = raw;
     }
   }
+  const double m = (double)members, r = 1.0 / m;
 #pragma unroll
-  for (int e = 0; e < CN; ++e) {
-    double v = acc[e];
-#pragma unroll
-    for (int off = CPR; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
-    acc[e] = v / (double)members;
+  for (int e = 0; e < CN; ++e) acc[e] = div_by(group_sum<CPR>(acc[e]), m, r);
+  if (ROPE) {
+    const BucketToken t = bucket_token(g, k, k.centre);
+    float2 cs[CN / 2];
+    rl.load(rope, t.f, t.h, t.w, cs);
+    rl.turn(cs, acc);
   }
-  if (ROPE) rope_turn<CN / 2>(rope, bucket_token(g, k, k.centre), c * (CN / 2), acc);
-  if (grp == 0) {
-    T* o = out + (long)centre_slot * D;
-#pragma unroll
-    for (int e = 0; e < CN; ++e) Elem<T>::store(o + e, acc[e]);
-  }
+  if (grp == 0) *(uint4*)(out + (long)centre_slot * D) = pack_chunk<T>(acc);
 }
 
 // text rows ride along unchanged behind the L_c pooled rows
@@ -560,80 +629,102 @@ int launch_bcs_pool(vorta_plan* p, const RouteLists& rl, const void* src, const 
 }
 
 // ------------------------------------------------------------------------------------------
-// Select and pool in one pass (what the layer call runs when a bucket holds at most 16 tokens and
-// a row is 16 chunks, which covers the paper's (2,3,2) bucket in bf16): one wavefront per (bucket,
-// head) requests, before it computes anything, the bucket's K rows in the index kernel's form (a
-// quarter row per lane) and its Q, K and V rows in the pool kernel's form (chunk c of tokens grp,
-// grp + 4, ...), so one memory round trip covers them all and K comes from HBM once; then it
-// ranks exactly as bcs_index_kernel does, writes keep_idx / assign, and merges and stores the
-// three tensors exactly as bcs_pool_kernel does (same operations in the same order: the results
-// of the two forms are identical bit for bit).
+// Select and pool in one pass (what the layer call runs): one wavefront per (bucket, head) requests the
+// bucket's K, Q and V rows before it computes anything, P passes of G tokens each, so one memory round
+// trip covers them all and every row comes from HBM once; then it ranks as bcs_index_kernel does, writes
+// keep_idx / assign, and merges and stores the three tensors as bcs_pool_kernel does (same operations in
+// the same order: the results of the two forms are identical bit for bit).  The last workgroups of a
+// head copy its text rows behind the pooled ones.
+//
+// Bound: HBM.  On 16 heads of 75,600 tokens (1.40 GB with the index) 283 us = 4.9 TB/s, what a large copy
+// reaches; with the rotary embedding 355 us (the fp64 turn of every pooled Q and K row).  An earlier form
+// that read K a second time as quarter rows, divided in fp64, took 64-bit integer quotients and stored
+// element by element: 397 us and 718 us.
 // ------------------------------------------------------------------------------------------
-template <typename T, int D, bool ROPE>
+template <typename T, int D, int P, bool ROPE>
 __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restrict__ q, const T* __restrict__ k,
                                                               const T* __restrict__ v, HeadList hl, Geo g, int n_buckets,
-                                                              const int* __restrict__ slot_base, long head_stride,
-                                                              long row_stride, int Lc, int n_core_rows,
+                                                              int bucket_blocks, const int* __restrict__ slot_base,
+                                                              long head_stride, long row_stride, int Lc, int n_core_rows,
                                                               int* __restrict__ keep_idx, int* __restrict__ assign,
                                                               T* __restrict__ qc, T* __restrict__ kc, T* __restrict__ vc,
                                                               Rope rope) {
-  constexpr int CN = Chunk<T>::N;
-  static_assert(D / CN == 16, "rows of 16 chunks");
-  constexpr int EP = D / 4, CH = EP / CN;   // index form: elements and chunks per lane
-  constexpr int G = 4, P = 4;               // pool form: token groups per pass, passes for up to 16 tokens
-  const int lane = threadIdx.x & 63;
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
+  constexpr int CN = Chunk<T>::N, CPR = D / CN, G = 64 / CPR;
   const int s = blockIdx.y;
-  if (b >= n_buckets) return;
-  const Bucket kb = bucket_of(g, b);        // kb.size <= 16: checked on the host
   const long head_off = hl.id[s] * head_stride;
+  if ((int)blockIdx.x >= bucket_blocks) {          // text rows
+    const int i = ((int)blockIdx.x - bucket_blocks) * 256 + threadIdx.x;
+    const int t = i / CPR, c = i % CPR;
+    if (t >= g.N - g.L) return;
+    const long from = head_off + (long)(g.L + t) * row_stride + c * CN, to = ((long)s * n_core_rows + Lc + t) * D + c * CN;
+    *(uint4*)(qc + to) = Chunk<T>::raw(q + from);
+    *(uint4*)(kc + to) = Chunk<T>::raw(k + from);
+    *(uint4*)(vc + to) = Chunk<T>::raw(v + from);
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const int b = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  if (b >= n_buckets) return;
+  const Bucket kb = bucket_of(g, b);               // kb.size <= P G: checked on the host
+  const int c = lane % CPR, grp = lane / CPR;
 
   // ---- every load of the wavefront
-  const int quarter = lane & 3, tl = lane >> 2;
-  const bool valid = tl < kb.size && tl != kb.centre;
-  uint4 craw[CH], xraw[CH];
-  {
-    const T* crow = k + head_off + (long)bucket_token(g, kb, kb.centre) * row_stride + quarter * EP;
-    const T* xrow = k + head_off + (long)bucket_token(g, kb, valid ? tl : kb.centre) * row_stride + quarter * EP;
-#pragma unroll
-    for (int ch = 0; ch < CH; ++ch) {
-      craw[ch] = Chunk<T>::raw(crow + ch * CN);
-      xraw[ch] = Chunk<T>::raw(xrow + ch * CN);
-    }
-  }
-  const int c = lane & 15, grp = lane >> 4;
+  const BucketToken centre = bucket_token(g, kb, kb.centre);
+  const uint4 craw = Chunk<T>::raw(k + head_off + (long)centre.tok * row_stride + c * CN);
   uint4 rq[P], rk[P], rv[P];
-  int tok_p[P];
+  BucketToken tok_p[P];
+  long off[P];
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     tok_p[p] = bucket_token(g, kb, min(G * p + grp, kb.size - 1));
-    const long off = head_off + (long)tok_p[p] * row_stride + c * CN;
-    rq[p] = Chunk<T>::raw(q + off);
-    rk[p] = Chunk<T>::raw(k + off);
-    rv[p] = Chunk<T>::raw(v + off);
+    off[p] = head_off + (long)tok_p[p].tok * row_stride + c * CN;
   }
+#pragma unroll
+  for (int p = 0; p < P; ++p) rk[p] = Chunk<T>::raw(k + off[p]);
+#pragma unroll
+  for (int p = 0; p < P; ++p) rq[p] = Chunk<T>::raw(q + off[p]);
+#pragma unroll
+  for (int p = 0; p < P; ++p) rv[p] = Chunk<T>::raw(v + off[p]);
+  const RopeLane<CN / 2> rl(rope, c * (CN / 2));
+  const int base_slot = slot_base[b], prune = kb.size - (slot_base[b + 1] - base_slot);
 
   // ---- select
-  double nc = 0.0;
-  const double sim = quad_similarity<T, CH>(craw, xraw, valid, true, nc);
-  const double mine = __shfl(sim, 4 * (lane & 15), 64);
-  const double my_sim = lane < 16 ? mine : 0.0;
+  double nc, self, my_dot = 0.0, my_norm = 0.0;
+  row_dots<T, CPR>(craw, craw, self, nc);
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    double dot, norm;
+    row_dots<T, CPR>(craw, rk[p], dot, norm);
+    to_token_lane<CPR>(dot, p, lane, my_dot);
+    to_token_lane<CPR>(norm, p, lane, my_norm);
+  }
   bool kept;
   int centre_slot;
-  const int slot_of_lane = rank_and_assign(kb, lane, my_sim, slot_base[b], kept, centre_slot);
+  const int slot_of_lane = rank_and_assign(kb, prune, lane, similarity(my_dot, nc, my_norm), base_slot, kept, centre_slot);
   if (lane < kb.size) {
-    const int tok = bucket_token(g, kb, lane);
+    const int tok = bucket_token(g, kb, lane).tok;
     if (kept) keep_idx[(long)s * Lc + slot_of_lane] = tok;
     assign[(long)s * g.L + tok] = slot_of_lane;
   }
 
   // ---- pool
-  const int centre_tok = bucket_token(g, kb, kb.centre);
-  const int members = kb.prune + 1;
+  const double m = (double)(prune + 1), r = 1.0 / m;
   int slot_p[P];
 #pragma unroll
-  for (int p = 0; p < P; ++p) slot_p[p] = __shfl(slot_of_lane, min(G * p + grp, kb.size - 1), 64);
-  auto pool = [&](const uint4 (&rows)[P], T* dst, bool rotate) {
+  for (int p = 0; p < P; ++p) {
+    slot_p[p] = __shfl(slot_of_lane, min(G * p + grp, kb.size - 1), 64);
+    // widen K again below instead of keeping its fp64 form in registers across the ranking
+    asm volatile("" : "+v"(rk[p].x), "+v"(rk[p].y), "+v"(rk[p].z), "+v"(rk[p].w));
+  }
+  // rotation of the bucket's tokens, looked up once for K and Q where it fits in registers
+  constexpr bool HOLD = ROPE && P <= 4;
+  float2 cs[HOLD ? P : 1][CN / 2], cs_centre[CN / 2];
+  if (HOLD) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) rl.load(rope, tok_p[p].f, tok_p[p].h, tok_p[p].w, cs[HOLD ? p : 0]);
+  }
+  if (ROPE) rl.load(rope, centre.f, centre.h, centre.w, cs_centre);
+  auto pool = [&](const uint4 (&rows)[P], T* dst, auto rotate) {
     T* out = dst + (long)s * n_core_rows * D + c * CN;
     double acc[CN];
 #pragma unroll
@@ -646,42 +737,34 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
         Chunk<T>::widen(rows[p], x);
 #pragma unroll
         for (int e = 0; e < CN; ++e) acc[e] += x[e];
-      } else if (rotate) {
+      } else if constexpr (rotate.value) {
         double x[CN];
         Chunk<T>::widen(rows[p], x);
-        rope_turn<CN / 2>(rope, tok_p[p], c * (CN / 2), x);
-        T* o = out + (long)slot_p[p] * D;
-#pragma unroll
-        for (int e = 0; e < CN; ++e) Elem<T>::store(o + e, x[e]);
+        if constexpr (!HOLD) rl.load(rope, tok_p[p].f, tok_p[p].h, tok_p[p].w, cs[0]);
+        rl.turn(cs[HOLD ? p : 0], x);
+        *(uint4*)(out + (long)slot_p[p] * D) = pack_chunk<T>(x);
       } else {
         *(uint4*)(out + (long)slot_p[p] * D) = rows[p];
       }
     }
 #pragma unroll
-    for (int e = 0; e < CN; ++e) {
-      double sum = acc[e];
-      sum += __shfl_xor(sum, 16, 64);
-      sum += __shfl_xor(sum, 32, 64);
-      acc[e] = sum / (double)members;
-    }
-    if (rotate) rope_turn<CN / 2>(rope, centre_tok, c * (CN / 2), acc);
-    if (grp == 0) {
-      T* o = out + (long)centre_slot * D;
-#pragma unroll
-      for (int e = 0; e < CN; ++e) Elem<T>::store(o + e, acc[e]);
-    }
+    for (int e = 0; e < CN; ++e) acc[e] = div_by(group_sum<CPR>(acc[e]), m, r);
+    if constexpr (rotate.value) rl.turn(cs_centre, acc);
+    if (grp == 0) *(uint4*)(out + (long)centre_slot * D) = pack_chunk<T>(acc);
   };
-  pool(rq, qc, ROPE);
-  pool(rk, kc, ROPE);
-  pool(rv, vc, false);
+  pool(rk, kc, std::integral_constant<bool, ROPE>());
+  pool(rq, qc, std::integral_constant<bool, ROPE>());
+  pool(rv, vc, std::integral_constant<bool, false>());
 }
 
-// True when the fused form applies: buckets of at most 16 tokens, rows of 16 chunks.
-bool bcs_fused_applies(const vorta_plan* p) {
-  const long bucket_tokens = (long)p->d.bucket[0] * p->d.bucket[1] * p->d.bucket[2];
+// True when one of the fused instances holds the plan's buckets: 12, 16 or 32 tokens in rows of 16 chunks,
+// 12 or 16 in rows of 32 (the rows of a bucket live in registers).
+static int fused_tokens(const vorta_plan* p) {
+  const int tokens = p->d.bucket[0] * p->d.bucket[1] * p->d.bucket[2];   // <= 64
   const int chunks = p->d.head_dim * p->elem_bytes / 16;
-  return bucket_tokens <= 16 && chunks == 16;
+  return tokens <= 12 ? 12 : tokens <= 16 ? 16 : tokens <= 32 && chunks == 16 ? 32 : 0;
 }
+bool bcs_fused_applies(const vorta_plan* p) { return fused_tokens(p) > 0; }
 
 // Index on K, then Q, K, V pooled (Q and K rotated if the plan has a rotary embedding) into
 // qc, kc, vc, and the text rows copied behind them.
@@ -689,68 +772,93 @@ int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, c
                            int32_t* keep_idx, int32_t* assign, void* qc, void* kc, void* vc, void* stream) {
   if (rl.count[2] == 0) return VORTA_OK;
   const UserTensor ut = user_tensor(p, k);
-  const dim3 grid((p->n_buckets + 3) / 4, rl.count[2]);
+  const int bucket_blocks = (p->n_buckets + 3) / 4;
+  const long text_chunks = (long)p->d.n_text << chunk_shift(p);
+  const dim3 grid((unsigned)(bucket_blocks + (text_chunks + 255) / 256), rl.count[2]);
   const HeadList hl = head_list(rl, 2);
   const Geo g = make_geo(p);
-  const int rows = (int)(p->Lc + p->d.n_text);
+  const int rows = (int)(p->Lc + p->d.n_text), fused = fused_tokens(p);
   const Rope rope = make_rope(p);
   hipStream_t st = (hipStream_t)stream;
-#define VORTA_FUSED(T_, D_, R_)                                                                                        \
-  hipLaunchKernelGGL((bcs_select_pool_kernel<T_, D_, R_>), grid, dim3(256), 0, st, (const T_*)q, (const T_*)k,         \
-                     (const T_*)v, hl, g, p->n_buckets, p->d_slot_base, ut.head_stride, ut.row_stride, (int)p->Lc, rows, \
-                     keep_idx, assign, (T_*)qc, (T_*)kc, (T_*)vc, rope)
+#define VORTA_FUSED(T_, D_, P_, R_)                                                                                     \
+  hipLaunchKernelGGL((bcs_select_pool_kernel<T_, D_, P_, R_>), grid, dim3(256), 0, st, (const T_*)q, (const T_*)k,      \
+                     (const T_*)v, hl, g, p->n_buckets, bucket_blocks, p->d_slot_base, ut.head_stride, ut.row_stride,   \
+                     (int)p->Lc, rows, keep_idx, assign, (T_*)qc, (T_*)kc, (T_*)vc, rope)
+#define VORTA_FUSED_R(T_, D_, P_) \
+  if (p->rope) VORTA_FUSED(T_, D_, P_, true); else VORTA_FUSED(T_, D_, P_, false)
   if (p->d.dtype == VORTA_BF16) {
-    if (p->rope) VORTA_FUSED(uint16_t, 128, true); else VORTA_FUSED(uint16_t, 128, false);
+    if (fused == 12) { VORTA_FUSED_R(uint16_t, 128, 3); }
+    else if (fused == 16) { VORTA_FUSED_R(uint16_t, 128, 4); }
+    else { VORTA_FUSED_R(uint16_t, 128, 8); }
+  } else if (p->d.head_dim == 64) {
+    if (fused == 12) { VORTA_FUSED_R(float, 64, 3); }
+    else if (fused == 16) { VORTA_FUSED_R(float, 64, 4); }
+    else { VORTA_FUSED_R(float, 64, 8); }
   } else {
-    if (p->rope) VORTA_FUSED(float, 64, true); else VORTA_FUSED(float, 64, false);
+    if (fused == 12) { VORTA_FUSED_R(float, 128, 6); }
+    else { VORTA_FUSED_R(float, 128, 8); }
   }
+#undef VORTA_FUSED_R
 #undef VORTA_FUSED
-  if (int rc = launch_status("bcs_select_pool_kernel")) return rc;
-  if (p->d.n_text > 0) {
-    const int cs = chunk_shift(p);
-    const int epc = 16 / p->elem_bytes;
-    const long total = (long)p->d.n_text << cs;
-    const void* srcs[3] = {q, k, v};
-    void* dsts[3] = {qc, kc, vc};
-    for (int t = 0; t < 3; ++t)
-      hipLaunchKernelGGL(copy_text_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                         (const uint4*)srcs[t], (uint4*)dsts[t], hl, (int)p->L, p->d.n_text, (int)p->Lc,
-                         ut.head_stride / epc, ut.row_stride / epc, cs);
-    return launch_status("copy_text_rows_kernel");
-  }
-  return VORTA_OK;
+  return launch_status("bcs_select_pool_kernel");
 }
 
 // ------------------------------------------------------------------------------------------
-// Rotary embedding of whole rows, heads of routes 0 and 1: one thread per (row, 16-byte chunk),
-// looping over the heads; dst has the caller's layout.  Text rows are copied.
+// Rotary embedding of whole rows, heads of routes 0 and 1: one thread per (row, 16-byte chunk) looks its
+// table entries up once and loops over the heads, four at a time so that four loads are in flight; dst
+// has the caller's layout.  blockIdx.y: tensor (the layer call turns Q and K in one launch).  Text rows
+// are copied.  Bound: HBM: Q and K of 14 heads x 119,056 tokens (1.7 GB) 339 us = 5.0 TB/s; with the table
+// read again for every head and a launch for each tensor 578 us.
 // ------------------------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void rope_rows_kernel(const T* __restrict__ src, T* __restrict__ dst, HeadList hl,
-                                                        int L, int N, long head_stride, long row_stride, int cshift,
-                                                        Rope rope) {
+struct RopeTensors {
+  const T* src[2];
+  T* dst[2];
+};
+template <typename T>
+__global__ __launch_bounds__(256) void rope_rows_kernel(RopeTensors<T> ts, HeadList hl, int L, int N, long head_stride,
+                                                        long row_stride, int cshift, Rope rope) {
   constexpr int CN = Chunk<T>::N;
+  const T* __restrict__ src = ts.src[blockIdx.y];
+  T* __restrict__ dst = ts.dst[blockIdx.y];
   const long gid = (long)blockIdx.x * 256 + threadIdx.x;
   const int i = (int)(gid >> cshift);
   const int c = (int)(gid & ((1 << cshift) - 1));
   if (i >= N) return;
   const long off0 = (long)i * row_stride + c * CN;
-#pragma unroll 2
-  for (int s = 0; s < hl.n; ++s) {
-    const long off = off0 + hl.id[s] * head_stride;
-    if (i >= L) {
+  if (i >= L) {
+    for (int s = 0; s < hl.n; ++s) {
+      const long off = off0 + hl.id[s] * head_stride;
       *(uint4*)(dst + off) = *(const uint4*)(src + off);
-      continue;
     }
-    double x[CN];
-    Chunk<T>::load(src + off, x);
-    rope_turn<CN / 2>(rope, i, c * (CN / 2), x);
+    return;
+  }
+  const RopeLane<CN / 2> rl(rope, c * (CN / 2));
+  float2 cs[CN / 2];
+  const int f = i / (rope.H * rope.W), rem = i - f * (rope.H * rope.W), h = rem / rope.W;
+  rl.load(rope, f, h, rem - h * rope.W, cs);
+  for (int s0 = 0; s0 < hl.n; s0 += 4) {
+    uint4 raw[4];
+    long off[4];
 #pragma unroll
-    for (int e = 0; e < CN; ++e) Elem<T>::store(dst + off + e, x[e]);
+    for (int u = 0; u < 4; ++u) {
+      off[u] = off0 + hl.id[min(s0 + u, hl.n - 1)] * head_stride;
+      raw[u] = Chunk<T>::raw(src + off[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (s0 + u >= hl.n) break;
+      double x[CN];
+      Chunk<T>::widen(raw[u], x);
+      rl.turn(cs, x);
+      *(uint4*)(dst + off[u]) = pack_chunk<T>(x);
+    }
   }
 }
 
-int launch_rope_rows(vorta_plan* p, const RouteLists& rl, const void* src, void* dst, void* stream) {
+// src2 / dst2: a second tensor for the same launch, or null
+int launch_rope_rows(vorta_plan* p, const RouteLists& rl, const void* src, void* dst, const void* src2, void* dst2,
+                     void* stream) {
   HeadList hl;
   hl.n = 0;
   for (int r = 0; r < 2; ++r)
@@ -759,15 +867,15 @@ int launch_rope_rows(vorta_plan* p, const RouteLists& rl, const void* src, void*
   const UserTensor ut = user_tensor(p, src);
   const int cs = chunk_shift(p);
   const long total = (long)p->N << cs;
-  const unsigned blocks = (unsigned)((total + 255) / 256);
+  const dim3 grid((unsigned)((total + 255) / 256), src2 ? 2 : 1);
   const Rope rope = make_rope(p);
   hipStream_t st = (hipStream_t)stream;
-  if (p->d.dtype == VORTA_BF16)
-    hipLaunchKernelGGL(rope_rows_kernel<uint16_t>, dim3(blocks), dim3(256), 0, st, (const uint16_t*)src, (uint16_t*)dst,
-                       hl, (int)p->L, (int)p->N, ut.head_stride, ut.row_stride, cs, rope);
-  else
-    hipLaunchKernelGGL(rope_rows_kernel<float>, dim3(blocks), dim3(256), 0, st, (const float*)src, (float*)dst, hl,
-                       (int)p->L, (int)p->N, ut.head_stride, ut.row_stride, cs, rope);
+#define VORTA_ROPE(T_)                                                                                              \
+  hipLaunchKernelGGL(rope_rows_kernel<T_>, grid, dim3(256), 0, st,                                                  \
+                     (RopeTensors<T_>{{(const T_*)src, (const T_*)src2}, {(T_*)dst, (T_*)dst2}}), hl, (int)p->L,    \
+                     (int)p->N, ut.head_stride, ut.row_stride, cs, rope)
+  if (p->d.dtype == VORTA_BF16) VORTA_ROPE(uint16_t); else VORTA_ROPE(float);
+#undef VORTA_ROPE
   return launch_status("rope_rows_kernel");
 }
 
