@@ -156,14 +156,14 @@ int vorta_window_boxes(const vorta_plan* plan, int32_t* boxes);
  * runs: host int32[n_tiles][max_runs][2]; n_runs: host int32[n_tiles]. */
 int vorta_window_runs(const vorta_plan* plan, int32_t* runs, int32_t* n_runs);
 
-/* How the bf16 layer call cuts the work of route 1 (tiles of at most 128 tokens): query tiles
- * whose runs are identical see the same keys (Algorithm 1: under the clamped centre rule a border
- * tile and its inner neighbour on every axis, under the block rule all tiles of a block) and are
- * computed together, up to three tiles and 256 rows per work item.  items: host
- * int32[counts[0] + counts[1]][4] = {tile, tile, tile, n_tiles_in_item}, first the counts[0] items
- * of more than 128 rows, then the counts[1] items of at most 128 rows; every tile appears in
- * exactly one item.  items may be NULL to query the counts.  Both counts are 0 when a tile holds
- * more than 128 tokens (such tiles are cut into 256-row query blocks instead). */
+/* Query tiles of route 1 that see the same keys (tiles of at most 128 tokens): under the clamped centre
+ * rule a border tile and its inner neighbour on every axis, under the block rule all tiles of a block,
+ * have identical runs.  The bf16 kernels compute such tiles together, one key stream for the rows of all
+ * of them; this table reports them up to three tiles and 256 rows at a time.  items: host
+ * int32[counts[0] + counts[1]][4] = {tile, tile, tile, n_tiles_in_item}, first the counts[0] entries
+ * of more than 128 rows, then the counts[1] entries of at most 128 rows; every tile appears in
+ * exactly one.  items may be NULL to query the counts.  Both counts are 0 when a tile holds
+ * more than 128 tokens. */
 int vorta_window_items(const vorta_plan* plan, int32_t* items, int32_t counts[2]);
 
 /* BCS slot layout (section 3.2): buckets in raster order of bucket coordinates; bucket b owns

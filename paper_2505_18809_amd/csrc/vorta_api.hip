@@ -59,9 +59,10 @@ int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io,
   a->row_stride0 = ut.row_stride;
   a->qc = io->q_c; a->kc = io->k_c; a->vc = io->v_c; a->oc = io->o_c;
   a->qt = io->q_t; a->kt = io->k_t; a->vt = io->v_t; a->ot = io->o_t;
-  a->tok_of = p->d_tok_of;
   a->tile_row0 = p->d_tile_row0;
   a->win_gather = io->q_t == nullptr;
+  a->tok_of = a->win_gather ? p->d_tok_of : p->d_iota;
+  a->win_row = a->win_gather ? p->d_win_tok : p->d_win_rows;
   a->runs = p->d_runs;
   a->n_runs = p->d_n_runs;
   a->max_runs = p->max_runs;
@@ -80,9 +81,8 @@ int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io,
   const long end_core = end_dense + (long)rl.count[2] * a->qb_core;
   long tile_items = (long)a->n_tiles * a->qb_tile;        // per window head
   if (win_list >= 0) {
-    a->win_items = p->d_win_items;
-    a->win_first = win_list == 0 ? 0 : p->n_win_big;
-    a->win_count = win_list == 0 ? p->n_win_big : p->n_win_small;
+    a->win_items = p->d_win_list[win_list];
+    a->win_count = (int)(p->win_list[win_list].size() / 4);
     tile_items = a->win_count;
   }
   const long end_tile = end_core + (win_part & WIN_TILES ? (long)rl.count[1] * tile_items : 0);

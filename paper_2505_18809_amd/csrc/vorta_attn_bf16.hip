@@ -1,9 +1,8 @@
-// bf16 routed attention for gfx950 (CDNA4): flash-style forward.  Two kernels: a software-
-// pipelined one (further down) that runs every segment of the layer call -- dense, core-set
-// and, gathering rows through the tile permutation, the window tiles -- and a simpler one
-// (first) for window tiles given as tile-ordered copies.  Common to both:
+// bf16 routed attention for gfx950 (CDNA4): flash-style forward.  One software-pipelined kernel runs
+// every segment -- dense, core-set and, reading rows through an index table (the tile permutation, or
+// the identity over tile-ordered copies), the window tiles.
 //
-// A wavefront owns 32 query rows; keys stream through LDS in blocks of 64 rows.  Both contractions run on
+// A wavefront owns 32 query rows; keys stream through LDS in blocks of 64 (or 32) rows.  Both contractions run on
 // v_mfma_f32_32x32x16_bf16 and are computed TRANSPOSED so that a lane owns one query:
 //     S^T = K Q^T      A = K rows from LDS (one ds_read_b128 per lane), B = Q^T kept in VGPRs
 //     O^T += V^T P^T   A = V^T read from row-major V with ds_read_b64_tr_b16, B = P^T
@@ -34,16 +33,7 @@ namespace {
 constexpr int D = 128;          // head dim
 constexpr int BM = 128;         // query rows per workgroup, window segment (4 wavefronts)
 constexpr int BM_LONG = 256;    // dense and core-set segments (8 wavefronts)
-constexpr int BN = 64;          // keys per LDS block
-// LDS row strides in elements (256 B of data + pad), chosen per access pattern with the LDS
-// bank-conflict counter: ds_read_b128 of 32 consecutive rows is conflict free at 272 B; the
-// ds_read_b64_tr_b16 pattern (per instruction 8 rows x 64 B) needs its rows 64 B apart modulo
-// 256 B, i.e. 320 B (at 288 B every such read takes twice the LDS cycles).
-constexpr int LSTR = 136;       // K block and output staging
-constexpr int VSTR = 160;       // V block
-constexpr int KTILE64 = BN * LSTR;
-constexpr int STAGE64_ELEMS = BN * (LSTR + VSTR);   // one K block + one V block
-constexpr int LDS_BYTES = 2 * STAGE64_ELEMS * 2;
+constexpr int LSTR = 136;       // output staging: row stride in elements (256 B of data + pad)
 constexpr float P_MAX = 256.f;  // largest probability (relative to the row reference) the softmax fast path accepts
 }  // namespace
 
@@ -51,13 +41,6 @@ __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
   f32x2 f = {lo, hi};
   bf16x2 b = __builtin_convertvector(f, bf16x2);
   return __builtin_bit_cast(unsigned, b);
-}
-
-__device__ __forceinline__ bf16x8 read_vt(const uint16_t* p_lo, const uint16_t* p_hi) {
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p_lo);
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p_hi);
-  const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_bit_cast(bf16x8, both);
 }
 
 __device__ __forceinline__ float max3(float a, float b, float c) {
@@ -72,10 +55,6 @@ __device__ __forceinline__ float max_xor32(float x) {
   float lo = x, hi = x;
   asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(lo), "+v"(hi));
   return __builtin_fmaxf(lo, hi);
-}
-
-__device__ __forceinline__ bf16x8 lds_frag(const uint16_t* p) {
-  return __builtin_bit_cast(bf16x8, *(const uint4*)p);
 }
 
 // LDS-address-space pointer flavours: a 32-bit base register plus immediate offsets.
@@ -98,272 +77,6 @@ __device__ __forceinline__ lds_ptr opaque(lds_ptr p) {
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 #define MFMA(a_, b_, c_) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_, b_, c_, 0, 0, 0)
-
-// Window segment over tile-ordered copies of Q, K, V (the staged call with q_t, k_t, v_t, o_t
-// given): a tile's key set is a short list of runs of consecutive rows.
-template <int NW>   // NW wavefronts per workgroup: 4 (two workgroups per CU)
-__global__ __launch_bounds__(64 * NW, 8 / NW) void attn_bf16_kernel(const AttnArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-  constexpr int STG_ROWS = 4 * NW, STG_PASSES = BN / STG_ROWS;   // staging: rows per pass, passes per block
-  const WorkItem w = decode_item<32 * NW, D>(a, xcd_item(blockIdx.x, gridDim.x, NW == 4));
-  const uint16_t* Q = (const uint16_t*)(w.seg == 0 ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
-  const uint16_t* K = (const uint16_t*)(w.seg == 0 ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
-  const uint16_t* V = (const uint16_t*)(w.seg == 0 ? a.v0 : w.seg == 1 ? a.vc : a.vt) + w.kv_off;
-  uint16_t* O = (uint16_t*)(w.seg == 0 ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
-  const unsigned row_stride = (unsigned)w.row_stride;   // rows * stride < 2^31 elements (checked on the host)
-  if (w.n_rows <= 0) return;       // q-block past the end of a clipped tile
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int l32 = lane & 31, g = lane >> 5;
-
-  // Q^T fragments: lane = query (l32), 8 consecutive dims per 16-wide k slice
-  bf16x8 qf[8];
-  {
-    const unsigned qrow = w.row(min(32 * wave + l32, w.n_rows - 1));
-    const uint16_t* qp = Q + qrow * row_stride + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qp + 16 * ks));
-  }
-
-  // global -> LDS staging: thread moves the 16-byte chunk (tid & 15) of rows (tid >> 4) + STG_ROWS i.
-  // The key rows of an item are the concatenation of its runs, cut into blocks of BN: a block
-  // that lies inside one run is addressed as (wave-uniform base of its first row) + (per-thread
-  // byte offset that never changes), so its loads need no per-block vector address arithmetic;
-  // a block that crosses into the next run(s) looks every row up in the run list, and the rows
-  // past the end of the last run repeat its last row (they are masked out of the softmax).
-  const int ld_row = tid >> 4, ld_col = (tid & 15) * 8;
-  const unsigned ld_off0 = 2u * ((unsigned)ld_row * row_stride + (unsigned)ld_col);   // bytes
-  const unsigned ld_step = 2u * STG_ROWS * row_stride;
-  uint4 kr0, kr1, kr2, kr3, vr0, vr1, vr2, vr3;
-#define FETCH_FULL(i_, kr_, vr_, kb_, vb_)                          \
-  kr_ = *(const uint4*)((kb_) + (ld_off0 + (i_)*ld_step));           \
-  vr_ = *(const uint4*)((vb_) + (ld_off0 + (i_)*ld_step));
-#define FETCH_TAIL(kr_, vr_, row_)                                                         \
-  {                                                                                        \
-    const unsigned off_ = (unsigned)(row_) * row_stride + ld_col;                          \
-    kr_ = *(const uint4*)(K + off_);                                                       \
-    vr_ = *(const uint4*)(V + off_);                                                       \
-  }
-#define FETCH(run_, start_, len_, pos_)                                                    \
-  if ((pos_) + BN <= (len_)) {                                                             \
-    const size_t base_ = (size_t)(unsigned)((start_) + (pos_)) * row_stride * 2u;          \
-    const char* kb_ = (const char*)K + base_;                                              \
-    const char* vb_ = (const char*)V + base_;                                              \
-    FETCH_FULL(0, kr0, vr0, kb_, vb_)                                                      \
-    FETCH_FULL(1, kr1, vr1, kb_, vb_)                                                      \
-    if constexpr (STG_PASSES == 4) {                                                       \
-      FETCH_FULL(2, kr2, vr2, kb_, vb_)                                                    \
-      FETCH_FULL(3, kr3, vr3, kb_, vb_)                                                    \
-    }                                                                                      \
-  } else {                                                                                 \
-    int rows_[STG_PASSES];                                                                 \
-    block_rows<STG_PASSES>(rl, run_, pos_, start_, len_, BN, ld_row, STG_ROWS, rows_);         \
-    FETCH_TAIL(kr0, vr0, rows_[0])                                                         \
-    FETCH_TAIL(kr1, vr1, rows_[1])                                                         \
-    if constexpr (STG_PASSES == 4) {                                                       \
-      FETCH_TAIL(kr2, vr2, rows_[2])                                                       \
-      FETCH_TAIL(kr3, vr3, rows_[3])                                                       \
-    }                                                                                      \
-  }
-#define STAGE(buf_)                                                       \
-  {                                                                       \
-    uint16_t* kb_ = smem + (buf_)*STAGE64_ELEMS + ld_row * LSTR + ld_col;   \
-    uint16_t* vb_ = smem + (buf_)*STAGE64_ELEMS + KTILE64 + ld_row * VSTR + ld_col; \
-    *(uint4*)(kb_) = kr0;                                                 \
-    *(uint4*)(kb_ + STG_ROWS * LSTR) = kr1;                               \
-    *(uint4*)(vb_) = vr0;                                                 \
-    *(uint4*)(vb_ + STG_ROWS * VSTR) = vr1;                               \
-    if constexpr (STG_PASSES == 4) {                                      \
-      *(uint4*)(kb_ + 2 * STG_ROWS * LSTR) = kr2;                         \
-      *(uint4*)(kb_ + 3 * STG_ROWS * LSTR) = kr3;                         \
-      *(uint4*)(vb_ + 2 * STG_ROWS * VSTR) = vr2;                         \
-      *(uint4*)(vb_ + 3 * STG_ROWS * VSTR) = vr3;                         \
-    }                                                                     \
-  }
-  const RunList rl(w);
-  auto run_start = [&](int r) { return rl.start(r); };
-  auto run_len = [&](int r) { return rl.len(r); };
-
-  int n_keys = 0;
-  for (int r = 0; r < w.n_runs; ++r) n_keys += run_len(r);
-  const int n_blocks = (n_keys + BN - 1) / BN;
-
-  f32x16 o0, o1, o2, o3;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) { o0[v] = 0.f; o1[v] = 0.f; o2[v] = 0.f; o3[v] = 0.f; }
-  float m_run = -INFINITY, l_run = 0.f;
-  const float c = a.scale * 1.4426950408889634f;
-
-  // fetch cursor (run, offset in it, its first row and length): the next block to request
-  int fr = 0, fpos = 0, fstart = run_start(0), flen = run_len(0), left = n_keys;
-  auto advance = [&]() {
-    fpos += BN;
-    while (fpos >= flen && fr + 1 < w.n_runs) {
-      fpos -= flen;
-      ++fr;
-      fstart = run_start(fr);
-      flen = run_len(fr);
-    }
-  };
-  // Prologue: block 0 goes to LDS, the rows of block 1 wait in the staging registers.  Iteration
-  // it then writes block it + 1 to the other buffer first thing and requests block it + 2, so
-  // a row has a whole iteration to arrive.
-  FETCH(fr, fstart, flen, fpos)
-  advance();
-  STAGE(0)
-  if (n_blocks > 1) {
-    FETCH(fr, fstart, flen, fpos)
-    advance();
-  }
-  __syncthreads();
-
-  // per-lane LDS read offsets
-  const uint16_t* k_rd = smem + l32 * LSTR + 8 * g;
-  const int t16 = lane & 15, blk = lane >> 4;
-  const uint16_t* v_rd = smem + KTILE64 + (4 * g + (t16 >> 2)) * VSTR + 16 * (blk & 1) + 4 * (t16 & 3);
-
-  for (int it = 0; it < n_blocks; ++it) {
-    if (it + 1 < n_blocks) { STAGE((it + 1) & 1) }        // rows requested an iteration ago
-    if (it + 2 < n_blocks) {
-      FETCH(fr, fstart, flen, fpos)
-      advance();
-    }
-
-    const int n_valid = min(BN, left);
-    const uint16_t* kp = k_rd + (it & 1) * STAGE64_ELEMS;
-    const uint16_t* vp = v_rd + (it & 1) * STAGE64_ELEMS;
-
-    // ---- S^T = K Q^T for keys [0,32) and [32,64) of the block
-    f32x16 s0, s1;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) { s0[v] = 0.f; s1[v] = 0.f; }
-    {
-      bf16x8 f0 = lds_frag(kp), f1 = lds_frag(kp + 32 * LSTR);
-      bf16x8 f2 = lds_frag(kp + 16), f3 = lds_frag(kp + 32 * LSTR + 16);
-      bf16x8 f4 = lds_frag(kp + 32), f5 = lds_frag(kp + 32 * LSTR + 32);
-      bf16x8 f6 = lds_frag(kp + 48), f7 = lds_frag(kp + 32 * LSTR + 48);
-      s0 = MFMA(f0, qf[0], s0); s1 = MFMA(f1, qf[0], s1);
-      f0 = lds_frag(kp + 64); f1 = lds_frag(kp + 32 * LSTR + 64);
-      s0 = MFMA(f2, qf[1], s0); s1 = MFMA(f3, qf[1], s1);
-      f2 = lds_frag(kp + 80); f3 = lds_frag(kp + 32 * LSTR + 80);
-      s0 = MFMA(f4, qf[2], s0); s1 = MFMA(f5, qf[2], s1);
-      f4 = lds_frag(kp + 96); f5 = lds_frag(kp + 32 * LSTR + 96);
-      s0 = MFMA(f6, qf[3], s0); s1 = MFMA(f7, qf[3], s1);
-      f6 = lds_frag(kp + 112); f7 = lds_frag(kp + 32 * LSTR + 112);
-      s0 = MFMA(f0, qf[4], s0); s1 = MFMA(f1, qf[4], s1);
-      s0 = MFMA(f2, qf[5], s0); s1 = MFMA(f3, qf[5], s1);
-      s0 = MFMA(f4, qf[6], s0); s1 = MFMA(f5, qf[6], s1);
-      s0 = MFMA(f6, qf[7], s0); s1 = MFMA(f7, qf[7], s1);
-      // keep the fragment reads ahead of their use: 8 reads in flight, then 2 per MFMA pair
-      __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-    }
-    if (n_valid < BN) {   // run tail: element v of a tile is key 8 (v >> 2) + 4 g + (v & 3)
-      const int nv0 = n_valid - 4 * g, nv1 = nv0 - 32;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        if (8 * (v >> 2) + (v & 3) >= nv0) s0[v] = -INFINITY;
-        if (8 * (v >> 2) + (v & 3) >= nv1) s1[v] = -INFINITY;
-      }
-    }
-
-    // ---- softmax against a lagging row reference m_run (this lane's query, its 32 keys; the
-    // other 32 are in lane ^ 32).  The probabilities go straight to bf16 pairs in B-operand
-    // order: k slice kk covers keys [16 kk, 16 kk + 16).  The row sums are plain fp32 adds of
-    // the probabilities (not v_dot2c_f32_bf16 on the packed pairs: see the pipelined kernel).
-    const float mc = m_run * c;
-    unsigned u0[8], u1[8];
-    float ps0 = 0.f, ps1 = 0.f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float a0 = __builtin_amdgcn_exp2f(fmaf(s0[2 * j], c, -mc)), a1 = __builtin_amdgcn_exp2f(fmaf(s0[2 * j + 1], c, -mc));
-      const float b0 = __builtin_amdgcn_exp2f(fmaf(s1[2 * j], c, -mc)), b1 = __builtin_amdgcn_exp2f(fmaf(s1[2 * j + 1], c, -mc));
-      u0[j] = pack_bf16(a0, a1);
-      u1[j] = pack_bf16(b0, b1);
-      ps0 += a0 + a1;
-      ps1 += b0 + b1;
-    }
-    float ps = ps0 + ps1;
-    // Reference check: no probability exceeds its row sum, so ps <= P_MAX proves that no score
-    // of the block was more than log2(P_MAX) above the reference.  Otherwise (always for the
-    // first block, whose reference is -inf; afterwards only when a row maximum jumps) the block
-    // is redone against the true running maximum: new reference, accumulators and sum rescaled
-    // to it, probabilities recomputed from the scores.
-    if (__any(!(ps <= P_MAX))) {
-      float mx = max3(s0[0], s1[0], s0[1]);
-#pragma unroll
-      for (int v = 1; v < 15; ++v) mx = max3(mx, s1[v], s0[v + 1]);
-      mx = max_xor32(fmaxf(mx, s1[15]));
-      const float m_new = fmaxf(m_run, mx);
-      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);   // 0 for the first block
-      m_run = m_new;
-      const float mc2 = m_new * c;
-      ps = 0.f;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float a0 = __builtin_amdgcn_exp2f(fmaf(s0[2 * j], c, -mc2)), a1 = __builtin_amdgcn_exp2f(fmaf(s0[2 * j + 1], c, -mc2));
-        const float b0 = __builtin_amdgcn_exp2f(fmaf(s1[2 * j], c, -mc2)), b1 = __builtin_amdgcn_exp2f(fmaf(s1[2 * j + 1], c, -mc2));
-        u0[j] = pack_bf16(a0, a1);
-        u1[j] = pack_bf16(b0, b1);
-        ps += (a0 + a1) + (b0 + b1);
-      }
-      l_run *= alpha;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) { o0[v] *= alpha; o1[v] *= alpha; o2[v] *= alpha; o3[v] *= alpha; }
-    }
-    l_run += ps;
-    bf16x8 pf[4];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      pf[h] = __builtin_bit_cast(bf16x8, make_uint4(u0[4 * h], u0[4 * h + 1], u0[4 * h + 2], u0[4 * h + 3]));
-      pf[2 + h] = __builtin_bit_cast(bf16x8, make_uint4(u1[4 * h], u1[4 * h + 1], u1[4 * h + 2], u1[4 * h + 3]));
-    }
-
-    // ---- O^T += V^T P^T
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const uint16_t* vk = vp + 16 * kk * VSTR;
-      const bf16x8 t0 = read_vt(vk, vk + 8 * VSTR);
-      const bf16x8 t1 = read_vt(vk + 32, vk + 8 * VSTR + 32);
-      const bf16x8 t2 = read_vt(vk + 64, vk + 8 * VSTR + 64);
-      const bf16x8 t3 = read_vt(vk + 96, vk + 8 * VSTR + 96);
-      o0 = MFMA(t0, pf[kk], o0);
-      o1 = MFMA(t1, pf[kk], o1);
-      o2 = MFMA(t2, pf[kk], o2);
-      o3 = MFMA(t3, pf[kk], o3);
-    }
-
-    __syncthreads();
-    left -= BN;
-  }
-
-  // ---- epilogue: normalise, transpose through LDS, store whole rows
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  const float inv = 1.f / l_tot;
-  uint16_t* st = smem + wave * 32 * LSTR;
-#define STORE_TILE(dt_, acc_)                                                        \
-  _Pragma("unroll") for (int q4 = 0; q4 < 4; ++q4) {                                 \
-    uint2 u;                                                                         \
-    u.x = pack_bf16(acc_[4 * q4] * inv, acc_[4 * q4 + 1] * inv);                     \
-    u.y = pack_bf16(acc_[4 * q4 + 2] * inv, acc_[4 * q4 + 3] * inv);                 \
-    *(uint2*)(st + l32 * LSTR + 32 * (dt_) + 8 * q4 + 4 * g) = u;                    \
-  }
-  STORE_TILE(0, o0) STORE_TILE(1, o1) STORE_TILE(2, o2) STORE_TILE(3, o3)
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int row = (lane >> 4) + 4 * i;
-    if (32 * wave + row < w.n_rows)
-      *(uint4*)(O + (unsigned)w.row(32 * wave + row) * row_stride + (lane & 15) * 8) =
-          *(const uint4*)(st + row * LSTR + (lane & 15) * 8);
-  }
-}
-
 
 // ------------------------------------------------------------------------------------------
 // Software-pipelined kernel (described for its main form: 8 wavefronts, 256 query rows, 64-key
@@ -412,10 +125,18 @@ constexpr int LEAD = 2;                  // slots between a fragment request and
 
 __device__ __forceinline__ float elem_of(const f32x16& t0, const f32x16& t1, int e) { return e < 16 ? t0[e] : t1[e - 16]; }
 
-// WIN: window items read through the tile permutation: the item's rows are tile-order indices
-// into the caller's tensors -- every query, key, value and output row goes through a.tok_of
-// (tile-order index -> token index) instead of living in tile-ordered copies; the key rows are
-// the concatenation of the tile's runs cut into blocks.  The token indices of a key block are
+// One 32 x 32 tile of O^T, normalised, as bf16 into the row staging `st` of the wavefront.
+#define STORE_TILE(dt_, acc_)                                                        \
+  _Pragma("unroll") for (int q4 = 0; q4 < 4; ++q4) {                                 \
+    uint2 u;                                                                         \
+    u.x = pack_bf16(acc_[4 * q4] * inv, acc_[4 * q4 + 1] * inv);                     \
+    u.y = pack_bf16(acc_[4 * q4 + 2] * inv, acc_[4 * q4 + 3] * inv);                 \
+    *(uint2*)(st + l32 * LSTR + 32 * (dt_) + 8 * q4 + 4 * g) = u;                    \
+  }
+
+// WIN: window items: query and output rows through a.win_row, key and value rows -- the concatenation of
+// the tile's runs, cut into blocks -- through a.tok_of (tile-order index -> token index in the caller's
+// tensors; the identity where tile-ordered copies are given).  The token indices of a key block are
 // looked up one block ahead of its rows, so the two dependent loads never wait for each other
 // inside one iteration.
 // NWV: wavefronts per workgroup.  8: 256 query rows, 64-key blocks, one workgroup per CU (dense,
@@ -442,10 +163,11 @@ __global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const
   constexpr int V_BASE = K_RING * K_STAGE;  // the K ring, then the V ring
   auto vstage = [](int b) { return (int)((unsigned)b % (unsigned)V_RING); };   // ring stage of V block b (K: b & 3)
   const WorkItem w = decode_item<32 * NWV, D>(a, xcd_item(blockIdx.x, gridDim.x, WIN));
-  const uint16_t* Q = (const uint16_t*)(w.seg == 0 || WIN ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
-  const uint16_t* K = (const uint16_t*)(w.seg == 0 || WIN ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
-  const uint16_t* V = (const uint16_t*)(w.seg == 0 || WIN ? a.v0 : w.seg == 1 ? a.vc : a.vt) + w.kv_off;
-  uint16_t* O = (uint16_t*)(w.seg == 0 || WIN ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
+  const bool user = WIN ? a.win_gather != 0 : w.seg == 0;     // rows of the caller's tensors
+  const uint16_t* Q = (const uint16_t*)(user ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
+  const uint16_t* K = (const uint16_t*)(user ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
+  const uint16_t* V = (const uint16_t*)(user ? a.v0 : w.seg == 1 ? a.vc : a.vt) + w.kv_off;
+  uint16_t* O = (uint16_t*)(user ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
   const unsigned row_stride = (unsigned)w.row_stride;
 
   if (w.n_rows <= 0) return;       // no rows: second half of a split item, or a q-block past the end of a clipped tile
@@ -455,8 +177,8 @@ __global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const
 
   bf16x8 qf[8];
   {
-    unsigned qrow = w.row(min(32 * wave + l32, w.n_rows - 1));
-    if (WIN) qrow = (unsigned)a.tok_of[qrow];
+    unsigned qrow = w.row0 + min(32 * wave + l32, w.n_rows - 1);
+    if (WIN) qrow = (unsigned)a.win_row[qrow];
     const uint16_t* qp = Q + qrow * row_stride + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qp + 16 * ks));
@@ -832,8 +554,8 @@ __global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const
   unsigned orow[8];                // looked up together, ahead of the barrier
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    orow[i] = w.row(min(32 * wave + (lane >> 4) + 4 * i, w.n_rows - 1));
-    if (WIN) orow[i] = (unsigned)a.tok_of[orow[i]];
+    orow[i] = w.row0 + min(32 * wave + (lane >> 4) + 4 * i, w.n_rows - 1);
+    if (WIN) orow[i] = (unsigned)a.win_row[orow[i]];
   }
   STORE_TILE(0, o[0]) STORE_TILE(1, o[1]) STORE_TILE(2, o[2]) STORE_TILE(3, o[3])
   __syncthreads();
@@ -873,6 +595,12 @@ static int set_lds_limit(const void* kernel, const char* name, int bytes) {
   return VORTA_OK;
 }
 
+static int launched() {
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(VORTA_EHIP, "launch of attn_bf16 kernels: %s", hipGetErrorString(e));
+  return VORTA_OK;
+}
+
 // mix: the launch is the full-attention branch of Eq. 5 over the heads of route 0 and blends the
 // other two branches in (their results must be complete on the stream).  win_text = false leaves
 // out the text rows of the window heads (under Eq. 5 they equal the full-attention branch's).
@@ -881,8 +609,7 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
   static std::once_flag once;
   static int attr_rc = VORTA_OK;
   std::call_once(once, [] {
-    attr_rc = set_lds_limit((const void*)attn_bf16_kernel<4>, "attn_bf16_kernel<4>", LDS_BYTES);
-    if (!attr_rc) attr_rc = set_lds_limit((const void*)attn_bf16_pipe_kernel<false, 8>, "attn_bf16_pipe_kernel<false, 8>", pipe_lds_bytes(8));
+    attr_rc = set_lds_limit((const void*)attn_bf16_pipe_kernel<false, 8>, "attn_bf16_pipe_kernel<false, 8>", pipe_lds_bytes(8));
     if (!attr_rc) attr_rc = set_lds_limit((const void*)attn_bf16_pipe_kernel<false, 8, true>, "attn_bf16_pipe_kernel<false, 8, true>", pipe_lds_bytes(8));
     if (!attr_rc) attr_rc = set_lds_limit((const void*)attn_bf16_pipe_kernel<true, 8>, "attn_bf16_pipe_kernel<true, 8>", pipe_lds_bytes(8));
     if (!attr_rc) attr_rc = set_lds_limit((const void*)attn_bf16_pipe_kernel<true, 4>, "attn_bf16_pipe_kernel<true, 4>", pipe_lds_bytes(4));
@@ -904,39 +631,19 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
     else
       hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8>), dim3(a.end_tile + n_split), dim3(512), pipe_lds_bytes(8), (hipStream_t)stream, a, NoMix());
   }
-  // Window tiles.  Gathered from the caller's tensors (no tile-ordered copies given): the
-  // pipelined kernel again -- tiles of more than 128 tokens in 256-row workgroups of 8
-  // wavefronts, smaller tiles in 128-row workgroups of 4 wavefronts on 32-key blocks, two per CU.
-  // Over tile-ordered copies: the plain 128-row kernel.
-  const bool win_long = a.win_gather && p->tile_tokens > BM;
-  const bool grouped = a.win_gather && !win_long && rl.count[1] > 0;
-  if (grouped) {
-    // tiles of at most 128 tokens, gathered: the plan's grouped items -- those of more than 128
-    // rows (two or three tiles with one key set) on the 8-wavefront instance, the rest on the
-    // 4-wavefront one
-    if (int rc = fill_attn_args(p, win_rl, io, BM_LONG, WIN_TILES, &a, 0)) return rc;
-    if (a.end_tile > 0) {
-      const int n_split = std::min(a.end_tile, p->n_cus / 2);
-      a.split_from = a.end_tile - n_split;
-      hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + n_split), dim3(512), pipe_lds_bytes(8), (hipStream_t)stream, a, NoMix());
-    }
-    if (int rc = fill_attn_args(p, win_rl, io, BM, WIN_TILES, &a, 1)) return rc;
-    if (a.end_tile > 0)
-      hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 4>), dim3(a.end_tile), dim3(256), pipe_lds_bytes(4), (hipStream_t)stream, a, NoMix());
-  } else {
-    if (int rc = fill_attn_args(p, win_rl, io, win_long ? BM_LONG : BM, WIN_TILES, &a)) return rc;
-    if (a.end_tile > 0 && win_long) {
-      const int n_split = std::min(a.end_tile, p->n_cus / 2);
-      a.split_from = a.end_tile - n_split;
-      hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + n_split), dim3(512), pipe_lds_bytes(8), (hipStream_t)stream, a, NoMix());
-    } else if (a.end_tile > 0) {
-      hipLaunchKernelGGL((attn_bf16_kernel<4>), dim3(a.end_tile), dim3(256), LDS_BYTES, (hipStream_t)stream, a);
-    }
+  // Window tiles: the plan's items of more than 128 rows on the 8-wavefront instance (256 rows, 64-key
+  // blocks, one workgroup per CU), the rest on the 4-wavefront one (128 rows, 32-key blocks, two per CU).
+  if (rl.count[1] == 0) return launched();
+  if (int rc = fill_attn_args(p, win_rl, io, BM_LONG, WIN_TILES, &a, 0)) return rc;
+  if (a.end_tile > 0) {
+    const int n_split = std::min(a.end_tile, p->n_cus / 2);
+    a.split_from = a.end_tile - n_split;
+    hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + n_split), dim3(512), pipe_lds_bytes(8), (hipStream_t)stream, a, NoMix());
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(VORTA_EHIP, "launch of attn_bf16 kernels: %s", hipGetErrorString(e));
-  return VORTA_OK;
+  if (int rc = fill_attn_args(p, win_rl, io, BM, WIN_TILES, &a, 1)) return rc;
+  if (a.end_tile > 0)
+    hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 4>), dim3(a.end_tile), dim3(256), pipe_lds_bytes(4), (hipStream_t)stream, a, NoMix());
+  return launched();
 }
 
 }  // namespace vorta
-

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_f32_kernel(const AttnArg
   auto row_off = [&](int row) { return (unsigned)row * (unsigned)w.row_stride; };
   unsigned my_off;
   {
-    int row = w.row(min(m, w.n_rows - 1));
+    int row = w.row0 + min(m, w.n_rows - 1);
     if (gather) row = a.tok_of[row];
     my_off = row_off(row);
   }

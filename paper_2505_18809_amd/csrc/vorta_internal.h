@@ -26,18 +26,25 @@ struct vorta_plan {
   std::vector<int32_t> runs;     // [n_tiles][max_runs][2]
   std::vector<int32_t> n_runs;   // [n_tiles]
   std::vector<int32_t> slot_base;  // [n_buckets + 1]
-  // window work items (tiles of at most 128 tokens): tiles with identical key sets grouped, up to
-  // three tiles and 256 rows per item; {tile, tile, tile, count} each, the n_win_big items of more
+  // what vorta_window_items reports (tiles of at most 128 tokens): tiles with identical key sets, up to
+  // three tiles and 256 rows together; {tile, tile, tile, count} each, the n_win_big entries of more
   // than 128 rows first, then the n_win_small others.  Empty when a tile holds more than 128 tokens.
   std::vector<int32_t> win_items;
   int n_win_big = 0, n_win_small = 0;
+  // window work items of the bf16 kernels: the rows of all tiles with one key set are one sequence (win_rows
+  // holds these sequences one after the other, as tile-order rows), cut into blocks whatever the tile
+  // borders.  {first, n_rows, tile, 0}: n_rows places of win_rows from `first`, keys as tile `tile` sees
+  // them.  List 0: blocks of 129 to 256 rows; list 1: what is left of a sequence, at most 128 rows.
+  std::vector<int32_t> win_rows;   // [L]
+  std::vector<int32_t> win_list[2];
   // rotary embedding: (cos, sin) of position * rate for every position of every axis,
   // [F][pairs_F] then [H][pairs_H] then [W][pairs_W]; empty without rope_dims
   bool rope = false;
   std::vector<float> rope_cs;
 
-  // device copies of runs / n_runs / slot_base and the tile-order -> sequence-order token table
-  // (identity for the text rows), uploaded on first device use
+  // device tables, all in one allocation, uploaded on first device use: copies of the tables above, the
+  // tile-order -> sequence-order token table (identity for the text rows), that table taken at win_rows, and
+  // 0, 1, 2, ... for tile-ordered copies, whose rows are their own indices
   std::mutex mu;
   bool on_device = false;
   int device = -1;
@@ -46,9 +53,13 @@ struct vorta_plan {
   int32_t* d_n_runs = nullptr;
   int32_t* d_slot_base = nullptr;
   int32_t* d_tok_of = nullptr;   // [N]
+  int32_t* d_iota = nullptr;     // [N]
+  int32_t* d_win_rows = nullptr; // [L]
+  int32_t* d_win_tok = nullptr;  // [L]
   int32_t* d_tile_row0 = nullptr;   // [n_tiles + 1]
   float* d_rope_cs = nullptr;
-  int32_t* d_win_items = nullptr;
+  int32_t* d_win_list[2] = {nullptr, nullptr};
+  void* d_tables = nullptr;      // the allocation
 };
 
 namespace vorta {

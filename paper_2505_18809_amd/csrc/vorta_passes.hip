@@ -24,44 +24,44 @@ static int launch_status(const char* what) {
   return VORTA_OK;
 }
 
-// Uploads one host table; the device pointer is registered in *slot before the copy so that a
-// failure anywhere leaves it for release_device_tables.
-template <typename T>
-static int upload_table(const std::vector<T>& host, T** slot) {
-  VORTA_HIP(hipMalloc(slot, host.size() * sizeof(T)));
-  VORTA_HIP(hipMemcpy(*slot, host.data(), host.size() * sizeof(T), hipMemcpyHostToDevice));
-  return VORTA_OK;
-}
-
 static void release_device_tables(vorta_plan* p) {
-  int32_t** tables[] = {&p->d_runs, &p->d_n_runs, &p->d_slot_base, &p->d_tok_of, &p->d_tile_row0};
-  for (int32_t** t : tables) {
-    if (*t) (void)hipFree(*t);
-    *t = nullptr;
-  }
-  if (p->d_rope_cs) (void)hipFree(p->d_rope_cs);
-  p->d_rope_cs = nullptr;
-  if (p->d_win_items) (void)hipFree(p->d_win_items);
-  p->d_win_items = nullptr;
+  if (p->d_tables) (void)hipFree(p->d_tables);
+  p->d_tables = nullptr;
 }
 // vorta_plan_destroy lives with the host code; it frees the device tables through this hook
 static const bool release_hook_set = (g_release_device_tables = release_device_tables, true);
 
+// All tables of the plan in one allocation and one copy, each 256-byte aligned.
 static int upload_device_tables(vorta_plan* p, int dev) {
-  if (int rc = upload_table(p->runs, &p->d_runs)) return rc;
-  if (int rc = upload_table(p->n_runs, &p->d_n_runs)) return rc;
-  if (int rc = upload_table(p->slot_base, &p->d_slot_base)) return rc;
-  if (int rc = upload_table(p->tile_row0, &p->d_tile_row0)) return rc;
   // tile-order row -> token (the inverse tile permutation; text rows keep their place)
-  std::vector<int32_t> perm((size_t)p->L), tok_of((size_t)p->N);
+  std::vector<int32_t> perm((size_t)p->L), tok_of((size_t)p->N), iota((size_t)p->N), win_tok((size_t)p->L);
   if (int rc = vorta_tile_permutation(p, perm.data())) return rc;
   for (int64_t i = 0; i < p->L; ++i) tok_of[perm[i]] = (int32_t)i;
   for (int64_t i = p->L; i < p->N; ++i) tok_of[i] = (int32_t)i;
-  if (int rc = upload_table(tok_of, &p->d_tok_of)) return rc;
-  if (p->rope)
-    if (int rc = upload_table(p->rope_cs, &p->d_rope_cs)) return rc;
-  if (!p->win_items.empty())
-    if (int rc = upload_table(p->win_items, &p->d_win_items)) return rc;
+  for (int64_t i = 0; i < p->N; ++i) iota[i] = (int32_t)i;
+  for (int64_t i = 0; i < p->L; ++i) win_tok[i] = tok_of[p->win_rows[i]];
+  struct Table {
+    const void* host;
+    size_t bytes;
+    void** slot;
+  };
+  auto table = [](const auto& v, auto** slot) { return Table{v.data(), v.size() * sizeof(v[0]), (void**)slot}; };
+  const Table tables[] = {
+      table(p->runs, &p->d_runs),         table(p->n_runs, &p->d_n_runs),     table(p->slot_base, &p->d_slot_base),
+      table(p->tile_row0, &p->d_tile_row0), table(tok_of, &p->d_tok_of),      table(iota, &p->d_iota),
+      table(p->win_rows, &p->d_win_rows), table(win_tok, &p->d_win_tok),      table(p->win_list[0], &p->d_win_list[0]),
+      table(p->win_list[1], &p->d_win_list[1]), table(p->rope_cs, &p->d_rope_cs)};
+  size_t total = 0;
+  for (const Table& t : tables) total += (t.bytes + 255) & ~(size_t)255;
+  std::vector<char> image(total);
+  VORTA_HIP(hipMalloc(&p->d_tables, total));
+  size_t at = 0;
+  for (const Table& t : tables) {
+    if (t.bytes) std::memcpy(image.data() + at, t.host, t.bytes);
+    *t.slot = (char*)p->d_tables + at;
+    at += (t.bytes + 255) & ~(size_t)255;
+  }
+  VORTA_HIP(hipMemcpy(p->d_tables, image.data(), total, hipMemcpyHostToDevice));
   int cus = 0;
   VORTA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   if (cus > 0) p->n_cus = cus;

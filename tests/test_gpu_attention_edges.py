@@ -69,3 +69,31 @@ def test_fp32_row_reference_follows_scores_far_beyond_its_slack():
     u[3] = 1.0
     k = (k + ramp * u).contiguous()
     layer_error(cfg, q, k, v, 1, lambda want: 1e-5 * np.maximum(1.0, np.abs(want)))
+
+
+@pytest.mark.parametrize("layout", [1, 0])
+@pytest.mark.parametrize("grid,n_text", [((1, 1, 1), 0), ((1, 4, 32), 0), ((1, 3, 43), 5), ((2, 8, 16), 0), ((1, 1, 257), 3),
+                                         ((4, 8, 12), 0), ((5, 7, 11), 70)])
+def test_bf16_window_rows_cut_across_tile_borders(grid, n_text, layout):
+    """Windows that cover the grid: every tile (of 1 to 6 tokens, clipped ones among them) has one key set, so
+    the rows of all tiles are one sequence of 1, 128, 129, 256, 257, 384 and 385 rows, cut into blocks of
+    256 with a rest of up to 128.  Gathered from the caller's tensors and over tile-ordered copies."""
+    cfg = LayerConfig(f"cut{grid}", grid, 3, 128, "bf16", (1, 2, 3), (99, 99, 999), seed=17, n_text=n_text, fixed_routes=(1, 0, 1))
+    say(cfg.name)
+    q, k, v = make_qkv(cfg, DEV, layout)
+    layer_error(cfg, q, k, v, layout, lambda want: 2e-2)
+    plan = vorta.plan_for(cfg, layout=layout)
+    r = cfg.fixed_routes
+    q_t, k_t, v_t = (vorta.vorta_reorder_to_tiles(plan, t, r) for t in (q, k, v))
+    o_t, out = torch.empty_like(q_t), torch.zeros_like(q)
+    vorta.vorta_attention_routed(plan, r, q=q, k=k, v=v, out=out, q_t=q_t, k_t=k_t, v_t=v_t, o_t=o_t)
+    vorta.vorta_scatter_back(plan, r, o_t, None, None, out)
+    torch.cuda.synchronize()
+    # video rows: the same items over the same rows, read from other places.  Text rows of the window heads meet
+    # all keys in sequence order here and in tile order there: equal up to the rounding of P and the output.
+    layer = vorta.vorta_routed_attention_layer(plan, q, k, v, r)
+    if layout == 0:
+        out, layer = out.transpose(0, 1), layer.transpose(0, 1)
+    n = cfg.n_video
+    assert torch.equal(out[:, :n], layer[:, :n]) and torch.equal(out[1], layer[1])
+    assert n_text == 0 or (out[:, n:].float() - layer[:, n:].float()).abs().max().item() <= 2e-2
