@@ -125,6 +125,28 @@ constexpr int LEAD = 2;                  // slots between a fragment request and
 
 __device__ __forceinline__ float elem_of(const f32x16& t0, const f32x16& t1, int e) { return e < 16 ? t0[e] : t1[e - 16]; }
 
+// Eq. 5 for one 16-byte chunk of the row of token tok: mine = the full-attention branch's, there = what `out`
+// holds, the sliding-tile branch's if the token is a video token (see MixArgs).
+__device__ __forceinline__ uint4 mix_row(const AttnArgs& a, const MixArgs& mx, int head, int tok, int chunk,
+                                         uint4 mine, uint4 there) {
+  const bool video = tok < a.L;
+  const int slot = video ? mx.assign[(long)head * a.L + tok] : mx.Lc + (tok - a.L);
+  const uint4 core = *(const uint4*)((const uint16_t*)mx.oc + ((long)head * a.Nc + slot) * D + chunk * 8);
+  const uint4 slide = make_uint4(video ? there.x : mine.x, video ? there.y : mine.y, video ? there.z : mine.z, video ? there.w : mine.w);
+  const float a1 = mx.alpha[head][0], a2 = mx.alpha[head][1], a3 = mx.alpha[head][2];
+  const unsigned f[4] = {mine.x, mine.y, mine.z, mine.w}, s2[4] = {slide.x, slide.y, slide.z, slide.w},
+                 c3[4] = {core.x, core.y, core.z, core.w};
+  unsigned r[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float lo = a1 * __uint_as_float(f[e] << 16) + a2 * __uint_as_float(s2[e] << 16) + a3 * __uint_as_float(c3[e] << 16);
+    const float hi = a1 * __uint_as_float(f[e] & 0xffff0000u) + a2 * __uint_as_float(s2[e] & 0xffff0000u) +
+                     a3 * __uint_as_float(c3[e] & 0xffff0000u);
+    r[e] = pack_bf16(lo, hi);
+  }
+  return make_uint4(r[0], r[1], r[2], r[3]);
+}
+
 // One 32 x 32 tile of O^T, normalised, as bf16 into the row staging `st` of the wavefront.
 #define STORE_TILE(dt_, acc_)                                                        \
   _Pragma("unroll") for (int q4 = 0; q4 < 4; ++q4) {                                 \
@@ -260,8 +282,8 @@ __global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const
   // memory operations complete -- returns as soon as the indices are there, whatever the row
   // loads behind them are doing (the counter retires in order).
   auto win_idx = [&]() {           // token indices of the noted block
-    int rows[2];
-    block_rows<2>(rl, wi_run, wi_pos, wi_start, wi_len, KB, ld_row, STG_STEP, rows);
+    int key[2] = {ld_row, ld_row + STG_STEP}, rows[2];
+    block_rows(rl, wi_run, wi_pos, wi_start, wi_len, KB, key, rows);
     asm volatile("global_load_dword %0, %2, %4\n\tglobal_load_dword %1, %3, %4"
                  : "=&v"(gi0), "=&v"(gi1)
                  : "v"(rows[0] * 4), "v"(rows[1] * 4), "s"(a.tok_of)
@@ -565,26 +587,372 @@ __global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const
     if (32 * wave + row < w.n_rows) {
       uint4 mine = *(const uint4*)(st + row * LSTR + (lane & 15) * 8);
       uint4* dst = (uint4*)(O + orow[i] * row_stride + (lane & 15) * 8);
-      if constexpr (MIX) {
-        const int tok = (int)orow[i];
-        const bool video = tok < a.L;
-        const int slot = video ? mx.assign[(long)w.head * a.L + tok] : mx.Lc + (tok - a.L);
-        const uint4 core = *(const uint4*)((const uint16_t*)mx.oc + ((long)w.head * a.Nc + slot) * D + (lane & 15) * 8);
-        const uint4 slide = video ? *dst : mine;
-        const float a1 = mx.alpha[w.head][0], a2 = mx.alpha[w.head][1], a3 = mx.alpha[w.head][2];
-        const unsigned f[4] = {mine.x, mine.y, mine.z, mine.w}, s2[4] = {slide.x, slide.y, slide.z, slide.w},
-                       c3[4] = {core.x, core.y, core.z, core.w};
-        unsigned r[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float lo = a1 * __uint_as_float(f[e] << 16) + a2 * __uint_as_float(s2[e] << 16) + a3 * __uint_as_float(c3[e] << 16);
-          const float hi = a1 * __uint_as_float(f[e] & 0xffff0000u) + a2 * __uint_as_float(s2[e] & 0xffff0000u) +
-                           a3 * __uint_as_float(c3[e] & 0xffff0000u);
-          r[e] = pack_bf16(lo, hi);
-        }
-        mine = make_uint4(r[0], r[1], r[2], r[3]);
-      }
+      if constexpr (MIX) mine = mix_row(a, mx, w.head, (int)orow[i], lane & 15, mine, *dst);
       *dst = mine;
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Split kernel: launches too small to fill the chip with 256-row items.  A workgroup owns 64 query rows, two
+// sets of 32, and the KS wavefronts of a set share the key stream: a superblock of 32 KS keys is one
+// 32-key block per wavefront, and the KS (reference, sum, accumulator) triples of a row are merged through
+// LDS at the end, in a fixed order.  KS = 4: one workgroup of 8 wavefronts per CU; KS = 2: two workgroups
+// of 4, one's prologue, merge and barriers under the other's matrix instructions.
+//
+// The iteration is the pipelined kernel's with 32-key blocks (16 slots), with these differences:
+//   * rings of two stages (KS = 4: K 65 KB, V 68 KB) and two barriers per iteration: K(i+2) is requested
+//     where iteration i begins, into the stage K(i) has left, V(i+1) in its middle, into the stage that
+//     V(i-1) has just left, and each is waited for one and a half iterations later, where its first reader is.
+//   * every row goes through an index table -- the tile permutation for window items, 0, 1, 2, ... for the
+//     others -- so that one launch carries all items of the layer, longest first.
+// Bound: the barriers.  The wavefronts of a workgroup reach its two barriers together, and what they do
+// around them (fragment requests, reference check, packing) no matrix instruction covers: about 2,000
+// cycles per 128-key superblock against 1,024 of matrix instructions (2,600 with one barrier, all loads
+// requested and waited for in the same iteration, and the addresses ahead of the slots).
+// 3,072-token layer, 8 heads on all routes: 88 -> 52 us; at 9,216 tokens, 24 heads, 477 -> 445 us.
+// ------------------------------------------------------------------------------------------
+namespace {
+constexpr int BM_SPLIT = 64;
+constexpr int split_lds_bytes(int ks) { return 2 * 8 * ks * (KG + VG) * 2; }   // two stages of 8 ks groups each
+}  // namespace
+
+template <int KS, bool MIX>
+__global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const AttnArgs a,
+                                                                 const std::conditional_t<MIX, MixArgs, NoMix> mx) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  constexpr int NS = 16, NPV = 8, NE = 16, NP = 8;
+  constexpr int NWV = 2 * KS;                      // wavefronts: KS key shares of two row sets
+  constexpr int SB = 32 * KS;                      // keys of a superblock
+  constexpr int SPLIT_K = 8 * KS * KG, SPLIT_V = 8 * KS * VG;      // elements of a K / V stage
+  // merge: references and sums of NWV x 32 rows, accumulator tiles [row set][tile][key share], then output rows
+  constexpr int RED = 2 * NWV * 32 * 4, ACC = 2 * 4 * KS * 4096;
+  static_assert(RED + ACC <= split_lds_bytes(KS) && BM_SPLIT * LSTR * 2 <= ACC, "the merge reuses the rings");
+  static_assert(split_lds_bytes(KS) * (4 / KS) <= 160 * 1024, "rings exceed the LDS of a CU");
+  const WorkItem w = decode_item<BM_SPLIT, D>(a, blockIdx.x);
+  if (w.n_rows <= 0) return;
+  const bool user = w.seg == 0 || (w.seg == 2 && a.win_gather);
+  const uint16_t* Q = (const uint16_t*)(user ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
+  const uint16_t* K = (const uint16_t*)(user ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
+  const uint16_t* V = (const uint16_t*)(user ? a.v0 : w.seg == 1 ? a.vc : a.vt) + w.kv_off;
+  uint16_t* O = (uint16_t*)(user ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
+  const int* tok = w.seg == 2 ? a.tok_of : a.iota;
+  const unsigned row_stride = (unsigned)w.row_stride;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+  const int kg = wave >> 1, rg = wave & 1;         // key share, row set
+
+  bf16x8 qf[8];
+  {
+    unsigned qrow = w.row0 + min(32 * rg + l32, w.n_rows - 1);
+    if (w.listed) qrow = (unsigned)a.win_row[qrow];
+    const uint16_t* qp = Q + qrow * row_stride + 8 * g;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qp + 16 * ks));
+  }
+
+  const RunList rl(w);
+  int n_keys = 0;
+  for (int r = 0; r < w.n_runs; ++r) n_keys += rl.len(r);
+  const int n_sb = (n_keys + SB - 1) / SB;
+
+  // ---- staging: a stage is 8 KS groups, wavefront j loads groups j + NWV h (h = 0..3) of K and of V; lane p of a
+  // load fills bytes 16 p .. 16 p + 15 of the group (group layout: see the pipelined kernel, 32-key blocks)
+  const int ld_q = (lane >> 3) & 3, ld_col = 8 * (8 * (lane >> 5) + (lane & 7));
+  auto group_key = [&](int h) {                    // this lane's key of the superblock in group j + NWV h
+    const int group = wave + NWV * h;
+    return 32 * (group >> 3) + (group & 7) + 8 * ld_q;
+  };
+  const unsigned long long k_pa = (unsigned long long)K, v_pa = (unsigned long long)V;
+  const i32x4 rs_k = {__builtin_amdgcn_readfirstlane((int)(unsigned)k_pa), __builtin_amdgcn_readfirstlane((int)((unsigned)(k_pa >> 32) & 0xffffu)), -1, 0x00020000};
+  const i32x4 rs_v = {__builtin_amdgcn_readfirstlane((int)(unsigned)v_pa), __builtin_amdgcn_readfirstlane((int)((unsigned)(v_pa >> 32) & 0xffffu)), -1, 0x00020000};
+  const unsigned lds0 = (unsigned)(uintptr_t)(lds_ptr)smem;
+  auto dma16 = [&](const i32x4& rs, unsigned lds_addr, unsigned off) {
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds_addr), "v"(off * 2u), "s"(rs) : "memory");
+  };
+  auto dma_k = [&](int sb, int h, unsigned off) { dma16(rs_k, lds0 + 2u * (unsigned)((sb & 1) * SPLIT_K + (wave + NWV * h) * KG), off); };
+  auto dma_v = [&](int sb, int h, unsigned off) { dma16(rs_v, lds0 + 2u * (unsigned)(2 * SPLIT_K + (sb & 1) * SPLIT_V + (wave + NWV * h) * VG), off); };
+  // Index lookups of the superblock under the fetch cursor, which then moves on; past the end of the last run
+  // they repeat its last row.  The loads are invisible to the compiler (see the pipelined kernel): what they
+  // write is not touched until a wait has named it.
+  int fr = 0, fpos = 0, fstart = rl.start(0), flen = rl.len(0);
+  int at_run = 0, at_pos = 0, at_start = 0, at_len = 1;
+  auto note = [&]() {                              // the superblock to look up; scalar work only
+    at_run = fr;
+    at_pos = fpos;
+    at_start = fstart;
+    at_len = flen;
+    fpos += SB;
+    while (fpos >= flen && fr + 1 < w.n_runs) {
+      fpos -= flen;
+      ++fr;
+      fstart = rl.start(fr);
+      flen = rl.len(fr);
+    }
+  };
+  auto lookup = [&](int (&gi)[4]) {
+    int key[4], rows[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) key[h] = group_key(h);
+    block_rows(rl, at_run, at_pos, at_start, at_len, SB, key, rows);
+    asm volatile("global_load_dword %0, %4, %8\n\tglobal_load_dword %1, %5, %8\n\t"
+                 "global_load_dword %2, %6, %8\n\tglobal_load_dword %3, %7, %8"
+                 : "=&v"(gi[0]), "=&v"(gi[1]), "=&v"(gi[2]), "=&v"(gi[3])
+                 : "v"(rows[0] * 4), "v"(rows[1] * 4), "v"(rows[2] * 4), "v"(rows[3] * 4), "s"(tok)
+                 : "memory");
+  };
+  auto named = [&](int (&gi)[4]) { asm volatile("" : "+v"(gi[0]), "+v"(gi[1]), "+v"(gi[2]), "+v"(gi[3])); };
+  auto offsets = [&](const int (&gi)[4], unsigned (&off)[4]) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h) off[h] = __umul24((unsigned)gi[h], row_stride) + (unsigned)ld_col;
+  };
+  int gi[4] = {0, 0, 0, 0};                        // indices of superblock i + 2 as iteration i begins
+  unsigned off1[4], off2[4];                       // row offsets of superblocks i + 1 and i + 2
+  {
+    int g0[4], g1[4];
+    note();
+    lookup(g0);
+    note();
+    lookup(g1);
+    note();
+    lookup(gi);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    named(g0);
+    named(g1);
+    named(gi);
+    // the query rows are here too: let the compiler wait for them now, not behind the row loads
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qf[ks]));
+    offsets(g0, off2);
+    offsets(g1, off1);
+#pragma unroll
+    for (int h = 0; h < 4; ++h) dma_k(0, h, off2[h]);
+#pragma unroll
+    for (int h = 0; h < 4; ++h) dma_k(1, h, off1[h]);
+#pragma unroll
+    for (int h = 0; h < 4; ++h) dma_v(0, h, off2[h]);
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // K(0); K(1) and V(0) are still on their way
+    __syncthreads();
+  }
+
+  // fragment addresses of the lane in stage 0 of its wavefront's block
+  const int t16 = lane & 15, blk = lane >> 4;
+  const lds_ptr k_rd = (lds_ptr)(smem + (8 * kg + (l32 & 7)) * KG + (l32 >> 3) * 64 + 8 * g);
+  const lds_ptr v_rd = (lds_ptr)(smem + 2 * SPLIT_K + (8 * kg + 4 * g + (t16 >> 2)) * VG + 16 * (blk & 1) + 4 * (t16 & 3));
+  auto k_frag = [&](lds_ptr kq, int ks) { return lds_frag3(kq + 16 * (ks & 3) + 256 * (ks >> 2)); };
+  auto v_frag = [&](lds_ptr vq, int n) {
+    const lds_ptr ap = vq + 128 * (n >> 2) + 32 * (n & 1) + 256 * ((n & 3) >> 1);
+    return read_vt3(ap, ap + 64);
+  };
+
+  f32x16 o[4], sa, sb;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) { o[0][v] = 0.f; o[1][v] = 0.f; o[2][v] = 0.f; o[3][v] = 0.f; sa[v] = 0.f; sb[v] = 0.f; }
+  float m_ref = -INFINITY, l_run = 0.f;
+  const float c = a.scale * 1.4426950408889634f;
+  bf16x8 pa[2], pb[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) pa[i] = pb[i] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+
+  auto mask_tail = [&](f32x16& t, int blk_sb) {    // element v of the tile is key 8 (v >> 2) + 4 g + (v & 3)
+    const int nv = n_keys - SB * blk_sb - 32 * kg;
+    if (nv >= 32) return;
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (8 * (v >> 2) + (v & 3) >= nv - 4 * g) t[v] = -INFINITY;
+  };
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) sa = MFMA(k_frag(k_rd, ks), qf[ks], sa);
+  mask_tail(sa, 0);
+
+#define SLOT_FENCE() __builtin_amdgcn_sched_barrier(0)
+  // One iteration.  sc: scores of superblock i (in), sn: scores of i+1 (out), pp: P^T(i-1) (in), pc: P^T(i)
+  // (out).  The first iteration has no second product: V(-1) does not exist and its stage holds nothing.
+  auto body = [&](int i, auto first, f32x16& sc, f32x16& sn, bf16x8 (&pp)[2], bf16x8 (&pc)[2]) {
+    constexpr bool FIRST = decltype(first)::value;
+    constexpr int AHEAD = 4;                       // fragments requested ahead of their use
+    const lds_ptr vq = opaque(v_rd + ((i + 1) & 1) * SPLIT_V);     // V(i-1)
+    const lds_ptr kq = opaque(k_rd + ((i + 1) & 1) * SPLIT_K);     // K(i+1)
+    bf16x8 vf[NPV], kf[NS - NPV];
+    if (!FIRST) {
+#pragma unroll
+      for (int n = 0; n < AHEAD; ++n) vf[n] = v_frag(vq, n);
+    }
+    note();                                        // superblock i+3
+    float ps0 = 0.f, ps1 = 0.f;
+    float x[NE], ex[NE];
+    unsigned u[8];
+    const float mc = m_ref * c;
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+      SLOT_FENCE();
+      if (n == NPV) {
+        // K(i+1) was requested one and a half iterations ago; behind it are V(i), the lookups and K(i+2)
+        asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < AHEAD; ++m) kf[m] = k_frag(kq, m);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sn[v] = 0.f;
+      }
+      if (n < NPV) {
+        if (!FIRST) o[n & 3] = MFMA(vf[n], pp[n >> 2], o[n & 3]);
+        if (!FIRST && n + AHEAD < NPV) vf[n + AHEAD] = v_frag(vq, n + AHEAD);
+      } else {
+        sn = MFMA(kf[n - NPV], qf[n - NPV], sn);
+        if (n + AHEAD < NS) kf[n + AHEAD - NPV] = k_frag(kq, n + AHEAD - NPV);
+      }
+      // staging: the lookups go ahead of the row loads, as the counts of the waits assume
+      if (n == 0) {
+        named(gi);
+        offsets(gi, off2);
+      }
+      if (n == 1) lookup(gi);                      // superblock i+3
+      if (n >= 2 && n < 6) dma_k(i + 2, n - 2, off2[n - 2]);
+      if (n > NPV && n <= NPV + 4) {
+        dma_v(i + 1, n - NPV - 1, off1[n - NPV - 1]);
+        off1[n - NPV - 1] = off2[n - NPV - 1];
+      }
+      // softmax, staggered by stage as in the pipelined kernel
+      if (n == 0) { x[0] = fmaf(sc[0], c, -mc); x[1] = fmaf(sc[1], c, -mc); }
+      if (n >= 1 && n <= NS - 2) x[n + 1] = fmaf(sc[n + 1], c, -mc);
+      if (n >= 1 && n <= NS - 2) ex[n - 1] = __builtin_amdgcn_exp2f(x[n - 1]);
+      if (n == NS - 1) { ex[NE - 2] = __builtin_amdgcn_exp2f(x[NE - 2]); ex[NE - 1] = __builtin_amdgcn_exp2f(x[NE - 1]); }
+      if (n >= 3 && (n & 1)) {
+        const int p = (n - 3) >> 1;
+        u[p] = pack_bf16(ex[2 * p], ex[2 * p + 1]);
+        asm volatile("" : "+v"(u[p]));
+      }
+      if (n >= 2) {
+        if (n & 1) ps1 += ex[n - 2];
+        else ps0 += ex[n - 2];
+      }
+    }
+    SLOT_FENCE();
+    u[NP - 1] = pack_bf16(ex[NE - 2], ex[NE - 1]);
+    float ps = (ps0 + ex[NE - 2]) + (ps1 + ex[NE - 1]);
+    // reference check, see the pipelined kernel.  A quarter of the key stream may have no key yet, or scores
+    // of -inf only: the reference then stays -inf and the probabilities are 0.
+    if (__any(!(ps <= P_MAX))) {
+      float top = max3(sc[0], sc[1], sc[2]);
+#pragma unroll
+      for (int k = 3; k < 15; k += 2) top = max3(top, sc[k], sc[k + 1]);
+      top = max_xor32(fmaxf(top, sc[15]));
+      const float m_new = fmaxf(m_ref, top);
+      const float alpha = m_ref == m_new ? 1.f : __builtin_amdgcn_exp2f((m_ref - m_new) * c);
+      m_ref = m_new;
+      const float mc2 = m_new == -INFINITY ? 0.f : m_new * c;
+      ps = 0.f;
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        const float e0 = __builtin_amdgcn_exp2f(fmaf(sc[2 * p], c, -mc2));
+        const float e1 = __builtin_amdgcn_exp2f(fmaf(sc[2 * p + 1], c, -mc2));
+        u[p] = pack_bf16(e0, e1);
+        ps += e0 + e1;
+      }
+      l_run *= alpha;
+#pragma unroll
+      for (int d = 0; d < 4; ++d)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[d][v] *= alpha;
+    }
+    l_run += ps;
+    pc[0] = __builtin_bit_cast(bf16x8, make_uint4(u[0], u[1], u[2], u[3]));
+    pc[1] = __builtin_bit_cast(bf16x8, make_uint4(u[4], u[5], u[6], u[7]));
+    mask_tail(sn, i + 1);
+    // V(i) and the indices of i+3 are here; K(i+2) and V(i+1) may still be on their way
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    __syncthreads();
+  };
+  // The two register sets alternate, so the loop takes superblocks in pairs and the odd one out of those after
+  // the first goes before it (leaving the loop in the middle would move the accumulators every iteration).
+  const std::integral_constant<bool, true> is_first;
+  const std::integral_constant<bool, false> not_first;
+  body(0, is_first, sa, sb, pa, pb);
+  int i = 1;
+  if (!(n_sb & 1)) {
+    body(i++, not_first, sb, sa, pb, pa);
+    sb = sa;
+    pb[0] = pa[0];
+    pb[1] = pa[1];
+  }
+  for (; i < n_sb; i += 2) {
+    body(i, not_first, sb, sa, pb, pa);
+    body(i + 1, not_first, sa, sb, pa, pb);
+  }
+#undef SLOT_FENCE
+  {                                                // second product of the last superblock
+    const lds_ptr vq = opaque(v_rd + ((n_sb - 1) & 1) * SPLIT_V);
+#pragma unroll
+    for (int n = 0; n < NPV; ++n) o[n & 3] = MFMA(v_frag(vq, n), pb[n >> 2], o[n & 3]);
+  }
+  constexpr int OR = BM_SPLIT / (8 * KS);          // output rows per thread (sixteen threads store a row)
+  unsigned orow[OR];
+#pragma unroll
+  for (int i = 0; i < OR; ++i) {
+    orow[i] = w.row0 + min((tid >> 4) + 8 * KS * i, w.n_rows - 1);
+    if (w.listed) orow[i] = (unsigned)a.win_row[orow[i]];
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();                                 // the rings are done with, and no row load is on its way into them
+
+  // ---- merge: a common reference per row, then every wavefront sums its 4 / KS tiles of 32 columns over the shares
+  float* s_ref = (float*)smem;
+  float* s_sum = s_ref + NWV * 32;
+  float4* s_acc = (float4*)(smem + RED / 2);
+  uint16_t* s_out = smem + RED / 2;                // over s_acc, once that has been read
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (g == 0) {
+    s_ref[32 * wave + l32] = m_ref;
+    s_sum[32 * wave + l32] = l_run;
+  }
+  __syncthreads();
+  float top = -INFINITY, total = 0.f;
+#pragma unroll
+  for (int j = 0; j < KS; ++j) top = fmaxf(top, s_ref[32 * (2 * j + rg) + l32]);
+  auto weight = [&](float r) { return r == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((r - top) * c); };
+#pragma unroll
+  for (int j = 0; j < KS; ++j) total += s_sum[32 * (2 * j + rg) + l32] * weight(s_ref[32 * (2 * j + rg) + l32]);
+  const float mine = weight(m_ref);
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      s_acc[((rg * 4 + t) * KS + kg) * 256 + 64 * v + lane] =
+          make_float4(o[t][4 * v] * mine, o[t][4 * v + 1] * mine, o[t][4 * v + 2] * mine, o[t][4 * v + 3] * mine);
+  __syncthreads();
+  const float inv = 1.f / total;
+  constexpr int TW = 4 / KS;                       // tiles per wavefront
+  uint2 rows[TW][4];
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int j = 0; j < KS; ++j) {
+        const float4 y = s_acc[((rg * 4 + TW * kg + t) * KS + j) * 256 + 64 * v + lane];
+        x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+      }
+      rows[t][v].x = pack_bf16(x.x * inv, x.y * inv);
+      rows[t][v].y = pack_bf16(x.z * inv, x.w * inv);
+    }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      *(uint2*)(s_out + (32 * rg + l32) * LSTR + 32 * (TW * kg + t) + 8 * v + 4 * g) = rows[t][v];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < OR; ++i) {
+    const int row = (tid >> 4) + 8 * KS * i;
+    if (row < w.n_rows) {
+      const uint4 mine_row = *(const uint4*)(s_out + row * LSTR + (tid & 15) * 8);
+      uint4* dst = (uint4*)(O + orow[i] * row_stride + (tid & 15) * 8);
+      if constexpr (MIX) *dst = mix_row(a, mx, w.head, (int)orow[i], tid & 15, mine_row, *dst);
+      else *dst = mine_row;
     }
   }
 }
@@ -601,6 +969,124 @@ static int launched() {
   return VORTA_OK;
 }
 
+// ------------------------------------------------------------------------------------------
+// Which kernel, and how a launch is cut.  The pipelined kernel does most work per cycle but in
+// 256-row items, a workgroup per CU, the window tiles in launches of their own; the split kernel takes a
+// quarter of the rows per item, all of a layer in one launch, at 70 to 85 % of the rate.  Which is
+// faster depends on how the items fill the chip, so that is estimated: the time of a launch is that of
+// handing its items, in launch order, to whichever CU is free first.  Item costs in microseconds, fitted
+// to 140 measured layers (256 to 75,600 tokens, 1 to 40 heads, one route or all): the form chosen from
+// them is on average 0.6 %, at most 8 %, slower than the fastest one measured.
+//   pipelined, per 64-key block of a 256-row item 1.45, of a half-row item 0.85; window form 1.7 and 0.95
+//   4-wavefront window form, two workgroups per CU, per 64-key block 1.55
+//   split kernel with two key shares 0.52 (two workgroups share a CU: counted as one at twice the rate)
+// Measured, us (pipelined with the last 128 items in halves / split with four / two key shares):
+//   3,072 tokens: 2 dense heads 44 / 29 / 34; 8 window heads 35 / 46 / 36; 8 heads on all routes 88 / 53 / 50
+//   9,216 tokens: 4 dense heads 252 / 229 / 233; 16 window heads 234 / 257 / 204; 40 heads 762 / 890 / 788
+//   32,760 tokens: 1 dense head 497 / 569 / 567; 4 window heads 219 / 264 / 206; 16 of them 701 / 993 / 812
+// ------------------------------------------------------------------------------------------
+namespace {
+struct Batch {
+  int items;
+  double cost;       // of each
+};
+struct Segment {
+  int items, blocks;  // 256-row (or 64-row) items, 64-key blocks of each
+};
+
+// Time at which `units` processors have finished the batches, each item going to the first one free.
+// Processors are kept in groups of equal time; a group list that runs full forgets its finest step.
+double makespan(const Batch* batch, int n, int units) {
+  constexpr int MAX = 48;
+  double t[MAX];
+  int c[MAX], ng = 1;
+  t[0] = 0.0;
+  c[0] = units;
+  for (int b = 0; b < n; ++b) {
+    int left = batch[b].items;
+    while (left > 0) {
+      const double done = t[0] + batch[b].cost;
+      const int take = std::min(left, c[0]);
+      left -= take;
+      c[0] -= take;
+      if (c[0] == 0) {
+        --ng;
+        for (int i = 0; i < ng; ++i) { t[i] = t[i + 1]; c[i] = c[i + 1]; }
+      }
+      int at = 0;
+      while (at < ng && t[at] < done - 1e-6) ++at;
+      if ((at < ng && t[at] < done + 1e-6) || ng == MAX) {
+        c[std::min(at, ng - 1)] += take;
+      } else {
+        for (int i = ng; i > at; --i) { t[i] = t[i - 1]; c[i] = c[i - 1]; }
+        t[at] = done;
+        c[at] = take;
+        ++ng;
+      }
+    }
+  }
+  return t[ng - 1];
+}
+
+constexpr double LAUNCH_US = 6.0;
+
+// Pipelined launch of the segments with its last `split` items issued as half-row items.
+double pipe_time(const Segment* seg, int n, int split, bool win, int units) {
+  const double fixed = win ? 6.0 : 3.0, full = win ? 1.7 : 1.45, half = win ? 0.95 : 0.85;
+  int total = 0;
+  for (int i = 0; i < n; ++i) total += seg[i].items;
+  if (total == 0) return 0.0;
+  int whole = total - std::min(split, total), nb = 0;
+  Batch b[8];
+  for (int pass = 0; pass < 2; ++pass) {
+    int keep = whole;
+    for (int i = 0; i < n; ++i) {
+      const int w = std::min(keep, seg[i].items);
+      keep -= w;
+      const int items = pass == 0 ? w : 2 * (seg[i].items - w);
+      if (items > 0) b[nb++] = {items, fixed + (pass == 0 ? full : half) * seg[i].blocks};
+    }
+  }
+  return LAUNCH_US + makespan(b, nb, units);
+}
+
+// How many of the last items to issue as half-row items.  The last items of a launch leave most CUs idle
+// while a few finish them; two half-row items cost 1.2 times the whole one, so halves pay for a
+// remainder of up to half the CUs and not for one that nearly fills them (two dense heads of 32,760 tokens
+// are 256 items: 958 us with the last 128 in halves, 851 us whole).
+int best_split(const Segment* seg, int n, bool win, int units, double* time) {
+  int total = 0;
+  for (int i = 0; i < n; ++i) total += seg[i].items;
+  const int candidates[4] = {units / 2, units / 4, total % units, 0};
+  int best = 0;
+  *time = 1e30;
+  for (int s : candidates) {
+    const double us = pipe_time(seg, n, s, win, units);
+    if (us < *time) {
+      *time = us;
+      best = std::min(s, total);
+    }
+  }
+  return best;
+}
+
+// Split launch; the last segment is the window tiles.
+double split_time(const Segment* seg, int n, int units) {
+  Batch b[4];
+  int nb = 0;
+  for (int i = 0; i < n; ++i)
+    if (seg[i].items > 0) b[nb++] = {seg[i].items, i == n - 1 ? 4.7 + 0.54 * seg[i].blocks : 2.5 + 0.52 * seg[i].blocks};
+  return nb ? LAUNCH_US + makespan(b, nb, units) : 0.0;
+}
+}  // namespace
+
+template <int KS>
+static void launch_split(const AttnArgs& a, const MixArgs* mix, void* stream) {
+  const dim3 grid(a.end_tile), block(128 * KS);
+  if (mix) hipLaunchKernelGGL((attn_bf16_split_kernel<KS, true>), grid, block, split_lds_bytes(KS), (hipStream_t)stream, a, *mix);
+  else hipLaunchKernelGGL((attn_bf16_split_kernel<KS, false>), grid, block, split_lds_bytes(KS), (hipStream_t)stream, a, NoMix());
+}
+
 // mix: the launch is the full-attention branch of Eq. 5 over the heads of route 0 and blends the
 // other two branches in (their results must be complete on the stream).  win_text = false leaves
 // out the text rows of the window heads (under Eq. 5 they equal the full-attention branch's).
@@ -609,40 +1095,93 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
   static std::once_flag once;
   static int attr_rc = VORTA_OK;
   std::call_once(once, [] {
-    attr_rc = set_lds_limit((const void*)attn_bf16_pipe_kernel<false, 8>, "attn_bf16_pipe_kernel<false, 8>", pipe_lds_bytes(8));
-    if (!attr_rc) attr_rc = set_lds_limit((const void*)attn_bf16_pipe_kernel<false, 8, true>, "attn_bf16_pipe_kernel<false, 8, true>", pipe_lds_bytes(8));
-    if (!attr_rc) attr_rc = set_lds_limit((const void*)attn_bf16_pipe_kernel<true, 8>, "attn_bf16_pipe_kernel<true, 8>", pipe_lds_bytes(8));
-    if (!attr_rc) attr_rc = set_lds_limit((const void*)attn_bf16_pipe_kernel<true, 4>, "attn_bf16_pipe_kernel<true, 4>", pipe_lds_bytes(4));
+    const struct { const void* kernel; const char* name; int lds; } all[] = {
+        {(const void*)attn_bf16_pipe_kernel<false, 8>, "attn_bf16_pipe_kernel<false, 8>", pipe_lds_bytes(8)},
+        {(const void*)attn_bf16_pipe_kernel<false, 8, true>, "attn_bf16_pipe_kernel<false, 8, true>", pipe_lds_bytes(8)},
+        {(const void*)attn_bf16_pipe_kernel<true, 8>, "attn_bf16_pipe_kernel<true, 8>", pipe_lds_bytes(8)},
+        {(const void*)attn_bf16_pipe_kernel<true, 4>, "attn_bf16_pipe_kernel<true, 4>", pipe_lds_bytes(4)},
+        {(const void*)attn_bf16_split_kernel<4, false>, "attn_bf16_split_kernel<4, false>", split_lds_bytes(4)},
+        {(const void*)attn_bf16_split_kernel<4, true>, "attn_bf16_split_kernel<4, true>", split_lds_bytes(4)},
+        {(const void*)attn_bf16_split_kernel<2, false>, "attn_bf16_split_kernel<2, false>", split_lds_bytes(2)},
+        {(const void*)attn_bf16_split_kernel<2, true>, "attn_bf16_split_kernel<2, true>", split_lds_bytes(2)}};
+    for (const auto& k : all)
+      if (!attr_rc) attr_rc = set_lds_limit(k.kernel, k.name, k.lds);
   });
   if (attr_rc) return attr_rc;
   if (mix && (rl.count[1] || rl.count[2])) return fail(VORTA_EINVAL, "the Eq. 5 epilogue takes full-attention heads only");
+  hipStream_t st = (hipStream_t)stream;
+  const int units = p->n_cus, n_win = rl.count[1];
+  const int rows_c = (int)(p->Lc + p->d.n_text), n_text = win_text ? p->d.n_text : 0;
+  const int blocks_n = (int)((p->N + 63) / 64), blocks_c = (rows_c + 63) / 64;
+  auto items_of = [](int64_t rows, int bm) { return (int)((rows + bm - 1) / bm); };
+  auto list_items = [&](int l) { return n_win * (int)(p->win_list[l].size() / 4); };
+
+  // Everything in 64-row items: one launch of the split kernel if that is estimated to be the faster form.
+  // With no more items than CUs four key shares shorten each of them (3,072 keys: 29 us against
+  // 34 with two shares; 256 keys, where the longer merge shows: 9.6 against 8.8).
+  const Segment fine[4] = {{n_win * items_of(n_text, BM_SPLIT), blocks_n}, {rl.count[0] * items_of(p->N, BM_SPLIT), blocks_n},
+                           {rl.count[2] * items_of(rows_c, BM_SPLIT), blocks_c}, {list_items(2), p->win_blocks[2]}};
+  int fine_items = 0, longest = 0;
+  for (const Segment& s : fine) {
+    fine_items += s.items;
+    if (s.items) longest = std::max(longest, s.blocks);
+  }
+  if (fine_items == 0) return VORTA_OK;
+  const Segment coarse[3] = {{n_win * items_of(n_text, BM_LONG), blocks_n}, {rl.count[0] * items_of(p->N, BM_LONG), blocks_n},
+                             {rl.count[2] * items_of(rows_c, BM_LONG), blocks_c}};
+  const Segment big = {list_items(0), p->win_blocks[0]};
+  bool split_all = fine_items <= units, split_win = false;
+  int half_long = 0, half_big = 0;
+  if (!split_all) {
+    double t_long, t_big;
+    half_long = best_split(coarse, 3, false, units, &t_long);
+    half_big = best_split(&big, 1, true, units, &t_big);
+    const Batch small = {list_items(1), 5.0 + 1.55 * p->win_blocks[1]};
+    const double t_win = t_big + (small.items ? LAUNCH_US + makespan(&small, 1, 2 * units) : 0.0);
+    // far above the sizes where the split kernel can win there is nothing to estimate
+    int64_t work = 0;
+    for (const Segment& s : fine) work += (int64_t)s.items * s.blocks;
+    if (work < (int64_t)4000 * units) {
+      const double t_split_win = split_time(&fine[3], 1, units);
+      split_win = n_win && t_split_win < t_win;
+      split_all = split_time(fine, 4, units) < t_long + std::min(t_win, t_split_win);
+    }
+  }
+  AttnArgs a;
+  if (split_all) {
+    if (int rc = fill_attn_args(p, rl, io, BM_SPLIT, win_text ? WIN_ALL : WIN_TILES, &a, 2)) return rc;
+    if (fine_items <= units && longest >= 16) launch_split<4>(a, mix, stream);
+    else launch_split<2>(a, mix, stream);
+    return launched();
+  }
   // Long items -- dense heads, core-set heads and the text rows of the window heads, which
   // attend to every row -- run on the pipelined kernel in 256-row workgroups.
   RouteLists win_rl = rl;
   win_rl.count[0] = win_rl.count[2] = 0;
-  AttnArgs a;
   if (int rc = fill_attn_args(p, rl, io, BM_LONG, win_text ? WIN_TEXT : WIN_NONE, &a)) return rc;
   if (a.end_tile > 0) {
-    // the last items (at most one per two CUs) go out as half-row items: see AttnArgs::split_from
-    const int n_split = std::min(a.end_tile, p->n_cus / 2);
-    a.split_from = a.end_tile - n_split;
-    if (mix)
-      hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8, true>), dim3(a.end_tile + n_split), dim3(512), pipe_lds_bytes(8), (hipStream_t)stream, a, *mix);
-    else
-      hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8>), dim3(a.end_tile + n_split), dim3(512), pipe_lds_bytes(8), (hipStream_t)stream, a, NoMix());
+    a.split_from = a.end_tile - half_long;
+    const dim3 grid(a.end_tile + half_long);
+    if (mix) hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8, true>), grid, dim3(512), pipe_lds_bytes(8), st, a, *mix);
+    else hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8>), grid, dim3(512), pipe_lds_bytes(8), st, a, NoMix());
   }
-  // Window tiles: the plan's items of more than 128 rows on the 8-wavefront instance (256 rows, 64-key
-  // blocks, one workgroup per CU), the rest on the 4-wavefront one (128 rows, 32-key blocks, two per CU).
-  if (rl.count[1] == 0) return launched();
+  // Window tiles: in 64-row items (above), or the plan's items of more than 128 rows on the 8-wavefront instance
+  // (256 rows, 64-key blocks, one workgroup per CU) and the rest on the 4-wavefront one (128 rows, 32-key
+  // blocks, two per CU).
+  if (n_win == 0) return launched();
+  if (split_win) {
+    if (int rc = fill_attn_args(p, win_rl, io, BM_SPLIT, WIN_TILES, &a, 2)) return rc;
+    launch_split<2>(a, nullptr, stream);
+    return launched();
+  }
   if (int rc = fill_attn_args(p, win_rl, io, BM_LONG, WIN_TILES, &a, 0)) return rc;
   if (a.end_tile > 0) {
-    const int n_split = std::min(a.end_tile, p->n_cus / 2);
-    a.split_from = a.end_tile - n_split;
-    hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + n_split), dim3(512), pipe_lds_bytes(8), (hipStream_t)stream, a, NoMix());
+    a.split_from = a.end_tile - half_big;
+    hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + half_big), dim3(512), pipe_lds_bytes(8), st, a, NoMix());
   }
   if (int rc = fill_attn_args(p, win_rl, io, BM, WIN_TILES, &a, 1)) return rc;
   if (a.end_tile > 0)
-    hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 4>), dim3(a.end_tile), dim3(256), pipe_lds_bytes(4), (hipStream_t)stream, a, NoMix());
+    hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 4>), dim3(a.end_tile), dim3(256), pipe_lds_bytes(4), st, a, NoMix());
   return launched();
 }
 

@@ -32,6 +32,7 @@ struct AttnArgs {
   // through tok_of (tile-order index -> token index); win_heads = head id of each window slot.  With
   // copies tok_of is the identity.
   const int* tok_of;                // [N]
+  const int* iota;                  // [N]: 0, 1, 2, ...
   const int* tile_row0;             // [n_tiles + 1]: first tile-order row of each tile (edge tiles may be clipped)
   int win_gather;
   const int* runs;                  // [n_tiles][max_runs][2]
@@ -79,7 +80,8 @@ struct WorkItem {
   long row_stride;             // elements
   int head;                    // head id (dense segment only)
   int seg;                     // 0 dense, 1 core-set, 2 window
-  int row0, n_rows;            // query rows row0 .. row0 + n_rows - 1 (with win_items: places of win_row)
+  int row0, n_rows;            // query rows row0 .. row0 + n_rows - 1; listed: places of win_row instead of rows
+  bool listed;
   int n_runs;
   const int* runs;             // null: the single run {0, single_len}
   int single_len;
@@ -91,6 +93,7 @@ __device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int item) {
   w.runs = nullptr;
   w.n_runs = 1;
   w.head = 0;
+  w.listed = false;
   int half = -1;
   if (item >= a.split_from) {
     half = (item - a.split_from) & 1;
@@ -133,6 +136,7 @@ __device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int item) {
     w.row_stride = a.win_gather ? a.row_stride0 : D;
     w.row0 = it[0];
     w.n_rows = it[1];
+    w.listed = true;
     w.runs = a.runs + (long)tile * a.max_runs * 2;
     w.n_runs = a.n_runs[tile];
     w.single_len = 0;
@@ -183,18 +187,17 @@ struct RunList {
   __device__ __forceinline__ int len(int r) const { return runs ? runs[2 * r + 1] : single_len; }
 };
 
-// Rows of keys j0 + step i (i < NR) of the bn-key block that begins pos keys into run r, whose
-// first row is s and whose length is len (r, pos, s, len wave-uniform; j0 per lane).  A block
+// Rows of the keys k[i] (i < NR, per lane, 0 <= k[i] < bn) of the bn-key block that begins pos keys into run
+// r, whose first row is s and whose length is len (r, pos, s, len wave-uniform).  A block
 // that reaches past the end of run r continues in the following runs: they are walked with
 // uniform control flow, each lane keeping the row of the run its key falls in.  Keys past the
 // end of the last run repeat its last row (they are masked out of the softmax).
 template <int NR>
-__device__ __forceinline__ void block_rows(const RunList& rl, int r, int pos, int s, int len, int bn, int j0, int step,
+__device__ __forceinline__ void block_rows(const RunList& rl, int r, int pos, int s, int len, int bn, int (&k)[NR],
                                            int (&rows)[NR]) {
-  int k[NR];
 #pragma unroll
   for (int i = 0; i < NR; ++i) {
-    k[i] = pos + j0 + step * i;
+    k[i] += pos;
     rows[i] = s + min(k[i], len - 1);
   }
   int end = pos + bn;
@@ -216,7 +219,7 @@ enum WindowPart { WIN_NONE = 0, WIN_TEXT = 1, WIN_TILES = 2, WIN_ALL = 3 };
 
 // Fills AttnArgs for a launch over the heads of rl with BM-row work items; win_part selects
 // which items of the window heads it carries.  win_list: -1 = one item per (tile, q-block);
-// 0 / 1 = the plan's lists of items of more than 128 rows / of at most 128 rows.
+// 0 / 1 / 2 = the plan's lists of items of more than 128 rows / of at most 128 rows / of at most 64 rows.
 int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, int BM, int win_part, AttnArgs* a,
                    int win_list = -1);
 

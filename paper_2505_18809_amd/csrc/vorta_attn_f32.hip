@@ -102,8 +102,8 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_f32_kernel(const AttnArg
   unsigned koff = 0;               // row offset of key m of the block
   float4 kf[NC];
   auto load_k = [&]() {            // rows of the block under the cursor, then on to this wavefront's next one
-    int rows[1];
-    block_rows<1>(rl, fr, fpos, fstart, flen, KB, m, 0, rows);
+    int key[1] = {m}, rows[1];
+    block_rows(rl, fr, fpos, fstart, flen, KB, key, rows);
     koff = row_off(gather ? a.tok_of[rows[0]] : rows[0]);
     const float* kp = K + koff + 4 * g;
 #pragma unroll

@@ -256,6 +256,19 @@ int vorta_plan_create(const vorta_layer_desc* desc, vorta_plan** out) {
         std::vector<int32_t>& list = p->win_list[n > 128 ? 0 : 1];
         list.insert(list.end(), {first, n, g->front(), 0});
       }
+      for (int32_t first = begin; first < end; first += 64)
+        p->win_list[2].insert(p->win_list[2].end(), {first, std::min(64, end - first), g->front(), 0});
+    }
+    std::vector<int64_t> blocks(p->n_tiles, 0);
+    for (int t = 0; t < p->n_tiles; ++t) {
+      for (size_t r = 1; r < run_lists[t].size(); r += 2) blocks[t] += run_lists[t][r];
+      blocks[t] = (blocks[t] + 63) / 64;
+    }
+    for (int l = 0; l < 3; ++l) {
+      const size_t n = p->win_list[l].size() / 4;
+      int64_t sum = 0;
+      for (size_t i = 0; i < n; ++i) sum += blocks[p->win_list[l][4 * i + 2]];
+      if (n) p->win_blocks[l] = (int)((sum + (int64_t)n - 1) / (int64_t)n);
     }
   }
   if (p->tile_tokens <= 128) {

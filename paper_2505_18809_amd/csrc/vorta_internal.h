@@ -34,9 +34,11 @@ struct vorta_plan {
   // window work items of the bf16 kernels: the rows of all tiles with one key set are one sequence (win_rows
   // holds these sequences one after the other, as tile-order rows), cut into blocks whatever the tile
   // borders.  {first, n_rows, tile, 0}: n_rows places of win_rows from `first`, keys as tile `tile` sees
-  // them.  List 0: blocks of 129 to 256 rows; list 1: what is left of a sequence, at most 128 rows.
+  // them.  List 0: blocks of 129 to 256 rows; list 1: what is left of a sequence, at most 128 rows; list 2:
+  // the sequences cut into blocks of at most 64 rows instead.
   std::vector<int32_t> win_rows;   // [L]
-  std::vector<int32_t> win_list[2];
+  std::vector<int32_t> win_list[3];
+  int win_blocks[3] = {0, 0, 0};   // 64-key blocks of the items of a list, on average (for the launch estimate)
   // rotary embedding: (cos, sin) of position * rate for every position of every axis,
   // [F][pairs_F] then [H][pairs_H] then [W][pairs_W]; empty without rope_dims
   bool rope = false;
@@ -58,7 +60,7 @@ struct vorta_plan {
   int32_t* d_win_tok = nullptr;  // [L]
   int32_t* d_tile_row0 = nullptr;   // [n_tiles + 1]
   float* d_rope_cs = nullptr;
-  int32_t* d_win_list[2] = {nullptr, nullptr};
+  int32_t* d_win_list[3] = {nullptr, nullptr, nullptr};
   void* d_tables = nullptr;      // the allocation
 };
 

@@ -97,3 +97,39 @@ def test_bf16_window_rows_cut_across_tile_borders(grid, n_text, layout):
     n = cfg.n_video
     assert torch.equal(out[:, :n], layer[:, :n]) and torch.equal(out[1], layer[1])
     assert n_text == 0 or (out[:, n:].float() - layer[:, n:].float()).abs().max().item() <= 2e-2
+
+
+@pytest.mark.parametrize("grid,heads,n_text,layout", [
+    ((1, 1, 1), 3, 0, 1),             # one key: shares of the key stream without any
+    ((1, 1, 31), 3, 2, 0),            # 33 keys
+    ((1, 8, 8), 3, 1, 1),             # 65 rows and keys: a second item of one row
+    ((2, 8, 8), 3, 0, 0),             # 128
+    ((3, 6, 9), 3, 31, 1),            # 193 keys, odd and even superblocks of the routes
+    ((1, 31, 31), 3, 0, 1),           # 961 keys: from here on four shares where the items fit the CUs
+    ((3, 7, 49), 3, 124, 0),          # 1,153 keys: nine superblocks of 128 and one key
+    ((4, 12, 16), 42, 0, 1),          # 42 heads of 768 tokens: more items than CUs
+])
+def test_bf16_attention_at_the_edges_of_its_key_split(grid, heads, n_text, layout):
+    """Small launches share the key stream of 64 query rows among two or four wavefronts: row and key
+    remainders, superblock counts of both parities, shares without a key, every route in one launch."""
+    cfg = LayerConfig(f"split{grid}", grid, heads, 128, "bf16", (2, 3, 4), (3, 1, 3), seed=41, n_text=n_text,
+                      fixed_routes=tuple(h % 3 for h in range(heads)))
+    say(cfg.name)
+    q, k, v = make_qkv(cfg, DEV, layout)
+    layer_error(cfg, q, k, v, layout, lambda want: 2e-2)
+    again = vorta.vorta_routed_attention_layer(vorta.plan_for(cfg, layout=layout), q, k, v, cfg.fixed_routes)
+    assert torch.equal(again, vorta.vorta_routed_attention_layer(vorta.plan_for(cfg, layout=layout), q, k, v, cfg.fixed_routes))
+
+
+def test_bf16_split_rows_whose_maxima_jump_from_share_to_share():
+    """Scores that rise and fall by hundreds of log2 units along the keys, so that the shares of one row end on
+    references far apart and all but one vanish from the merge."""
+    cfg = LayerConfig("jumps", (4, 16, 18), 3, 128, "bf16", (2, 4, 6), (3, 3, 3), seed=43, fixed_routes=(0, 1, 2))
+    say(cfg.name)
+    q, k, v = make_qkv(cfg, DEV)
+    ramp = torch.sin(torch.linspace(0.0, 25.0, cfg.n_tokens, device=DEV))[:, None] * 400.0
+    u = torch.zeros(128, device=DEV)
+    u[5] = 1.0
+    k = (k.float() + ramp * u).to(torch.bfloat16)
+    # rows that few keys dominate return those value rows: half an ulp of the output, and P's rounding
+    layer_error(cfg, q, k, v, 1, lambda want: np.maximum(2e-2, 2.0 ** -7 * np.abs(want)))
