@@ -286,8 +286,8 @@ int vorta_scatter_back(vorta_plan* plan, const uint8_t* routes_host, const void*
 /* ---- the whole path ----------------------------------------------------------------------- */
 
 /* Bytes of device scratch the layer call needs for these routes (internal buffers above; the layer
- * call makes no tile-ordered copies: those four buffers are empty with bf16, reserved but unused
- * with fp32). */
+ * call makes no tile-ordered copies -- those four buffers are empty with bf16, reserved but unused
+ * with fp32 -- and writes the core-set rows straight to their tokens, o_c staying unused too). */
 int vorta_workspace_bytes(const vorta_plan* plan, const uint8_t* routes_host, size_t* bytes);
 
 /* Byte offsets of the internal buffers inside the workspace, in the order

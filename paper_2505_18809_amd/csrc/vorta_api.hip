@@ -50,14 +50,23 @@ static int begin(vorta_plan* p, const uint8_t* routes, RouteLists* rl) {
   return ensure_device_tables(p);
 }
 
-int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, int BM, int win_part, AttnArgs* a,
-                   int win_list) {
+int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, const CoreIndex* core, int BM,
+                   int win_part, AttnArgs* a, int win_list) {
   std::memset(a, 0, sizeof(*a));
   const UserTensor ut = user_tensor(p, io->q);
   a->q0 = io->q; a->k0 = io->k; a->v0 = io->v; a->o0 = io->out;
   a->head_stride0 = ut.head_stride;
   a->row_stride0 = ut.row_stride;
   a->qc = io->q_c; a->kc = io->k_c; a->vc = io->v_c; a->oc = io->o_c;
+  if (core) {
+    a->keep_idx = core->keep_idx;
+    a->assign = core->assign;
+  }
+  a->slot_bucket = (const int2*)p->d_slot_bucket;
+  a->Lc = (int)p->Lc;
+  a->grid_H = p->d.H;
+  a->grid_W = p->d.W;
+  a->bucket_max = p->d.bucket[0] * p->d.bucket[1] * p->d.bucket[2];
   a->qt = io->q_t; a->kt = io->k_t; a->vt = io->v_t; a->ot = io->o_t;
   a->tile_row0 = p->d_tile_row0;
   a->win_gather = io->q_t == nullptr;
@@ -96,14 +105,16 @@ int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io,
   a->scale = p->scale;
   for (int i = 0; i < rl.count[0]; ++i) a->dense_heads[i] = (uint8_t)rl.heads[0][i];
   for (int i = 0; i < rl.count[1]; ++i) a->win_heads[i] = (uint8_t)rl.heads[1][i];
+  for (int i = 0; i < rl.count[2]; ++i) a->core_heads[i] = (uint8_t)rl.heads[2][i];
   return VORTA_OK;
 }
 
-// staged: the caller's own vorta_attention_routed call, where fp32 takes the tile-ordered copies only
-static int attention(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, void* stream, bool staged) {
+// core: null for the caller's own (staged) vorta_attention_routed call, where fp32 takes the tile-ordered copies
+// only and the core-set rows go to io.o_c; else the layer call's index
+static int attention(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, const CoreIndex* core, void* stream) {
   if (!io) return fail(VORTA_EINVAL, "io is null");
   const bool gather = rl.count[1] && !io->q_t && !io->k_t && !io->v_t && !io->o_t;   // window heads read q, k, v directly
-  if (gather && staged && p->d.dtype != VORTA_BF16)
+  if (gather && !core && p->d.dtype != VORTA_BF16)
     return fail(VORTA_EINVAL, "the fp32 path needs the tile-ordered copies io.q_t, k_t, v_t, o_t");
   if (rl.count[0] || gather) {
     VORTA_TRY(check_ptr(io->q, "io.q")); VORTA_TRY(check_ptr(io->k, "io.k"));
@@ -117,8 +128,8 @@ static int attention(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* i
     VORTA_TRY(check_ptr(io->q_c, "io.q_c")); VORTA_TRY(check_ptr(io->k_c, "io.k_c"));
     VORTA_TRY(check_ptr(io->v_c, "io.v_c")); VORTA_TRY(check_ptr(io->o_c, "io.o_c"));
   }
-  return p->d.dtype == VORTA_BF16 ? launch_attention_bf16(p, rl, io, stream)
-                                  : launch_attention_f32(p, rl, io, stream);
+  return p->d.dtype == VORTA_BF16 ? launch_attention_bf16(p, rl, io, core, stream)
+                                  : launch_attention_f32(p, rl, io, core, stream);
 }
 
 struct Carved {
@@ -167,10 +178,9 @@ static int layer(vorta_plan* p, const RouteLists& rl, const void* q, const void*
   io.q_t = io.k_t = io.v_t = nullptr;
   io.o_t = nullptr;
   io.q_c = c.buf[4]; io.k_c = c.buf[5]; io.v_c = c.buf[6]; io.o_c = c.buf[7];
-  VORTA_TRY(attention(p, rl, &io, stream, false));
-  VORTA_TRY(launch_unpool(p, rl, c.buf[7], assign, out, stream));
+  const CoreIndex core = {keep_idx, assign};
   (void)routes;
-  return VORTA_OK;
+  return attention(p, rl, &io, &core, stream);
 }
 
 }  // namespace vorta
@@ -256,7 +266,7 @@ int vorta_bcs_pool(vorta_plan* p, const void* src, const uint8_t* routes, const 
 int vorta_attention_routed(vorta_plan* p, const uint8_t* routes, const vorta_attn_io* io, void* stream) {
   RouteLists rl;
   VORTA_TRY(begin(p, routes, &rl));
-  return attention(p, rl, io, stream, true);
+  return attention(p, rl, io, nullptr, stream);
 }
 
 int vorta_scatter_back(vorta_plan* p, const uint8_t* routes, const void* o_t, const void* o_c,
@@ -335,10 +345,10 @@ int vorta_soft_mixture_layer(vorta_plan* p, const void* q, const void* k, const 
     std::memset(&io, 0, sizeof(io));
     io.q = q_att; io.k = k_att; io.v = v; io.out = out;
     io.q_c = c.buf[4]; io.k_c = c.buf[5]; io.v_c = c.buf[6]; io.o_c = c.buf[7];
-    VORTA_TRY(launch_attention_bf16(p, rl, &io, stream));
+    VORTA_TRY(launch_attention_bf16(p, rl, &io, nullptr, stream));
     std::memset(routes, VORTA_ROUTE_WINDOW, sizeof(routes));
     VORTA_TRY(split_routes(p, routes, &rl));
-    VORTA_TRY(launch_attention_bf16(p, rl, &io, stream, nullptr, false));
+    VORTA_TRY(launch_attention_bf16(p, rl, &io, nullptr, stream, nullptr, false));
     std::memset(routes, VORTA_ROUTE_FULL, sizeof(routes));
     VORTA_TRY(split_routes(p, routes, &rl));
     MixArgs mix;
@@ -348,7 +358,7 @@ int vorta_soft_mixture_layer(vorta_plan* p, const void* q, const void* k, const 
     mix.Lc = (int)p->Lc;
     for (int h = 0; h < p->d.heads; ++h)
       for (int r = 0; r < 3; ++r) mix.alpha[h][r] = alpha_host[3 * h + r];
-    return launch_attention_bf16(p, rl, &io, stream, &mix);
+    return launch_attention_bf16(p, rl, &io, nullptr, stream, &mix);
   }
   // fp32 (the exact path): every branch into a buffer of its own, then one blend pass
   const size_t out_bytes = ((size_t)p->d.heads * p->N * p->d.head_dim * p->elem_bytes + 255) & ~(size_t)255;

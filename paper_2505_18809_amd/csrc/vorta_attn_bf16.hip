@@ -147,6 +147,54 @@ __device__ __forceinline__ uint4 mix_row(const AttnArgs& a, const MixArgs& mx, i
   return make_uint4(r[0], r[1], r[2], r[3]);
 }
 
+// Core-set rows on their way to the tokens that read them (unpool).  Sixteen lanes store a row: the slot's own
+// token first, and where that is the centre of its bucket also the tokens pruned into it.  The lookups of
+// all rows of a thread go out together, lane j of a row's sixteen asking about token j of the bucket.
+// Writing them from here saves the pass that read oc back and wrote `out` (16 heads of 75,600 tokens: 97 us;
+// of 3,072 tokens: 5 us).
+template <int NR>
+struct CoreRows {
+  int tok[NR], member[NR], slot[NR];     // the slot's token; this lane's token if it reads the slot, else -1
+  int2 bucket[NR];
+  __device__ __forceinline__ CoreRows(const AttnArgs& a, const WorkItem& w, const int (&row)[NR], int lane16) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      slot[i] = w.row0 + row[i];
+      const int s = min(slot[i], a.Lc - 1);
+      tok[i] = a.keep_idx[(long)w.head * a.Lc + s];
+      bucket[i] = a.slot_bucket[s];
+    }
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      if (slot[i] >= a.Lc) tok[i] = a.L + (slot[i] - a.Lc);          // text rows
+      member[i] = reader(a, w, i, lane16);
+    }
+  }
+  __device__ __forceinline__ int reader(const AttnArgs& a, const WorkItem& w, int i, int j) const {
+    if (slot[i] >= a.Lc || tok[i] != bucket[i].x) return -1;
+    const int t = slot_bucket_token(a, bucket[i], j);
+    return t >= 0 && t != tok[i] && a.assign[(long)w.head * a.L + t] == slot[i] ? t : -1;
+  }
+  // row i, this lane's 16 bytes; called by all sixteen lanes of the row or none
+  __device__ __forceinline__ void store(const AttnArgs& a, const WorkItem& w, int i, uint16_t* out, int lane, const uint4& value) const {
+    const unsigned stride = (unsigned)a.row_stride0;
+    const int lane16 = lane & 15;
+    auto put = [&](int t) { *(uint4*)(out + (unsigned)t * stride + lane16 * 8) = value; };
+    put(tok[i]);
+    int mine = member[i];
+    for (int j0 = 0;;) {
+      unsigned readers = (unsigned)(__ballot(mine >= 0) >> (lane & 48)) & 0xffffu;
+      while (readers) {
+        put(__shfl(mine, (lane & 48) + __ffs(readers) - 1, 64));
+        readers &= readers - 1;
+      }
+      j0 += 16;
+      if (j0 >= a.bucket_max) break;
+      mine = reader(a, w, i, j0 + lane16);
+    }
+  }
+};
+
 // One 32 x 32 tile of O^T, normalised, as bf16 into the row staging `st` of the wavefront.
 #define STORE_TILE(dt_, acc_)                                                        \
   _Pragma("unroll") for (int q4 = 0; q4 < 4; ++q4) {                                 \
@@ -189,7 +237,9 @@ __global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const
   const uint16_t* Q = (const uint16_t*)(user ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
   const uint16_t* K = (const uint16_t*)(user ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
   const uint16_t* V = (const uint16_t*)(user ? a.v0 : w.seg == 1 ? a.vc : a.vt) + w.kv_off;
-  uint16_t* O = (uint16_t*)(user ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
+  const bool unpool = !WIN && !MIX && w.seg == 1 && a.keep_idx;   // core-set rows straight to their tokens
+  uint16_t* O = unpool ? (uint16_t*)a.o0 + a.core_heads[w.head] * a.head_stride0
+                       : (uint16_t*)(user ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
   const unsigned row_stride = (unsigned)w.row_stride;
 
   if (w.n_rows <= 0) return;       // no rows: second half of a split item, or a q-block past the end of a clipped tile
@@ -581,6 +631,21 @@ __global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const
   }
   STORE_TILE(0, o[0]) STORE_TILE(1, o[1]) STORE_TILE(2, o[2]) STORE_TILE(3, o[3])
   __syncthreads();
+  if (unpool) {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      int row[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) row[i] = min(32 * wave + (lane >> 4) + 4 * (4 * half + i), w.n_rows - 1);
+      const CoreRows<4> core(a, w, row, lane & 15);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = (lane >> 4) + 4 * (4 * half + i);
+        if (32 * wave + r < w.n_rows) core.store(a, w, i, O, lane, *(const uint4*)(st + r * LSTR + (lane & 15) * 8));
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int row = (lane >> 4) + 4 * i;
@@ -635,7 +700,9 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
   const uint16_t* Q = (const uint16_t*)(user ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
   const uint16_t* K = (const uint16_t*)(user ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
   const uint16_t* V = (const uint16_t*)(user ? a.v0 : w.seg == 1 ? a.vc : a.vt) + w.kv_off;
-  uint16_t* O = (uint16_t*)(user ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
+  const bool unpool = !MIX && w.seg == 1 && a.keep_idx;          // core-set rows straight to their tokens
+  uint16_t* O = unpool ? (uint16_t*)a.o0 + a.core_heads[w.head] * a.head_stride0
+                       : (uint16_t*)(user ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
   const int* tok = w.seg == 2 ? a.tok_of : a.iota;
   const unsigned row_stride = (unsigned)w.row_stride;
 
@@ -945,6 +1012,16 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
     for (int v = 0; v < 4; ++v)
       *(uint2*)(s_out + (32 * rg + l32) * LSTR + 32 * (TW * kg + t) + 8 * v + 4 * g) = rows[t][v];
   __syncthreads();
+  if (unpool) {
+    int row[OR];
+#pragma unroll
+    for (int i = 0; i < OR; ++i) row[i] = min((tid >> 4) + 8 * KS * i, w.n_rows - 1);
+    const CoreRows<OR> core(a, w, row, lane & 15);
+#pragma unroll
+    for (int i = 0; i < OR; ++i)
+      if ((tid >> 4) + 8 * KS * i < w.n_rows) core.store(a, w, i, O, lane, *(const uint4*)(s_out + row[i] * LSTR + (tid & 15) * 8));
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < OR; ++i) {
     const int row = (tid >> 4) + 8 * KS * i;
@@ -1090,8 +1167,8 @@ static void launch_split(const AttnArgs& a, const MixArgs* mix, void* stream) {
 // mix: the launch is the full-attention branch of Eq. 5 over the heads of route 0 and blends the
 // other two branches in (their results must be complete on the stream).  win_text = false leaves
 // out the text rows of the window heads (under Eq. 5 they equal the full-attention branch's).
-int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, void* stream,
-                          const MixArgs* mix, bool win_text) {
+int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, const CoreIndex* core,
+                          void* stream, const MixArgs* mix, bool win_text) {
   static std::once_flag once;
   static int attr_rc = VORTA_OK;
   std::call_once(once, [] {
@@ -1149,7 +1226,7 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
   }
   AttnArgs a;
   if (split_all) {
-    if (int rc = fill_attn_args(p, rl, io, BM_SPLIT, win_text ? WIN_ALL : WIN_TILES, &a, 2)) return rc;
+    if (int rc = fill_attn_args(p, rl, io, core, BM_SPLIT, win_text ? WIN_ALL : WIN_TILES, &a, 2)) return rc;
     if (fine_items <= units && longest >= 16) launch_split<4>(a, mix, stream);
     else launch_split<2>(a, mix, stream);
     return launched();
@@ -1158,7 +1235,7 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
   // attend to every row -- run on the pipelined kernel in 256-row workgroups.
   RouteLists win_rl = rl;
   win_rl.count[0] = win_rl.count[2] = 0;
-  if (int rc = fill_attn_args(p, rl, io, BM_LONG, win_text ? WIN_TEXT : WIN_NONE, &a)) return rc;
+  if (int rc = fill_attn_args(p, rl, io, core, BM_LONG, win_text ? WIN_TEXT : WIN_NONE, &a)) return rc;
   if (a.end_tile > 0) {
     a.split_from = a.end_tile - half_long;
     const dim3 grid(a.end_tile + half_long);
@@ -1170,16 +1247,16 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
   // blocks, two per CU).
   if (n_win == 0) return launched();
   if (split_win) {
-    if (int rc = fill_attn_args(p, win_rl, io, BM_SPLIT, WIN_TILES, &a, 2)) return rc;
+    if (int rc = fill_attn_args(p, win_rl, io, core, BM_SPLIT, WIN_TILES, &a, 2)) return rc;
     launch_split<2>(a, nullptr, stream);
     return launched();
   }
-  if (int rc = fill_attn_args(p, win_rl, io, BM_LONG, WIN_TILES, &a, 0)) return rc;
+  if (int rc = fill_attn_args(p, win_rl, io, core, BM_LONG, WIN_TILES, &a, 0)) return rc;
   if (a.end_tile > 0) {
     a.split_from = a.end_tile - half_big;
     hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + half_big), dim3(512), pipe_lds_bytes(8), st, a, NoMix());
   }
-  if (int rc = fill_attn_args(p, win_rl, io, BM, WIN_TILES, &a, 1)) return rc;
+  if (int rc = fill_attn_args(p, win_rl, io, core, BM, WIN_TILES, &a, 1)) return rc;
   if (a.end_tile > 0)
     hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 4>), dim3(a.end_tile), dim3(256), pipe_lds_bytes(4), st, a, NoMix());
   return launched();

@@ -25,6 +25,11 @@ struct AttnArgs {
   // route 2: [n_lr][Nc][d]
   const void *qc, *kc, *vc;
   void* oc;
+  // Core-set index, or null: with it the rows of route 2 go to the caller's output instead of oc, every slot's row
+  // to the tokens that read it (unpool).
+  const int *keep_idx, *assign;     // [n_lr][Lc], [n_lr][L]
+  const int2* slot_bucket;          // [Lc]: centre token and extents of the slot's bucket
+  int Lc, grid_H, grid_W, bucket_max;      // bucket_max: tokens of an unclipped bucket
   // route 1: [n_win][N][d] in tile order
   const void *qt, *kt, *vt;
   void* ot;
@@ -60,6 +65,7 @@ struct AttnArgs {
   float scale;
   uint8_t dense_heads[VORTA_MAX_HEADS];
   uint8_t win_heads[VORTA_MAX_HEADS];
+  uint8_t core_heads[VORTA_MAX_HEADS];
 };
 
 // Eq. 5 epilogue of a dense launch over all heads: the rows it writes are
@@ -78,7 +84,7 @@ struct NoMix {};
 struct WorkItem {
   long q_off, kv_off, o_off;   // element offsets of the head's row 0 in q / k,v / o
   long row_stride;             // elements
-  int head;                    // head id (dense segment only)
+  int head;                    // head id (dense segment), head slot (core-set segment)
   int seg;                     // 0 dense, 1 core-set, 2 window
   int row0, n_rows;            // query rows row0 .. row0 + n_rows - 1; listed: places of win_row instead of rows
   bool listed;
@@ -121,6 +127,7 @@ __device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int item) {
     item -= a.end_dense;
     const int slot = item / a.qb_core, qb = item - slot * a.qb_core;
     w.seg = 1;
+    w.head = slot;
     w.q_off = w.kv_off = w.o_off = (long)slot * a.Nc * D;
     w.row_stride = D;
     w.row0 = qb * BM;
@@ -220,10 +227,19 @@ enum WindowPart { WIN_NONE = 0, WIN_TEXT = 1, WIN_TILES = 2, WIN_ALL = 3 };
 // Fills AttnArgs for a launch over the heads of rl with BM-row work items; win_part selects
 // which items of the window heads it carries.  win_list: -1 = one item per (tile, q-block);
 // 0 / 1 / 2 = the plan's lists of items of more than 128 rows / of at most 128 rows / of at most 64 rows.
-int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, int BM, int win_part, AttnArgs* a,
-                   int win_list = -1);
+int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, const CoreIndex* core, int BM,
+                   int win_part, AttnArgs* a, int win_list = -1);
 
-int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, void* stream,
-                          const MixArgs* mix = nullptr, bool win_text = true);
+int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, const CoreIndex* core,
+                          void* stream, const MixArgs* mix = nullptr, bool win_text = true);
+
+// Token j (< 64) of the bucket whose centre token and packed extents are given; -1 past its end.  The
+// quotients are taken in fp32, which is exact for such small numbers (see the selection kernels).
+__device__ __forceinline__ int slot_bucket_token(const AttnArgs& a, int2 bucket, int j) {
+  const int df = bucket.y & 255, dh = (bucket.y >> 8) & 255, dw = bucket.y >> 16;
+  const int x = (int)(((float)j + 0.5f) * __builtin_amdgcn_rcpf((float)(dh * dw))), r = j - x * (dh * dw);
+  const int y = (int)(((float)r + 0.5f) * __builtin_amdgcn_rcpf((float)dw)), z = r - y * dw;
+  return j < df * dh * dw ? bucket.x + ((x - df / 2) * a.grid_H + y - dh / 2) * a.grid_W + z - dw / 2 : -1;
+}
 
 }  // namespace vorta

@@ -60,7 +60,9 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_f32_kernel(const AttnArg
   const float* Q = (const float*)(w.seg == 0 || gather ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
   const float* K = (const float*)(w.seg == 0 || gather ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
   const float* V = (const float*)(w.seg == 0 || gather ? a.v0 : w.seg == 1 ? a.vc : a.vt) + w.kv_off;
-  float* O = (float*)(w.seg == 0 || gather ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
+  const bool unpool = w.seg == 1 && a.keep_idx;
+  float* O = unpool ? (float*)a.o0 + a.core_heads[w.head] * a.head_stride0
+                    : (float*)(w.seg == 0 || gather ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int m = lane & 15, g = lane >> 4;
 
@@ -207,19 +209,47 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_f32_kernel(const AttnArg
   }
   if (wave == 0 && m < w.n_rows) {
     const double inv = 1.0 / total;
-    float* op = O + my_off + 4 * g;
+    auto store = [&](unsigned off) {
+      float* op = O + off + 4 * g;
 #pragma unroll
-    for (int h = 0; h < NH; ++h)
+      for (int h = 0; h < NH; ++h)
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        *(float4*)(op + 64 * h + 16 * v) = make_float4((float)(o[4 * h][v] * inv), (float)(o[4 * h + 1][v] * inv),
-                                                       (float)(o[4 * h + 2][v] * inv), (float)(o[4 * h + 3][v] * inv));
+        for (int v = 0; v < 4; ++v)
+          *(float4*)(op + 64 * h + 16 * v) = make_float4((float)(o[4 * h][v] * inv), (float)(o[4 * h + 1][v] * inv),
+                                                         (float)(o[4 * h + 2][v] * inv), (float)(o[4 * h + 3][v] * inv));
+    };
+    if (!unpool) {
+      store(my_off);
+    } else {                                   // to every token that reads this slot
+      const unsigned stride = (unsigned)a.row_stride0;
+      const int slot = w.row0 + m;
+      if (slot >= a.Lc) {
+        store((unsigned)(a.L + slot - a.Lc) * stride);
+      } else {
+        const int tok = a.keep_idx[(long)w.head * a.Lc + slot];
+        const int2 bucket = a.slot_bucket[slot];
+        store((unsigned)tok * stride);
+        if (tok == bucket.x)                   // the bucket's centre: the tokens pruned into it
+          for (int j0 = 0; j0 < a.bucket_max; j0 += 4) {
+            int t[4];
+            bool reads[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              t[u] = slot_bucket_token(a, bucket, j0 + u);
+              reads[u] = t[u] >= 0 && t[u] != tok && a.assign[(long)w.head * a.L + t[u]] == slot;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (reads[u]) store((unsigned)t[u] * stride);
+          }
+      }
+    }
   }
 }
 
-int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, void* stream) {
+int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, const CoreIndex* core, void* stream) {
   AttnArgs a;
-  if (int rc = fill_attn_args(p, rl, io, 16, WIN_ALL, &a)) return rc;
+  if (int rc = fill_attn_args(p, rl, io, core, 16, WIN_ALL, &a)) return rc;
   if (a.end_tile == 0) return VORTA_OK;
   const dim3 grid(a.end_tile);
   hipStream_t st = (hipStream_t)stream;

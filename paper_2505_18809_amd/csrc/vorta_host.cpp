@@ -314,6 +314,9 @@ int vorta_plan_create(const vorta_layer_desc* desc, vorta_plan** out) {
         const int k = std::min(B - 1, (int)(((int64_t)B * (d.keep_den - d.keep_num)) / d.keep_den));
         p->slot_base[b++] = (int32_t)slot;
         slot += B - k;
+        const int df = std::min(d.bucket[0], d.F - f0), dh = std::min(d.bucket[1], d.H - h0), dw = std::min(d.bucket[2], d.W - w0);
+        const int centre = ((f0 + df / 2) * d.H + h0 + dh / 2) * d.W + w0 + dw / 2;
+        for (int s = 0; s < B - k; ++s) p->slot_bucket.insert(p->slot_bucket.end(), {centre, df | dh << 8 | dw << 16});
       }
   p->slot_base[b] = (int32_t)slot;
   p->Lc = slot;

@@ -26,6 +26,9 @@ struct vorta_plan {
   std::vector<int32_t> runs;     // [n_tiles][max_runs][2]
   std::vector<int32_t> n_runs;   // [n_tiles]
   std::vector<int32_t> slot_base;  // [n_buckets + 1]
+  // [Lc][2]: the bucket of every core-set slot, as its centre token and its clipped extents (df | dh << 8 | dw << 16);
+  // which slots a bucket owns depends on its size only, so this is known before any selection
+  std::vector<int32_t> slot_bucket;
   // what vorta_window_items reports (tiles of at most 128 tokens): tiles with identical key sets, up to
   // three tiles and 256 rows together; {tile, tile, tile, count} each, the n_win_big entries of more
   // than 128 rows first, then the n_win_small others.  Empty when a tile holds more than 128 tokens.
@@ -54,6 +57,7 @@ struct vorta_plan {
   int32_t* d_runs = nullptr;
   int32_t* d_n_runs = nullptr;
   int32_t* d_slot_base = nullptr;
+  int32_t* d_slot_bucket = nullptr;
   int32_t* d_tok_of = nullptr;   // [N]
   int32_t* d_iota = nullptr;     // [N]
   int32_t* d_win_rows = nullptr; // [L]
@@ -101,7 +105,13 @@ int launch_rope_rows(vorta_plan* p, const RouteLists& rl, const void* src, void*
                      void* stream);
 int launch_unpool(vorta_plan* p, const RouteLists& rl, const void* o_c, const int32_t* assign, void* out,
                   void* stream);
-int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, void* stream);
+// Core-set index of a layer call: with it the attention launch writes the rows of route 2 to the tokens that
+// read them (unpool) instead of to io.o_c.
+struct CoreIndex {
+  const int32_t* keep_idx;   // [n_lr][L_c]
+  const int32_t* assign;     // [n_lr][L]
+};
+int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, const CoreIndex* core, void* stream);
 int launch_router(const float* t_emb, const float* w_r, int n_steps, int d_t, int heads, float* alpha,
                   uint8_t* routes, void* stream);
 int launch_blend3(vorta_plan* p, const void* o0, const void* o1, const void* o2, const float* alpha_host,

@@ -51,6 +51,7 @@ static int upload_device_tables(vorta_plan* p, int dev) {
       table(p->tile_row0, &p->d_tile_row0), table(tok_of, &p->d_tok_of),      table(iota, &p->d_iota),
       table(p->win_rows, &p->d_win_rows), table(win_tok, &p->d_win_tok),      table(p->win_list[0], &p->d_win_list[0]),
       table(p->win_list[1], &p->d_win_list[1]), table(p->win_list[2], &p->d_win_list[2]),
+      table(p->slot_bucket, &p->d_slot_bucket),
       table(p->rope_cs, &p->d_rope_cs)};
   size_t total = 0;
   for (const Table& t : tables) total += (t.bytes + 255) & ~(size_t)255;

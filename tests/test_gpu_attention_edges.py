@@ -133,3 +133,32 @@ def test_bf16_split_rows_whose_maxima_jump_from_share_to_share():
     k = (k.float() + ramp * u).to(torch.bfloat16)
     # rows that few keys dominate return those value rows: half an ulp of the output, and P's rounding
     layer_error(cfg, q, k, v, 1, lambda want: np.maximum(2e-2, 2.0 ** -7 * np.abs(want)))
+
+
+@pytest.mark.parametrize("grid,bucket,keep,heads,dtype,d,n_text,layout", [
+    ((4, 8, 8), (2, 3, 2), (1, 2), 3, "bf16", 128, 0, 1),
+    ((5, 7, 9), (4, 4, 4), (1, 4), 3, "bf16", 128, 21, 0),       # up to 64 tokens a bucket, most of them merged, clipped
+    ((5, 9, 11), (1, 17, 1), (1, 3), 4, "bf16", 128, 0, 1),
+    ((3, 4, 5), (1, 1, 1), (1, 2), 2, "bf16", 128, 5, 1),        # every token its own bucket
+    ((21, 30, 52), (3, 5, 4), (3, 4), 6, "bf16", 128, 40, 0),    # long items: the pipelined kernel
+    ((21, 30, 52), (2, 3, 2), (1, 2), 8, "bf16", 128, 0, 1),
+    ((5, 7, 9), (4, 4, 4), (1, 4), 3, "fp32", 64, 21, 0),
+    ((4, 8, 8), (2, 3, 2), (1, 2), 3, "fp32", 128, 2, 1),
+])
+def test_core_set_rows_written_to_their_tokens_equal_the_staged_unpool(grid, bucket, keep, heads, dtype, d, n_text, layout):
+    """The layer call writes core-set rows from the attention kernel to the tokens that read them; the staged
+    calls leave them in o_c and unpool in a pass.  Same launches otherwise: equal bit for bit."""
+    cfg = LayerConfig(f"unpool{bucket}", grid, heads, d, dtype, (2, 4, 4), (3, 3, 3), seed=47, n_text=n_text, bucket=bucket,
+                      keep_num=keep[0], keep_den=keep[1], fixed_routes=(2,) * heads)
+    say(f"{cfg.name} {grid} {dtype}")
+    q, k, v = make_qkv(cfg, DEV, layout)
+    plan = vorta.plan_for(cfg, layout=layout)
+    r = cfg.fixed_routes
+    out = torch.full_like(q, float("nan"))
+    vorta.vorta_routed_attention_layer(plan, q, k, v, r, out=out)
+    _, assign, q_c, k_c, v_c = vorta.vorta_bcs_select_pool(plan, q, k, v, r)
+    o_c, staged = torch.empty_like(q_c), torch.full_like(q, float("nan"))
+    vorta.vorta_attention_routed(plan, r, q_c=q_c, k_c=k_c, v_c=v_c, o_c=o_c)
+    vorta.vorta_scatter_back(plan, r, None, o_c, assign, staged)
+    torch.cuda.synchronize()
+    assert torch.equal(out, staged)
