@@ -214,9 +214,8 @@ struct CoreRows {
 // ring, two workgroups per CU (smaller window tiles): the iteration has 16 slots instead of 32.
 // MIX: the launch is the last of the three branches of Eq. 5 (dense items over every head) and
 // its epilogue writes the gate-weighted sum of the three (see MixArgs).
-template <bool WIN, int NWV, bool MIX = false>
-__global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const AttnArgs a,
-                                                                            const std::conditional_t<MIX, MixArgs, NoMix> mx) {
+template <bool WIN, int NWV, bool MIX>
+__device__ __forceinline__ void pipe_item(const AttnArgs a, const std::conditional_t<MIX, MixArgs, NoMix> mx, int item) {
   static_assert(!(MIX && WIN), "the Eq. 5 epilogue belongs to the dense launch");
   static_assert(pipe_lds_bytes(NWV) <= 160 * 1024, "K and V rings exceed the 160 KB of LDS of a CU");
   static_assert(32 * NWV * LSTR * 2 <= pipe_lds_bytes(NWV), "output staging does not fit in the rings it reuses");
@@ -232,7 +231,7 @@ __global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const
   constexpr int K_STAGE = NG * KG, V_STAGE = NG * VG;   // elements of a K / V stage
   constexpr int V_BASE = K_RING * K_STAGE;  // the K ring, then the V ring
   auto vstage = [](int b) { return (int)((unsigned)b % (unsigned)V_RING); };   // ring stage of V block b (K: b & 3)
-  const WorkItem w = decode_item<32 * NWV, D>(a, xcd_item(blockIdx.x, gridDim.x, WIN));
+  const WorkItem w = decode_item<32 * NWV, D>(a, item);
   const bool user = WIN ? a.win_gather != 0 : w.seg == 0;     // rows of the caller's tensors
   const uint16_t* Q = (const uint16_t*)(user ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
   const uint16_t* K = (const uint16_t*)(user ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
@@ -658,6 +657,21 @@ __global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const
   }
 }
 
+template <bool WIN, int NWV, bool MIX = false>
+__global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const AttnArgs a,
+                                                                            const std::conditional_t<MIX, MixArgs, NoMix> mx) {
+  pipe_item<WIN, NWV, MIX>(a, mx, xcd_item(blockIdx.x, gridDim.x, WIN));
+}
+
+// Long items and window items of more than 128 rows in one launch.  The last long items of a launch end
+// hundreds of microseconds apart (a core-set item of 591 blocks takes 0.9 ms); the window items, a tenth as
+// long, fill the CUs that have none left instead of waiting for the launch to drain.  (Two argument blocks:
+// one that both branches took would be copied to private memory.)
+__global__ __launch_bounds__(512, 1) void attn_bf16_layer_kernel(const AttnArgs a, const AttnArgs win, int n_long) {
+  if ((int)blockIdx.x < n_long) pipe_item<false, 8, false>(a, NoMix(), blockIdx.x);
+  else pipe_item<true, 8, false>(win, NoMix(), xcd_item(blockIdx.x - n_long, gridDim.x - n_long, true));
+}
+
 // ------------------------------------------------------------------------------------------
 // Split kernel: launches too small to fill the chip with 256-row items.  A workgroup owns 64 query rows, two
 // sets of 32, and the KS wavefronts of a set share the key stream: a superblock of 32 KS keys is one
@@ -1069,6 +1083,7 @@ struct Batch {
 };
 struct Segment {
   int items, blocks;  // 256-row (or 64-row) items, 64-key blocks of each
+  bool win;
 };
 
 // Time at which `units` processors have finished the batches, each item going to the first one free.
@@ -1108,8 +1123,7 @@ double makespan(const Batch* batch, int n, int units) {
 constexpr double LAUNCH_US = 6.0;
 
 // Pipelined launch of the segments with its last `split` items issued as half-row items.
-double pipe_time(const Segment* seg, int n, int split, bool win, int units) {
-  const double fixed = win ? 6.0 : 3.0, full = win ? 1.7 : 1.45, half = win ? 0.95 : 0.85;
+double pipe_time(const Segment* seg, int n, int split, int units) {
   int total = 0;
   for (int i = 0; i < n; ++i) total += seg[i].items;
   if (total == 0) return 0.0;
@@ -1118,6 +1132,7 @@ double pipe_time(const Segment* seg, int n, int split, bool win, int units) {
   for (int pass = 0; pass < 2; ++pass) {
     int keep = whole;
     for (int i = 0; i < n; ++i) {
+      const double fixed = seg[i].win ? 6.0 : 3.0, full = seg[i].win ? 1.7 : 1.45, half = seg[i].win ? 0.95 : 0.85;
       const int w = std::min(keep, seg[i].items);
       keep -= w;
       const int items = pass == 0 ? w : 2 * (seg[i].items - w);
@@ -1131,28 +1146,29 @@ double pipe_time(const Segment* seg, int n, int split, bool win, int units) {
 // while a few finish them; two half-row items cost 1.2 times the whole one, so halves pay for a
 // remainder of up to half the CUs and not for one that nearly fills them (two dense heads of 32,760 tokens
 // are 256 items: 958 us with the last 128 in halves, 851 us whole).
-int best_split(const Segment* seg, int n, bool win, int units, double* time) {
+// At most `most`.
+int best_split(const Segment* seg, int n, int most, int units, double* time) {
   int total = 0;
   for (int i = 0; i < n; ++i) total += seg[i].items;
   const int candidates[4] = {units / 2, units / 4, total % units, 0};
   int best = 0;
   *time = 1e30;
   for (int s : candidates) {
-    const double us = pipe_time(seg, n, s, win, units);
+    s = std::min(s, most);
+    const double us = pipe_time(seg, n, s, units);
     if (us < *time) {
       *time = us;
-      best = std::min(s, total);
+      best = s;
     }
   }
   return best;
 }
 
-// Split launch; the last segment is the window tiles.
 double split_time(const Segment* seg, int n, int units) {
   Batch b[4];
   int nb = 0;
   for (int i = 0; i < n; ++i)
-    if (seg[i].items > 0) b[nb++] = {seg[i].items, i == n - 1 ? 4.7 + 0.54 * seg[i].blocks : 2.5 + 0.52 * seg[i].blocks};
+    if (seg[i].items > 0) b[nb++] = {seg[i].items, seg[i].win ? 4.7 + 0.54 * seg[i].blocks : 2.5 + 0.52 * seg[i].blocks};
   return nb ? LAUNCH_US + makespan(b, nb, units) : 0.0;
 }
 }  // namespace
@@ -1177,6 +1193,7 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
         {(const void*)attn_bf16_pipe_kernel<false, 8, true>, "attn_bf16_pipe_kernel<false, 8, true>", pipe_lds_bytes(8)},
         {(const void*)attn_bf16_pipe_kernel<true, 8>, "attn_bf16_pipe_kernel<true, 8>", pipe_lds_bytes(8)},
         {(const void*)attn_bf16_pipe_kernel<true, 4>, "attn_bf16_pipe_kernel<true, 4>", pipe_lds_bytes(4)},
+        {(const void*)attn_bf16_layer_kernel, "attn_bf16_layer_kernel", pipe_lds_bytes(8)},
         {(const void*)attn_bf16_split_kernel<4, false>, "attn_bf16_split_kernel<4, false>", split_lds_bytes(4)},
         {(const void*)attn_bf16_split_kernel<4, true>, "attn_bf16_split_kernel<4, true>", split_lds_bytes(4)},
         {(const void*)attn_bf16_split_kernel<2, false>, "attn_bf16_split_kernel<2, false>", split_lds_bytes(2)},
@@ -1196,32 +1213,39 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
   // Everything in 64-row items: one launch of the split kernel if that is estimated to be the faster form.
   // With no more items than CUs four key shares shorten each of them (3,072 keys: 29 us against
   // 34 with two shares; 256 keys, where the longer merge shows: 9.6 against 8.8).
-  const Segment fine[4] = {{n_win * items_of(n_text, BM_SPLIT), blocks_n}, {rl.count[0] * items_of(p->N, BM_SPLIT), blocks_n},
-                           {rl.count[2] * items_of(rows_c, BM_SPLIT), blocks_c}, {list_items(2), p->win_blocks[2]}};
+  const Segment fine[4] = {{n_win * items_of(n_text, BM_SPLIT), blocks_n, false}, {rl.count[0] * items_of(p->N, BM_SPLIT), blocks_n, false},
+                           {rl.count[2] * items_of(rows_c, BM_SPLIT), blocks_c, false}, {list_items(2), p->win_blocks[2], true}};
   int fine_items = 0, longest = 0;
   for (const Segment& s : fine) {
     fine_items += s.items;
     if (s.items) longest = std::max(longest, s.blocks);
   }
   if (fine_items == 0) return VORTA_OK;
-  const Segment coarse[3] = {{n_win * items_of(n_text, BM_LONG), blocks_n}, {rl.count[0] * items_of(p->N, BM_LONG), blocks_n},
-                             {rl.count[2] * items_of(rows_c, BM_LONG), blocks_c}};
-  const Segment big = {list_items(0), p->win_blocks[0]};
+  const Segment coarse[4] = {{n_win * items_of(n_text, BM_LONG), blocks_n, false}, {rl.count[0] * items_of(p->N, BM_LONG), blocks_n, false},
+                             {rl.count[2] * items_of(rows_c, BM_LONG), blocks_c, false}, {list_items(0), p->win_blocks[0], true}};
+  const int n_long = coarse[0].items + coarse[1].items + coarse[2].items, n_big = coarse[3].items;
   bool split_all = fine_items <= units, split_win = false;
+  const bool together = n_long && n_big && !mix;         // long and big window items in one launch
   int half_long = 0, half_big = 0;
   if (!split_all) {
-    double t_long, t_big;
-    half_long = best_split(coarse, 3, false, units, &t_long);
-    half_big = best_split(&big, 1, true, units, &t_big);
+    double t_long, t_big, t_both;
+    half_long = best_split(coarse, 3, n_long, units, &t_long);
+    half_big = best_split(coarse + 3, 1, n_big, units, &t_big);
     const Batch small = {list_items(1), 5.0 + 1.55 * p->win_blocks[1]};
-    const double t_win = t_big + (small.items ? LAUNCH_US + makespan(&small, 1, 2 * units) : 0.0);
+    const double t_small = small.items ? LAUNCH_US + makespan(&small, 1, 2 * units) : 0.0;
+    double t_pipe = t_long + t_big + t_small;
+    if (together) {
+      const int half_both = best_split(coarse, 4, n_big, units, &t_both);
+      t_pipe = t_both + t_small;
+      half_big = half_both;
+    }
     // far above the sizes where the split kernel can win there is nothing to estimate
     int64_t work = 0;
     for (const Segment& s : fine) work += (int64_t)s.items * s.blocks;
     if (work < (int64_t)4000 * units) {
       const double t_split_win = split_time(&fine[3], 1, units);
-      split_win = n_win && t_split_win < t_win;
-      split_all = split_time(fine, 4, units) < t_long + std::min(t_win, t_split_win);
+      split_win = n_win && t_long + t_split_win < t_pipe;
+      split_all = split_time(fine, 4, units) < std::min(t_pipe, n_win ? t_long + t_split_win : t_pipe);
     }
   }
   AttnArgs a;
@@ -1232,11 +1256,18 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
     return launched();
   }
   // Long items -- dense heads, core-set heads and the text rows of the window heads, which
-  // attend to every row -- run on the pipelined kernel in 256-row workgroups.
+  // attend to every row -- run on the pipelined kernel in 256-row workgroups, and the window items of more
+  // than 128 rows behind them.
   RouteLists win_rl = rl;
   win_rl.count[0] = win_rl.count[2] = 0;
-  if (int rc = fill_attn_args(p, rl, io, core, BM_LONG, win_text ? WIN_TEXT : WIN_NONE, &a)) return rc;
-  if (a.end_tile > 0) {
+  if (together && !split_win) {
+    AttnArgs win;
+    if (int rc = fill_attn_args(p, rl, io, core, BM_LONG, win_text ? WIN_TEXT : WIN_NONE, &a)) return rc;
+    if (int rc = fill_attn_args(p, win_rl, io, core, BM_LONG, WIN_TILES, &win, 0)) return rc;
+    win.split_from = win.end_tile - half_big;
+    hipLaunchKernelGGL(attn_bf16_layer_kernel, dim3(a.end_tile + win.end_tile + half_big), dim3(512), pipe_lds_bytes(8), st, a, win, a.end_tile);
+  } else if (n_long) {
+    if (int rc = fill_attn_args(p, rl, io, core, BM_LONG, win_text ? WIN_TEXT : WIN_NONE, &a)) return rc;
     a.split_from = a.end_tile - half_long;
     const dim3 grid(a.end_tile + half_long);
     if (mix) hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8, true>), grid, dim3(512), pipe_lds_bytes(8), st, a, *mix);
@@ -1251,8 +1282,8 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
     launch_split<2>(a, nullptr, stream);
     return launched();
   }
-  if (int rc = fill_attn_args(p, win_rl, io, core, BM_LONG, WIN_TILES, &a, 0)) return rc;
-  if (a.end_tile > 0) {
+  if (n_big && !together) {
+    if (int rc = fill_attn_args(p, win_rl, io, core, BM_LONG, WIN_TILES, &a, 0)) return rc;
     a.split_from = a.end_tile - half_big;
     hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + half_big), dim3(512), pipe_lds_bytes(8), st, a, NoMix());
   }

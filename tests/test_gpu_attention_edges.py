@@ -162,3 +162,24 @@ def test_core_set_rows_written_to_their_tokens_equal_the_staged_unpool(grid, buc
     vorta.vorta_scatter_back(plan, r, None, o_c, assign, staged)
     torch.cuda.synchronize()
     assert torch.equal(out, staged)
+
+
+@pytest.mark.parametrize("n_text,layout", [(0, 1), (77, 0)])
+def test_long_and_window_items_in_one_launch(n_text, layout):
+    """A layer large enough for 256-row items on every route: window items follow the long ones in one launch (an
+    odd number of them with text), the last window items in halves.  Sampled rows of one head per route."""
+    cfg = LayerConfig("one_launch", (21, 29, 52), 8, 128, "bf16", (3, 6, 4), (3, 3, 3), seed=53, n_text=n_text,
+                      fixed_routes=(1, 0, 2, 1, 2, 1, 2, 1))
+    say(cfg.name)
+    q, k, v = make_qkv(cfg, DEV, layout)
+    plan = vorta.plan_for(cfg, layout=layout)
+    out = vorta.vorta_routed_attention_layer(plan, q, k, v, cfg.fixed_routes)
+    torch.cuda.synchronize()
+    hnd = (lambda t: t) if layout == 1 else (lambda t: t.transpose(0, 1))
+    rows = np.unique(np.concatenate([np.arange(0, cfg.n_tokens, 397), np.arange(cfg.n_tokens - 9, cfg.n_tokens)]))
+    for h in (0, 7, 1, 6):
+        r = cfg.fixed_routes[h]
+        want = vo.head_attention(r, f64(hnd(q)[h]), f64(hnd(k)[h]), f64(hnd(v)[h]), spec_of(cfg), rows)
+        err = np.abs(f64(hnd(out)[h][torch.as_tensor(rows, device=DEV)]) - want).max()
+        say(f"one launch, head {h} route {r}: max-abs {err:.3e}")
+        assert err <= 2e-2
