@@ -314,11 +314,11 @@ int vorta_soft_mixture_layer(vorta_plan* p, const void* q, const void* k, const 
   uint8_t routes[VORTA_MAX_HEADS];
   if (p->d.dtype == VORTA_BF16) {
     // Fused form: no branch is written out in full and there is no blend pass.
-    //   1. core-set branch of every head -> o_c (pooled rows only)
-    //   2. sliding-tile branch of every head -> the video rows of `out`, unscaled
-    //   3. full-attention branch of every head; its epilogue reads the row `out` holds and the
+    //   1. core-set branch of every head -> o_c (pooled rows only), and in the same launch
+    //      sliding-tile branch of every head -> the video rows of `out`, unscaled
+    //   2. full-attention branch of every head; its epilogue reads the row `out` holds and the
     //      row of o_c the token is assigned to, and writes a1 full + a2 sliding + a3 core-set.
-    // The three run in this order on the stream, so each finds its inputs complete.
+    // The two run in this order on the stream, so the second finds its inputs complete.
     RouteLists rl;
     Carved c;
     std::memset(routes, VORTA_ROUTE_CORESET, sizeof(routes));
@@ -345,9 +345,8 @@ int vorta_soft_mixture_layer(vorta_plan* p, const void* q, const void* k, const 
     std::memset(&io, 0, sizeof(io));
     io.q = q_att; io.k = k_att; io.v = v; io.out = out;
     io.q_c = c.buf[4]; io.k_c = c.buf[5]; io.v_c = c.buf[6]; io.o_c = c.buf[7];
-    VORTA_TRY(launch_attention_bf16(p, rl, &io, nullptr, stream));
-    std::memset(routes, VORTA_ROUTE_WINDOW, sizeof(routes));
-    VORTA_TRY(split_routes(p, routes, &rl));
+    rl.count[1] = rl.count[2];               // every head on route 1 as well
+    std::memcpy(rl.heads[1], rl.heads[2], sizeof(rl.heads[1]));
     VORTA_TRY(launch_attention_bf16(p, rl, &io, nullptr, stream, nullptr, false));
     std::memset(routes, VORTA_ROUTE_FULL, sizeof(routes));
     VORTA_TRY(split_routes(p, routes, &rl));
