@@ -148,11 +148,13 @@ static int carve(const vorta_plan* p, const uint8_t* routes, void* workspace, si
 
 // Route 2, first half: core-set index on K as given (before any rotation), then Q, K, V pooled;
 // the pooled rows of Q and K are rotated at their slot owner's position.  One fused pass where
-// the bucket is small enough, else the index pass and three pool passes.
+// the bucket is small enough, else the index pass and three pool passes.  copies (or null): rotated copies
+// of Q and K for the heads of rl on routes 0 and 1, in the fused launch or one of their own.
 static int select_and_pool(vorta_plan* p, const RouteLists& rl, const void* q, const void* k, const void* v,
-                           int32_t* keep_idx, int32_t* assign, const Carved& c, void* stream) {
-  if (bcs_fused_applies(p))
-    return launch_bcs_select_pool(p, rl, q, k, v, keep_idx, assign, c.buf[4], c.buf[5], c.buf[6], stream);
+                           int32_t* keep_idx, int32_t* assign, const Carved& c, const RopeCopies* copies, void* stream) {
+  if (bcs_fused_applies(p) && rl.count[2])
+    return launch_bcs_select_pool(p, rl, q, k, v, keep_idx, assign, c.buf[4], c.buf[5], c.buf[6], copies, stream);
+  if (copies) VORTA_TRY(launch_rope_rows(p, rl, *copies, stream));
   VORTA_TRY(launch_bcs_index(p, rl, user_tensor(p, k), keep_idx, assign, stream));
   VORTA_TRY(launch_bcs_pool(p, rl, q, keep_idx, assign, true, c.buf[4], stream));
   VORTA_TRY(launch_bcs_pool(p, rl, k, keep_idx, assign, true, c.buf[5], stream));
@@ -167,12 +169,13 @@ static int layer(vorta_plan* p, const RouteLists& rl, const void* q, const void*
   // output rows the same way, so the layer call makes no tile-ordered copies
   // routes 0 and 1 with a rotary embedding: attention reads rotated copies of Q and K
   const void *q_att = q, *k_att = k;
-  if (p->rope && rl.count[0] + rl.count[1] > 0) {
-    VORTA_TRY(launch_rope_rows(p, rl, q, c.buf[10], k, c.buf[11], stream));
+  const RopeCopies copies = {{q, k}, {c.buf[10], c.buf[11]}};
+  const bool turn = p->rope && rl.count[0] + rl.count[1] > 0;
+  if (turn) {
     q_att = c.buf[10];
     k_att = c.buf[11];
   }
-  VORTA_TRY(select_and_pool(p, rl, q, k, v, keep_idx, assign, c, stream));
+  VORTA_TRY(select_and_pool(p, rl, q, k, v, keep_idx, assign, c, turn ? &copies : nullptr, stream));
   vorta_attn_io io;
   io.q = q_att; io.k = k_att; io.v = v; io.out = out;
   io.q_t = io.k_t = io.v_t = nullptr;
@@ -239,7 +242,7 @@ int vorta_bcs_select_pool(vorta_plan* p, const void* q, const void* k, const voi
   Carved c;
   std::memset(&c, 0, sizeof(c));
   c.buf[4] = (char*)q_c; c.buf[5] = (char*)k_c; c.buf[6] = (char*)v_c;
-  return select_and_pool(p, rl, q, k, v, keep_idx, assign, c, stream);
+  return select_and_pool(p, rl, q, k, v, keep_idx, assign, c, nullptr, stream);
 }
 
 int vorta_rope_apply(vorta_plan* p, const void* src, const uint8_t* routes, void* dst, void* stream) {
@@ -248,7 +251,7 @@ int vorta_rope_apply(vorta_plan* p, const void* src, const uint8_t* routes, void
   if (!p->rope || rl.count[0] + rl.count[1] == 0) return VORTA_OK;
   VORTA_TRY(check_ptr(src, "src"));
   VORTA_TRY(check_ptr(dst, "dst"));
-  return launch_rope_rows(p, rl, src, dst, nullptr, nullptr, stream);
+  return launch_rope_rows(p, rl, RopeCopies{{src, nullptr}, {dst, nullptr}}, stream);
 }
 
 int vorta_bcs_pool(vorta_plan* p, const void* src, const uint8_t* routes, const int32_t* keep_idx,
@@ -326,27 +329,26 @@ int vorta_soft_mixture_layer(vorta_plan* p, const void* q, const void* k, const 
     VORTA_TRY(carve(p, routes, workspace, workspace_bytes, &c));
     int32_t* keep_idx = (int32_t*)c.buf[8];
     int32_t* assign = (int32_t*)c.buf[9];
-    VORTA_TRY(select_and_pool(p, rl, q, k, v, keep_idx, assign, c, stream));
+    rl.count[1] = rl.count[2];               // every head on route 1 as well
+    std::memcpy(rl.heads[1], rl.heads[2], sizeof(rl.heads[1]));
     const void *q_att = q, *k_att = k;
+    RopeCopies copies = {{q, k}, {nullptr, nullptr}};
     if (p->rope) {       // rotated copies for the other two branches, behind the core-set buffers
       size_t core_bytes = 0;
       VORTA_TRY(vorta_workspace_bytes(p, routes, &core_bytes));
       const size_t tensor_bytes = ((size_t)p->d.heads * p->N * p->d.head_dim * p->elem_bytes + 255) & ~(size_t)255;
       char* q_r = (char*)workspace + core_bytes;
       char* k_r = q_r + tensor_bytes;
-      RouteLists all_full;
-      std::memset(routes, VORTA_ROUTE_FULL, sizeof(routes));
-      VORTA_TRY(split_routes(p, routes, &all_full));
-      VORTA_TRY(launch_rope_rows(p, all_full, q, q_r, k, k_r, stream));
+      copies.dst[0] = q_r;
+      copies.dst[1] = k_r;
       q_att = q_r;
       k_att = k_r;
     }
+    VORTA_TRY(select_and_pool(p, rl, q, k, v, keep_idx, assign, c, p->rope ? &copies : nullptr, stream));
     vorta_attn_io io;
     std::memset(&io, 0, sizeof(io));
     io.q = q_att; io.k = k_att; io.v = v; io.out = out;
     io.q_c = c.buf[4]; io.k_c = c.buf[5]; io.v_c = c.buf[6]; io.o_c = c.buf[7];
-    rl.count[1] = rl.count[2];               // every head on route 1 as well
-    std::memcpy(rl.heads[1], rl.heads[2], sizeof(rl.heads[1]));
     VORTA_TRY(launch_attention_bf16(p, rl, &io, nullptr, stream, nullptr, false));
     std::memset(routes, VORTA_ROUTE_FULL, sizeof(routes));
     VORTA_TRY(split_routes(p, routes, &rl));

@@ -99,10 +99,16 @@ int launch_bcs_index(vorta_plan* p, const RouteLists& rl, const UserTensor& feat
 int launch_bcs_pool(vorta_plan* p, const RouteLists& rl, const void* src, const int32_t* keep_idx,
                     const int32_t* assign, bool rotate, void* dst, void* stream);
 bool bcs_fused_applies(const vorta_plan* p);
+// One or two (src[1] not null) tensors whose rows of the heads on routes 0 and 1 go to dst turned.
+struct RopeCopies {
+  const void* src[2];
+  void* dst[2];
+};
+// copies: not null, the rotation of the heads on routes 0 and 1 rides in the same launch
 int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, const void* k, const void* v,
-                           int32_t* keep_idx, int32_t* assign, void* qc, void* kc, void* vc, void* stream);
-int launch_rope_rows(vorta_plan* p, const RouteLists& rl, const void* src, void* dst, const void* src2, void* dst2,
-                     void* stream);
+                           int32_t* keep_idx, int32_t* assign, void* qc, void* kc, void* vc, const RopeCopies* copies,
+                           void* stream);
+int launch_rope_rows(vorta_plan* p, const RouteLists& rl, const RopeCopies& copies, void* stream);
 int launch_unpool(vorta_plan* p, const RouteLists& rl, const void* o_c, const int32_t* assign, void* out,
                   void* stream);
 // Core-set index of a layer call: with it the attention launch writes the rows of route 2 to the tokens that

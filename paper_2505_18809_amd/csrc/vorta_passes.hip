@@ -631,12 +631,88 @@ int launch_bcs_pool(vorta_plan* p, const RouteLists& rl, const void* src, const 
 }
 
 // ------------------------------------------------------------------------------------------
+// Rotary embedding of whole rows, heads of routes 0 and 1: one thread per (row, 16-byte chunk) looks its
+// table entries up once and loops over the heads, four at a time so that four loads are in flight; dst
+// has the caller's layout.  One or two tensors (the layer call turns Q and K).  Text rows
+// are copied.  Bound: HBM: Q and K of 14 heads x 119,056 tokens (1.7 GB) 339 us = 5.0 TB/s; with the table
+// read again for every head and a launch for each tensor 578 us.
+// ------------------------------------------------------------------------------------------
+template <typename T>
+struct RopeRows {
+  const T* src[2];
+  T* dst[2];
+  HeadList hl;
+  int L, N, cshift;
+  long head_stride, row_stride;
+  int blocks;          // workgroups per tensor
+  int tensors;
+};
+template <typename T>
+__device__ __forceinline__ void rope_rows_block(const RopeRows<T>& job, const Rope& rope, int block) {
+  constexpr int CN = Chunk<T>::N;
+  const bool second = block >= job.blocks;
+  const T* __restrict__ src = second ? job.src[1] : job.src[0];
+  T* __restrict__ dst = second ? job.dst[1] : job.dst[0];
+  const HeadList& hl = job.hl;
+  const long gid = (long)(second ? block - job.blocks : block) * 256 + threadIdx.x;
+  const int i = (int)(gid >> job.cshift);
+  const int c = (int)(gid & ((1 << job.cshift) - 1));
+  if (i >= job.N) return;
+  const long off0 = (long)i * job.row_stride + c * CN;
+  if (i >= job.L) {
+    for (int s = 0; s < hl.n; ++s) {
+      const long off = off0 + hl.id[s] * job.head_stride;
+      *(uint4*)(dst + off) = *(const uint4*)(src + off);
+    }
+    return;
+  }
+  const RopeLane<CN / 2> rl(rope, c * (CN / 2));
+  float2 cs[CN / 2];
+  const int f = i / (rope.H * rope.W), rem = i - f * (rope.H * rope.W), h = rem / rope.W;
+  rl.load(rope, f, h, rem - h * rope.W, cs);
+  for (int s0 = 0; s0 < hl.n; s0 += 4) {
+    uint4 raw[4];
+    long off[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      off[u] = off0 + hl.id[min(s0 + u, hl.n - 1)] * job.head_stride;
+      raw[u] = Chunk<T>::raw(src + off[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (s0 + u >= hl.n) break;
+      double x[CN];
+      Chunk<T>::widen(raw[u], x);
+      rl.turn(cs, x);
+      *(uint4*)(dst + off[u]) = pack_chunk<T>(x);
+    }
+  }
+}
+
+template <typename T>
+static RopeRows<T> rope_rows_job(const vorta_plan* p, const RouteLists& rl, const RopeCopies& r) {
+  RopeRows<T> job;
+  job.src[0] = (const T*)r.src[0]; job.src[1] = (const T*)r.src[1];
+  job.dst[0] = (T*)r.dst[0]; job.dst[1] = (T*)r.dst[1];
+  job.hl.n = 0;
+  for (int route = 0; route < 2; ++route)
+    for (int i = 0; i < rl.count[route]; ++i) job.hl.id[job.hl.n++] = (uint8_t)rl.heads[route][i];
+  const UserTensor ut = user_tensor(p, r.src[0]);
+  job.L = (int)p->L; job.N = (int)p->N; job.cshift = chunk_shift(p);
+  job.head_stride = ut.head_stride; job.row_stride = ut.row_stride;
+  job.blocks = (int)((((long)p->N << job.cshift) + 255) / 256);
+  job.tensors = r.src[1] ? 2 : 1;
+  return job;
+}
+
+// ------------------------------------------------------------------------------------------
 // Select and pool in one pass (what the layer call runs): one wavefront per (bucket, head) requests the
 // bucket's K, Q and V rows before it computes anything, P passes of G tokens each, so one memory round
 // trip covers them all and every row comes from HBM once; then it ranks as bcs_index_kernel does, writes
 // keep_idx / assign, and merges and stores the three tensors as bcs_pool_kernel does (same operations in
-// the same order: the results of the two forms are identical bit for bit).  The last workgroups of a
-// head copy its text rows behind the pooled ones.
+// the same order: the results of the two forms are identical bit for bit).  Further workgroups of a
+// head copy its text rows behind the pooled ones, and the last ones turn the rows of the heads on
+// routes 0 and 1 where the layer call asks for that too (a launch of its own costs a small layer 4 us).
 //
 // Bound: HBM.  On 16 heads of 75,600 tokens (1.40 GB with the index) 283 us = 4.9 TB/s, what a large copy
 // reaches; with the rotary embedding 355 us (the fp64 turn of every pooled Q and K row).  An earlier form
@@ -650,9 +726,14 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
                                                               long head_stride, long row_stride, int Lc, int n_core_rows,
                                                               int* __restrict__ keep_idx, int* __restrict__ assign,
                                                               T* __restrict__ qc, T* __restrict__ kc, T* __restrict__ vc,
-                                                              Rope rope) {
+                                                              Rope rope, int text_blocks, RopeRows<T> rows_job) {
   constexpr int CN = Chunk<T>::N, CPR = D / CN, G = 64 / CPR;
   const int s = blockIdx.y;
+  if (ROPE && (int)blockIdx.x >= bucket_blocks + text_blocks) {
+    const int block = ((int)blockIdx.x - bucket_blocks - text_blocks) * gridDim.y + s;
+    if (block < rows_job.blocks * rows_job.tensors) rope_rows_block(rows_job, rope, block);
+    return;
+  }
   const long head_off = hl.id[s] * head_stride;
   if ((int)blockIdx.x >= bucket_blocks) {          // text rows
     const int i = ((int)blockIdx.x - bucket_blocks) * 256 + threadIdx.x;
@@ -771,23 +852,33 @@ bool bcs_fused_applies(const vorta_plan* p) { return fused_tokens(p) > 0; }
 // Index on K, then Q, K, V pooled (Q and K rotated if the plan has a rotary embedding) into
 // qc, kc, vc, and the text rows copied behind them.
 int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, const void* k, const void* v,
-                           int32_t* keep_idx, int32_t* assign, void* qc, void* kc, void* vc, void* stream) {
+                           int32_t* keep_idx, int32_t* assign, void* qc, void* kc, void* vc, const RopeCopies* copies,
+                           void* stream) {
   if (rl.count[2] == 0) return VORTA_OK;
   const UserTensor ut = user_tensor(p, k);
   const int bucket_blocks = (p->n_buckets + 3) / 4;
-  const long text_chunks = (long)p->d.n_text << chunk_shift(p);
-  const dim3 grid((unsigned)(bucket_blocks + (text_chunks + 255) / 256), rl.count[2]);
+  const int text_blocks = (int)((((long)p->d.n_text << chunk_shift(p)) + 255) / 256);
   const HeadList hl = head_list(rl, 2);
   const Geo g = make_geo(p);
   const int rows = (int)(p->Lc + p->d.n_text), fused = fused_tokens(p);
+  int turn_blocks = 0;                       // workgroups along x of the rotation
   const Rope rope = make_rope(p);
   hipStream_t st = (hipStream_t)stream;
 #define VORTA_FUSED(T_, D_, P_, R_)                                                                                     \
-  hipLaunchKernelGGL((bcs_select_pool_kernel<T_, D_, P_, R_>), grid, dim3(256), 0, st, (const T_*)q, (const T_*)k,      \
-                     (const T_*)v, hl, g, p->n_buckets, bucket_blocks, p->d_slot_base, ut.head_stride, ut.row_stride,   \
-                     (int)p->Lc, rows, keep_idx, assign, (T_*)qc, (T_*)kc, (T_*)vc, rope)
+  {                                                                                                                     \
+    RopeRows<T_> job;                                                                                                   \
+    std::memset(&job, 0, sizeof(job));                                                                                  \
+    if (R_ && copies) {                                                                                                 \
+      job = rope_rows_job<T_>(p, rl, *copies);                                                                          \
+      turn_blocks = (job.blocks * job.tensors + rl.count[2] - 1) / rl.count[2];                                         \
+    }                                                                                                                   \
+    hipLaunchKernelGGL((bcs_select_pool_kernel<T_, D_, P_, R_>), dim3(bucket_blocks + text_blocks + turn_blocks, rl.count[2]), \
+                       dim3(256), 0, st, (const T_*)q, (const T_*)k, (const T_*)v, hl, g, p->n_buckets, bucket_blocks,  \
+                       p->d_slot_base, ut.head_stride, ut.row_stride, (int)p->Lc, rows, keep_idx, assign, (T_*)qc,      \
+                       (T_*)kc, (T_*)vc, rope, text_blocks, job);                                                       \
+  }
 #define VORTA_FUSED_R(T_, D_, P_) \
-  if (p->rope) VORTA_FUSED(T_, D_, P_, true); else VORTA_FUSED(T_, D_, P_, false)
+  if (p->rope) VORTA_FUSED(T_, D_, P_, true) else VORTA_FUSED(T_, D_, P_, false)
   if (p->d.dtype == VORTA_BF16) {
     if (fused == 12) { VORTA_FUSED_R(uint16_t, 128, 3); }
     else if (fused == 16) { VORTA_FUSED_R(uint16_t, 128, 4); }
@@ -805,78 +896,21 @@ int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, c
   return launch_status("bcs_select_pool_kernel");
 }
 
-// ------------------------------------------------------------------------------------------
-// Rotary embedding of whole rows, heads of routes 0 and 1: one thread per (row, 16-byte chunk) looks its
-// table entries up once and loops over the heads, four at a time so that four loads are in flight; dst
-// has the caller's layout.  blockIdx.y: tensor (the layer call turns Q and K in one launch).  Text rows
-// are copied.  Bound: HBM: Q and K of 14 heads x 119,056 tokens (1.7 GB) 339 us = 5.0 TB/s; with the table
-// read again for every head and a launch for each tensor 578 us.
-// ------------------------------------------------------------------------------------------
 template <typename T>
-struct RopeTensors {
-  const T* src[2];
-  T* dst[2];
-};
-template <typename T>
-__global__ __launch_bounds__(256) void rope_rows_kernel(RopeTensors<T> ts, HeadList hl, int L, int N, long head_stride,
-                                                        long row_stride, int cshift, Rope rope) {
-  constexpr int CN = Chunk<T>::N;
-  const T* __restrict__ src = ts.src[blockIdx.y];
-  T* __restrict__ dst = ts.dst[blockIdx.y];
-  const long gid = (long)blockIdx.x * 256 + threadIdx.x;
-  const int i = (int)(gid >> cshift);
-  const int c = (int)(gid & ((1 << cshift) - 1));
-  if (i >= N) return;
-  const long off0 = (long)i * row_stride + c * CN;
-  if (i >= L) {
-    for (int s = 0; s < hl.n; ++s) {
-      const long off = off0 + hl.id[s] * head_stride;
-      *(uint4*)(dst + off) = *(const uint4*)(src + off);
-    }
-    return;
-  }
-  const RopeLane<CN / 2> rl(rope, c * (CN / 2));
-  float2 cs[CN / 2];
-  const int f = i / (rope.H * rope.W), rem = i - f * (rope.H * rope.W), h = rem / rope.W;
-  rl.load(rope, f, h, rem - h * rope.W, cs);
-  for (int s0 = 0; s0 < hl.n; s0 += 4) {
-    uint4 raw[4];
-    long off[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      off[u] = off0 + hl.id[min(s0 + u, hl.n - 1)] * head_stride;
-      raw[u] = Chunk<T>::raw(src + off[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (s0 + u >= hl.n) break;
-      double x[CN];
-      Chunk<T>::widen(raw[u], x);
-      rl.turn(cs, x);
-      *(uint4*)(dst + off[u]) = pack_chunk<T>(x);
-    }
-  }
+__global__ __launch_bounds__(256) void rope_rows_kernel(RopeRows<T> job, Rope rope) {
+  rope_rows_block(job, rope, blockIdx.x);
 }
 
-// src2 / dst2: a second tensor for the same launch, or null
-int launch_rope_rows(vorta_plan* p, const RouteLists& rl, const void* src, void* dst, const void* src2, void* dst2,
-                     void* stream) {
-  HeadList hl;
-  hl.n = 0;
-  for (int r = 0; r < 2; ++r)
-    for (int i = 0; i < rl.count[r]; ++i) hl.id[hl.n++] = (uint8_t)rl.heads[r][i];
-  if (hl.n == 0 || !p->rope) return VORTA_OK;
-  const UserTensor ut = user_tensor(p, src);
-  const int cs = chunk_shift(p);
-  const long total = (long)p->N << cs;
-  const dim3 grid((unsigned)((total + 255) / 256), src2 ? 2 : 1);
+int launch_rope_rows(vorta_plan* p, const RouteLists& rl, const RopeCopies& copies, void* stream) {
+  if (rl.count[0] + rl.count[1] == 0 || !p->rope) return VORTA_OK;
   const Rope rope = make_rope(p);
   hipStream_t st = (hipStream_t)stream;
-#define VORTA_ROPE(T_)                                                                                              \
-  hipLaunchKernelGGL(rope_rows_kernel<T_>, grid, dim3(256), 0, st,                                                  \
-                     (RopeTensors<T_>{{(const T_*)src, (const T_*)src2}, {(T_*)dst, (T_*)dst2}}), hl, (int)p->L,    \
-                     (int)p->N, ut.head_stride, ut.row_stride, cs, rope)
-  if (p->d.dtype == VORTA_BF16) VORTA_ROPE(uint16_t); else VORTA_ROPE(float);
+#define VORTA_ROPE(T_)                                                                                          \
+  {                                                                                                             \
+    const RopeRows<T_> job = rope_rows_job<T_>(p, rl, copies);                                                  \
+    hipLaunchKernelGGL(rope_rows_kernel<T_>, dim3(job.blocks * job.tensors), dim3(256), 0, st, job, rope);      \
+  }
+  if (p->d.dtype == VORTA_BF16) VORTA_ROPE(uint16_t) else VORTA_ROPE(float)
 #undef VORTA_ROPE
   return launch_status("rope_rows_kernel");
 }
