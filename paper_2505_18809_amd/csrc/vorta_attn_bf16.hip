@@ -846,6 +846,7 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) sa = MFMA(k_frag(k_rd, ks), qf[ks], sa);
   mask_tail(sa, 0);
+  __syncthreads();                                 // K(0) is read: the first iteration requests K(2) into its stage
 
 #define SLOT_FENCE() __builtin_amdgcn_sched_barrier(0)
   // One iteration.  sc: scores of superblock i (in), sn: scores of i+1 (out), pp: P^T(i-1) (in), pc: P^T(i)
