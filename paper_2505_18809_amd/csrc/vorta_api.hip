@@ -72,7 +72,6 @@ int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io,
   a->win_gather = io->q_t == nullptr;
   a->tok_of = a->win_gather ? p->d_tok_of : p->d_iota;
   a->win_row = a->win_gather ? p->d_win_tok : p->d_win_rows;
-  a->iota = p->d_iota;
   a->runs = p->d_runs;
   a->n_runs = p->d_n_runs;
   a->max_runs = p->max_runs;

@@ -683,8 +683,8 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_layer_kernel(const AttnArgs 
 //   * rings of two stages (KS = 4: K 65 KB, V 68 KB) and two barriers per iteration: K(i+2) is requested
 //     where iteration i begins, into the stage K(i) has left, V(i+1) in its middle, into the stage that
 //     V(i-1) has just left, and each is waited for one and a half iterations later, where its first reader is.
-//   * every row goes through an index table -- the tile permutation for window items, 0, 1, 2, ... for the
-//     others -- so that one launch carries all items of the layer, longest first.
+//   * one launch carries all items of the layer, longest first: the key stream exists twice, for window items
+//     (rows through the index table) and for the others (consecutive rows).
 // Bound: the barriers.  The wavefronts of a workgroup reach its two barriers together, and what they do
 // around them (fragment requests, reference check, packing) no matrix instruction covers: about 2,000
 // cycles per 128-key superblock against 1,024 of matrix instructions (2,600 with one barrier, all loads
@@ -717,7 +717,7 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
   const bool unpool = !MIX && w.seg == 1 && a.keep_idx;          // core-set rows straight to their tokens
   uint16_t* O = unpool ? (uint16_t*)a.o0 + a.core_heads[w.head] * a.head_stride0
                        : (uint16_t*)(user ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
-  const int* tok = w.seg == 2 ? a.tok_of : a.iota;
+  const int* tok = a.tok_of;                       // of items with a run list (the identity over tile-ordered copies)
   const unsigned row_stride = (unsigned)w.row_stride;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -788,35 +788,6 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
 #pragma unroll
     for (int h = 0; h < 4; ++h) off[h] = __umul24((unsigned)gi[h], row_stride) + (unsigned)ld_col;
   };
-  int gi[4] = {0, 0, 0, 0};                        // indices of superblock i + 2 as iteration i begins
-  unsigned off1[4], off2[4];                       // row offsets of superblocks i + 1 and i + 2
-  {
-    int g0[4], g1[4];
-    note();
-    lookup(g0);
-    note();
-    lookup(g1);
-    note();
-    lookup(gi);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    named(g0);
-    named(g1);
-    named(gi);
-    // the query rows are here too: let the compiler wait for them now, not behind the row loads
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qf[ks]));
-    offsets(g0, off2);
-    offsets(g1, off1);
-#pragma unroll
-    for (int h = 0; h < 4; ++h) dma_k(0, h, off2[h]);
-#pragma unroll
-    for (int h = 0; h < 4; ++h) dma_k(1, h, off1[h]);
-#pragma unroll
-    for (int h = 0; h < 4; ++h) dma_v(0, h, off2[h]);
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // K(0); K(1) and V(0) are still on their way
-    __syncthreads();
-  }
-
   // fragment addresses of the lane in stage 0 of its wavefront's block
   const int t16 = lane & 15, blk = lane >> 4;
   const lds_ptr k_rd = (lds_ptr)(smem + (8 * kg + (l32 & 7)) * KG + (l32 >> 3) * 64 + 8 * g);
@@ -843,127 +814,179 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
     for (int v = 0; v < 16; ++v)
       if (8 * (v >> 2) + (v & 3) >= nv - 4 * g) t[v] = -INFINITY;
   };
+
+  // The whole key stream.  TABLE: rows through the index table (window items); otherwise the item's keys are
+  // consecutive rows from row 0 and their offsets arithmetic, a tenth of the iteration's instructions less.
+  auto stream = [&](auto table) {
+    constexpr bool TABLE = decltype(table)::value;
+    int gi[4] = {0, 0, 0, 0};                        // indices of superblock i + 2 as iteration i begins
+    unsigned off1[4], off2[4];                       // row offsets of superblocks i + 1 and i + 2
+    unsigned off_key[4], off_last = 0;               // without table: of superblock 0, and the last row's
+    if constexpr (TABLE) {
+      int g0[4], g1[4];
+      note();
+      lookup(g0);
+      note();
+      lookup(g1);
+      note();
+      lookup(gi);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      named(g0);
+      named(g1);
+      named(gi);
+      // the query rows are here too: let the compiler wait for them now, not behind the row loads
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) sa = MFMA(k_frag(k_rd, ks), qf[ks], sa);
-  mask_tail(sa, 0);
-  __syncthreads();                                 // K(0) is read: the first iteration requests K(2) into its stage
+      for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qf[ks]));
+      offsets(g0, off2);
+      offsets(g1, off1);
+    } else {
+      off_last = (unsigned)(n_keys - 1) * row_stride + (unsigned)ld_col;
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        off_key[h] = (unsigned)group_key(h) * row_stride + (unsigned)ld_col;
+        off2[h] = min(off_key[h], off_last);
+        off1[h] = min(off_key[h] + SB * row_stride, off_last);
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 4; ++h) dma_k(0, h, off2[h]);
+#pragma unroll
+    for (int h = 0; h < 4; ++h) dma_k(1, h, off1[h]);
+#pragma unroll
+    for (int h = 0; h < 4; ++h) dma_v(0, h, off2[h]);
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // K(0); K(1) and V(0) are still on their way
+    __syncthreads();
+
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) sa = MFMA(k_frag(k_rd, ks), qf[ks], sa);
+    mask_tail(sa, 0);
+    __syncthreads();                                 // K(0) is read: the first iteration requests K(2) into its stage
 
 #define SLOT_FENCE() __builtin_amdgcn_sched_barrier(0)
-  // One iteration.  sc: scores of superblock i (in), sn: scores of i+1 (out), pp: P^T(i-1) (in), pc: P^T(i)
-  // (out).  The first iteration has no second product: V(-1) does not exist and its stage holds nothing.
-  auto body = [&](int i, auto first, f32x16& sc, f32x16& sn, bf16x8 (&pp)[2], bf16x8 (&pc)[2]) {
-    constexpr bool FIRST = decltype(first)::value;
-    constexpr int AHEAD = 4;                       // fragments requested ahead of their use
-    const lds_ptr vq = opaque(v_rd + ((i + 1) & 1) * SPLIT_V);     // V(i-1)
-    const lds_ptr kq = opaque(k_rd + ((i + 1) & 1) * SPLIT_K);     // K(i+1)
-    bf16x8 vf[NPV], kf[NS - NPV];
-    if (!FIRST) {
+    // One iteration.  sc: scores of superblock i (in), sn: scores of i+1 (out), pp: P^T(i-1) (in), pc: P^T(i)
+    // (out).  The first iteration has no second product: V(-1) does not exist and its stage holds nothing.
+    auto body = [&](int i, auto first, f32x16& sc, f32x16& sn, bf16x8 (&pp)[2], bf16x8 (&pc)[2]) {
+      constexpr bool FIRST = decltype(first)::value;
+      constexpr int AHEAD = 4;                       // fragments requested ahead of their use
+      const lds_ptr vq = opaque(v_rd + ((i + 1) & 1) * SPLIT_V);     // V(i-1)
+      const lds_ptr kq = opaque(k_rd + ((i + 1) & 1) * SPLIT_K);     // K(i+1)
+      bf16x8 vf[NPV], kf[NS - NPV];
+      if (!FIRST) {
 #pragma unroll
-      for (int n = 0; n < AHEAD; ++n) vf[n] = v_frag(vq, n);
-    }
-    note();                                        // superblock i+3
-    float ps0 = 0.f, ps1 = 0.f;
-    float x[NE], ex[NE];
-    unsigned u[8];
-    const float mc = m_ref * c;
+        for (int n = 0; n < AHEAD; ++n) vf[n] = v_frag(vq, n);
+      }
+      if constexpr (TABLE) note();                   // superblock i+3
+      float ps0 = 0.f, ps1 = 0.f;
+      float x[NE], ex[NE];
+      unsigned u[8];
+      const float mc = m_ref * c;
 #pragma unroll
-    for (int n = 0; n < NS; ++n) {
+      for (int n = 0; n < NS; ++n) {
+        SLOT_FENCE();
+        if (n == NPV) {
+          // K(i+1) was requested one and a half iterations ago; behind it are V(i), the lookups and K(i+2)
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TABLE ? 12 : 8) : "memory");
+          __syncthreads();
+#pragma unroll
+          for (int m = 0; m < AHEAD; ++m) kf[m] = k_frag(kq, m);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) sn[v] = 0.f;
+        }
+        if (n < NPV) {
+          if (!FIRST) o[n & 3] = MFMA(vf[n], pp[n >> 2], o[n & 3]);
+          if (!FIRST && n + AHEAD < NPV) vf[n + AHEAD] = v_frag(vq, n + AHEAD);
+        } else {
+          sn = MFMA(kf[n - NPV], qf[n - NPV], sn);
+          if (n + AHEAD < NS) kf[n + AHEAD - NPV] = k_frag(kq, n + AHEAD - NPV);
+        }
+        // staging: the lookups go ahead of the row loads, as the counts of the waits assume
+        if (n == 0) {
+          if constexpr (TABLE) {
+            named(gi);
+            offsets(gi, off2);
+          } else {
+            const unsigned base = (unsigned)(i + 2) * (SB * row_stride);
+#pragma unroll
+            for (int h = 0; h < 4; ++h) off2[h] = min(off_key[h] + base, off_last);
+          }
+        }
+        if (TABLE && n == 1) lookup(gi);             // superblock i+3
+        if (n >= 2 && n < 6) dma_k(i + 2, n - 2, off2[n - 2]);
+        if (n > NPV && n <= NPV + 4) {
+          dma_v(i + 1, n - NPV - 1, off1[n - NPV - 1]);
+          off1[n - NPV - 1] = off2[n - NPV - 1];
+        }
+        // softmax, staggered by stage as in the pipelined kernel
+        if (n == 0) { x[0] = fmaf(sc[0], c, -mc); x[1] = fmaf(sc[1], c, -mc); }
+        if (n >= 1 && n <= NS - 2) x[n + 1] = fmaf(sc[n + 1], c, -mc);
+        if (n >= 1 && n <= NS - 2) ex[n - 1] = __builtin_amdgcn_exp2f(x[n - 1]);
+        if (n == NS - 1) { ex[NE - 2] = __builtin_amdgcn_exp2f(x[NE - 2]); ex[NE - 1] = __builtin_amdgcn_exp2f(x[NE - 1]); }
+        if (n >= 3 && (n & 1)) {
+          const int p = (n - 3) >> 1;
+          u[p] = pack_bf16(ex[2 * p], ex[2 * p + 1]);
+          asm volatile("" : "+v"(u[p]));
+        }
+        if (n >= 2) {
+          if (n & 1) ps1 += ex[n - 2];
+          else ps0 += ex[n - 2];
+        }
+      }
       SLOT_FENCE();
-      if (n == NPV) {
-        // K(i+1) was requested one and a half iterations ago; behind it are V(i), the lookups and K(i+2)
-        asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
-        __syncthreads();
+      u[NP - 1] = pack_bf16(ex[NE - 2], ex[NE - 1]);
+      float ps = (ps0 + ex[NE - 2]) + (ps1 + ex[NE - 1]);
+      // reference check, see the pipelined kernel.  A quarter of the key stream may have no key yet, or scores
+      // of -inf only: the reference then stays -inf and the probabilities are 0.
+      if (__any(!(ps <= P_MAX))) {
+        float top = max3(sc[0], sc[1], sc[2]);
 #pragma unroll
-        for (int m = 0; m < AHEAD; ++m) kf[m] = k_frag(kq, m);
+        for (int k = 3; k < 15; k += 2) top = max3(top, sc[k], sc[k + 1]);
+        top = max_xor32(fmaxf(top, sc[15]));
+        const float m_new = fmaxf(m_ref, top);
+        const float alpha = m_ref == m_new ? 1.f : __builtin_amdgcn_exp2f((m_ref - m_new) * c);
+        m_ref = m_new;
+        const float mc2 = m_new == -INFINITY ? 0.f : m_new * c;
+        ps = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sn[v] = 0.f;
+        for (int p = 0; p < NP; ++p) {
+          const float e0 = __builtin_amdgcn_exp2f(fmaf(sc[2 * p], c, -mc2));
+          const float e1 = __builtin_amdgcn_exp2f(fmaf(sc[2 * p + 1], c, -mc2));
+          u[p] = pack_bf16(e0, e1);
+          ps += e0 + e1;
+        }
+        l_run *= alpha;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) o[d][v] *= alpha;
       }
-      if (n < NPV) {
-        if (!FIRST) o[n & 3] = MFMA(vf[n], pp[n >> 2], o[n & 3]);
-        if (!FIRST && n + AHEAD < NPV) vf[n + AHEAD] = v_frag(vq, n + AHEAD);
-      } else {
-        sn = MFMA(kf[n - NPV], qf[n - NPV], sn);
-        if (n + AHEAD < NS) kf[n + AHEAD - NPV] = k_frag(kq, n + AHEAD - NPV);
-      }
-      // staging: the lookups go ahead of the row loads, as the counts of the waits assume
-      if (n == 0) {
-        named(gi);
-        offsets(gi, off2);
-      }
-      if (n == 1) lookup(gi);                      // superblock i+3
-      if (n >= 2 && n < 6) dma_k(i + 2, n - 2, off2[n - 2]);
-      if (n > NPV && n <= NPV + 4) {
-        dma_v(i + 1, n - NPV - 1, off1[n - NPV - 1]);
-        off1[n - NPV - 1] = off2[n - NPV - 1];
-      }
-      // softmax, staggered by stage as in the pipelined kernel
-      if (n == 0) { x[0] = fmaf(sc[0], c, -mc); x[1] = fmaf(sc[1], c, -mc); }
-      if (n >= 1 && n <= NS - 2) x[n + 1] = fmaf(sc[n + 1], c, -mc);
-      if (n >= 1 && n <= NS - 2) ex[n - 1] = __builtin_amdgcn_exp2f(x[n - 1]);
-      if (n == NS - 1) { ex[NE - 2] = __builtin_amdgcn_exp2f(x[NE - 2]); ex[NE - 1] = __builtin_amdgcn_exp2f(x[NE - 1]); }
-      if (n >= 3 && (n & 1)) {
-        const int p = (n - 3) >> 1;
-        u[p] = pack_bf16(ex[2 * p], ex[2 * p + 1]);
-        asm volatile("" : "+v"(u[p]));
-      }
-      if (n >= 2) {
-        if (n & 1) ps1 += ex[n - 2];
-        else ps0 += ex[n - 2];
-      }
+      l_run += ps;
+      pc[0] = __builtin_bit_cast(bf16x8, make_uint4(u[0], u[1], u[2], u[3]));
+      pc[1] = __builtin_bit_cast(bf16x8, make_uint4(u[4], u[5], u[6], u[7]));
+      mask_tail(sn, i + 1);
+      // V(i) and the indices of i+3 are here; K(i+2) and V(i+1) may still be on their way
+      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      __syncthreads();
+    };
+    // The two register sets alternate, so the loop takes superblocks in pairs and the odd one out of those after
+    // the first goes before it (leaving the loop in the middle would move the accumulators every iteration).
+    const std::integral_constant<bool, true> is_first;
+    const std::integral_constant<bool, false> not_first;
+    body(0, is_first, sa, sb, pa, pb);
+    int i = 1;
+    if (!(n_sb & 1)) {
+      body(i++, not_first, sb, sa, pb, pa);
+      sb = sa;
+      pb[0] = pa[0];
+      pb[1] = pa[1];
     }
-    SLOT_FENCE();
-    u[NP - 1] = pack_bf16(ex[NE - 2], ex[NE - 1]);
-    float ps = (ps0 + ex[NE - 2]) + (ps1 + ex[NE - 1]);
-    // reference check, see the pipelined kernel.  A quarter of the key stream may have no key yet, or scores
-    // of -inf only: the reference then stays -inf and the probabilities are 0.
-    if (__any(!(ps <= P_MAX))) {
-      float top = max3(sc[0], sc[1], sc[2]);
-#pragma unroll
-      for (int k = 3; k < 15; k += 2) top = max3(top, sc[k], sc[k + 1]);
-      top = max_xor32(fmaxf(top, sc[15]));
-      const float m_new = fmaxf(m_ref, top);
-      const float alpha = m_ref == m_new ? 1.f : __builtin_amdgcn_exp2f((m_ref - m_new) * c);
-      m_ref = m_new;
-      const float mc2 = m_new == -INFINITY ? 0.f : m_new * c;
-      ps = 0.f;
-#pragma unroll
-      for (int p = 0; p < NP; ++p) {
-        const float e0 = __builtin_amdgcn_exp2f(fmaf(sc[2 * p], c, -mc2));
-        const float e1 = __builtin_amdgcn_exp2f(fmaf(sc[2 * p + 1], c, -mc2));
-        u[p] = pack_bf16(e0, e1);
-        ps += e0 + e1;
-      }
-      l_run *= alpha;
-#pragma unroll
-      for (int d = 0; d < 4; ++d)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o[d][v] *= alpha;
+    for (; i < n_sb; i += 2) {
+      body(i, not_first, sb, sa, pb, pa);
+      body(i + 1, not_first, sa, sb, pa, pb);
     }
-    l_run += ps;
-    pc[0] = __builtin_bit_cast(bf16x8, make_uint4(u[0], u[1], u[2], u[3]));
-    pc[1] = __builtin_bit_cast(bf16x8, make_uint4(u[4], u[5], u[6], u[7]));
-    mask_tail(sn, i + 1);
-    // V(i) and the indices of i+3 are here; K(i+2) and V(i+1) may still be on their way
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-    __syncthreads();
-  };
-  // The two register sets alternate, so the loop takes superblocks in pairs and the odd one out of those after
-  // the first goes before it (leaving the loop in the middle would move the accumulators every iteration).
-  const std::integral_constant<bool, true> is_first;
-  const std::integral_constant<bool, false> not_first;
-  body(0, is_first, sa, sb, pa, pb);
-  int i = 1;
-  if (!(n_sb & 1)) {
-    body(i++, not_first, sb, sa, pb, pa);
-    sb = sa;
-    pb[0] = pa[0];
-    pb[1] = pa[1];
-  }
-  for (; i < n_sb; i += 2) {
-    body(i, not_first, sb, sa, pb, pa);
-    body(i + 1, not_first, sa, sb, pa, pb);
-  }
 #undef SLOT_FENCE
+  };
+  if (w.runs) stream(std::integral_constant<bool, true>());
+  else stream(std::integral_constant<bool, false>());
   {                                                // second product of the last superblock
     const lds_ptr vq = opaque(v_rd + ((n_sb - 1) & 1) * SPLIT_V);
 #pragma unroll

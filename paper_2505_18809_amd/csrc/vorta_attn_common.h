@@ -37,7 +37,6 @@ struct AttnArgs {
   // through tok_of (tile-order index -> token index); win_heads = head id of each window slot.  With
   // copies tok_of is the identity.
   const int* tok_of;                // [N]
-  const int* iota;                  // [N]: 0, 1, 2, ...
   const int* tile_row0;             // [n_tiles + 1]: first tile-order row of each tile (edge tiles may be clipped)
   int win_gather;
   const int* runs;                  // [n_tiles][max_runs][2]
