@@ -2,8 +2,8 @@
 """Benchmark of the routed attention layer on one MI355X.
 
 A step is one pass of the whole hot path -- core-set selection and pooling, the routed
-attention launches (window rows gathered through the tile permutation), unpool / scatter back
--- over one seeded synthetic layer, with Q/K/V already resident in HBM.  Prints ONE JSON line.
+attention launches (window rows gathered through the tile permutation, core-set rows written to
+the tokens that read them) -- over one seeded synthetic layer, with Q/K/V already resident in HBM.  Prints ONE JSON line.
 
   value       effective TFLOP/s of the whole layer call: FLOPs of the two contractions
               actually required by each head's route (padding and softmax not counted)
@@ -282,8 +282,8 @@ def main():
             res["zero_ms"] = timed(3)
         return res
 
-    # dominant kernel alone: the dense and core-set heads of this layer form one launch of the
-    # pipelined kernel (the window heads are the launches after it)
+    # dominant kernel alone: the dense and core-set heads of this layer as one launch of the pipelined
+    # kernel (in the layer call the larger window items follow them in the same launch)
     dom = {"kernel": "attn_f32_kernel", "ms": attn_ms, "flops": flops}
     win_ms = None
     route_alone = {}
@@ -292,8 +292,8 @@ def main():
             # (zero operands: off by default, so that a profile of the default command holds launches of one kind)
             dom = {"kernel": "attn_bf16_pipe_kernel<false, 8>", "flops": per_route[0] + per_route[2],
                    **heads_alone(routes != 1, zero=args.zero_operands)}
-        # the window heads alone (their tiles are the attention call's later launches; their text
-        # rows, if the layer has text tokens, ride in a short launch of the pipelined kernel)
+        # the window heads alone (their text rows, if the layer has text tokens, go first in the
+        # same launch)
         if counts[1] > 0:
             win_ms = heads_alone(routes == 1)["ms"]
         # and, on request, every route alone (launches of the dominant kernel on other head sets:
@@ -320,7 +320,7 @@ def main():
                    "routes_full_window_coreset": counts, "layout": "HND" if args.layout == 1 else "NHD",
                    "flops_per_layer": flops},
         "roofline": {"bound": "mfma", "kernel": dom["kernel"],
-                     "launch": f"{counts[0]} dense + {counts[2]} core-set heads of the layer (the window heads are a separate launch)",
+                     "launch": f"{counts[0]} dense + {counts[2]} core-set heads of the layer (launched alone; in the layer call the window items follow)",
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                      "flops_per_launch": dom["flops"], "ms_per_launch": dom["ms"],
                      "traffic": traffic["bytes"] if traffic else None,
