@@ -125,6 +125,7 @@ struct Rope {
   int pF, pH, pW;       // channel pairs that turn with the frame index, the row, the column
   int baseH, baseW;     // first table entry of the H and W axes
   int H, W;             // grid extents, to decode a token index
+  bool all;             // the spans cover every channel of a head
 };
 
 static Rope make_rope(const vorta_plan* p) {
@@ -134,40 +135,51 @@ static Rope make_rope(const vorta_plan* p) {
   r.baseH = p->d.F * r.pF;
   r.baseW = r.baseH + p->d.H * r.pH;
   r.H = p->d.H; r.W = p->d.W;
+  r.all = 2 * (r.pF + r.pH + r.pW) == p->d.head_dim;
   return r;
 }
 
 // What of the table a lane needs for its NP channel pairs, whatever the token: pair i's entry is
-// base[i] + (the token's coordinate on axis[i]) * stride[i]; base < 0 for a pair past the spans, which
-// is left alone.
+// base[i] + the token's row of the table of axis[i]; a pair past the spans is left alone, and takes the first
+// entry so that the read stays inside.  Spans that cover the head (rope.all, the same for every lane) need no
+// such test, a fifth of the instructions of a turn; a token's three table rows are multiplied out once, not
+// once per pair (an integer product costs four additions).
 template <int NP>
 struct RopeLane {
-  int base[NP], stride[NP], axis[NP];
-  __device__ __forceinline__ RopeLane(const Rope& r, int pair0) {
+  int base[NP], axis[NP];
+  bool past[NP], all;
+  __device__ __forceinline__ RopeLane(const Rope& r, int pair0) : all(r.all) {
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
       const int j = pair0 + i, jh = j - r.pF, jw = jh - r.pH;
       axis[i] = j < r.pF ? 0 : jh < r.pH ? 1 : 2;
-      stride[i] = j < r.pF ? r.pF : jh < r.pH ? r.pH : r.pW;
-      base[i] = j < r.pF ? j : jh < r.pH ? r.baseH + jh : jw < r.pW ? r.baseW + jw : -1;
+      base[i] = j < r.pF ? j : jh < r.pH ? r.baseH + jh : r.baseW + jw;
+      past[i] = jw >= r.pW;
     }
   }
   __device__ __forceinline__ void load(const Rope& r, int f, int h, int w, float2 (&cs)[NP]) const {
+    const int of = f * r.pF, oh = h * r.pH, ow = w * r.pW;
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-      const int x = axis[i] == 0 ? f : axis[i] == 1 ? h : w;
-      cs[i] = r.cs[max(base[i], 0) + (base[i] < 0 ? 0 : x * stride[i])];
+      int at = base[i] + (axis[i] == 0 ? of : axis[i] == 1 ? oh : ow);
+      if (!all) at = past[i] ? 0 : at;
+      cs[i] = r.cs[at];
     }
   }
   // Turns x[2i], x[2i+1].  fp64; for rows as given (bf16 or fp32 elements times fp32 table entries) the
   // products are exact, so the fused form changes no bit there.
   __device__ __forceinline__ void turn(const float2 (&cs)[NP], double* x) const {
+    if (all) turn_pairs<true>(cs, x);
+    else turn_pairs<false>(cs, x);
+  }
+  template <bool ALL>
+  __device__ __forceinline__ void turn_pairs(const float2 (&cs)[NP], double* x) const {
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
       const double c = (double)cs[i].x, sn = (double)cs[i].y, u = x[2 * i], v = x[2 * i + 1];
       const double x0 = __builtin_fma(u, c, -(v * sn)), x1 = __builtin_fma(u, sn, v * c);
-      x[2 * i] = base[i] < 0 ? u : x0;
-      x[2 * i + 1] = base[i] < 0 ? v : x1;
+      x[2 * i] = !ALL && past[i] ? u : x0;
+      x[2 * i + 1] = !ALL && past[i] ? v : x1;
     }
   }
 };
@@ -715,7 +727,8 @@ static RopeRows<T> rope_rows_job(const vorta_plan* p, const RouteLists& rl, cons
 // routes 0 and 1 where the layer call asks for that too (a launch of its own costs a small layer 4 us).
 //
 // Bound: HBM.  On 16 heads of 75,600 tokens (1.40 GB with the index) 283 us = 4.9 TB/s, what a large copy
-// reaches; with the rotary embedding 355 us (the fp64 turn of every pooled Q and K row).  An earlier form
+// reaches; with the rotary embedding 337 us, bound by vector instructions (the fp64 turn of every pooled Q and K
+// row and its look-ups; 355 with a test and an integer product per channel pair).  An earlier form
 // that read K a second time as quarter rows, divided in fp64, took 64-bit integer quotients and stored
 // element by element: 397 us and 718 us.
 // ------------------------------------------------------------------------------------------

@@ -39,3 +39,30 @@ def test_one_pass_selection_at_the_edges_of_its_instances(bucket, dtype, d, rope
             assert gap > 1e-9 and np.array_equal(keep_idx[slot].cpu().numpy(), want_ki)
         assert np.array_equal(assign[slot].cpu().numpy(), want_asg)
         assert torch.equal(v_c[slot, plan.n_core:], (v[h] if layout == 1 else v[:, h])[cfg.n_video:])
+
+
+@pytest.mark.parametrize("dims", [(44, 42, 42), (44, 42, 40), (2, 0, 126), (0, 64, 62), (0, 2, 0)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_rotation_with_spans_that_cover_the_head_and_that_do_not(dims, dtype):
+    """Spans that cover the head run without the test for channels past them.  One rounding to the element
+    type (8 or 24 significant bits: up to 2^-8 or 2^-24 of a turned value, itself at most |u| + |v|), for bf16
+    after one to fp32, and the fp32 table (2^-24 of each product) separate a turned pair from fp64; channels past the spans and text rows keep their bits."""
+    cfg = LayerConfig("spans", (5, 6, 7), 2, 128, dtype, (1, 1, 1), (1, 1, 1), seed=41, n_text=5, fixed_routes=(0, 2),
+                      bucket=(2, 3, 2), keep_num=1, keep_den=2, rope_dims=dims)
+    print(dims, dtype, flush=True)
+    q, k, v = make_qkv(cfg, DEV, 1)
+    plan = vorta.plan_for(cfg, layout=1)
+    got = vorta.vorta_rope_apply(plan, k, cfg.fixed_routes)[0]
+    assert torch.equal(got[cfg.n_video:], k[0, cfg.n_video:])
+    assert torch.equal(got[:, sum(dims):], k[0, :, sum(dims):])
+    tok = np.arange(cfg.n_video)
+    F, H, W = cfg.grid
+    coords = np.stack([tok // (H * W), tok // W % H, tok % W], axis=1)
+    x = f64(k[0])[:cfg.n_video]
+    want = vo.rope_rotate(x, coords, dims, cfg.rope_theta)
+    size = np.repeat(np.abs(x[:, 0::2]) + np.abs(x[:, 1::2]), 2, axis=1)
+    eps = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -24) + 2 * 2.0 ** -24
+    assert (np.abs(f64(got)[:cfg.n_video] - want) <= eps * size).all()
+    keep_idx, assign, q_c, k_c, v_c = vorta.vorta_bcs_select_pool(plan, q, k, v, cfg.fixed_routes)
+    for one, src in ((q_c, q), (k_c, k)):
+        assert torch.equal(one, vorta.vorta_bcs_pool(plan, src, cfg.fixed_routes, keep_idx, assign, rotate=True))
