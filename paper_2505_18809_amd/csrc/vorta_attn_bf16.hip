@@ -605,6 +605,12 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
       __syncthreads();
     }
   }
+  // The last lookups are still on their way into gi0 and gi1, which nothing reads any more: without this wait
+  // their registers would be free for the fragments below while the loads can still write them.
+  if constexpr (WIN) {
+    win_wait(true);
+    SLOT_FENCE();
+  }
 #undef SLOT_FENCE
 
   // ---- second product of the last iteration's block (its probabilities are in pa)
