@@ -286,8 +286,9 @@ int vorta_scatter_back(vorta_plan* plan, const uint8_t* routes_host, const void*
 /* ---- the whole path ----------------------------------------------------------------------- */
 
 /* Bytes of device scratch the layer call needs for these routes (internal buffers above; the layer
- * call makes no tile-ordered copies -- those four buffers are empty with bf16, reserved but unused
- * with fp32 -- and writes the core-set rows straight to their tokens, o_c staying unused too). */
+ * call writes the core-set rows straight to their tokens, so that o_c stays unused, and makes tile-ordered
+ * copies only with fp32 and only where `out` shares memory with the inputs: those four buffers are empty
+ * with bf16). */
 int vorta_workspace_bytes(const vorta_plan* plan, const uint8_t* routes_host, size_t* bytes);
 
 /* Byte offsets of the internal buffers inside the workspace, in the order
@@ -300,7 +301,10 @@ int vorta_workspace_layout(const vorta_plan* plan, const uint8_t* routes_host, s
  * branch of section 3.2.  reorder + index build + pool + fused attention + scatter back, all on
  * `stream`: q, k, v (user layout) -> out (user layout).  The BCS feature is K.  With rope_dims,
  * q and k are the projections BEFORE the rotary embedding: routes 0 and 1 attend on rotated
- * copies, route 2 selects and pools on the rows as given and rotates the pooled rows. */
+ * copies, route 2 selects and pools on the rows as given and rotates the pooled rows.
+ * `out` may be q itself.  It may share memory with k or v (or with other rows of q) only if no head takes
+ * route 0 and, with bf16, none takes route 1 either (k and q with rope_dims: always, attention reads the rotated
+ * copies); otherwise a row could be written while another still reads it, and the result is undefined. */
 int vorta_routed_attention_layer(vorta_plan* plan, const void* q, const void* k, const void* v,
                                  const uint8_t* routes_host, void* out, void* workspace,
                                  size_t workspace_bytes, void* stream);

@@ -160,12 +160,17 @@ static int select_and_pool(vorta_plan* p, const RouteLists& rl, const void* q, c
   return launch_bcs_pool(p, rl, v, keep_idx, assign, false, c.buf[6], stream);
 }
 
+// Whether two tensors of the plan's size share memory.
+static bool overlap(const vorta_plan* p, const void* a, const void* b) {
+  const size_t bytes = (size_t)p->d.heads * p->N * p->d.head_dim * p->elem_bytes;
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + bytes && y < x + bytes;
+}
+
 static int layer(vorta_plan* p, const RouteLists& rl, const void* q, const void* k, const void* v,
-                 const uint8_t* routes, void* out, const Carved& c, void* stream) {
+                 void* out, const Carved& c, void* stream) {
   int32_t* keep_idx = (int32_t*)c.buf[8];
   int32_t* assign = (int32_t*)c.buf[9];
-  // route 1: the attention kernels gather token rows through the tile permutation and scatter their
-  // output rows the same way, so the layer call makes no tile-ordered copies
   // routes 0 and 1 with a rotary embedding: attention reads rotated copies of Q and K
   const void *q_att = q, *k_att = k;
   const RopeCopies copies = {{q, k}, {c.buf[10], c.buf[11]}};
@@ -177,12 +182,22 @@ static int layer(vorta_plan* p, const RouteLists& rl, const void* q, const void*
   VORTA_TRY(select_and_pool(p, rl, q, k, v, keep_idx, assign, c, turn ? &copies : nullptr, stream));
   vorta_attn_io io;
   io.q = q_att; io.k = k_att; io.v = v; io.out = out;
-  io.q_t = io.k_t = io.v_t = nullptr;
-  io.o_t = nullptr;
+  io.q_t = io.k_t = io.v_t = io.o_t = nullptr;
   io.q_c = c.buf[4]; io.k_c = c.buf[5]; io.v_c = c.buf[6]; io.o_c = c.buf[7];
   const CoreIndex core = {keep_idx, assign};
-  (void)routes;
-  return attention(p, rl, &io, &core, stream);
+  // Route 1: the attention kernels gather token rows through the tile permutation and scatter their output
+  // rows the same way.  An item may write rows of `out` that another one has yet to read as keys or values if
+  // they share memory (an item's own query rows are read before it writes them, so `out` may be q): fp32 takes
+  // such calls, over tile-ordered copies.
+  const bool apart = p->d.dtype == VORTA_F32 && rl.count[1] &&
+                     (overlap(p, out, k_att) || overlap(p, out, v) || (out != q_att && overlap(p, out, q_att)));
+  if (!apart) return attention(p, rl, &io, &core, stream);
+  io.q_t = c.buf[0]; io.k_t = c.buf[1]; io.v_t = c.buf[2]; io.o_t = c.buf[3];
+  VORTA_TRY(launch_reorder(p, rl, q_att, c.buf[0], true, stream));
+  VORTA_TRY(launch_reorder(p, rl, k_att, c.buf[1], true, stream));
+  VORTA_TRY(launch_reorder(p, rl, v, c.buf[2], true, stream));
+  VORTA_TRY(attention(p, rl, &io, &core, stream));
+  return launch_reorder(p, rl, out, c.buf[3], false, stream);
 }
 
 }  // namespace vorta
@@ -299,7 +314,7 @@ int vorta_routed_attention_layer(vorta_plan* p, const void* q, const void* k, co
   VORTA_TRY(check_ptr(v, "v")); VORTA_TRY(check_ptr(out, "out"));
   Carved c;
   VORTA_TRY(carve(p, routes, workspace, workspace_bytes, &c));
-  return layer(p, rl, q, k, v, routes, out, c, stream);
+  return layer(p, rl, q, k, v, out, c, stream);
 }
 
 int vorta_soft_mixture_layer(vorta_plan* p, const void* q, const void* k, const void* v,
@@ -371,7 +386,7 @@ int vorta_soft_mixture_layer(vorta_plan* p, const void* q, const void* k, const 
     VORTA_TRY(begin(p, routes, &rl));
     Carved c;
     VORTA_TRY(carve(p, routes, inner, inner_bytes, &c));
-    VORTA_TRY(layer(p, rl, q, k, v, routes, branch[r], c, stream));
+    VORTA_TRY(layer(p, rl, q, k, v, branch[r], c, stream));
   }
   return launch_blend3(p, branch[0], branch[1], branch[2], alpha_host, out, stream);
 }
@@ -424,7 +439,7 @@ int vorta_routed_attention_layer_static(vorta_plan* p, const void* q, const void
   VORTA_TRY(static_scratch(&scratch_ptr));
   Carved c;
   VORTA_TRY(carve(p, routes, scratch_ptr, VORTA_STATIC_SCRATCH_BYTES, &c));
-  return layer(p, rl, q, k, v, routes, out, c, stream);
+  return layer(p, rl, q, k, v, out, c, stream);
 }
 
 }  // extern "C"

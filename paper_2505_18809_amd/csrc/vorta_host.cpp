@@ -466,8 +466,8 @@ int vorta_route_select(const float* alpha, int32_t heads, uint8_t* routes) {
 // Workspace: q_t,k_t,v_t,o_t,q_c,k_c,v_c,o_c,keep_idx,assign,q_r,k_r, each 256-byte aligned.
 static void workspace_sizes(const vorta_plan* p, const RouteLists& rl, size_t sizes[12]) {
   const size_t row = (size_t)p->d.head_dim * p->elem_bytes;
-  // tile-ordered copies: no layer call makes them (the attention kernels gather rows); the fp32 layout
-  // keeps their places, so that sizes and offsets are what callers of earlier versions laid out
+  // tile-ordered copies: the attention kernels gather rows; only an fp32 layer call whose output shares memory
+  // with its inputs makes them, and what it needs does not depend on the pointers it will be called with
   const size_t tiled = p->d.dtype == VORTA_BF16 ? 0 : (size_t)rl.count[1] * p->N * row;
   const size_t core = (size_t)rl.count[2] * (p->Lc + p->d.n_text) * row;
   for (int i = 0; i < 4; ++i) sizes[i] = tiled;

@@ -183,3 +183,41 @@ def test_long_and_window_items_in_one_launch(n_text, layout):
         err = np.abs(f64(hnd(out)[h][torch.as_tensor(rows, device=DEV)]) - want).max()
         say(f"one launch, head {h} route {r}: max-abs {err:.3e}")
         assert err <= 2e-2
+
+
+@pytest.mark.parametrize("dtype,d,routes,rope,shared", [
+    ("fp32", 64, (1, 2, 1), None, "qkv"),             # window heads over tile-ordered copies where k or v is overwritten
+    ("fp32", 128, (1, 2, 1, 1, 2), None, "qkv"),
+    ("fp32", 128, (1, 2, 1), (44, 42, 42), "qkv"),
+    ("fp32", 128, (0, 2, 1), (44, 42, 42), "qk"),     # attention reads the rotated copies of q and k
+    ("fp32", 64, (0, 1, 2), None, "q"),
+    ("bf16", 128, (2, 2, 2), None, "qkv"),
+    ("bf16", 128, (0, 1, 2), (44, 42, 42), "qk"),
+    ("bf16", 128, (0, 1, 2), None, "q"),
+])
+@pytest.mark.parametrize("layout,n_text", [(1, 0), (0, 19)])
+def test_output_in_the_memory_of_an_input(dtype, d, routes, rope, shared, layout, n_text):
+    """The layer call with `out` in the memory of q, k or v, where that is allowed, gives what it gives with a tensor of
+    its own: bit for bit, but for text rows of fp32 window heads over copies, which meet their keys in another
+    order (half an ulp of the result either way)."""
+    cfg = LayerConfig(f"shared{dtype}", (7, 12, 13), len(routes), d, dtype, (2, 3, 4), (3, 3, 3), seed=59, n_text=n_text,
+                      fixed_routes=routes, rope_dims=rope)
+    say(f"{cfg.name} {routes} layout {layout}")
+    plan = vorta.plan_for(cfg, layout=layout)
+    vorta.vorta_plan_upload(plan)
+    inputs = make_qkv(cfg, DEV, layout)
+    want = vorta.vorta_routed_attention_layer(plan, *inputs, routes)
+    ws = torch.empty(vorta.vorta_workspace_bytes(plan, routes), dtype=torch.uint8, device=DEV)
+    for name in shared:
+        for static in (False, True):
+            x = [t.clone() for t in inputs]
+            out = x["qkv".index(name)]
+            if static:
+                vorta.vorta_routed_attention_layer_static(plan, *x, routes, out)
+            else:
+                vorta.vorta_routed_attention_layer(plan, *x, routes, out=out, workspace=ws.random_(0, 255))
+            torch.cuda.synchronize()
+            a, b = (out, want) if layout == 1 else (out.transpose(0, 1), want.transpose(0, 1))
+            assert torch.equal(a[:, :cfg.n_video], b[:, :cfg.n_video]), name
+            a, b = a[:, cfg.n_video:].double(), b[:, cfg.n_video:].double()
+            assert ((a - b).abs() <= 2.0 ** -23 * b.abs()).all(), name
