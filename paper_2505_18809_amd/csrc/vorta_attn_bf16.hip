@@ -560,9 +560,9 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
       }
       mx = max_xor32(mx);
       const float m_new = fmaxf(m_ref, mx);
-      const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * c);     // 0 for the first block
+      const float alpha = m_ref == m_new ? 1.f : __builtin_amdgcn_exp2f((m_ref - m_new) * c);   // 0 for the first block
       m_ref = m_new;
-      const float mc2 = m_new * c;
+      const float mc2 = m_new == -INFINITY ? 0.f : m_new * c;    // scores of -inf only so far: probabilities 0
       ps = 0.f;
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
@@ -940,8 +940,8 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
       SLOT_FENCE();
       u[NP - 1] = pack_bf16(ex[NE - 2], ex[NE - 1]);
       float ps = (ps0 + ex[NE - 2]) + (ps1 + ex[NE - 1]);
-      // reference check, see the pipelined kernel.  A quarter of the key stream may have no key yet, or scores
-      // of -inf only: the reference then stays -inf and the probabilities are 0.
+      // reference check, see the pipelined kernel; a share of the key stream may also have no key yet, which
+      // looks like scores of -inf
       if (__any(!(ps <= P_MAX))) {
         float top = max3(sc[0], sc[1], sc[2]);
 #pragma unroll

@@ -221,3 +221,35 @@ def test_output_in_the_memory_of_an_input(dtype, d, routes, rope, shared, layout
             assert torch.equal(a[:, :cfg.n_video], b[:, :cfg.n_video]), name
             a, b = a[:, cfg.n_video:].double(), b[:, cfg.n_video:].double()
             assert ((a - b).abs() <= 2.0 ** -23 * b.abs()).all(), name
+
+
+@pytest.mark.parametrize("masked", [-float("inf"), torch.finfo(torch.bfloat16).min], ids=["inf", "lowest"])
+@pytest.mark.parametrize("grid,heads,dtype", [((21, 29, 52), 8, "bf16"),      # the pipelined kernel on every route
+                                              ((9, 8, 12), 4, "bf16"),        # the split kernel
+                                              ((9, 8, 12), 4, "fp32")])
+def test_rows_whose_first_keys_are_all_masked(grid, heads, dtype, masked):
+    """Masked keys as programs mark them: a channel in which every query is at least 1.5 holds -inf, or the
+    lowest bf16 value, in the keys of the first six frames, so the scores of the first blocks of many rows are
+    -inf (in fp32 arithmetic also for the lowest value).  No row sees masked keys only, and masked keys weigh 0.
+    The core-set branch takes the finite mask only, and its rows of those frames are left out: the
+    similarities of masked tokens are ties of a rounding's size."""
+    if dtype == "fp32" and masked != -float("inf"):
+        masked = torch.finfo(torch.float32).min
+    routes = (0, 1, 2, 1, 0, 1, 2, 1)[:heads] if masked != -float("inf") else (0, 1, 1, 0, 1, 1, 1, 1)[:heads]
+    cfg = LayerConfig("masked", grid, heads, 128, dtype, (3, 6, 4), (3, 3, 3), seed=61, n_text=21, fixed_routes=routes)
+    say(f"{cfg.name} {grid} {dtype} {masked}")
+    q, k, v = make_qkv(cfg, DEV)
+    q[..., 7] = q[..., 7].abs() + 1.5
+    k[:, : 6 * grid[1] * grid[2], 7] = masked
+    plan = vorta.plan_for(cfg)
+    out = vorta.vorta_routed_attention_layer(plan, q, k, v, routes)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(0, cfg.n_tokens, max(1, cfg.n_tokens // 97)), np.arange(cfg.n_tokens - 9, cfg.n_tokens)]))
+    for h in range(min(heads, 4)):
+        some = rows[rows >= 6 * grid[1] * grid[2]] if routes[h] == 2 else rows
+        with np.errstate(all="ignore"):
+            want = vo.head_attention(routes[h], f64(q[h]), f64(k[h]), f64(v[h]), spec_of(cfg), some)
+        assert np.isfinite(want).all()
+        err = np.abs(f64(out[h][torch.as_tensor(some, device=DEV)]) - want).max()
+        say(f"masked, head {h} route {routes[h]}: max-abs {err:.3e}")
+        assert err <= (2e-2 if dtype == "bf16" else 1e-5)
