@@ -6,7 +6,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <map>
 #include <new>
 
 #include "vorta_internal.h"
@@ -231,74 +230,58 @@ int vorta_plan_create(const vorta_layer_desc* desc, vorta_plan** out) {
     std::copy(run_lists[t].begin(), run_lists[t].end(), p->runs.begin() + (size_t)t * p->max_runs * 2);
   }
 
-  // Query tiles whose run lists are identical see the same keys (under the clamped centre rule the
-  // border tile and its inner neighbour on every axis, under the block rule all tiles of a block): one
-  // pass over the key stream serves them together.
-  std::map<std::vector<int32_t>, std::vector<int>> same_keys;
-  for (int t = 0; t < p->n_tiles; ++t) same_keys[run_lists[t]].push_back(t);
+  // Query tiles with the same box see the same keys (under the clamped centre rule the border tile and its
+  // inner neighbour on every axis, under the block rule all tiles of a block): one pass over the key stream
+  // serves them together.  win_tiles holds them group after group, the groups in the order of their first tiles
+  // (neighbours in the lists are neighbours on the grid).  A box is a product of three ranges, so the first tile of
+  // a group follows axis by axis.
+  std::vector<int32_t> leader(p->n_tiles), place((size_t)p->n_tiles + 1, 0);
   {
-    // Work items of the kernels: a group's rows as one sequence, cut into 256-row blocks across tile
-    // borders.  Cut tile by tile, a 432-token tile was a block of 256 rows and one of 176 that cost as
-    // much: 350 blocks per head on a 20x45x80 grid with (6,9,8) tiles, now 287 -- window launches of 20
-    // heads 7.92 -> 6.90 ms.
-    std::vector<const std::vector<int>*> groups;
-    for (auto& g : same_keys) groups.push_back(&g.second);
-    std::sort(groups.begin(), groups.end(),      // neighbours in the lists are neighbours on the grid
-              [](const std::vector<int>* a, const std::vector<int>* b) { return a->front() < b->front(); });
-    p->win_rows.reserve((size_t)p->L);
-    for (const std::vector<int>* g : groups) {
-      const int32_t begin = (int32_t)p->win_rows.size();
-      for (int t : *g)
-        for (int32_t r = p->tile_row0[t]; r < p->tile_row0[t + 1]; ++r) p->win_rows.push_back(r);
-      const int32_t end = (int32_t)p->win_rows.size();
-      for (int32_t first = begin; first < end; first += 256) {
-        const int32_t n = std::min(256, end - first);
-        std::vector<int32_t>& list = p->win_list[n > 128 ? 0 : 1];
-        list.insert(list.end(), {first, n, g->front(), 0});
+    std::vector<int> first_like[3];      // per axis, the first tile coordinate with the same range
+    for (int a = 0; a < 3; ++a) {
+      const int stride = a == 0 ? p->nt[1] * p->nt[2] : a == 1 ? p->nt[2] : 1;
+      for (int c = 0; c < p->nt[a]; ++c) {             // ranges move along the axis: equal ones are neighbours
+        const int32_t* box = &p->boxes[(size_t)c * stride * 6 + 2 * a];
+        const int32_t* before = &p->boxes[(size_t)std::max(c - 1, 0) * stride * 6 + 2 * a];
+        const bool same = c > 0 && box[0] == before[0] && box[1] == before[1];
+        first_like[a].push_back(same ? first_like[a].back() : c);
       }
-      for (int32_t first = begin; first < end; first += 64)
-        p->win_list[2].insert(p->win_list[2].end(), {first, std::min(64, end - first), g->front(), 0});
     }
-    std::vector<int64_t> blocks(p->n_tiles, 0);
-    for (int t = 0; t < p->n_tiles; ++t) {
-      for (size_t r = 1; r < run_lists[t].size(); r += 2) blocks[t] += run_lists[t][r];
-      blocks[t] = (blocks[t] + 63) / 64;
-    }
-    for (int l = 0; l < 3; ++l) {
-      const size_t n = p->win_list[l].size() / 4;
-      int64_t sum = 0;
-      for (size_t i = 0; i < n; ++i) sum += blocks[p->win_list[l][4 * i + 2]];
-      if (n) p->win_blocks[l] = (int)((sum + (int64_t)n - 1) / (int64_t)n);
-    }
+    int t = 0;
+    for (int f : first_like[0])
+      for (int h : first_like[1])
+        for (int w : first_like[2]) leader[t++] = (f * p->nt[1] + h) * p->nt[2] + w;
   }
-  if (p->tile_tokens <= 128) {
-    std::vector<std::array<int32_t, 4>> big, small;
-    auto flush = [&](std::array<int32_t, 4>& item, int rows) {
-      if (item[3] == 0) return;
-      (rows > 128 ? big : small).push_back(item);
-      item = {0, 0, 0, 0};
+  for (int t = 0; t < p->n_tiles; ++t) ++place[leader[t] + 1];
+  for (int t = 0; t < p->n_tiles; ++t) place[t + 1] += place[t];
+  p->win_tiles.resize((size_t)p->n_tiles);
+  {
+    std::vector<int32_t> next(place.begin(), place.end() - 1);
+    for (int t = 0; t < p->n_tiles; ++t) p->win_tiles[next[leader[t]]++] = t;
+  }
+  // Work items of the kernels: a group's rows as one sequence, cut into 256-row blocks across tile
+  // borders.  Cut tile by tile, a 432-token tile was a block of 256 rows and one of 176 that cost as
+  // much: 350 blocks per head on a 20x45x80 grid with (6,9,8) tiles, now 287 -- window launches of 20
+  // heads 7.92 -> 6.90 ms.
+  int64_t list_blocks[3] = {0, 0, 0};
+  int32_t end = 0;
+  for (int g = 0; g < p->n_tiles; ++g) {
+    if (place[g] == place[g + 1]) continue;      // not the first tile of a group
+    const int32_t begin = end;
+    for (int32_t i = place[g]; i < place[g + 1]; ++i) end += p->tile_row0[p->win_tiles[i] + 1] - p->tile_row0[p->win_tiles[i]];
+    int64_t blocks = 0;
+    for (size_t r = 1; r < run_lists[g].size(); r += 2) blocks += run_lists[g][r];
+    blocks = (blocks + 63) / 64;
+    auto add = [&](int list, int32_t first, int32_t rows) {
+      p->win_list[list].insert(p->win_list[list].end(), {first, rows, g, 0});
+      list_blocks[list] += blocks;
     };
-    for (auto& group : same_keys) {
-      std::array<int32_t, 4> item = {0, 0, 0, 0};
-      int rows = 0;
-      for (int t : group.second) {                       // ascending tile ids
-        const int n = p->tile_row0[t + 1] - p->tile_row0[t];
-        if (item[3] == 3 || rows + n > 256) {
-          flush(item, rows);
-          rows = 0;
-        }
-        item[item[3]++] = t;
-        rows += n;
-      }
-      flush(item, rows);
-    }
-    auto by_first_tile = [](const std::array<int32_t, 4>& a, const std::array<int32_t, 4>& b) { return a[0] < b[0]; };
-    std::sort(big.begin(), big.end(), by_first_tile);    // neighbours in the list are neighbours on the grid
-    std::sort(small.begin(), small.end(), by_first_tile);
-    p->n_win_big = (int)big.size();
-    p->n_win_small = (int)small.size();
-    for (auto* list : {&big, &small})
-      for (auto& item : *list) p->win_items.insert(p->win_items.end(), item.begin(), item.end());
+    for (int32_t first = begin; first < end; first += 256) add(end - first > 128 ? 0 : 1, first, std::min(256, end - first));
+    for (int32_t first = begin; first < end; first += 64) add(2, first, std::min(64, end - first));
+  }
+  for (int l = 0; l < 3; ++l) {
+    const int64_t n = (int64_t)p->win_list[l].size() / 4;
+    if (n) p->win_blocks[l] = (int)((list_blocks[l] + n - 1) / n);
   }
 
   // BCS slot layout: a (border-clipped) bucket of B' tokens keeps B' - k of them,
@@ -314,9 +297,6 @@ int vorta_plan_create(const vorta_layer_desc* desc, vorta_plan** out) {
         const int k = std::min(B - 1, (int)(((int64_t)B * (d.keep_den - d.keep_num)) / d.keep_den));
         p->slot_base[b++] = (int32_t)slot;
         slot += B - k;
-        const int df = std::min(d.bucket[0], d.F - f0), dh = std::min(d.bucket[1], d.H - h0), dw = std::min(d.bucket[2], d.W - w0);
-        const int centre = ((f0 + df / 2) * d.H + h0 + dh / 2) * d.W + w0 + dw / 2;
-        for (int s = 0; s < B - k; ++s) p->slot_bucket.insert(p->slot_bucket.end(), {centre, df | dh << 8 | dw << 16});
       }
   p->slot_base[b] = (int32_t)slot;
   p->Lc = slot;
@@ -406,9 +386,34 @@ int vorta_window_runs(const vorta_plan* p, int32_t* runs, int32_t* n_runs) {
 int vorta_window_items(const vorta_plan* p, int32_t* items, int32_t counts[2]) {
   clear_error();
   if (!p || !counts) return fail(VORTA_EINVAL, "null argument");
-  counts[0] = p->n_win_big;
-  counts[1] = p->n_win_small;
-  if (items) std::copy(p->win_items.begin(), p->win_items.end(), items);
+  std::vector<std::array<int32_t, 4>> big, small;
+  if (p->tile_tokens <= 128) {
+    std::array<int32_t, 4> item = {0, 0, 0, 0};
+    int rows = 0;
+    auto flush = [&]() {
+      if (item[3] > 0) (rows > 128 ? big : small).push_back(item);
+      item = {0, 0, 0, 0};
+      rows = 0;
+    };
+    const int32_t* box = nullptr;
+    for (int32_t t : p->win_tiles) {
+      const int32_t* its = &p->boxes[(size_t)t * 6];
+      const int n = p->tile_row0[t + 1] - p->tile_row0[t];
+      if (item[3] == 3 || rows + n > 256 || (box && !std::equal(its, its + 6, box))) flush();
+      box = its;
+      item[item[3]++] = t;
+      rows += n;
+    }
+    flush();
+    auto by_first_tile = [](const std::array<int32_t, 4>& a, const std::array<int32_t, 4>& b) { return a[0] < b[0]; };
+    std::sort(big.begin(), big.end(), by_first_tile);    // neighbours in the list are neighbours on the grid
+    std::sort(small.begin(), small.end(), by_first_tile);
+  }
+  counts[0] = (int32_t)big.size();
+  counts[1] = (int32_t)small.size();
+  if (items)
+    for (auto* list : {&big, &small})
+      for (auto& item : *list) items = std::copy(item.begin(), item.end(), items);
   return VORTA_OK;
 }
 

@@ -26,20 +26,12 @@ struct vorta_plan {
   std::vector<int32_t> runs;     // [n_tiles][max_runs][2]
   std::vector<int32_t> n_runs;   // [n_tiles]
   std::vector<int32_t> slot_base;  // [n_buckets + 1]
-  // [Lc][2]: the bucket of every core-set slot, as its centre token and its clipped extents (df | dh << 8 | dw << 16);
-  // which slots a bucket owns depends on its size only, so this is known before any selection
-  std::vector<int32_t> slot_bucket;
-  // what vorta_window_items reports (tiles of at most 128 tokens): tiles with identical key sets, up to
-  // three tiles and 256 rows together; {tile, tile, tile, count} each, the n_win_big entries of more
-  // than 128 rows first, then the n_win_small others.  Empty when a tile holds more than 128 tokens.
-  std::vector<int32_t> win_items;
-  int n_win_big = 0, n_win_small = 0;
-  // window work items of the bf16 kernels: the rows of all tiles with one key set are one sequence (win_rows
-  // holds these sequences one after the other, as tile-order rows), cut into blocks whatever the tile
-  // borders.  {first, n_rows, tile, 0}: n_rows places of win_rows from `first`, keys as tile `tile` sees
-  // them.  List 0: blocks of 129 to 256 rows; list 1: what is left of a sequence, at most 128 rows; list 2:
-  // the sequences cut into blocks of at most 64 rows instead.
-  std::vector<int32_t> win_rows;   // [L]
+  // window work items of the bf16 kernels: the rows of all tiles with one key set are one sequence, cut into
+  // blocks whatever the tile borders; win_tiles holds the tiles of these sequences one after the other.
+  // {first, n_rows, tile, 0}: n_rows places of the sequences' rows from `first`, keys as tile `tile` sees them.
+  // List 0: blocks of 129 to 256 rows; list 1: what is left of a sequence, at most 128 rows; list 2: the
+  // sequences cut into blocks of at most 64 rows instead.
+  std::vector<int32_t> win_tiles;  // [n_tiles]
   std::vector<int32_t> win_list[3];
   int win_blocks[3] = {0, 0, 0};   // 64-key blocks of the items of a list, on average (for the launch estimate)
   // rotary embedding: (cos, sin) of position * rate for every position of every axis,
@@ -47,9 +39,8 @@ struct vorta_plan {
   bool rope = false;
   std::vector<float> rope_cs;
 
-  // device tables, all in one allocation, uploaded on first device use: copies of the tables above, the
-  // tile-order -> sequence-order token table (identity for the text rows), that table taken at win_rows, and
-  // 0, 1, 2, ... for tile-ordered copies, whose rows are their own indices
+  // device tables, all in one allocation, uploaded on first device use: copies of the tables above and those that
+  // have one entry per token and are made for the upload only
   std::mutex mu;
   bool on_device = false;
   int device = -1;
@@ -57,11 +48,13 @@ struct vorta_plan {
   int32_t* d_runs = nullptr;
   int32_t* d_n_runs = nullptr;
   int32_t* d_slot_base = nullptr;
+  // [Lc][2]: the bucket of every core-set slot, as its centre token and its clipped extents (df | dh << 8 | dw << 16);
+  // which slots a bucket owns depends on its size only, so this is known before any selection
   int32_t* d_slot_bucket = nullptr;
-  int32_t* d_tok_of = nullptr;   // [N]
-  int32_t* d_iota = nullptr;     // [N]
-  int32_t* d_win_rows = nullptr; // [L]
-  int32_t* d_win_tok = nullptr;  // [L]
+  int32_t* d_tok_of = nullptr;   // [N]: tile-order row -> token (identity for the text rows)
+  int32_t* d_iota = nullptr;     // [N]: 0, 1, 2, ... for tile-ordered copies, whose rows are their own indices
+  int32_t* d_win_rows = nullptr; // [L]: the tile-order rows of the sequences of win_tiles
+  int32_t* d_win_tok = nullptr;  // [L]: their tokens
   int32_t* d_tile_row0 = nullptr;   // [n_tiles + 1]
   float* d_rope_cs = nullptr;
   int32_t* d_win_list[3] = {nullptr, nullptr, nullptr};
