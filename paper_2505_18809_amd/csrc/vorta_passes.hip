@@ -518,13 +518,26 @@ __global__ __launch_bounds__(256) void bcs_index_kernel(const T* __restrict__ fe
   const uint4 craw = Chunk<T>::raw(base + (long)bucket_token(g, k, k.centre).tok * row_stride);
   double nc, self, my_dot = 0.0, my_norm = 0.0;
   row_dots<T, CPR>(craw, craw, self, nc);
-  for (int pass = 0; pass * G < k.size; ++pass) {
-    const int j = min(G * pass + grp, k.size - 1);
+  // Rows of 32 chunks, two tokens a pass: four passes at a time, so that their loads go out together and their sums
+  // run in each other's latency (64-token buckets of 3,072 tokens, 8 heads, 18.7 -> 15.3 us; a large grid 4 to 11 %
+  // faster).  With 16 chunks the registers cost more than the latency (75,600 tokens, 94 -> 100 us).
+  constexpr int U = CPR == 32 ? 4 : 1;
+  int pass = 0;
+  auto row = [&](int p) { return Chunk<T>::raw(base + (long)bucket_token(g, k, min(G * p + grp, k.size - 1)).tok * row_stride); };
+  auto take = [&](int p, const uint4& raw) {
     double dot, norm;
-    row_dots<T, CPR>(craw, Chunk<T>::raw(base + (long)bucket_token(g, k, j).tok * row_stride), dot, norm);
-    to_token_lane<CPR>(dot, pass, lane, my_dot);
-    to_token_lane<CPR>(norm, pass, lane, my_norm);
+    row_dots<T, CPR>(craw, raw, dot, norm);
+    to_token_lane<CPR>(dot, p, lane, my_dot);
+    to_token_lane<CPR>(norm, p, lane, my_norm);
+  };
+  for (; (pass + U - 1) * G < k.size; pass += U) {
+    uint4 raw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) raw[u] = row(pass + u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) take(pass + u, raw[u]);
   }
+  for (; pass * G < k.size; ++pass) take(pass, row(pass));
   bool kept;
   int centre_slot;
   const int slot = rank_and_assign(k, prune, lane, similarity(my_dot, nc, my_norm), base_slot, kept, centre_slot);
@@ -715,7 +728,8 @@ __device__ __forceinline__ void rope_rows_block(const RopeRows<T>& job, const Ro
     long off[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      off[u] = off0 + hl.id[min(s0 + u, hl.n - 1)] * job.head_stride;
+      if (s0 + u >= hl.n) break;
+      off[u] = off0 + hl.id[s0 + u] * job.head_stride;
       raw[u] = Chunk<T>::raw(src + off[u]);
     }
 #pragma unroll
