@@ -85,80 +85,15 @@ static int window_centre(int q, int n, int w, int mode) {
   return std::min(std::max(q, lo), hi);
 }
 
-int vorta_plan_create(const vorta_layer_desc* desc, vorta_plan** out) {
-  clear_error();
-  if (!desc || !out) return fail(VORTA_EINVAL, "null desc or out");
-  *out = nullptr;
-  vorta_layer_desc d = *desc;
-  if (d.F < 1 || d.H < 1 || d.W < 1 || d.n_text < 0)
-    return fail(VORTA_ESHAPE, "grid %dx%dx%d / n_text %d must be positive", d.F, d.H, d.W, d.n_text);
-  {
-    // axis by axis, so that no product leaves the range of int64
-    const int64_t cap = (int64_t)1 << 30;
-    int64_t tokens = d.F;
-    for (int64_t axis : {(int64_t)d.H, (int64_t)d.W}) {
-      if (tokens > cap || axis > cap) return fail(VORTA_ESHAPE, "more than 2^30 tokens");
-      tokens *= axis;
-    }
-    if (tokens + d.n_text > cap) return fail(VORTA_ESHAPE, "more than 2^30 tokens");
-  }
-  if (d.heads < 1 || d.heads > VORTA_MAX_HEADS)
-    return fail(VORTA_ESHAPE, "heads = %d, supported 1..%d", d.heads, VORTA_MAX_HEADS);
-  if (d.dtype != VORTA_F32 && d.dtype != VORTA_BF16) return fail(VORTA_EDTYPE, "dtype %d", d.dtype);
-  if (d.dtype == VORTA_BF16 && d.head_dim != 128)
-    return fail(VORTA_ESHAPE, "bf16 supports head_dim 128, got %d", d.head_dim);
-  if (d.dtype == VORTA_F32 && d.head_dim != 64 && d.head_dim != 128)
-    return fail(VORTA_ESHAPE, "fp32 supports head_dim 64 or 128, got %d", d.head_dim);
-  if (d.layout != VORTA_LAYOUT_NHD && d.layout != VORTA_LAYOUT_HND)
-    return fail(VORTA_EINVAL, "layout %d", d.layout);
-  if (d.center_mode != VORTA_CENTER_CLAMP && d.center_mode != VORTA_CENTER_IDENTITY &&
-      d.center_mode != VORTA_CENTER_BLOCK)
-    return fail(VORTA_EINVAL, "center_mode %d", d.center_mode);
+// Tables of a plan whose description has been checked and clipped.  Allocates: may throw std::bad_alloc.
+static void build_plan(vorta_plan* p) {
+  const vorta_layer_desc& d = p->d;
   const int grid[3] = {d.F, d.H, d.W};
-  int64_t bucket_tokens = 1, tile_tokens = 1;
-  for (int a = 0; a < 3; ++a) {
-    if (d.tile[a] < 1) return fail(VORTA_ESHAPE, "tile[%d] = %d < 1", a, d.tile[a]);
-    if (d.window[a] < 1) return fail(VORTA_ESHAPE, "window[%d] = %d < 1", a, d.window[a]);
-    if (d.bucket[a] < 1) return fail(VORTA_ESHAPE, "bucket[%d] = %d < 1", a, d.bucket[a]);
-    // A tile or bucket larger than the axis is one clipped tile / bucket; a window of 2 n + 1
-    // tiles or more sees the whole axis under every centre rule.  From here on the plan works
-    // with the clipped values, so no product or sum below can leave the range of the grid.
-    d.tile[a] = std::min(d.tile[a], grid[a]);
-    d.bucket[a] = std::min(d.bucket[a], grid[a]);
-    const int n_axis = (grid[a] + d.tile[a] - 1) / d.tile[a];
-    d.window[a] = (int)std::min<int64_t>(d.window[a], 2 * (int64_t)n_axis + 1);
-    bucket_tokens *= d.bucket[a];
-    tile_tokens *= d.tile[a];
-  }
-  if (bucket_tokens > 64) return fail(VORTA_ESHAPE, "bucket holds %lld tokens, at most 64", (long long)bucket_tokens);
-  if (d.keep_num < 1 || d.keep_den < d.keep_num)
-    return fail(VORTA_ESHAPE, "core-set ratio %d/%d outside (0, 1]", d.keep_num, d.keep_den);
-  int64_t rope_sum = 0;
-  for (int a = 0; a < 3; ++a) {
-    if (d.rope_dims[a] < 0 || d.rope_dims[a] % 2 || d.rope_dims[a] > d.head_dim)
-      return fail(VORTA_ESHAPE, "rope_dims[%d] = %d: an even channel count in 0..head_dim expected", a, d.rope_dims[a]);
-    rope_sum += d.rope_dims[a];
-  }
-  if (rope_sum > d.head_dim)
-    return fail(VORTA_ESHAPE, "rope_dims add up to %lld channels, the head has %d", (long long)rope_sum, d.head_dim);
-  if (!(d.rope_theta > 0.f)) d.rope_theta = 10000.f;
-
-  {
-    // the kernels address rows of a head with 32-bit element offsets (row index times row stride)
-    const int64_t n_tokens = (int64_t)d.F * d.H * d.W + d.n_text;
-    const int64_t row_stride = d.layout == VORTA_LAYOUT_NHD ? (int64_t)d.heads * d.head_dim : d.head_dim;
-    if (n_tokens * row_stride > 0x7fffffffLL)
-      return fail(VORTA_ESHAPE, "%lld tokens x row stride %lld elements exceed 2^31 elements per tensor",
-                  (long long)n_tokens, (long long)row_stride);
-  }
-  vorta_plan* p = new (std::nothrow) vorta_plan();
-  if (!p) return fail(VORTA_EINVAL, "out of host memory");
-  p->d = d;
   p->L = (int64_t)d.F * d.H * d.W;
   p->N = p->L + d.n_text;
   p->elem_bytes = d.dtype == VORTA_BF16 ? 2 : 4;
   p->scale = d.softmax_scale > 0.f ? d.softmax_scale : (float)(1.0 / std::sqrt((double)d.head_dim));
-  p->tile_tokens = (int)tile_tokens;   // <= L <= 2^30: every tile extent is clipped to its axis
+  p->tile_tokens = d.tile[0] * d.tile[1] * d.tile[2];   // <= L <= 2^30: every tile extent is clipped to its axis
   for (int a = 0; a < 3; ++a) {
     p->nt[a] = (grid[a] + d.tile[a] - 1) / d.tile[a];   // the last tile of an axis is clipped to the grid
     p->nb[a] = (grid[a] + d.bucket[a] - 1) / d.bucket[a];
@@ -302,7 +237,7 @@ int vorta_plan_create(const vorta_layer_desc* desc, vorta_plan** out) {
   p->Lc = slot;
 
   // rotary embedding table: (cos, sin) of position * theta^(-2 i / span), angles in double
-  p->rope = rope_sum > 0;
+  p->rope = d.rope_dims[0] + d.rope_dims[1] + d.rope_dims[2] > 0;
   if (p->rope) {
     for (int a = 0; a < 3; ++a) {
       const int span = d.rope_dims[a];
@@ -313,6 +248,82 @@ int vorta_plan_create(const vorta_layer_desc* desc, vorta_plan** out) {
           p->rope_cs.push_back((float)std::sin(angle));
         }
     }
+  }
+}
+
+int vorta_plan_create(const vorta_layer_desc* desc, vorta_plan** out) {
+  clear_error();
+  if (!desc || !out) return fail(VORTA_EINVAL, "null desc or out");
+  *out = nullptr;
+  vorta_layer_desc d = *desc;
+  if (d.F < 1 || d.H < 1 || d.W < 1 || d.n_text < 0)
+    return fail(VORTA_ESHAPE, "grid %dx%dx%d / n_text %d must be positive", d.F, d.H, d.W, d.n_text);
+  {
+    // axis by axis, so that no product leaves the range of int64
+    const int64_t cap = (int64_t)1 << 30;
+    int64_t tokens = d.F;
+    for (int64_t axis : {(int64_t)d.H, (int64_t)d.W}) {
+      if (tokens > cap || axis > cap) return fail(VORTA_ESHAPE, "more than 2^30 tokens");
+      tokens *= axis;
+    }
+    if (tokens + d.n_text > cap) return fail(VORTA_ESHAPE, "more than 2^30 tokens");
+  }
+  if (d.heads < 1 || d.heads > VORTA_MAX_HEADS)
+    return fail(VORTA_ESHAPE, "heads = %d, supported 1..%d", d.heads, VORTA_MAX_HEADS);
+  if (d.dtype != VORTA_F32 && d.dtype != VORTA_BF16) return fail(VORTA_EDTYPE, "dtype %d", d.dtype);
+  if (d.dtype == VORTA_BF16 && d.head_dim != 128)
+    return fail(VORTA_ESHAPE, "bf16 supports head_dim 128, got %d", d.head_dim);
+  if (d.dtype == VORTA_F32 && d.head_dim != 64 && d.head_dim != 128)
+    return fail(VORTA_ESHAPE, "fp32 supports head_dim 64 or 128, got %d", d.head_dim);
+  if (d.layout != VORTA_LAYOUT_NHD && d.layout != VORTA_LAYOUT_HND)
+    return fail(VORTA_EINVAL, "layout %d", d.layout);
+  if (d.center_mode != VORTA_CENTER_CLAMP && d.center_mode != VORTA_CENTER_IDENTITY &&
+      d.center_mode != VORTA_CENTER_BLOCK)
+    return fail(VORTA_EINVAL, "center_mode %d", d.center_mode);
+  const int grid[3] = {d.F, d.H, d.W};
+  int64_t bucket_tokens = 1;
+  for (int a = 0; a < 3; ++a) {
+    if (d.tile[a] < 1) return fail(VORTA_ESHAPE, "tile[%d] = %d < 1", a, d.tile[a]);
+    if (d.window[a] < 1) return fail(VORTA_ESHAPE, "window[%d] = %d < 1", a, d.window[a]);
+    if (d.bucket[a] < 1) return fail(VORTA_ESHAPE, "bucket[%d] = %d < 1", a, d.bucket[a]);
+    // A tile or bucket larger than the axis is one clipped tile / bucket; a window of 2 n + 1
+    // tiles or more sees the whole axis under every centre rule.  From here on the plan works
+    // with the clipped values, so no product or sum below can leave the range of the grid.
+    d.tile[a] = std::min(d.tile[a], grid[a]);
+    d.bucket[a] = std::min(d.bucket[a], grid[a]);
+    const int n_axis = (grid[a] + d.tile[a] - 1) / d.tile[a];
+    d.window[a] = (int)std::min<int64_t>(d.window[a], 2 * (int64_t)n_axis + 1);
+    bucket_tokens *= d.bucket[a];
+  }
+  if (bucket_tokens > 64) return fail(VORTA_ESHAPE, "bucket holds %lld tokens, at most 64", (long long)bucket_tokens);
+  if (d.keep_num < 1 || d.keep_den < d.keep_num)
+    return fail(VORTA_ESHAPE, "core-set ratio %d/%d outside (0, 1]", d.keep_num, d.keep_den);
+  int64_t rope_sum = 0;
+  for (int a = 0; a < 3; ++a) {
+    if (d.rope_dims[a] < 0 || d.rope_dims[a] % 2 || d.rope_dims[a] > d.head_dim)
+      return fail(VORTA_ESHAPE, "rope_dims[%d] = %d: an even channel count in 0..head_dim expected", a, d.rope_dims[a]);
+    rope_sum += d.rope_dims[a];
+  }
+  if (rope_sum > d.head_dim)
+    return fail(VORTA_ESHAPE, "rope_dims add up to %lld channels, the head has %d", (long long)rope_sum, d.head_dim);
+  if (!(d.rope_theta > 0.f)) d.rope_theta = 10000.f;
+
+  {
+    // the kernels address rows of a head with 32-bit element offsets (row index times row stride)
+    const int64_t n_tokens = (int64_t)d.F * d.H * d.W + d.n_text;
+    const int64_t row_stride = d.layout == VORTA_LAYOUT_NHD ? (int64_t)d.heads * d.head_dim : d.head_dim;
+    if (n_tokens * row_stride > 0x7fffffffLL)
+      return fail(VORTA_ESHAPE, "%lld tokens x row stride %lld elements exceed 2^31 elements per tensor",
+                  (long long)n_tokens, (long long)row_stride);
+  }
+  vorta_plan* p = new (std::nothrow) vorta_plan();
+  if (!p) return fail(VORTA_EINVAL, "out of host memory");
+  p->d = d;
+  try {
+    build_plan(p);
+  } catch (const std::bad_alloc&) {
+    delete p;
+    return fail(VORTA_EINVAL, "out of host memory");
   }
   *out = p;
   return VORTA_OK;
@@ -387,7 +398,7 @@ int vorta_window_items(const vorta_plan* p, int32_t* items, int32_t counts[2]) {
   clear_error();
   if (!p || !counts) return fail(VORTA_EINVAL, "null argument");
   std::vector<std::array<int32_t, 4>> big, small;
-  if (p->tile_tokens <= 128) {
+  if (p->tile_tokens <= 128) try {
     std::array<int32_t, 4> item = {0, 0, 0, 0};
     int rows = 0;
     auto flush = [&]() {
@@ -408,6 +419,8 @@ int vorta_window_items(const vorta_plan* p, int32_t* items, int32_t counts[2]) {
     auto by_first_tile = [](const std::array<int32_t, 4>& a, const std::array<int32_t, 4>& b) { return a[0] < b[0]; };
     std::sort(big.begin(), big.end(), by_first_tile);    // neighbours in the list are neighbours on the grid
     std::sort(small.begin(), small.end(), by_first_tile);
+  } catch (const std::bad_alloc&) {
+    return fail(VORTA_EINVAL, "out of host memory");
   }
   counts[0] = (int32_t)big.size();
   counts[1] = (int32_t)small.size();

@@ -365,3 +365,26 @@ def test_host_code_under_address_and_undefined_behaviour_sanitizers(tmp_path):
     run = subprocess.run([exe], capture_output=True, text=True, env=env)
     assert run.returncode == 0, (run.stdout[-2000:], run.stderr[-3000:])
     assert "host entry points clean" in run.stdout
+
+
+def test_a_plan_that_does_not_fit_in_memory_is_an_error_code():
+    """Nothing is thrown through the C ABI: with the address space used up, creating a plan of two million
+    one-token tiles returns an error (in a process of its own: the limit stays)."""
+    import subprocess
+    import sys
+    code = """if True:
+        import resource, sys
+        import paper_2505_18809_amd as vorta
+        vorta.load_library()
+        small = vorta.vorta_plan_create((4, 8, 8), 1, 128, "bf16", (1, 1, 1), (1, 1, 1))
+        used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+        resource.setrlimit(resource.RLIMIT_AS, (used + (48 << 20),) * 2)
+        try:
+            vorta.vorta_plan_create((128, 128, 128), 1, 128, "bf16", (1, 1, 1), (3, 3, 3))
+        except vorta.VortaError as e:
+            assert e.code == -1 and "memory" in str(e), e
+            vorta.vorta_plan_create((4, 8, 8), 1, 128, "bf16", (1, 1, 1), (1, 1, 1))
+            print("refused", flush=True)
+    """
+    run = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and "refused" in run.stdout, (run.returncode, run.stdout[-500:], run.stderr[-1500:])
