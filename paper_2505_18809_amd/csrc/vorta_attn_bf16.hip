@@ -14,7 +14,6 @@
 // Softmax statistics are fp32, exp via v_exp_f32 on scores pre-multiplied by log2(e).
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <type_traits>
 
 #include "vorta_attn_common.h"
@@ -32,7 +31,7 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 namespace {
 constexpr int D = 128;          // head dim
 constexpr int BM = 128;         // query rows per workgroup, window segment (4 wavefronts)
-constexpr int BM_LONG = 256;    // dense and core-set segments (8 wavefronts)
+constexpr int BM_LONG = ATTN_ROWS_LONG;    // dense and core-set segments (8 wavefronts)
 constexpr int LSTR = 136;       // output staging: row stride in elements (256 B of data + pad)
 constexpr float P_MAX = 256.f;  // largest probability (relative to the row reference) the softmax fast path accepts
 }  // namespace
@@ -698,7 +697,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_layer_kernel(const AttnArgs 
 // 3,072-token layer, 8 heads on all routes: 88 -> 52 us; at 9,216 tokens, 24 heads, 477 -> 445 us.
 // ------------------------------------------------------------------------------------------
 namespace {
-constexpr int BM_SPLIT = 64;
+constexpr int BM_SPLIT = ATTN_ROWS_SPLIT;
 constexpr int split_lds_bytes(int ks) { return 2 * 8 * ks * (KG + VG) * 2; }   // two stages of 8 ks groups each
 }  // namespace
 
@@ -1090,119 +1089,6 @@ static int launched() {
   return VORTA_OK;
 }
 
-// ------------------------------------------------------------------------------------------
-// Which kernel, and how a launch is cut.  The pipelined kernel does most work per cycle but in
-// 256-row items, a workgroup per CU, the window tiles in launches of their own; the split kernel takes a
-// quarter of the rows per item, all of a layer in one launch, at 70 to 85 % of the rate.  Which is
-// faster depends on how the items fill the chip, so that is estimated: the time of a launch is that of
-// handing its items, in launch order, to whichever CU is free first.  Item costs in microseconds, fitted
-// to 140 measured layers (256 to 75,600 tokens, 1 to 40 heads, one route or all): the form chosen from
-// them is on average 0.6 %, at most 8 %, slower than the fastest one measured.
-//   pipelined, per 64-key block of a 256-row item 1.45, of a half-row item 0.85; window form 1.7 and 0.95
-//   4-wavefront window form, two workgroups per CU, per 64-key block 1.55
-//   split kernel with two key shares 0.52 (two workgroups share a CU: counted as one at twice the rate)
-// Measured, us (pipelined with the last 128 items in halves / split with four / two key shares):
-//   3,072 tokens: 2 dense heads 44 / 29 / 34; 8 window heads 35 / 46 / 36; 8 heads on all routes 88 / 53 / 50
-//   9,216 tokens: 4 dense heads 252 / 229 / 233; 16 window heads 234 / 257 / 204; 40 heads 762 / 890 / 788
-//   32,760 tokens: 1 dense head 497 / 569 / 567; 4 window heads 219 / 264 / 206; 16 of them 701 / 993 / 812
-// ------------------------------------------------------------------------------------------
-namespace {
-struct Batch {
-  int items;
-  double cost;       // of each
-};
-struct Segment {
-  int items, blocks;  // 256-row (or 64-row) items, 64-key blocks of each
-  bool win;
-};
-
-// Time at which `units` processors have finished the batches, each item going to the first one free.
-// Processors are kept in groups of equal time; a group list that runs full forgets its finest step.
-double makespan(const Batch* batch, int n, int units) {
-  constexpr int MAX = 48;
-  double t[MAX];
-  int c[MAX], ng = 1;
-  t[0] = 0.0;
-  c[0] = units;
-  for (int b = 0; b < n; ++b) {
-    int left = batch[b].items;
-    while (left > 0) {
-      const double done = t[0] + batch[b].cost;
-      const int take = std::min(left, c[0]);
-      left -= take;
-      c[0] -= take;
-      if (c[0] == 0) {
-        --ng;
-        for (int i = 0; i < ng; ++i) { t[i] = t[i + 1]; c[i] = c[i + 1]; }
-      }
-      int at = 0;
-      while (at < ng && t[at] < done - 1e-6) ++at;
-      if ((at < ng && t[at] < done + 1e-6) || ng == MAX) {
-        c[std::min(at, ng - 1)] += take;
-      } else {
-        for (int i = ng; i > at; --i) { t[i] = t[i - 1]; c[i] = c[i - 1]; }
-        t[at] = done;
-        c[at] = take;
-        ++ng;
-      }
-    }
-  }
-  return t[ng - 1];
-}
-
-constexpr double LAUNCH_US = 6.0;
-
-// Pipelined launch of the segments with its last `split` items issued as half-row items.
-double pipe_time(const Segment* seg, int n, int split, int units) {
-  int total = 0;
-  for (int i = 0; i < n; ++i) total += seg[i].items;
-  if (total == 0) return 0.0;
-  int whole = total - std::min(split, total), nb = 0;
-  Batch b[8];
-  for (int pass = 0; pass < 2; ++pass) {
-    int keep = whole;
-    for (int i = 0; i < n; ++i) {
-      const double fixed = seg[i].win ? 6.0 : 3.0, full = seg[i].win ? 1.7 : 1.45, half = seg[i].win ? 0.95 : 0.85;
-      const int w = std::min(keep, seg[i].items);
-      keep -= w;
-      const int items = pass == 0 ? w : 2 * (seg[i].items - w);
-      if (items > 0) b[nb++] = {items, fixed + (pass == 0 ? full : half) * seg[i].blocks};
-    }
-  }
-  return LAUNCH_US + makespan(b, nb, units);
-}
-
-// How many of the last items to issue as half-row items.  The last items of a launch leave most CUs idle
-// while a few finish them; two half-row items cost 1.2 times the whole one, so halves pay for a
-// remainder of up to half the CUs and not for one that nearly fills them (two dense heads of 32,760 tokens
-// are 256 items: 958 us with the last 128 in halves, 851 us whole).
-// At most `most`.
-int best_split(const Segment* seg, int n, int most, int units, double* time) {
-  int total = 0;
-  for (int i = 0; i < n; ++i) total += seg[i].items;
-  const int candidates[4] = {units / 2, units / 4, total % units, 0};
-  int best = 0;
-  *time = 1e30;
-  for (int s : candidates) {
-    s = std::min(s, most);
-    const double us = pipe_time(seg, n, s, units);
-    if (us < *time) {
-      *time = us;
-      best = s;
-    }
-  }
-  return best;
-}
-
-double split_time(const Segment* seg, int n, int units) {
-  Batch b[4];
-  int nb = 0;
-  for (int i = 0; i < n; ++i)
-    if (seg[i].items > 0) b[nb++] = {seg[i].items, seg[i].win ? 4.7 + 0.54 * seg[i].blocks : 2.5 + 0.52 * seg[i].blocks};
-  return nb ? LAUNCH_US + makespan(b, nb, units) : 0.0;
-}
-}  // namespace
-
 template <int KS>
 static void launch_split(const AttnArgs& a, const MixArgs* mix, void* stream) {
   const dim3 grid(a.end_tile), block(128 * KS);
@@ -1233,55 +1119,13 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
   });
   if (attr_rc) return attr_rc;
   if (mix && (rl.count[1] || rl.count[2])) return fail(VORTA_EINVAL, "the Eq. 5 epilogue takes full-attention heads only");
+  const AttnForm form = choose_attention_form(p, rl, mix != nullptr, win_text, p->n_cus);
+  if (form.empty) return VORTA_OK;
   hipStream_t st = (hipStream_t)stream;
-  const int units = p->n_cus, n_win = rl.count[1];
-  const int rows_c = (int)(p->Lc + p->d.n_text), n_text = win_text ? p->d.n_text : 0;
-  const int blocks_n = (int)((p->N + 63) / 64), blocks_c = (rows_c + 63) / 64;
-  auto items_of = [](int64_t rows, int bm) { return (int)((rows + bm - 1) / bm); };
-  auto list_items = [&](int l) { return n_win * (int)(p->win_list[l].size() / 4); };
-
-  // Everything in 64-row items: one launch of the split kernel if that is estimated to be the faster form.
-  // With no more items than CUs four key shares shorten each of them (3,072 keys: 29 us against
-  // 34 with two shares; 256 keys, where the longer merge shows: 9.6 against 8.8).
-  const Segment fine[4] = {{n_win * items_of(n_text, BM_SPLIT), blocks_n, false}, {rl.count[0] * items_of(p->N, BM_SPLIT), blocks_n, false},
-                           {rl.count[2] * items_of(rows_c, BM_SPLIT), blocks_c, false}, {list_items(2), p->win_blocks[2], true}};
-  int fine_items = 0, longest = 0;
-  for (const Segment& s : fine) {
-    fine_items += s.items;
-    if (s.items) longest = std::max(longest, s.blocks);
-  }
-  if (fine_items == 0) return VORTA_OK;
-  const Segment coarse[4] = {{n_win * items_of(n_text, BM_LONG), blocks_n, false}, {rl.count[0] * items_of(p->N, BM_LONG), blocks_n, false},
-                             {rl.count[2] * items_of(rows_c, BM_LONG), blocks_c, false}, {list_items(0), p->win_blocks[0], true}};
-  const int n_long = coarse[0].items + coarse[1].items + coarse[2].items, n_big = coarse[3].items;
-  bool split_all = fine_items <= units, split_win = false;
-  const bool together = n_long && n_big && !mix;         // long and big window items in one launch
-  int half_long = 0, half_big = 0;
-  if (!split_all) {
-    double t_long, t_big, t_both;
-    half_long = best_split(coarse, 3, n_long, units, &t_long);
-    half_big = best_split(coarse + 3, 1, n_big, units, &t_big);
-    const Batch small = {list_items(1), 5.0 + 1.55 * p->win_blocks[1]};
-    const double t_small = small.items ? LAUNCH_US + makespan(&small, 1, 2 * units) : 0.0;
-    double t_pipe = t_long + t_big + t_small;
-    if (together) {
-      const int half_both = best_split(coarse, 4, n_big, units, &t_both);
-      t_pipe = t_both + t_small;
-      half_big = half_both;
-    }
-    // far above the sizes where the split kernel can win there is nothing to estimate
-    int64_t work = 0;
-    for (const Segment& s : fine) work += (int64_t)s.items * s.blocks;
-    if (work < (int64_t)4000 * units) {
-      const double t_split_win = split_time(&fine[3], 1, units);
-      split_win = n_win && t_long + t_split_win < t_pipe;
-      split_all = split_time(fine, 4, units) < std::min(t_pipe, n_win ? t_long + t_split_win : t_pipe);
-    }
-  }
   AttnArgs a;
-  if (split_all) {
+  if (form.split_all) {
     if (int rc = fill_attn_args(p, rl, io, core, BM_SPLIT, win_text ? WIN_ALL : WIN_TILES, &a, 2)) return rc;
-    if (fine_items <= units && longest >= 16) launch_split<4>(a, mix, stream);
+    if (form.shares == 4) launch_split<4>(a, mix, stream);
     else launch_split<2>(a, mix, stream);
     return launched();
   }
@@ -1290,32 +1134,32 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
   // than 128 rows behind them.
   RouteLists win_rl = rl;
   win_rl.count[0] = win_rl.count[2] = 0;
-  if (together && !split_win) {
+  if (form.together) {
     AttnArgs win;
     if (int rc = fill_attn_args(p, rl, io, core, BM_LONG, win_text ? WIN_TEXT : WIN_NONE, &a)) return rc;
     if (int rc = fill_attn_args(p, win_rl, io, core, BM_LONG, WIN_TILES, &win, 0)) return rc;
-    win.split_from = win.end_tile - half_big;
-    hipLaunchKernelGGL(attn_bf16_layer_kernel, dim3(a.end_tile + win.end_tile + half_big), dim3(512), pipe_lds_bytes(8), st, a, win, a.end_tile);
-  } else if (n_long) {
+    win.split_from = win.end_tile - form.half_big;
+    hipLaunchKernelGGL(attn_bf16_layer_kernel, dim3(a.end_tile + win.end_tile + form.half_big), dim3(512), pipe_lds_bytes(8), st, a, win, a.end_tile);
+  } else if (form.n_long) {
     if (int rc = fill_attn_args(p, rl, io, core, BM_LONG, win_text ? WIN_TEXT : WIN_NONE, &a)) return rc;
-    a.split_from = a.end_tile - half_long;
-    const dim3 grid(a.end_tile + half_long);
+    a.split_from = a.end_tile - form.half_long;
+    const dim3 grid(a.end_tile + form.half_long);
     if (mix) hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8, true>), grid, dim3(512), pipe_lds_bytes(8), st, a, *mix);
     else hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8>), grid, dim3(512), pipe_lds_bytes(8), st, a, NoMix());
   }
   // Window tiles: in 64-row items (above), or the plan's items of more than 128 rows on the 8-wavefront instance
   // (256 rows, 64-key blocks, one workgroup per CU) and the rest on the 4-wavefront one (128 rows, 32-key
   // blocks, two per CU).
-  if (n_win == 0) return launched();
-  if (split_win) {
+  if (rl.count[1] == 0) return launched();
+  if (form.split_win) {
     if (int rc = fill_attn_args(p, win_rl, io, core, BM_SPLIT, WIN_TILES, &a, 2)) return rc;
     launch_split<2>(a, nullptr, stream);
     return launched();
   }
-  if (n_big && !together) {
+  if (form.n_big && !form.together) {
     if (int rc = fill_attn_args(p, win_rl, io, core, BM_LONG, WIN_TILES, &a, 0)) return rc;
-    a.split_from = a.end_tile - half_big;
-    hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + half_big), dim3(512), pipe_lds_bytes(8), st, a, NoMix());
+    a.split_from = a.end_tile - form.half_big;
+    hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + form.half_big), dim3(512), pipe_lds_bytes(8), st, a, NoMix());
   }
   if (int rc = fill_attn_args(p, win_rl, io, core, BM, WIN_TILES, &a, 1)) return rc;
   if (a.end_tile > 0)

@@ -39,6 +39,8 @@ struct vorta_plan {
   bool rope = false;
   std::vector<float> rope_cs;
 
+  int force_form = 0, force_halves = -1;   // tests only, see vorta_test_force_form
+
   // device tables, all in one allocation, uploaded on first device use: copies of the tables above and those that
   // have one entry per token and are made for the upload only
   std::mutex mu;
@@ -110,6 +112,18 @@ struct CoreIndex {
   const int32_t* keep_idx;   // [n_lr][L_c]
   const int32_t* assign;     // [n_lr][L]
 };
+// How a bf16 attention launch is cut.
+constexpr int ATTN_ROWS_SPLIT = 64, ATTN_ROWS_LONG = 256;    // query rows of an item of the split and of the pipelined kernel
+struct AttnForm {
+  bool empty;              // no items at all
+  bool split_all;          // everything on the split kernel, with `shares` key shares
+  int shares;
+  bool split_win;          // window rows on the split kernel (two shares), the rest on the pipelined one
+  bool together;           // long and window items of more than 128 rows in one launch
+  int n_long, half_long;   // 256-row items of dense, core-set and text rows; how many of them as half-row items
+  int n_big, half_big;     // the same of the window items of more than 128 rows
+};
+AttnForm choose_attention_form(const vorta_plan* p, const RouteLists& rl, bool mix, bool win_text, int units);
 int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, const CoreIndex* core, void* stream);
 int launch_router(const float* t_emb, const float* w_r, int n_steps, int d_t, int heads, float* alpha,
                   uint8_t* routes, void* stream);

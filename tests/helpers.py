@@ -1,7 +1,10 @@
 """Glue shared by the tests: config -> oracle spec, tensor -> fp64 array."""
+import ctypes
+
 import numpy as np
 import torch
 
+import paper_2505_18809_amd as vorta
 from oracle import vorta_oracle as vo
 from synth_inputs import LayerConfig
 
@@ -29,3 +32,23 @@ def smooth_field(rng, grid, d, noise=0.5):
     x = x + np.roll(x, 1, 0) + np.roll(x, 1, 1) + np.roll(x, 1, 2)
     x = x / x.std() + noise * rng.standard_normal((F, H, W, d))
     return x.reshape(F * H * W, d)
+
+
+# Forms of a bf16 attention launch (an internal hook of the library): 0 = the library's own choice; split kernel
+# with two or four key shares; pipelined kernels; pipelined with the window rows on the split kernel.
+SPLIT2, SPLIT4, PIPE, PIPE_SPLIT_WIN = 2, 4, 3, 5
+
+
+def force_form(plan, form, halves=-1):
+    """All attention launches of the plan take this form; halves: items issued as half-row items, -1 = the rule's."""
+    assert vorta.load_library().vorta_test_force_form(plan.handle, ctypes.c_int32(form), ctypes.c_int32(halves)) == 0
+    return plan
+
+
+def attention_form(plan, routes, mix=False, units=256):
+    """What the library chooses for a layer call with these routes on a device of `units` CUs."""
+    r = np.ascontiguousarray(routes, dtype=np.uint8)
+    out = np.zeros(8, dtype=np.int32)
+    assert vorta.load_library().vorta_test_form(plan.handle, r.ctypes.data_as(ctypes.c_void_p), ctypes.c_int32(mix),
+                                                ctypes.c_int32(units), out.ctypes.data_as(ctypes.c_void_p)) == 0
+    return dict(zip(("split_all", "shares", "split_win", "together", "n_long", "half_long", "n_big", "half_big"), map(int, out)))

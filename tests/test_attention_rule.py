@@ -1,0 +1,78 @@
+"""The rule that chooses the form of a bf16 attention launch, for a device of 256 CUs: the forms that the GPU tests
+and the benchmark layers are meant to take, and the hook by which tests take the others.  No GPU is needed."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2505_18809_amd as vorta
+from synth_inputs import get_config, make_routes
+from helpers import PIPE, PIPE_SPLIT_WIN, SPLIT2, SPLIT4, attention_form, force_form
+
+
+def plan_of(grid, heads, tile=(3, 3, 3), window=(3, 3, 3), **kw):
+    return vorta.vorta_plan_create(grid, heads, 128, "bf16", tile, window, **kw)
+
+
+@pytest.mark.parametrize("grid,heads,tile,window,n_text", [
+    ((1, 1, 1), 3, (1, 1, 1), (1, 1, 1), 0), ((4, 6, 8), 4, (2, 3, 4), (3, 3, 3), 515), ((10, 12, 9), 5, (6, 9, 8), (3, 3, 3), 9),
+    ((12, 16, 16), 6, (4, 8, 8), (3, 3, 3), 0), ((2, 4, 6), 128, (1, 2, 3), (3, 3, 3), 3), ((12, 16, 16), 8, (4, 4, 4), (3, 3, 3), 77)])
+def test_small_layers_run_on_the_split_kernel(grid, heads, tile, window, n_text):
+    form = attention_form(plan_of(grid, heads, tile, window, n_text=n_text), [h % 3 for h in range(heads)])
+    assert form["split_all"] and not form["together"]
+
+
+def test_four_key_shares_where_the_items_fit_the_cus_and_the_stream_is_long():
+    assert attention_form(plan_of((1, 31, 31), 3), (0, 1, 2))["shares"] == 4            # 961 keys: 16 blocks
+    assert attention_form(plan_of((1, 30, 31), 3), (0, 1, 2))["shares"] == 2            # 930: 15
+    assert attention_form(plan_of((4, 12, 16), 42), [h % 3 for h in range(42)])["shares"] == 2       # more items than CUs
+
+
+@pytest.mark.parametrize("name", ["wan480p", "wan720p", "hunyuan720p", "paper720p", "paper_wan720p"])
+def test_full_size_layers_run_on_the_pipelined_kernels_in_one_launch(name):
+    cfg = get_config(name)
+    form = attention_form(vorta.plan_for(cfg), make_routes(cfg).numpy())
+    assert not form["split_all"] and not form["split_win"] and form["together"]
+
+
+def test_forms_of_the_layers_that_gpu_tests_rely_on():
+    routes = (1, 0, 2, 1, 2, 1, 2, 1)
+    one = attention_form(plan_of((21, 29, 52), 8, (3, 6, 4)), routes)
+    assert one["together"] and 0 < one["half_big"] < one["n_big"]
+    text = attention_form(plan_of((21, 29, 52), 8, (3, 6, 4), n_text=77), routes)
+    assert text["together"] and text["half_big"] == 0                                    # the test asks for halves itself
+    masked = attention_form(plan_of((21, 29, 52), 8, (3, 6, 4), n_text=21), (0, 1, 2, 1, 0, 1, 2, 1))
+    assert masked["together"]
+    for bucket, keep, heads, n_text in (((3, 5, 4), (3, 4), 6, 40), ((2, 3, 2), (1, 2), 8, 0)):
+        long = attention_form(plan_of((21, 30, 52), heads, (2, 4, 4), n_text=n_text, bucket=bucket, keep_num=keep[0], keep_den=keep[1]), (2,) * heads)
+        assert not long["split_all"] and long["n_long"] > 256
+    mix = attention_form(plan_of((21, 30, 52), 12, (3, 6, 4)), (0,) * 12, mix=True)
+    assert not mix["split_all"] and not mix["together"]
+
+
+def test_a_form_can_be_asked_for_at_any_size():
+    plan = plan_of((5, 7, 11), 3, (1, 2, 3), (99, 99, 999))
+    routes = (0, 1, 2)
+    chosen = attention_form(plan, routes)
+    assert chosen["split_all"]
+    for form, shares in ((SPLIT2, 2), (SPLIT4, 4)):
+        got = attention_form(force_form(plan, form), routes)
+        assert got["split_all"] and got["shares"] == shares
+    got = attention_form(force_form(plan, PIPE, 1), routes)
+    assert not got["split_all"] and not got["split_win"] and got["together"] and got["half_long"] == got["half_big"] == 1
+    got = attention_form(force_form(plan, PIPE, 1 << 20), routes)
+    assert got["half_long"] == got["n_long"] == 3 and got["half_big"] == got["n_big"] == 2   # 385 rows: 256 and 129
+    got = attention_form(force_form(plan, PIPE_SPLIT_WIN, 0), routes)
+    assert got["split_win"] and not got["together"] and got["half_long"] == 0
+    assert attention_form(force_form(plan, 0), routes) == chosen
+    lib = vorta.load_library()
+    for form, halves in ((1, -1), (6, -1), (-1, -1), (PIPE, -2)):
+        assert lib.vorta_test_force_form(plan.handle, ctypes.c_int32(form), ctypes.c_int32(halves)) == -1
+    assert attention_form(plan, routes) == chosen
+
+
+def test_no_items_and_no_heads_on_a_route():
+    plan = plan_of((21, 29, 52), 4, (3, 6, 4))
+    assert attention_form(plan, (1, 1, 1, 1))["n_long"] == 0
+    assert attention_form(plan, (0, 0, 2, 2))["n_big"] == 0
+    assert np.sum(list(attention_form(plan, (2, 2, 2, 2)).values())) > 0

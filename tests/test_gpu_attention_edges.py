@@ -10,7 +10,7 @@ import torch
 import paper_2505_18809_amd as vorta
 from oracle import vorta_oracle as vo
 from synth_inputs import LayerConfig, make_qkv
-from helpers import f64, spec_of
+from helpers import PIPE, f64, force_form, spec_of
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -76,8 +76,9 @@ def test_fp32_row_reference_follows_scores_far_beyond_its_slack():
                                          ((4, 8, 12), 0), ((5, 7, 11), 70)])
 def test_bf16_window_rows_cut_across_tile_borders(grid, n_text, layout):
     """Windows that cover the grid: every tile (of 1 to 6 tokens, clipped ones among them) has one key set, so
-    the rows of all tiles are one sequence of 1, 128, 129, 256, 257, 384 and 385 rows, cut into blocks of
-    256 with a rest of up to 128.  Gathered from the caller's tensors and over tile-ordered copies."""
+    the rows of all tiles are one sequence of 1, 128, 129, 256, 257, 384 and 385 rows, cut into blocks of 64 (the
+    split kernel, which the rule takes at these sizes; blocks of 256 with a rest: test_gpu_attention_forms.py).
+    Gathered from the caller's tensors and over tile-ordered copies."""
     cfg = LayerConfig(f"cut{grid}", grid, 3, 128, "bf16", (1, 2, 3), (99, 99, 999), seed=17, n_text=n_text, fixed_routes=(1, 0, 1))
     say(cfg.name)
     q, k, v = make_qkv(cfg, DEV, layout)
@@ -164,15 +165,17 @@ def test_core_set_rows_written_to_their_tokens_equal_the_staged_unpool(grid, buc
     assert torch.equal(out, staged)
 
 
-@pytest.mark.parametrize("n_text,layout", [(0, 1), (77, 0)])
-def test_long_and_window_items_in_one_launch(n_text, layout):
-    """A layer large enough for 256-row items on every route: window items follow the long ones in one launch (an
-    odd number of them with text), the last window items in halves.  Sampled rows of one head per route."""
+@pytest.mark.parametrize("n_text,layout,halves", [(0, 1, -1), (77, 0, -1), (77, 0, 131)])
+def test_long_and_window_items_in_one_launch(n_text, layout, halves):
+    """A layer large enough for 256-row items on every route: window items follow the long ones in one launch, the last
+    of them in halves where the rule has it so (without text) or is told to.  Sampled rows of one head per route."""
     cfg = LayerConfig("one_launch", (21, 29, 52), 8, 128, "bf16", (3, 6, 4), (3, 3, 3), seed=53, n_text=n_text,
                       fixed_routes=(1, 0, 2, 1, 2, 1, 2, 1))
     say(cfg.name)
     q, k, v = make_qkv(cfg, DEV, layout)
     plan = vorta.plan_for(cfg, layout=layout)
+    if halves >= 0:
+        force_form(plan, PIPE, halves)
     out = vorta.vorta_routed_attention_layer(plan, q, k, v, cfg.fixed_routes)
     torch.cuda.synchronize()
     hnd = (lambda t: t) if layout == 1 else (lambda t: t.transpose(0, 1))

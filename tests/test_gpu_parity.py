@@ -10,7 +10,7 @@ import torch
 import paper_2505_18809_amd as vorta
 from oracle import vorta_oracle as vo
 from synth_inputs import LayerConfig, get_config, make_qkv, make_routes
-from helpers import f64, spec_of
+from helpers import PIPE, PIPE_SPLIT_WIN, SPLIT2, SPLIT4, f64, force_form, spec_of
 
 pytestmark = pytest.mark.gpu
 
@@ -192,7 +192,7 @@ def test_seeded_random_small_layers(seed):
     run lists crossing 64-key blocks, tiles above and below a query block, text tokens or none,
     both layouts, every route mix -- each head against the oracle on all rows."""
     rng = np.random.default_rng(1000 + seed)
-    big = seed % 3 == 2                     # tiles of more than 128 tokens take the pipelined window path
+    big = seed % 3 == 2                     # tiles of more than 128 tokens (layers this small run on the split kernel)
     tile = tuple(int(rng.integers(4, 8)) for _ in range(3)) if big else tuple(int(rng.integers(1, 5)) for _ in range(3))
     reps = tuple(int(rng.integers(1, 4 if big else 5)) for _ in range(3))
     grid = tuple(t * r for t, r in zip(tile, reps))
@@ -229,9 +229,9 @@ def test_tiles_and_buckets_that_exceed_the_grid(tile, bucket):
 
 @pytest.mark.parametrize("n_text,layout", [(300, 1), (515, 0)])
 def test_text_rows_spanning_several_query_blocks(n_text, layout):
-    """Text rows of a window head attend to every row and run as long items of the pipelined
-    kernel, next to the dense heads: more text rows than one 256-row item holds, a ragged last
-    item, and (the grid being small) every item issued as two half-row items."""
+    """Text rows of a window head attend to every row and run as items of their own, next to those of the
+    dense heads: more text rows than an item holds (64 on the split kernel, which layers this small run on),
+    and a ragged last item.  (256-row items and half-row items of text rows: test_gpu_attention_forms.py.)"""
     cfg = small_cfg(f"text{n_text}", (4, 6, 8), 4, "bf16", (2, 3, 4), (3, 3, 3), [1, 0, 2, 1], n_text=n_text, seed=31)
     check_layer(cfg, cfg.fixed_routes, layout=layout)
 
@@ -248,7 +248,7 @@ def test_layers_whose_tiles_do_not_divide_the_grid(grid, tile, dtype, layout):
     cfg = small_cfg(f"clip{grid}", grid, 5, dtype, tile, (3, 3, 3), [1, 0, 1, 2, 1], d=d, n_text=9, seed=61)
     check_layer(cfg, cfg.fixed_routes, layout=layout)
     check_layer(cfg, cfg.fixed_routes, layout=layout, center_mode=1)
-    # the staged path over tile-ordered copies (reorder passes, plain window kernel)
+    # the staged path over tile-ordered copies
     if layout == 1 and dtype == "bf16":
         routes = np.array(cfg.fixed_routes, dtype=np.uint8)
         q, k, v = make_qkv(cfg, DEV)
@@ -302,13 +302,15 @@ def test_degenerate_cases():
     check_layer(big_tile, big_tile.fixed_routes)
 
 
+@pytest.mark.parametrize("form", [0, SPLIT2, SPLIT4, PIPE, PIPE_SPLIT_WIN])
 @pytest.mark.parametrize("tile", [(4, 4, 4), (4, 8, 8)], ids=["tile64", "tile256"])
-def test_row_maxima_that_jump_or_creep_late_in_the_key_stream(tile):
+def test_row_maxima_that_jump_or_creep_late_in_the_key_stream(tile, form):
     """The attention kernels keep a lagging row reference instead of the running maximum.
     Inputs built to move the maxima late: one key far down the key stream that dominates a
     few rows outright, and scores that rise steadily along the key axis for half the rows.
-    Window heads (64-token tiles: the 128-row kernel; 256-token tiles: the pipelined one) get
-    their dominating keys at the end of the row's key set in tile order."""
+    Window heads get their dominating keys at the end of the row's key set in tile order.  In the form the
+    rule chooses (at this size the split kernel) and in every other one; tiles of 64 tokens give the
+    pipelined kernels window items of 129 to 256 rows and of at most 128, tiles of 256 the former only."""
     cfg = small_cfg("late_max", (12, 16, 16), 6, "bf16", tile, (3, 3, 3), [0, 0, 2, 2, 1, 1], seed=23)
     q, k, v = make_qkv(cfg, DEV, 1)
     N, d = cfg.n_tokens, cfg.head_dim
@@ -336,7 +338,8 @@ def test_row_maxima_that_jump_or_creep_late_in_the_key_stream(tile):
             kh[j] = (1.5 if r == 2 else 4.0) * q[h, row].float()   # a late key that dominates one row
         k[h] = kh.to(torch.bfloat16)
     routes = np.array(cfg.fixed_routes, dtype=np.uint8)
-    plan, out = run_layer(cfg, q, k, v, routes)
+    out = vorta.vorta_routed_attention_layer(force_form(vorta.plan_for(cfg), form), q, k, v, routes)
+    torch.cuda.synchronize()
     spec = spec_of(cfg)
     for h, r in enumerate(routes):
         want = vo.head_attention(int(r), f64(q[h]), f64(k[h]), f64(v[h]), spec, None)
@@ -368,8 +371,8 @@ def test_layer_equals_the_staged_calls_and_is_deterministic():
                                  q_c=q_c, k_c=k_c, v_c=v_c, o_c=o_c)
     vorta.vorta_scatter_back(plan, routes, o_t, o_c, assign, staged)
     torch.cuda.synchronize()
-    # over tile-ordered copies the window heads run on a different kernel (other block size,
-    # other summation order): those heads are held to the oracle, the others are the same launch
+    # over tile-ordered copies the text rows of window heads meet their keys in tile order, another order of
+    # summation: those heads are held to the oracle, the others are the same launch
     spec = spec_of(cfg)
     for h, r in enumerate(routes):
         if r != 1:
