@@ -1156,12 +1156,12 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
     launch_split<2>(a, nullptr, stream);
     return launched();
   }
-  if (form.n_big && !form.together) {
+  if (form.n_big && !form.together && !form.win_128) {
     if (int rc = fill_attn_args(p, win_rl, io, core, BM_LONG, WIN_TILES, &a, 0)) return rc;
     a.split_from = a.end_tile - form.half_big;
     hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + form.half_big), dim3(512), pipe_lds_bytes(8), st, a, NoMix());
   }
-  if (int rc = fill_attn_args(p, win_rl, io, core, BM, WIN_TILES, &a, 1)) return rc;
+  if (int rc = fill_attn_args(p, win_rl, io, core, BM, WIN_TILES, &a, form.win_128 ? 3 : 1)) return rc;
   if (a.end_tile > 0)
     hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 4>), dim3(a.end_tile), dim3(256), pipe_lds_bytes(4), st, a, NoMix());
   return launched();

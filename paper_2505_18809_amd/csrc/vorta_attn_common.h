@@ -225,7 +225,7 @@ enum WindowPart { WIN_NONE = 0, WIN_TEXT = 1, WIN_TILES = 2, WIN_ALL = 3 };
 
 // Fills AttnArgs for a launch over the heads of rl with BM-row work items; win_part selects
 // which items of the window heads it carries.  win_list: -1 = one item per (tile, q-block);
-// 0 / 1 / 2 = the plan's lists of items of more than 128 rows / of at most 128 rows / of at most 64 rows.
+// 0 .. 3 = the plan's lists of window items (see vorta_plan).
 int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, const CoreIndex* core, int BM,
                    int win_part, AttnArgs* a, int win_list = -1);
 

@@ -6,29 +6,57 @@
 namespace vorta {
 
 // ------------------------------------------------------------------------------------------
-// Which kernel, and how a launch is cut.  The pipelined kernel does most work per cycle but in
-// 256-row items, a workgroup per CU, the window tiles in launches of their own; the split kernel takes a
-// quarter of the rows per item, all of a layer in one launch, at 70 to 85 % of the rate.  Which is
+// Which kernel, and how a launch is cut.  The pipelined kernel does most work per cycle but in 256-row items, a
+// workgroup per CU, and the window rows that fill no such item -- or all of them -- in 128-row items in a launch
+// of their own; the split kernel takes 64 rows per item, all of a layer in one launch, at 70 to 85 % of the rate.  Which is
 // faster depends on how the items fill the chip, so that is estimated: the time of a launch is that of
-// handing its items, in launch order, to whichever CU is free first.  Item costs in microseconds, fitted
-// to 140 measured layers (256 to 75,600 tokens, 1 to 40 heads, one route or all): the form chosen from
-// them is on average 0.6 %, at most 8 %, slower than the fastest one measured.
-//   pipelined, per 64-key block of a 256-row item 1.45, of a half-row item 0.85; window form 1.7 and 0.95
-//   4-wavefront window form, two workgroups per CU, per 64-key block 1.55
-//   split kernel with two key shares 0.52 (two workgroups share a CU: counted as one at twice the rate)
-// Measured, us (pipelined with the last 128 items in halves / split with four / two key shares):
-//   3,072 tokens: 2 dense heads 44 / 29 / 34; 8 window heads 35 / 46 / 36; 8 heads on all routes 88 / 53 / 50
-//   9,216 tokens: 4 dense heads 252 / 229 / 233; 16 window heads 234 / 257 / 204; 40 heads 762 / 890 / 788
-//   32,760 tokens: 1 dense head 497 / 569 / 567; 4 window heads 219 / 264 / 206; 16 of them 701 / 993 / 812
+// handing each XCD's items, in launch order, to whichever of its CUs is free first.
+//
+// Item costs are microseconds, fixed + per 64-key block, fitted to 2,098 measured layers (256 to 80,000 tokens, 1 to 40
+// heads, every route alone and mixed, with and without text, every form timed on each).  On 500 others the form
+// chosen is 1.2 % slower than the fastest on average, 14 of them by more than 10 %, one by 33 %
+// (profiles/attention_forms.txt); costs fitted to earlier versions of the kernels were 2.6 % off on average, 71 of
+// 798 by more than 10 % and up to 55 %, and without items of 128 rows a layer of 768 tokens, 24 window heads and
+// 32-token tiles took 20.2 us instead of 17.1.
 // ------------------------------------------------------------------------------------------
 namespace {
+struct Cost {
+  double fixed, block;
+  double of(double blocks) const { return fixed + block * blocks; }
+};
+constexpr Cost LONG = {4.0, 0.98}, LONG_HALF = {4.0, 0.737};   // pipelined: dense, core-set and text items of 256 rows; of half
+constexpr Cost WIN = {7.4, 1.45}, WIN_HALF = {7.4, 0.867};     // pipelined: window items of 256 rows; of half
+// 4-wavefront window items and split kernel with two key shares: two workgroups share a CU, counted as one at twice
+// the rate; an item that has its CU to itself takes .._ALONE per block.  A 4-wavefront item takes WIN_128_WAVE per
+// block more for each wavefront that has rows.
+constexpr Cost WIN_128 = {3.3, 0.543}, SPLIT2 = {1.6, 0.4125}, SPLIT2_WIN = {3.5, 0.53};
+constexpr double WIN_128_WAVE = 0.075, WIN_128_ALONE = 1.19, SPLIT2_ALONE = 0.705;
+constexpr Cost SPLIT4 = {4.2, 0.573}, SPLIT4_WIN = {7.5, 0.505};  // split kernel with four: one workgroup per CU
+constexpr double LAUNCH_US = 2.5;
+// Half-row items read every key row twice: window items, and long items of a launch that the CUs hold at once, are
+// halved only where that saves something (144 dense items of 144 blocks: 174 us whole, 189 us with 64 in halves).  Of
+// more long items than CUs the last are halved unless that costs something: the order in which CUs become free is not
+// quite the one assumed here, and halves even it out (306 long items: 918 us whole, 828 us with 64 in halves).
+constexpr double HALVES_SAVE = 1.02, HALVES_EVEN = 0.96;
+constexpr int XCDS = 8;                     // workgroups are dealt to them in turn, and each has its own CUs
+
 struct Batch {
   int items;
   double cost;       // of each
 };
 struct Segment {
-  int items, blocks;  // 256-row (or 64-row) items, 64-key blocks of each
-  bool win;
+  int items, blocks;  // items, 64-key blocks of each
+};
+struct Window {       // the items of a list, head after head
+  int heads = 0, list = 0;                // list: items of a head
+  const int64_t* sums = nullptr;          // blocks of the items before each one of the list
+  int most = 0;                           // blocks of the longest
+  double waves = 0.0;                     // wavefronts with rows of an item, on average
+  int items() const { return heads * list; }
+  double before(int i) const { return (double)(i / list) * (double)sums[list] + (double)sums[i % list]; }
+  // blocks of the items [first, last), on average
+  double blocks(int first, int last) const { return last > first ? (before(last) - before(first)) / (last - first) : 0.0; }
+  double blocks() const { return (double)sums[list] / list; }
 };
 
 // Time at which `units` processors have finished the batches, each item going to the first one free.
@@ -42,6 +70,12 @@ double makespan(const Batch* batch, int n, int units) {
   for (int b = 0; b < n; ++b) {
     int left = batch[b].items;
     while (left > 0) {
+      if (left >= units && t[ng - 1] - t[0] <= batch[b].cost) {      // whole rounds: every processor takes one item of each
+        const int rounds = left / units;
+        for (int i = 0; i < ng; ++i) t[i] += rounds * batch[b].cost;
+        left -= rounds * units;
+        continue;
+      }
       const double done = t[0] + batch[b].cost;
       const int take = std::min(left, c[0]);
       left -= take;
@@ -65,56 +99,126 @@ double makespan(const Batch* batch, int n, int units) {
   return t[ng - 1];
 }
 
-constexpr double LAUNCH_US = 6.0;
-
-// Pipelined launch of the segments with its last `split` items issued as half-row items.
-double pipe_time(const Segment* seg, int n, int split, int units) {
-  int total = 0;
-  for (int i = 0; i < n; ++i) total += seg[i].items;
-  if (total == 0) return 0.0;
-  int whole = total - std::min(split, total), nb = 0;
-  Batch b[8];
-  for (int pass = 0; pass < 2; ++pass) {
-    int keep = whole;
-    for (int i = 0; i < n; ++i) {
-      const double fixed = seg[i].win ? 6.0 : 3.0, full = seg[i].win ? 1.7 : 1.45, half = seg[i].win ? 0.95 : 0.85;
-      const int w = std::min(keep, seg[i].items);
-      keep -= w;
-      const int items = pass == 0 ? w : 2 * (seg[i].items - w);
-      if (items > 0) b[nb++] = {items, fixed + (pass == 0 ? full : half) * seg[i].blocks};
-    }
+// Time of a launch from the batches of each of its XCDs: the latest of them.  XCDs with the same batches as the one
+// before are not computed again.
+class Launch {
+ public:
+  explicit Launch(int units) : units_(std::max(1, units / XCDS)) {}
+  void batch(int items, double cost) {
+    if (items > 0) b_[n_++] = {items, cost};
   }
-  return LAUNCH_US + makespan(b, nb, units);
+  // items from index `at` of the launch on, dealt round robin: how many XCD x gets
+  static int share(int at, int items, int x) { return (at + items - x + XCDS - 1) / XCDS - (at - x + XCDS - 1) / XCDS; }
+  void close() {
+    if (n_ != last_n_ || !std::equal(b_, b_ + n_, last_, [](const Batch& a, const Batch& b) { return a.items == b.items && a.cost == b.cost; })) {
+      if (n_) worst_ = std::max(worst_, makespan(b_, n_, units_));
+      last_n_ = n_;
+      std::copy(b_, b_ + n_, last_);
+    }
+    n_ = 0;
+  }
+  double worst() const { return worst_; }
+
+ private:
+  int units_, n_ = 0, last_n_ = -1;
+  double worst_ = 0.0;
+  Batch b_[8], last_[8];
+};
+
+// Items [first, last) of XCD x where n items are dealt in contiguous ranges.
+struct Range {
+  int first, last;
+};
+Range xcd_range(int n, int x) {
+  const int each = n / XCDS, more = n % XCDS, first = each * x + std::min(x, more);
+  return {first, first + each + (x < more)};
 }
 
-// How many of the last items to issue as half-row items.  The last items of a launch leave most CUs idle
-// while a few finish them; two half-row items cost 1.2 times the whole one, so halves pay for a
-// remainder of up to half the CUs and not for one that nearly fills them (two dense heads of 32,760 tokens
-// are 256 items: 958 us with the last 128 in halves, 851 us whole).
-// At most `most`.
-int best_split(const Segment* seg, int n, int most, int units, double* time) {
-  int total = 0;
-  for (int i = 0; i < n; ++i) total += seg[i].items;
-  const int candidates[4] = {units / 2, units / 4, total % units, 0};
+// Pipelined launch of three segments of long items (the last half_long of them as half-row items), dealt round
+// robin, and one of window items (the last half_win), dealt in contiguous ranges, so that the halves are all on the
+// last XCDs; 0 without items.
+double pipe_time(const Segment* longs, const Window& win, int half_long, int half_win, int units) {
+  const int n_long = longs[0].items + longs[1].items + longs[2].items, n_win = win.items();
+  if (n_long + n_win == 0) return 0.0;
+  Launch launch(units);
+  for (int x = 0; x < XCDS; ++x) {
+    int at = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+      int keep = n_long - half_long;
+      for (int i = 0; i < 3; ++i) {
+        const int w = std::min(keep, longs[i].items), items = pass == 0 ? w : 2 * (longs[i].items - w);
+        keep -= w;
+        launch.batch(Launch::share(at, items, x), (pass == 0 ? LONG : LONG_HALF).of(longs[i].blocks));
+        at += items;
+      }
+    }
+    if (n_win) {
+      const int whole = n_win - half_win;
+      const Range r = xcd_range(n_win + half_win, (x + XCDS - at % XCDS) % XCDS);
+      const int end = std::min(r.last, whole), begin = std::max(r.first, whole);      // whole items to end, halves from begin
+      auto item = [&](int half) { return whole + (half - whole) / 2; };
+      if (end > r.first) launch.batch(end - r.first, WIN.of(win.blocks(r.first, end)));
+      if (r.last > begin) launch.batch(r.last - begin, WIN_HALF.of(win.blocks(item(begin), std::max(item(begin) + 1, item(r.last)))));
+    }
+    launch.close();
+  }
+  const double alone = n_win ? (half_win < n_win ? WIN : WIN_HALF).of(win.most) : 0.0;
+  return LAUNCH_US + std::max(alone, launch.worst());
+}
+
+double win_128_time(const Window& win, int units) {
+  if (win.items() == 0) return 0.0;
+  Launch launch(units);
+  for (int x = 0; x < XCDS; ++x) {
+    const Range r = xcd_range(win.items(), x);
+    const double blocks = win.blocks(r.first, r.last);
+    launch.batch(r.last - r.first, WIN_128.of(blocks) + WIN_128_WAVE * win.waves * blocks);
+    launch.close();
+  }
+  return LAUNCH_US + std::max(WIN_128.fixed + WIN_128_ALONE * win.most, launch.worst());
+}
+
+// Split launch of the three segments of long items (or none: null) and the window items, dealt round robin.
+double split_time(const Segment* longs, const Window& win, int shares, int units) {
+  Launch launch(units);
+  int items = win.items();
+  double alone = 0.0;                      // the longest item by itself
+  for (int i = 0; longs && i < 3; ++i) {
+    items += longs[i].items;
+    if (longs[i].items) alone = std::max(alone, shares == 2 ? SPLIT2.fixed + SPLIT2_ALONE * longs[i].blocks : SPLIT4.of(longs[i].blocks));
+  }
+  if (win.items()) alone = std::max(alone, shares == 2 ? SPLIT2_WIN.fixed + SPLIT2_ALONE * win.most : SPLIT4_WIN.of(win.most));
+  if (items == 0) return 0.0;
+  if (items <= units) return LAUNCH_US + alone;      // every item has a CU to itself
+  for (int x = 0; x < XCDS; ++x) {
+    int at = 0;
+    auto add = [&](int items_here, double cost) {
+      launch.batch(Launch::share(at, items_here, x), cost);
+      at += items_here;
+    };
+    for (int i = 0; longs && i < 3; ++i) add(longs[i].items, (shares == 2 ? SPLIT2 : SPLIT4).of(longs[i].blocks));
+    if (win.items()) add(win.items(), (shares == 2 ? SPLIT2_WIN : SPLIT4_WIN).of(win.blocks()));
+    launch.close();
+  }
+  return LAUNCH_US + std::max(alone, launch.worst());
+}
+
+// The number of items to issue as half-row items, and its estimate: the last items of a launch leave most CUs
+// idle while a few finish them, and two half-row items take 1.3 times one whole item.
+template <class Time>
+int best_halves(int items, int units, double margin, Time time_of, double* best_us) {
   int best = 0;
-  *time = 1e30;
-  for (int s : candidates) {
-    s = std::min(s, most);
-    const double us = pipe_time(seg, n, s, units);
-    if (us < *time) {
-      *time = us;
-      best = s;
+  double best_cost = *best_us = time_of(0);
+  for (int h : {units / 4, units / 2, items}) {
+    h = std::min(h, items);
+    const double us = time_of(h);
+    if (us * margin < best_cost) {
+      best_cost = us * margin;
+      *best_us = us;
+      best = h;
     }
   }
   return best;
-}
-
-double split_time(const Segment* seg, int n, int units) {
-  Batch b[4];
-  int nb = 0;
-  for (int i = 0; i < n; ++i)
-    if (seg[i].items > 0) b[nb++] = {seg[i].items, seg[i].win ? 4.7 + 0.54 * seg[i].blocks : 2.5 + 0.52 * seg[i].blocks};
-  return nb ? LAUNCH_US + makespan(b, nb, units) : 0.0;
 }
 }  // namespace
 
@@ -125,58 +229,71 @@ AttnForm choose_attention_form(const vorta_plan* p, const RouteLists& rl, bool m
   const int rows_c = (int)(p->Lc + p->d.n_text), n_text = win_text ? p->d.n_text : 0;
   const int blocks_n = (int)((p->N + 63) / 64), blocks_c = (rows_c + 63) / 64;
   auto items_of = [](int64_t rows, int bm) { return (int)((rows + bm - 1) / bm); };
-  auto list_items = [&](int l) { return n_win * (int)(p->win_list[l].size() / 4); };
-
-  // Everything in 64-row items: one launch of the split kernel if that is estimated to be the faster form.
-  // With no more items than CUs four key shares shorten each of them (3,072 keys: 29 us against
-  // 34 with two shares; 256 keys, where the longer merge shows: 9.6 against 8.8).
-  const Segment fine[4] = {{n_win * items_of(n_text, ATTN_ROWS_SPLIT), blocks_n, false}, {rl.count[0] * items_of(p->N, ATTN_ROWS_SPLIT), blocks_n, false},
-                           {rl.count[2] * items_of(rows_c, ATTN_ROWS_SPLIT), blocks_c, false}, {list_items(2), p->win_blocks[2], true}};
-  int fine_items = 0, longest = 0;
-  for (const Segment& s : fine) {
-    fine_items += s.items;
-    if (s.items) longest = std::max(longest, s.blocks);
-  }
+  auto longs_of = [&](int bm, Segment (&s)[3]) {
+    s[0] = {n_win * items_of(n_text, bm), blocks_n};
+    s[1] = {rl.count[0] * items_of(p->N, bm), blocks_n};
+    s[2] = {rl.count[2] * items_of(rows_c, bm), blocks_c};
+    return s[0].items + s[1].items + s[2].items;
+  };
+  auto list = [&](int l) {
+    Window w;
+    w.heads = n_win;
+    w.list = (int)(p->win_list[l].size() / 4);
+    w.sums = p->win_sums[l].data();
+    w.most = p->win_most_blocks[l];
+    w.waves = p->win_waves[l];
+    return w;
+  };
+  Segment fine[3], coarse[3];
+  const Segment no_longs[3] = {};
+  const Window none, big = list(0), rest = list(1), fine_win = list(2), win_128 = list(3);
+  const int fine_items = longs_of(ATTN_ROWS_SPLIT, fine) + fine_win.items();
   AttnForm f = {};
   f.empty = fine_items == 0;
   if (f.empty) return f;
-  const Segment coarse[4] = {{n_win * items_of(n_text, ATTN_ROWS_LONG), blocks_n, false}, {rl.count[0] * items_of(p->N, ATTN_ROWS_LONG), blocks_n, false},
-                             {rl.count[2] * items_of(rows_c, ATTN_ROWS_LONG), blocks_c, false}, {list_items(0), p->win_blocks[0], true}};
-  f.n_long = coarse[0].items + coarse[1].items + coarse[2].items;
-  f.n_big = coarse[3].items;
-  f.shares = fine_items <= units && longest >= 16 ? 4 : 2;
-  f.split_all = fine_items <= units;
+  f.n_long = longs_of(ATTN_ROWS_LONG, coarse);
+  f.n_big = big.items();
   f.together = f.n_long && f.n_big && !mix;
+  f.split_all = fine_items <= units;       // 256-row items would leave three of four CUs idle
+  const double t_split2 = split_time(fine, fine_win, 2, units), t_split4 = split_time(fine, fine_win, 4, units);
+  f.shares = t_split4 < t_split2 ? 4 : 2;
   if (!f.split_all || p->force_form) {
-    double t_long, t_big, t_both;
-    f.half_long = best_split(coarse, 3, f.n_long, units, &t_long);
-    f.half_big = best_split(coarse + 3, 1, f.n_big, units, &t_big);
-    const Batch small = {list_items(1), 5.0 + 1.55 * p->win_blocks[1]};
-    const double t_small = small.items ? LAUNCH_US + makespan(&small, 1, 2 * units) : 0.0;
-    double t_pipe = t_long + t_big + t_small;
-    if (f.together) {
-      f.half_big = best_split(coarse, 4, f.n_big, units, &t_both);
-      t_pipe = t_both + t_small;
-    }
-    // far above the sizes where the split kernel can win there is nothing to estimate
-    int64_t work = 0;
-    for (const Segment& s : fine) work += (int64_t)s.items * s.blocks;
-    if (!f.split_all && work < (int64_t)4000 * units) {
-      const double t_split_win = split_time(&fine[3], 1, units);
-      f.split_win = n_win && t_long + t_split_win < t_pipe;
-      f.split_all = split_time(fine, 4, units) < std::min(t_pipe, n_win ? t_long + t_split_win : t_pipe);
+    double t_long, t_pipe;
+    f.half_long = best_halves(f.n_long, units, f.n_long > units ? HALVES_EVEN : HALVES_SAVE, [&](int h) { return pipe_time(coarse, none, h, 0, units); }, &t_long);
+    f.half_big = best_halves(f.n_big, units, HALVES_SAVE, [&](int h) { return pipe_time(f.together ? coarse : no_longs, big, 0, h, units); }, &t_pipe);
+    if (!f.together) t_pipe += t_long;
+    t_pipe += win_128_time(rest, units);
+    // Far above the sizes where another form can win by much there is nothing to choose, and the chip's power limit
+    // changes the costs: core-set and window items of 12 heads of 32,760 tokens, 3,900 blocks per CU, are estimated
+    // faster with the window rows in 128-row items and measured 0 to 1.8 % slower (the whole mixture).
+    double work = fine_win.items() ? fine_win.items() * fine_win.blocks() : 0.0;
+    for (const Segment& s : fine) work += (double)s.items * s.blocks;
+    if (!f.split_all && work < 3000.0 * units) {
+      double best = t_pipe;
+      auto take = [&](bool& form, double us) {
+        if (us >= best) return;
+        best = us;
+        f.split_win = f.win_128 = f.split_all = false;
+        form = true;
+      };
+      if (n_win) {
+        take(f.split_win, t_long + split_time(nullptr, fine_win, 2, units));
+        take(f.win_128, t_long + win_128_time(win_128, units));
+      }
+      take(f.split_all, std::min(t_split2, t_split4));
     }
   }
   if (p->force_form) {           // tests: one form for every size
     f.split_all = p->force_form == 2 || p->force_form == 4;
     if (f.split_all) f.shares = p->force_form;
     f.split_win = p->force_form == 5 && n_win;
+    f.win_128 = p->force_form == 6 && n_win;
     if (p->force_halves >= 0) {
       f.half_long = std::min(p->force_halves, f.n_long);
       f.half_big = std::min(p->force_halves, f.n_big);
     }
   }
-  f.together = f.together && !f.split_all && !f.split_win;
+  f.together = f.together && !f.split_all && !f.split_win && !f.win_128;
   return f;
 }
 
@@ -188,23 +305,23 @@ extern "C" {
 
 // For the tests, not part of the ABI: every form of the bf16 attention launch at any size.  form: 0 = by the rule;
 // 2, 4 = split kernel with so many key shares; 3 = pipelined kernels; 5 = pipelined, window rows on the split
-// kernel.  halves: items issued as half-row items, -1 = by the rule.  A property of the plan; not to be changed
+// kernel; 6 = pipelined, all window rows in 128-row items.  halves: items issued as half-row items, -1 = by the rule.  A property of the plan; not to be changed
 // while a call on it runs.
 int vorta_test_force_form(vorta_plan* p, int32_t form, int32_t halves) {
-  if (!p || !(form == 0 || (form >= 2 && form <= 5)) || halves < -1) return fail(VORTA_EINVAL, "form %d, halves %d", form, halves);
+  if (!p || !(form == 0 || (form >= 2 && form <= 6)) || halves < -1) return fail(VORTA_EINVAL, "form %d, halves %d", form, halves);
   p->force_form = form;
   p->force_halves = halves;
   return VORTA_OK;
 }
 
 // What a layer call (mix = 0) or the full-attention launch of the mixture (1) chooses with `units` CUs:
-// {split_all, shares, split_win, together, n_long, half_long, n_big, half_big}.
-int vorta_test_form(const vorta_plan* p, const uint8_t* routes_host, int32_t mix, int32_t units, int32_t out[8]) {
+// {split_all, shares, split_win, together, n_long, half_long, n_big, half_big, win_128}.
+int vorta_test_form(const vorta_plan* p, const uint8_t* routes_host, int32_t mix, int32_t units, int32_t out[9]) {
   RouteLists rl;
   if (int rc = split_routes(p, routes_host, &rl)) return rc;
   const AttnForm f = choose_attention_form(p, rl, mix != 0, true, units);
-  const int32_t v[8] = {f.split_all, f.shares, f.split_win, f.together, f.n_long, f.half_long, f.n_big, f.half_big};
-  std::copy(v, v + 8, out);
+  const int32_t v[9] = {f.split_all, f.shares, f.split_win, f.together, f.n_long, f.half_long, f.n_big, f.half_big, f.win_128};
+  std::copy(v, v + 9, out);
   return VORTA_OK;
 }
 

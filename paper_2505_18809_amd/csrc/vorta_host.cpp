@@ -198,25 +198,29 @@ static void build_plan(vorta_plan* p) {
   // borders.  Cut tile by tile, a 432-token tile was a block of 256 rows and one of 176 that cost as
   // much: 350 blocks per head on a 20x45x80 grid with (6,9,8) tiles, now 287 -- window launches of 20
   // heads 7.92 -> 6.90 ms.
-  int64_t list_blocks[3] = {0, 0, 0};
+  int64_t list_waves[4] = {0, 0, 0, 0};
+  for (auto& sums : p->win_sums) sums.assign(1, 0);
   int32_t end = 0;
   for (int g = 0; g < p->n_tiles; ++g) {
     if (place[g] == place[g + 1]) continue;      // not the first tile of a group
     const int32_t begin = end;
     for (int32_t i = place[g]; i < place[g + 1]; ++i) end += p->tile_row0[p->win_tiles[i] + 1] - p->tile_row0[p->win_tiles[i]];
-    int64_t blocks = 0;
-    for (size_t r = 1; r < run_lists[g].size(); r += 2) blocks += run_lists[g][r];
-    blocks = (blocks + 63) / 64;
+    int64_t keys = 0;
+    for (size_t r = 1; r < run_lists[g].size(); r += 2) keys += run_lists[g][r];
+    const int blocks = (int)((keys + 63) / 64);
     auto add = [&](int list, int32_t first, int32_t rows) {
       p->win_list[list].insert(p->win_list[list].end(), {first, rows, g, 0});
-      list_blocks[list] += blocks;
+      p->win_sums[list].push_back(p->win_sums[list].back() + blocks);
+      p->win_most_blocks[list] = std::max(p->win_most_blocks[list], blocks);
+      list_waves[list] += (rows + 31) / 32;
     };
     for (int32_t first = begin; first < end; first += 256) add(end - first > 128 ? 0 : 1, first, std::min(256, end - first));
     for (int32_t first = begin; first < end; first += 64) add(2, first, std::min(64, end - first));
+    for (int32_t first = begin; first < end; first += 128) add(3, first, std::min(128, end - first));
   }
-  for (int l = 0; l < 3; ++l) {
+  for (int l = 0; l < 4; ++l) {
     const int64_t n = (int64_t)p->win_list[l].size() / 4;
-    if (n) p->win_blocks[l] = (int)((list_blocks[l] + n - 1) / n);
+    if (n) p->win_waves[l] = (double)list_waves[l] / (double)n;
   }
 
   // BCS slot layout: a (border-clipped) bucket of B' tokens keeps B' - k of them,

@@ -30,10 +30,14 @@ struct vorta_plan {
   // blocks whatever the tile borders; win_tiles holds the tiles of these sequences one after the other.
   // {first, n_rows, tile, 0}: n_rows places of the sequences' rows from `first`, keys as tile `tile` sees them.
   // List 0: blocks of 129 to 256 rows; list 1: what is left of a sequence, at most 128 rows; list 2: the
-  // sequences cut into blocks of at most 64 rows instead.
+  // sequences cut into blocks of at most 64 rows instead; list 3: of at most 128 rows.
   std::vector<int32_t> win_tiles;  // [n_tiles]
-  std::vector<int32_t> win_list[3];
-  int win_blocks[3] = {0, 0, 0};   // 64-key blocks of the items of a list, on average (for the launch estimate)
+  std::vector<int32_t> win_list[4];
+  // of the items of a list, for the launch estimate: 64-key blocks of the items before each one ([n + 1]), blocks of
+  // the longest, and 32-row wavefronts that have rows, on average
+  std::vector<int64_t> win_sums[4];
+  int win_most_blocks[4] = {0, 0, 0, 0};
+  double win_waves[4] = {0, 0, 0, 0};
   // rotary embedding: (cos, sin) of position * rate for every position of every axis,
   // [F][pairs_F] then [H][pairs_H] then [W][pairs_W]; empty without rope_dims
   bool rope = false;
@@ -59,7 +63,7 @@ struct vorta_plan {
   int32_t* d_win_tok = nullptr;  // [L]: their tokens
   int32_t* d_tile_row0 = nullptr;   // [n_tiles + 1]
   float* d_rope_cs = nullptr;
-  int32_t* d_win_list[3] = {nullptr, nullptr, nullptr};
+  int32_t* d_win_list[4] = {nullptr, nullptr, nullptr, nullptr};
   void* d_tables = nullptr;      // the allocation
 };
 
@@ -119,6 +123,7 @@ struct AttnForm {
   bool split_all;          // everything on the split kernel, with `shares` key shares
   int shares;
   bool split_win;          // window rows on the split kernel (two shares), the rest on the pipelined one
+  bool win_128;            // all window rows on the 4-wavefront kernel in 128-row items
   bool together;           // long and window items of more than 128 rows in one launch
   int n_long, half_long;   // 256-row items of dense, core-set and text rows; how many of them as half-row items
   int n_big, half_big;     // the same of the window items of more than 128 rows

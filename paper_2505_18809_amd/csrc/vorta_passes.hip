@@ -50,6 +50,7 @@ static int upload_device_tables(vorta_plan* p, int dev) {
                     table(p->runs, &p->d_runs), table(p->n_runs, &p->d_n_runs), table(p->slot_base, &p->d_slot_base),
                     table(p->tile_row0, &p->d_tile_row0), table(p->win_list[0], &p->d_win_list[0]),
                     table(p->win_list[1], &p->d_win_list[1]), table(p->win_list[2], &p->d_win_list[2]),
+                    table(p->win_list[3], &p->d_win_list[3]),
                     table(p->rope_cs, &p->d_rope_cs)};
   size_t total = 0;
   for (Table& t : tables) {

@@ -35,8 +35,9 @@ def smooth_field(rng, grid, d, noise=0.5):
 
 
 # Forms of a bf16 attention launch (an internal hook of the library): 0 = the library's own choice; split kernel
-# with two or four key shares; pipelined kernels; pipelined with the window rows on the split kernel.
-SPLIT2, SPLIT4, PIPE, PIPE_SPLIT_WIN = 2, 4, 3, 5
+# with two or four key shares; pipelined kernels; pipelined with the window rows on the split kernel, and with all
+# of them in 128-row items.
+SPLIT2, SPLIT4, PIPE, PIPE_SPLIT_WIN, PIPE_WIN_128 = 2, 4, 3, 5, 6
 
 
 def force_form(plan, form, halves=-1):
@@ -48,7 +49,7 @@ def force_form(plan, form, halves=-1):
 def attention_form(plan, routes, mix=False, units=256):
     """What the library chooses for a layer call with these routes on a device of `units` CUs."""
     r = np.ascontiguousarray(routes, dtype=np.uint8)
-    out = np.zeros(8, dtype=np.int32)
+    out = np.zeros(9, dtype=np.int32)
     assert vorta.load_library().vorta_test_form(plan.handle, r.ctypes.data_as(ctypes.c_void_p), ctypes.c_int32(mix),
                                                 ctypes.c_int32(units), out.ctypes.data_as(ctypes.c_void_p)) == 0
-    return dict(zip(("split_all", "shares", "split_win", "together", "n_long", "half_long", "n_big", "half_big"), map(int, out)))
+    return dict(zip(("split_all", "shares", "split_win", "together", "n_long", "half_long", "n_big", "half_big", "win_128"), map(int, out)))

@@ -7,7 +7,7 @@ import pytest
 
 import paper_2505_18809_amd as vorta
 from synth_inputs import get_config, make_routes
-from helpers import PIPE, PIPE_SPLIT_WIN, SPLIT2, SPLIT4, attention_form, force_form
+from helpers import PIPE, PIPE_SPLIT_WIN, PIPE_WIN_128, SPLIT2, SPLIT4, attention_form, force_form
 
 
 def plan_of(grid, heads, tile=(3, 3, 3), window=(3, 3, 3), **kw):
@@ -22,10 +22,13 @@ def test_small_layers_run_on_the_split_kernel(grid, heads, tile, window, n_text)
     assert form["split_all"] and not form["together"]
 
 
-def test_four_key_shares_where_the_items_fit_the_cus_and_the_stream_is_long():
-    assert attention_form(plan_of((1, 31, 31), 3), (0, 1, 2))["shares"] == 4            # 961 keys: 16 blocks
-    assert attention_form(plan_of((1, 30, 31), 3), (0, 1, 2))["shares"] == 2            # 930: 15
+def test_four_key_shares_where_a_long_stream_sets_the_end():
+    assert attention_form(plan_of((1, 48, 48), 3), (0, 1, 2))["shares"] == 4            # 2,304 keys: 36 blocks
+    assert attention_form(plan_of((4, 8, 8), 3), (0, 1, 2))["shares"] == 2              # 256: 4
     assert attention_form(plan_of((4, 12, 16), 42), [h % 3 for h in range(42)])["shares"] == 2       # more items than CUs
+    # two items of text rows over 15,000 keys beside 600 short window items
+    form = attention_form(plan_of((19, 24, 33), 2, (6, 9, 8), n_text=20, center_mode=1), (1, 1))
+    assert form["split_all"] and form["shares"] == 4
 
 
 @pytest.mark.parametrize("name", ["wan480p", "wan720p", "hunyuan720p", "paper720p", "paper_wan720p"])
@@ -36,13 +39,12 @@ def test_full_size_layers_run_on_the_pipelined_kernels_in_one_launch(name):
 
 
 def test_forms_of_the_layers_that_gpu_tests_rely_on():
-    routes = (1, 0, 2, 1, 2, 1, 2, 1)
-    one = attention_form(plan_of((21, 29, 52), 8, (3, 6, 4)), routes)
-    assert one["together"] and 0 < one["half_big"] < one["n_big"]
-    text = attention_form(plan_of((21, 29, 52), 8, (3, 6, 4), n_text=77), routes)
-    assert text["together"] and text["half_big"] == 0                                    # the test asks for halves itself
+    for n_text in (0, 77):       # the test asks for the pipelined kernels and the number of halves itself
+        plan = force_form(plan_of((21, 29, 52), 8, (3, 6, 4), n_text=n_text), PIPE, 131)
+        one = attention_form(plan, (1, 0, 2, 1, 2, 1, 2, 1))
+        assert one["together"] and one["half_big"] == 131 and one["n_big"] == 584
     masked = attention_form(plan_of((21, 29, 52), 8, (3, 6, 4), n_text=21), (0, 1, 2, 1, 0, 1, 2, 1))
-    assert masked["together"]
+    assert not masked["split_all"] and not masked["split_win"]
     for bucket, keep, heads, n_text in (((3, 5, 4), (3, 4), 6, 40), ((2, 3, 2), (1, 2), 8, 0)):
         long = attention_form(plan_of((21, 30, 52), heads, (2, 4, 4), n_text=n_text, bucket=bucket, keep_num=keep[0], keep_den=keep[1]), (2,) * heads)
         assert not long["split_all"] and long["n_long"] > 256
@@ -64,11 +66,27 @@ def test_a_form_can_be_asked_for_at_any_size():
     assert got["half_long"] == got["n_long"] == 3 and got["half_big"] == got["n_big"] == 2   # 385 rows: 256 and 129
     got = attention_form(force_form(plan, PIPE_SPLIT_WIN, 0), routes)
     assert got["split_win"] and not got["together"] and got["half_long"] == 0
+    got = attention_form(force_form(plan, PIPE_WIN_128, 1 << 20), routes)
+    assert got["win_128"] and not got["together"] and got["half_long"] == 3
     assert attention_form(force_form(plan, 0), routes) == chosen
     lib = vorta.load_library()
-    for form, halves in ((1, -1), (6, -1), (-1, -1), (PIPE, -2)):
+    for form, halves in ((1, -1), (7, -1), (-1, -1), (PIPE, -2)):
         assert lib.vorta_test_force_form(plan.handle, ctypes.c_int32(form), ctypes.c_int32(halves)) == -1
     assert attention_form(plan, routes) == chosen
+
+
+def test_window_rows_that_leave_256_row_items_half_empty_take_128_row_items():
+    """Sequences of 144 and 288 rows (72-token tiles in pairs along two axes): items of 144 rows in 256."""
+    assert attention_form(plan_of((21, 30, 52), 16, (3, 6, 4)), (1,) * 16)["win_128"]
+    full = attention_form(plan_of((20, 32, 32), 16, (4, 8, 8)), (1,) * 16)              # 256-token tiles
+    assert not full["win_128"] and full["n_big"] > 0
+
+
+def test_half_row_items_only_where_they_save_something():
+    whole = attention_form(plan_of((16, 24, 24), 4), (0,) * 4)                          # 144 items on 256 CUs
+    assert not whole["split_all"] and whole["n_long"] == 144 and whole["half_long"] == 0
+    more = attention_form(plan_of((16, 24, 24), 8), (0,) * 8)                           # 288: 32 too many for one round
+    assert not more["split_all"] and more["n_long"] == 288 and 0 < more["half_long"] <= 128
 
 
 def test_no_items_and_no_heads_on_a_route():

@@ -106,8 +106,9 @@ def test_bf16_window_rows_cut_across_tile_borders(grid, n_text, layout):
     ((1, 8, 8), 3, 1, 1),             # 65 rows and keys: a second item of one row
     ((2, 8, 8), 3, 0, 0),             # 128
     ((3, 6, 9), 3, 31, 1),            # 193 keys, odd and even superblocks of the routes
-    ((1, 31, 31), 3, 0, 1),           # 961 keys: from here on four shares where the items fit the CUs
+    ((1, 31, 31), 3, 0, 1),           # 961 keys
     ((3, 7, 49), 3, 124, 0),          # 1,153 keys: nine superblocks of 128 and one key
+    ((1, 47, 49), 3, 2, 0),           # 2,305: four shares, 18 superblocks and one key
     ((4, 12, 16), 42, 0, 1),          # 42 heads of 768 tokens: more items than CUs
 ])
 def test_bf16_attention_at_the_edges_of_its_key_split(grid, heads, n_text, layout):
@@ -165,17 +166,15 @@ def test_core_set_rows_written_to_their_tokens_equal_the_staged_unpool(grid, buc
     assert torch.equal(out, staged)
 
 
-@pytest.mark.parametrize("n_text,layout,halves", [(0, 1, -1), (77, 0, -1), (77, 0, 131)])
+@pytest.mark.parametrize("n_text,layout,halves", [(0, 1, 0), (0, 1, 128), (77, 0, 131)])
 def test_long_and_window_items_in_one_launch(n_text, layout, halves):
     """A layer large enough for 256-row items on every route: window items follow the long ones in one launch, the last
-    of them in halves where the rule has it so (without text) or is told to.  Sampled rows of one head per route."""
+    of them in halves.  Sampled rows of one head per route."""
     cfg = LayerConfig("one_launch", (21, 29, 52), 8, 128, "bf16", (3, 6, 4), (3, 3, 3), seed=53, n_text=n_text,
                       fixed_routes=(1, 0, 2, 1, 2, 1, 2, 1))
     say(cfg.name)
     q, k, v = make_qkv(cfg, DEV, layout)
-    plan = vorta.plan_for(cfg, layout=layout)
-    if halves >= 0:
-        force_form(plan, PIPE, halves)
+    plan = force_form(vorta.plan_for(cfg, layout=layout), PIPE, halves)
     out = vorta.vorta_routed_attention_layer(plan, q, k, v, cfg.fixed_routes)
     torch.cuda.synchronize()
     hnd = (lambda t: t) if layout == 1 else (lambda t: t.transpose(0, 1))

@@ -1,7 +1,8 @@
 """Every form of the bf16 attention launch at the sizes where it can go wrong.  The library chooses the form from
 the size of the layer, and small layers run on the split kernel; here each of them is held to the fp64
 oracle on the same small layers: split kernel with two and four key shares, pipelined kernels with none, some
-and all items issued as half-row items, and pipelined with the window rows on the split kernel."""
+and all items issued as half-row items, and pipelined with the window rows on the split kernel or all of them in
+128-row items."""
 import sys
 
 import numpy as np
@@ -11,11 +12,12 @@ import torch
 import paper_2505_18809_amd as vorta
 from oracle import vorta_oracle as vo
 from synth_inputs import LayerConfig, make_qkv
-from helpers import PIPE, PIPE_SPLIT_WIN, SPLIT2, SPLIT4, f64, force_form, spec_of
+from helpers import PIPE, PIPE_SPLIT_WIN, PIPE_WIN_128, SPLIT2, SPLIT4, f64, force_form, spec_of
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
-FORMS = [(SPLIT2, -1), (SPLIT4, -1), (PIPE, 0), (PIPE, 2), (PIPE, 1 << 20), (PIPE_SPLIT_WIN, 0), (PIPE_SPLIT_WIN, 1 << 20)]
+FORMS = [(SPLIT2, -1), (SPLIT4, -1), (PIPE, 0), (PIPE, 2), (PIPE, 1 << 20), (PIPE_SPLIT_WIN, 0), (PIPE_SPLIT_WIN, 1 << 20),
+         (PIPE_WIN_128, 0), (PIPE_WIN_128, 1 << 20)]
 
 
 def say(msg):
@@ -53,6 +55,7 @@ LAYERS = [
     ((7, 10, 13), (3, 4, 5), (3, 3, 3), 300, (1, 0, 2, 1), 1),             # text rows over two long items
     ((3, 7, 49), (2, 3, 4), (3, 1, 3), 124, (0, 1, 2), 0),                 # 1,153 keys: one more than 18 blocks
     ((4, 8, 16), (2, 4, 4), (3, 3, 3), 0, (0, 2, 0, 1), 1),                # 512 keys: whole blocks
+    ((1, 31, 31), (2, 3, 4), (3, 1, 3), 0, (0, 1, 2), 1),                  # 961
 ]
 
 

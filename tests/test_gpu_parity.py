@@ -10,7 +10,7 @@ import torch
 import paper_2505_18809_amd as vorta
 from oracle import vorta_oracle as vo
 from synth_inputs import LayerConfig, get_config, make_qkv, make_routes
-from helpers import PIPE, PIPE_SPLIT_WIN, SPLIT2, SPLIT4, f64, force_form, spec_of
+from helpers import PIPE, PIPE_SPLIT_WIN, PIPE_WIN_128, SPLIT2, SPLIT4, f64, force_form, spec_of
 
 pytestmark = pytest.mark.gpu
 
@@ -302,7 +302,7 @@ def test_degenerate_cases():
     check_layer(big_tile, big_tile.fixed_routes)
 
 
-@pytest.mark.parametrize("form", [0, SPLIT2, SPLIT4, PIPE, PIPE_SPLIT_WIN])
+@pytest.mark.parametrize("form", [0, SPLIT2, SPLIT4, PIPE, PIPE_SPLIT_WIN, PIPE_WIN_128])
 @pytest.mark.parametrize("tile", [(4, 4, 4), (4, 8, 8)], ids=["tile64", "tile256"])
 def test_row_maxima_that_jump_or_creep_late_in_the_key_stream(tile, form):
     """The attention kernels keep a lagging row reference instead of the running maximum.
