@@ -1,6 +1,7 @@
 // bf16 routed attention for gfx950 (CDNA4): flash-style forward.  One software-pipelined kernel runs
 // every segment -- dense, core-set and, reading rows through an index table (the tile permutation, or
-// the identity over tile-ordered copies), the window tiles.
+// the identity over tile-ordered copies), the window tiles; small layers run on a kernel that splits the key
+// stream instead (vorta_attn_rule.cpp chooses).
 //
 // A wavefront owns 32 query rows; keys stream through LDS in blocks of 64 (or 32) rows.  Both contractions run on
 // v_mfma_f32_32x32x16_bf16 and are computed TRANSPOSED so that a lane owns one query:
@@ -694,7 +695,8 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_layer_kernel(const AttnArgs 
 // around them (fragment requests, reference check, packing) no matrix instruction covers: about 2,000
 // cycles per 128-key superblock against 1,024 of matrix instructions (2,600 with one barrier, all loads
 // requested and waited for in the same iteration, and the addresses ahead of the slots).
-// 3,072-token layer, 8 heads on all routes: 88 -> 52 us; at 9,216 tokens, 24 heads, 477 -> 445 us.
+// Whole layers, before there was this kernel and now: 3,072 tokens, 8 heads on all routes 85 -> 43 us, 8 core-set heads
+// 47 -> 34 us.
 // ------------------------------------------------------------------------------------------
 namespace {
 constexpr int BM_SPLIT = ATTN_ROWS_SPLIT;
@@ -1147,9 +1149,9 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
     if (mix) hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8, true>), grid, dim3(512), pipe_lds_bytes(8), st, a, *mix);
     else hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8>), grid, dim3(512), pipe_lds_bytes(8), st, a, NoMix());
   }
-  // Window tiles: in 64-row items (above), or the plan's items of more than 128 rows on the 8-wavefront instance
-  // (256 rows, 64-key blocks, one workgroup per CU) and the rest on the 4-wavefront one (128 rows, 32-key
-  // blocks, two per CU).
+  // Window tiles: in 64-row items, or the plan's items of more than 128 rows on the 8-wavefront instance (256 rows,
+  // 64-key blocks, one workgroup per CU) and the rest on the 4-wavefront one (128 rows, 32-key blocks, two per CU),
+  // or all of them on the latter.
   if (rl.count[1] == 0) return launched();
   if (form.split_win) {
     if (int rc = fill_attn_args(p, win_rl, io, core, BM_SPLIT, WIN_TILES, &a, 2)) return rc;

@@ -171,9 +171,9 @@ __device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int item) {
 // Work item of a workgroup.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs
 // (each with its own L2); with chunked = true the ids are re-dealt so that every XCD gets one
 // contiguous range of the n items instead -- neighbouring window tiles, whose key sets
-// overlap, then run on the same XCD at about the same time and share its L2.  Only for
-// launches whose items all cost the same (a contiguous deal of unequal items would leave
-// some XCDs with all the long ones).
+// overlap, then run on the same XCD at about the same time and share its L2.  For launches whose
+// items cost about the same: a contiguous deal of unequal items leaves some XCDs with all the long ones.  The half-row
+// items at the end of a window launch are unequal, and all of them fall to the last XCDs; the launch rule counts with that.
 __device__ __forceinline__ int xcd_item(int block, int n, bool chunked) {
   if (!chunked) return block;
   const int xcd = block & 7, loc = block >> 3, q = n >> 3, r = n & 7;

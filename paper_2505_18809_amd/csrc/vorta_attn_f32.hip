@@ -33,8 +33,8 @@
 //
 // Measured (attention launch and whole layer; the vector-ALU kernel before it in brackets): eight dense
 // heads of 3,072 tokens x 128 run at 57 TFLOP/s, 73 % of the matrix instruction's rate, without the
-// exponentials at 59; the 3,072-token layer with 2 full, 3 window and 3 core-set heads 484 us
-// [1,701 us], two heads of 256 tokens x 64 22 us [140 us, four of its launches reorder passes].
+// exponentials at 59; the 3,072-token layer with 2 full, 3 window and 3 core-set heads 440 us
+// [1,701 us], two heads of 256 tokens x 64 17 us [140 us, four of its launches reorder passes].
 #include <hip/hip_runtime.h>
 
 #include "vorta_attn_common.h"
