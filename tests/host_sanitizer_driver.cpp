@@ -1,12 +1,16 @@
 // Walks the host-only entry points of libvorta (plan construction, index tables, route
 // bookkeeping, router) under AddressSanitizer / UBSan.  Built and run by
-// tests/test_host_tables.py; links vorta_host.cpp alone (it has no reference into the device side).
+// tests/test_host_tables.py; links vorta_host.cpp and vorta_attn_rule.cpp alone (they have no reference into the device side).
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <vector>
 
 #include "vorta_internal.h"
+
+extern "C" int vorta_test_force_form(vorta_plan* p, int32_t form, int32_t halves);
+extern "C" int vorta_test_form(const vorta_plan* p, const uint8_t* routes_host, int32_t mix, int32_t units, int32_t out[9]);
 
 static int failures = 0;
 #define EXPECT(cond)                                                   \
@@ -57,6 +61,22 @@ static void walk(const vorta_layer_desc& d) {
   EXPECT(vorta_workspace_bytes(p, routes.data(), &bytes) == VORTA_OK && bytes >= 256);
   EXPECT(vorta_workspace_layout(p, routes.data(), off) == VORTA_OK);
   EXPECT(vorta_soft_mixture_workspace_bytes(p, &bytes) == VORTA_OK);
+  int32_t n_items[2];
+  EXPECT(vorta_window_items(p, nullptr, n_items) == VORTA_OK);
+  std::vector<int32_t> items(4 * (size_t)(n_items[0] + n_items[1]));
+  EXPECT(vorta_window_items(p, items.data(), n_items) == VORTA_OK);
+  const std::vector<uint8_t> mixed = routes;
+  for (int kind = 0; kind < 4; ++kind) {         // every head on one route, and mixed
+    if (kind < 3) std::fill(routes.begin(), routes.end(), (uint8_t)kind);
+    else routes = mixed;
+    for (int form : {0, 2, 3, 4, 5, 6})
+      for (int units : {1, 8, 256}) {
+        int32_t out[9];
+        EXPECT(vorta_test_force_form(p, form, -1) == VORTA_OK);
+        EXPECT(vorta_test_form(p, routes.data(), kind == 0, units, out) == VORTA_OK);
+        EXPECT(out[5] >= 0 && out[5] <= out[4] && out[7] >= 0 && out[7] <= out[6]);
+      }
+  }
   routes[0] = 9;
   EXPECT(vorta_route_partition(p, routes.data(), by_route.data(), counts) == VORTA_EROUTE);
   EXPECT(vorta_plan_destroy(p) == VORTA_OK);

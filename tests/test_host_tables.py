@@ -346,7 +346,7 @@ def test_tensor_arguments_are_checked_before_the_c_call():
 
 
 def test_host_code_under_address_and_undefined_behaviour_sanitizers(tmp_path):
-    """vorta_host.cpp is plain C++: build it with -fsanitize=address,undefined together with a
+    """vorta_host.cpp and vorta_attn_rule.cpp are plain C++: build them with -fsanitize=address,undefined together with a
     driver that walks every host entry point over ordinary, clipped, oversized and rejected
     descriptions, and run it.  Any report makes the driver exit non-zero."""
     import shutil
@@ -358,7 +358,7 @@ def test_host_code_under_address_and_undefined_behaviour_sanitizers(tmp_path):
     exe = str(tmp_path / "host_sanitized")
     cmd = [gxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
            "-I", os.path.join(ROOT, "include"), "-I", csrc, os.path.join(csrc, "vorta_host.cpp"),
-           os.path.join(ROOT, "tests", "host_sanitizer_driver.cpp"), "-o", exe]
+           os.path.join(csrc, "vorta_attn_rule.cpp"), os.path.join(ROOT, "tests", "host_sanitizer_driver.cpp"), "-o", exe]
     res = subprocess.run(cmd, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-3000:]
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", LD_PRELOAD="")
