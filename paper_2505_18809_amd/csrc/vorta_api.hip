@@ -70,7 +70,8 @@ int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io,
   a->qt = io->q_t; a->kt = io->k_t; a->vt = io->v_t; a->ot = io->o_t;
   a->tile_row0 = p->d_tile_row0;
   a->win_gather = io->q_t == nullptr;
-  a->tok_of = a->win_gather ? p->d_tok_of : p->d_iota;
+  a->tok_of = p->d_tok_of;
+  a->row_of = p->d_row_of;
   a->win_row = a->win_gather ? p->d_win_tok : p->d_win_rows;
   a->runs = p->d_runs;
   a->n_runs = p->d_n_runs;
@@ -91,7 +92,7 @@ int fill_attn_args(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io,
   long tile_items = (long)a->n_tiles * a->qb_tile;        // per window head
   if (win_list >= 0) {
     a->win_items = p->d_win_list[win_list];
-    a->win_count = (int)(p->win_list[win_list].size() / 4);
+    a->win_count = (int)(p->win_list[win_list].size() / WIN_ITEM_INTS);
     tile_items = a->win_count;
   }
   const long end_tile = end_core + (win_part & WIN_TILES ? (long)rl.count[1] * tile_items : 0);

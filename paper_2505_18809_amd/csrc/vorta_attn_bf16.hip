@@ -1,7 +1,6 @@
 // bf16 routed attention for gfx950 (CDNA4): flash-style forward.  One software-pipelined kernel runs
-// every segment -- dense, core-set and, reading rows through an index table (the tile permutation, or
-// the identity over tile-ordered copies), the window tiles; small layers run on a kernel that splits the key
-// stream instead (vorta_attn_rule.cpp chooses).
+// every segment -- dense, core-set and, computing which rows it reads, the window tiles; small layers run
+// on a kernel that splits the key stream instead (vorta_attn_rule.cpp chooses).
 //
 // A wavefront owns 32 query rows; keys stream through LDS in blocks of 64 (or 32) rows.  Both contractions run on
 // v_mfma_f32_32x32x16_bf16 and are computed TRANSPOSED so that a lane owns one query:
@@ -67,6 +66,13 @@ __device__ __forceinline__ bf16x8 read_vt3(lds_ptr p_lo, lds_ptr p_hi) {
   const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   return __builtin_bit_cast(bf16x8, both);
 }
+// v of lane 16 q + j (j < 4) in all lanes 16 q .. 16 q + 15: row_newbcast:j.  The selector is part of the instruction,
+// so j has to be known once the caller is unrolled.
+__device__ __forceinline__ unsigned row_bcast(unsigned v, int j) {
+#define VORTA_BCAST(j_) (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + j_, 0xf, 0xf, true)
+  return j == 0 ? VORTA_BCAST(0) : j == 1 ? VORTA_BCAST(1) : j == 2 ? VORTA_BCAST(2) : VORTA_BCAST(3);
+#undef VORTA_BCAST
+}
 // Hide how a per-sub-step LDS base was computed, so every fragment read is base + immediate
 // instead of one precomputed address register per fragment.
 __device__ __forceinline__ lds_ptr opaque(lds_ptr p) {
@@ -105,9 +111,10 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 // between V groups (the ds_read_b64_tr_b16 pattern wants consecutive rows 64 B apart).
 //   64-key blocks: rows j, j+16, j+32, j+48 form group j, each row 256 consecutive bytes.
 //   32-key blocks: rows j, j+8, j+16, j+24 form group j, and all four fall among the 32 rows one
-//   ds_read_b128 covers, so the group is stored in 128-byte pieces: half h of the group's row q
-//   at 512 h + 128 q.  (With 64-byte pieces at 256 c + 64 G every K read took twice its LDS
-//   cycles, by the bank-conflict counter.)
+//   ds_read_b128 covers, so the third and the fourth hold their halves of 128 bytes exchanged.  (With
+//   64-byte pieces at 256 c + 64 G every K read took twice its LDS cycles, by the bank-conflict counter.)
+// Sixteen lanes fetch a row.  A lane computes the offset of one of the rows that its wavefront fetches, lane 16 q + h
+// that of row q of the wavefront's group h, and the others take it from there (row_bcast).
 // Wavefront w loads groups w and w + NWV of K and of V: four loads per iteration.  K blocks live
 // in a ring of four stages, V blocks in a ring of five: in iteration i, V(i-1) and K(i+1) are
 // read (and, at its end, the first fragments of V(i)), block i+2 is landing and block i+3 is
@@ -204,18 +211,18 @@ struct CoreRows {
     *(uint2*)(st + l32 * LSTR + 32 * (dt_) + 8 * q4 + 4 * g) = u;                    \
   }
 
-// WIN: window items: query and output rows through a.win_row, key and value rows -- the concatenation of
-// the tile's runs, cut into blocks -- through a.tok_of (tile-order index -> token index in the caller's
-// tensors; the identity where tile-ordered copies are given).  The token indices of a key block are
-// looked up one block ahead of its rows, so the two dependent loads never wait for each other
-// inside one iteration.
+// WIN: window items: query and output rows through a.win_row, key and value rows from the numbers of the item
+// (WindowKeys).  WIN_COPIES: over tile-ordered copies; the row of a token is looked up, one block ahead of
+// the rows themselves, so the two dependent loads never wait for each other inside one iteration.
 // NWV: wavefronts per workgroup.  8: 256 query rows, 64-key blocks, one workgroup per CU (dense,
 // core-set, window tiles of more than 128 tokens).  4: 128 query rows, 32-key blocks, half the
 // ring, two workgroups per CU (smaller window tiles): the iteration has 16 slots instead of 32.
 // MIX: the launch is the last of the three branches of Eq. 5 (dense items over every head) and
 // its epilogue writes the gate-weighted sum of the three (see MixArgs).
-template <bool WIN, int NWV, bool MIX>
+enum KeySource { LONG_KEYS, WIN_TOKENS, WIN_COPIES };    // consecutive rows; window items over the caller's tensors / over copies
+template <int SRC, int NWV, bool MIX>
 __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::conditional_t<MIX, MixArgs, NoMix> mx, int item) {
+  constexpr bool WIN = SRC != LONG_KEYS, COPIES = SRC == WIN_COPIES;
   static_assert(!(MIX && WIN), "the Eq. 5 epilogue belongs to the dense launch");
   static_assert(pipe_lds_bytes(NWV) <= 160 * 1024, "K and V rings exceed the 160 KB of LDS of a CU");
   static_assert(32 * NWV * LSTR * 2 <= pipe_lds_bytes(NWV), "output staging does not fit in the rings it reuses");
@@ -230,9 +237,9 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
   constexpr int NG = KB / 4;                // four-row groups per stage: group j holds rows j, j + NG, j + 2 NG, j + 3 NG
   constexpr int K_STAGE = NG * KG, V_STAGE = NG * VG;   // elements of a K / V stage
   constexpr int V_BASE = K_RING * K_STAGE;  // the K ring, then the V ring
-  auto vstage = [](int b) { return (int)((unsigned)b % (unsigned)V_RING); };   // ring stage of V block b (K: b & 3)
+  auto after = [](int stage) { return stage == (V_RING - 1) * V_STAGE ? 0 : stage + V_STAGE; };   // V stages, as offsets; K block b: stage b & 3
   const WorkItem w = decode_item<32 * NWV, D>(a, item);
-  const bool user = WIN ? a.win_gather != 0 : w.seg == 0;     // rows of the caller's tensors
+  const bool user = WIN ? !COPIES : w.seg == 0;     // rows of the caller's tensors
   const uint16_t* Q = (const uint16_t*)(user ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
   const uint16_t* K = (const uint16_t*)(user ? a.k0 : w.seg == 1 ? a.kc : a.kt) + w.kv_off;
   const uint16_t* V = (const uint16_t*)(user ? a.v0 : w.seg == 1 ? a.vc : a.vt) + w.kv_off;
@@ -255,39 +262,22 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
     for (int ks = 0; ks < 8; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qp + 16 * ks));
   }
 
-  const RunList rl(w);
-  auto run_start = [&](int r) { return rl.start(r); };
-  auto run_len = [&](int r) { return rl.len(r); };
-  int n_keys = 0;
-  for (int r = 0; r < w.n_runs; ++r) n_keys += run_len(r);
-  const int n_blocks = (n_keys + KB - 1) / KB;   // dense / core-set: one run
+  WindowKeys keys(w);
+  if constexpr (WIN) keys.keep();
+  const int n_keys = WIN ? keys.n_keys : w.single_len;
+  const int n_blocks = (n_keys + KB - 1) / KB;
 
   // ---- staging: a lane moves one 16-byte chunk of two rows of the block, of K and of V: its
   // wavefront loads groups wave and wave + NWV, and lane p of a load fills bytes 16 p .. 16 p + 15
-  // of the group -- which of the group's four rows (ld_q) and which chunk of that row follows
-  // from the group layout.  The fetch stream walks the run list one block per call and stays on
-  // the last block once it is past the end (those extra copies land in ring stages nobody
+  // of the group.  Blocks past the end repeat the last row (those copies land in ring stages nobody
   // reads), so the loads need no guard.
-  const int ld_q = KB == 64 ? lane >> 4 : (lane >> 3) & 3;
-  const int ld_chunk = KB == 64 ? lane & 15 : 8 * (lane >> 5) + (lane & 7);
-  const int ld_row = wave + NG * ld_q, ld_col = 8 * ld_chunk;
-  constexpr int STG_STEP = NWV;    // rows from a lane's first staging row to its second
-  int fr = 0, fpos = 0, fstart = run_start(0), flen = run_len(0);
-  unsigned f_row0 = 0, f_lim = 0;
-  auto fetch_cursor = [&]() {      // first row and last valid row offset of the block, then advance
-    f_row0 = (unsigned)(fstart + fpos);
-    f_lim = (unsigned)(flen - 1 - fpos);
-    if (fpos + KB < flen) {
-      fpos += KB;
-    } else if (fr + 1 < w.n_runs) {
-      ++fr;
-      fpos = 0;
-      fstart = run_start(fr);
-      flen = run_len(fr);
-    }
-  };
-  auto row_off = [&](int i) {      // element offset of this thread's chunk in staging row i
-    return __umul24(f_row0 + min((unsigned)(ld_row + STG_STEP * i), f_lim), row_stride) + (unsigned)ld_col;
+  const int ld_q = lane >> 4, ld_chunk = (lane & 15) ^ (KB == 32 && (ld_q & 2) ? 8 : 0);
+  const unsigned ld_col = 8 * ld_chunk;
+  const int lane_key = wave + NWV * (lane & 1) + NG * ld_q;      // key of this lane's row, group wave + NWV (lane & 1), in block 0
+  const unsigned lane_row = (unsigned)lane_key * row_stride, last_row = (unsigned)(n_keys - 1) * row_stride, block_rows = KB * row_stride;
+  auto row_of_block = [&](int b) -> unsigned {  // element offset of this lane's row of block b
+    if constexpr (WIN) return __umul24(keys.token(lane_key + KB * b), row_stride);
+    return min(lane_row + (unsigned)b * block_rows, last_row);
   };
   // K / V rows come through buffer loads: a scalar resource descriptor per tensor (raw buffer, no
   // range check: offsets are in bounds by construction) plus one 32-bit byte offset per lane.
@@ -306,83 +296,37 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
   };
   // group wave + NWV h of K / V block b (h = 0, 1: this lane's first and second staging row)
   auto dma_k = [&](int h, int b, unsigned off) { dma16(rs_k, lds0 + 2u * (unsigned)((b & 3) * K_STAGE + (wave_u + NWV * h) * KG), off); };
-  auto dma_v = [&](int h, int b, unsigned off) { dma16(rs_v, lds0 + 2u * (unsigned)(V_BASE + vstage(b) * V_STAGE + (wave_u + NWV * h) * VG), off); };
-  // WIN: token indices of this thread's two staging rows of the NEXT block whose rows will be
-  // loaded (gi0, gi1), looked up one block ahead of the rows; win_at / win_idx produce them for
-  // the block under the fetch cursor (uniform parameters first, then the per-lane lookup).
-  int gi0 = 0, gi1 = 0;
-  int wi_run = 0, wi_pos = 0, wi_start = 0, wi_len = 1;
-  auto win_at = [&]() {            // note the block under the cursor, advance the cursor (scalar work only)
-    wi_run = fr;
-    wi_pos = fpos;
-    wi_start = fstart;
-    wi_len = flen;
-    fpos += KB;
-    while (fpos >= flen && fr + 1 < w.n_runs) {
-      fpos -= flen;
-      ++fr;
-      fstart = run_start(fr);
-      flen = run_len(fr);
-    }
-  };
+  auto dma_v = [&](int h, int stage, unsigned off) { dma16(rs_v, lds0 + 2u * (unsigned)(V_BASE + stage + (wave_u + NWV * h) * VG), off); };
+  // WIN_COPIES: the row of this lane's token of the NEXT block whose rows will be loaded, looked up one block ahead.
   // The lookups are loads the compiler does not see either (it would wait for them with
   // vmcnt(0), which also drains the row loads requested after them): they are requested BEFORE
   // the row loads of their iteration, so that win_wait -- everything but the last four vector
-  // memory operations complete -- returns as soon as the indices are there, whatever the row
-  // loads behind them are doing (the counter retires in order).
-  auto win_idx = [&]() {           // token indices of the noted block
-    int key[2] = {ld_row, ld_row + STG_STEP}, rows[2];
-    block_rows(rl, wi_run, wi_pos, wi_start, wi_len, KB, key, rows);
-    asm volatile("global_load_dword %0, %2, %4\n\tglobal_load_dword %1, %3, %4"
-                 : "=&v"(gi0), "=&v"(gi1)
-                 : "v"(rows[0] * 4), "v"(rows[1] * 4), "s"(a.tok_of)
-                 : "memory");
+  // memory operations complete -- returns as soon as the index is there, whatever the row
+  // loads behind it are doing (the counter retires in order).
+  int gi = 0;
+  auto win_idx = [&](int b) {
+    asm volatile("global_load_dword %0, %1, %2" : "=&v"(gi) : "v"(keys.token(lane_key + KB * b) * 4u), "s"(a.row_of) : "memory");
   };
-  auto win_wait = [&](bool rows_behind) {   // indices usable; rows_behind: four row loads were requested after them
-    if (rows_behind) asm volatile("s_waitcnt vmcnt(4)" : "+v"(gi0), "+v"(gi1)::"memory");
-    else asm volatile("s_waitcnt vmcnt(0)" : "+v"(gi0), "+v"(gi1)::"memory");
+  auto win_wait = [&](bool rows_behind) {   // index usable; rows_behind: four row loads were requested after it
+    if (rows_behind) asm volatile("s_waitcnt vmcnt(4)" : "+v"(gi)::"memory");
+    else asm volatile("s_waitcnt vmcnt(0)" : "+v"(gi)::"memory");
   };
-  auto win_off = [&](int gi) { return __umul24((unsigned)gi, row_stride) + (unsigned)ld_col; };
-  auto fetch_all = [&](int b, bool first = false) {   // rows of the block under the cursor, block b, into its ring stages
-    unsigned o0_, o1_;
-    if constexpr (WIN) {
+  int v_load = 0, v_prev = 0, v_cur = 0;              // V stages of the block to request, of blocks i - 1 and i
+  auto fetch_all = [&](int b, bool first = false) {   // rows of block b into its ring stages
+    unsigned row;
+    if constexpr (COPIES) {
       win_wait(!first);
-      o0_ = win_off(gi0);
-      o1_ = win_off(gi1);
-      win_at();
-      win_idx();                   // indices of the block after it
+      row = __umul24((unsigned)gi, row_stride);
+      win_idx(b + 1);              // of the block after it
     } else {
-      fetch_cursor();
-      o0_ = row_off(0);
-      o1_ = row_off(1);
+      row = row_of_block(b);
     }
-    dma_k(0, b, o0_); dma_v(0, b, o0_);
-    dma_k(1, b, o1_); dma_v(1, b, o1_);
+    const unsigned o0_ = row_bcast(row, 0) + ld_col, o1_ = row_bcast(row, 1) + ld_col;
+    dma_k(0, b, o0_); dma_v(0, v_load, o0_);
+    dma_k(1, b, o1_); dma_v(1, v_load, o1_);
+    v_load = after(v_load);
   };
-  // valid keys of the blocks in compute order
-  int cr = 0, cpos = 0, clen = flen, cblk = 0;
-  auto next_valid = [&]() {      // 0 past the last block: a block of masked keys adds nothing
-    if constexpr (WIN) {
-      const int nv = min(KB, max(0, n_keys - KB * cblk));
-      ++cblk;
-      return nv;
-    }
-    const int nv = cblk < n_blocks ? min(KB, clen - cpos) : 0;
-    ++cblk;
-    if (cpos + KB < clen) {
-      cpos += KB;
-    } else if (cr + 1 < w.n_runs) {
-      ++cr;
-      cpos = 0;
-      clen = run_len(cr);
-    }
-    return nv;
-  };
-
-  if constexpr (WIN) {             // prime the index pipeline with block 0
-    win_at();
-    win_idx();
-  }
+  if constexpr (COPIES) win_idx(0);  // prime the index pipeline with block 0
   fetch_all(0, true);              // blocks 0, 1 and 2 into their stages; iteration i requests block i+3
   fetch_all(1);
   fetch_all(2);
@@ -391,15 +335,16 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
 
   // Fragment addresses of the lane in stage 0 (elements), and what to add for further fragments.
   // 64-key blocks: row r sits in group r % 16 at (r / 16) * 256 B, chunks in order.
-  // 32-key blocks: row r sits in group r % 8, half h of it at 512 h + 128 (r / 8) B.
+  // 32-key blocks: row r sits in group r % 8 at (r / 8) * 256 B, its halves exchanged where r / 8 >= 2.
   const int t16 = lane & 15, blk = lane >> 4;
   const lds_ptr k_rd = KB == 64 ? (lds_ptr)(smem + (l32 & 15) * KG + (l32 >> 4) * 128 + 8 * g)
-                                : (lds_ptr)(smem + (l32 & 7) * KG + (l32 >> 3) * 64 + 8 * g);
+                                : (lds_ptr)(smem + (l32 & 7) * KG + (l32 >> 3) * 128 + 8 * g + (l32 & 16 ? 64 : 0));
+  const lds_ptr k_rd2 = KB == 64 ? k_rd + 64 : (lds_ptr)(smem + (l32 & 7) * KG + (l32 >> 3) * 128 + 8 * g + (l32 & 16 ? 0 : 64));
   const lds_ptr v_rd = (lds_ptr)(smem + V_BASE + (4 * g + (t16 >> 2)) * VG + 16 * (blk & 1) + 4 * (t16 & 3));
   constexpr int K_T2 = 256;                                  // 64-key blocks: second 32-key tile
-  auto k_slice = [](int ks) { return KB == 64 ? 16 * ks : 16 * (ks & 3) + 256 * (ks >> 2); };   // head-dim columns 16 ks ..
-  auto v_cols = [](int cb) { return KB == 64 ? 32 * cb : 32 * (cb & 1) + 256 * (cb >> 1); };     // head-dim columns 32 cb ..
-  constexpr int V_R16 = 128, V_R8 = KB == 64 ? 8 * VG : 64;  // 16 and 8 rows further
+  // V: the 16 rows of slice n >> 2 are rows q (64-key blocks; and 8 groups on) or 2 q and 2 q + 1 of their groups
+  constexpr int V_SLICE = KB == 64 ? 128 : 256, V_R8 = KB == 64 ? 8 * VG : 128;
+  auto v_cols = [](int n) { return 32 * ((n & 3) ^ (KB == 32 && n >= 4 ? 2 : 0)); };     // head-dim columns 32 (n & 3) ..
 
   f32x16 o[4], sa0, sa1, sb0, sb1;
 #pragma unroll
@@ -426,19 +371,17 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
   // scores of block 0
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) {
-    sa0 = MFMA(lds_frag3(k_rd + k_slice(ks)), qf[ks], sa0);
-    if constexpr (KB == 64) sa1 = MFMA(lds_frag3(k_rd + K_T2 + k_slice(ks)), qf[ks], sa1);
+    const lds_ptr kq = (ks < 4 ? k_rd : k_rd2) + 16 * (ks & 3);      // head-dim columns 16 ks ..
+    sa0 = MFMA(lds_frag3(kq), qf[ks], sa0);
+    if constexpr (KB == 64) sa1 = MFMA(lds_frag3(kq + K_T2), qf[ks], sa1);
   }
-  {
-    const int nv = next_valid();
-    if (nv < KB) mask_tail(sa0, sa1, nv);
-  }
+  if (n_keys < KB) mask_tail(sa0, sa1, n_keys);
 
 #define SLOT_FENCE() __builtin_amdgcn_sched_barrier(0)
   // first V^T fragments of the coming iteration, requested before the barrier of this one
   bf16x8 vpre[LEAD];
   auto v_frag = [&](lds_ptr vq, int n) {
-    const lds_ptr ap = vq + V_R16 * (n >> 2) + v_cols(n & 3);
+    const lds_ptr ap = vq + V_SLICE * (n >> 2) + v_cols(n);
     return read_vt3(ap, ap + V_R8);
   };
 #pragma unroll
@@ -446,21 +389,23 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
   // One iteration.  sc*: scores of block i (in), sn*: scores of block i+1 (out),
   // pp: P^T(i-1) (in), pc: P^T(i) (out).
   auto body = [&](int i, f32x16& sc0, f32x16& sc1, f32x16& sn0, f32x16& sn1, bf16x8 (&pp)[NKS], bf16x8 (&pc)[NKS]) {
-    const lds_ptr vq = opaque(v_rd + vstage(i ? i - 1 : 0) * V_STAGE);
+    const lds_ptr vq = opaque(v_rd + v_prev);        // iteration 0 multiplies V(0) by P = 0
     const lds_ptr kq = opaque(k_rd + ((i + 1) & 3) * K_STAGE);
-    if constexpr (WIN) win_at();                     // block i+4: its token indices are looked up in slot 27
-    else fetch_cursor();                             // block i+3 (scalar work and branches: before the slots)
+    const lds_ptr kq2 = KB == 64 ? kq + 64 : opaque(k_rd2 + ((i + 1) & 3) * K_STAGE);
     bf16x8 vf[NPV], kf[NS - NPV];
     auto v_req = [&](int n) { vf[n] = v_frag(vq, n); };
-    auto k_req = [&](int n) { kf[n] = lds_frag3(KB == 64 ? kq + K_T2 * (n & 1) + k_slice(n >> 1) : kq + k_slice(n)); };
-    const lds_ptr vq_next = opaque(v_rd + vstage(i) * V_STAGE);     // V(i): second product of iteration i+1
+    auto k_req = [&](int n) {
+      const int ks = KB == 64 ? n >> 1 : n;
+      kf[n] = lds_frag3((ks < 4 ? kq : kq2) + 16 * (ks & 3) + (KB == 64 ? K_T2 * (n & 1) : 0));
+    };
+    const lds_ptr vq_next = opaque(v_rd + v_cur);    // V(i): second product of iteration i+1
 #pragma unroll
     for (int n = 0; n < LEAD; ++n) vf[n] = vpre[n];
     float ps0 = 0.f, ps1 = 0.f;
     float x[NE], ex[NE];
     unsigned u[2][8];                  // pair p of the block is u[p >> 3][p & 7]
     const float mc = m_ref * c;
-    unsigned off0 = 0, off1 = 0;
+    unsigned row = 0, off0 = 0, off1 = 0;
 #pragma unroll
     for (int n = 0; n < NS; ++n) {
       SLOT_FENCE();
@@ -511,24 +456,34 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
         if (n & 1) ps1 += ex[n - 2];
         else ps0 += ex[n - 2];
       }
-      // ---- staging: the rows of block i+3 are requested -- addresses in slot SO, the four loads
+      // ---- staging: the rows of block i+3 are requested -- addresses in slots SO and SO + 1, the four loads
       // from slot SL + 1 on, SP slots apart (32 slots: spread over the iteration; 16 slots: in
-      // a row) -- and (WIN) the token indices of block i+4 looked up in slot SI, right after the
-      // addresses, which were the last use of the indices they replace, and ahead of the row
+      // a row) -- and (WIN_COPIES) the rows of the tokens of block i+4 looked up in slot SI, right after the
+      // address that was the last use of the index they replace, and ahead of the row
       // loads, so that waiting for them a whole iteration later does not wait for those.
       constexpr int SL = NS == 32 ? 8 : 9, SP = NS == 32 ? 4 : 1;
-      constexpr int SO = WIN ? 1 : SL, SI = 2;
+      constexpr int SO = COPIES ? 1 : SL - 2, SI = 2;
       if (n == SO) {
-        if constexpr (WIN) win_wait(true);
-        off0 = WIN ? win_off(gi0) : row_off(0);
-        off1 = WIN ? win_off(gi1) : row_off(1);
+        if constexpr (COPIES) {
+          win_wait(true);
+          row = __umul24((unsigned)gi, row_stride);
+        } else {
+          row = row_of_block(i + 3);
+        }
       }
-      if (WIN && n == SI) win_idx();
+      if (COPIES && n == SI) win_idx(i + 4);
+      if (n == SL) {
+        off0 = row_bcast(row, 0) + ld_col;
+        off1 = row_bcast(row, 1) + ld_col;
+      }
       if (n == SL + 1) dma_k(0, i + 3, off0);
-      if (n == SL + 1 + SP) dma_v(0, i + 3, off0);
+      if (n == SL + 1 + SP) dma_v(0, v_load, off0);
       if (n == SL + 1 + 2 * SP) dma_k(1, i + 3, off1);
-      if (n == SL + 1 + 3 * SP) dma_v(1, i + 3, off1);
+      if (n == SL + 1 + 3 * SP) dma_v(1, v_load, off1);
     }
+    v_load = after(v_load);
+    v_prev = v_cur;
+    v_cur = after(v_cur);
     SLOT_FENCE();
     constexpr int LP = NP - 1;         // last pair: packed here, its two elements summed
     u[LP >> 3][LP & 7] = pack_bf16(ex[NE - 2], ex[NE - 1]);
@@ -536,9 +491,9 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
     ps1 += ex[NE - 1];
     float ps = ps0 + ps1;
     asm volatile("" : "+v"(u[LP >> 3][LP & 7]), "+v"(ps));
-    // all but this iteration's memory operations (four row loads, WIN: and two index lookups) are
+    // all but this iteration's memory operations (four row loads, WIN_COPIES: and an index lookup) are
     // complete: the rows requested in the previous iteration are in LDS
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(WIN ? 6 : 4) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES ? 5 : 4) : "memory");
     __syncthreads();
     // ---- reference check.  No probability exceeds its row sum, so ps <= P_MAX proves that no
     // score of the block was more than log2(P_MAX) above the reference.  Otherwise (always for
@@ -584,8 +539,7 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
       if constexpr (KB == 64)
         pc[2 + h] = __builtin_bit_cast(bf16x8, make_uint4(u[1][4 * h], u[1][4 * h + 1], u[1][4 * h + 2], u[1][4 * h + 3]));
     }
-    const int nv = next_valid();
-    if (nv < KB) mask_tail(sn0, sn1, nv);
+    if (n_keys < KB * (i + 2)) mask_tail(sn0, sn1, n_keys - KB * (i + 1));    // none of a block past the last
   };
   // An even number of iterations, so the two register sets swap back; when the block count
   // is odd the last iteration works on a block of masked keys (probabilities 0) and only its
@@ -601,13 +555,13 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
     // keeps its share of the staging going, with the same barriers as the others
     for (int i = 0; i < ((n_blocks + 1) & ~1); ++i) {
       fetch_all(i + 3);
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(WIN ? 6 : 4) : "memory");
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES ? 5 : 4) : "memory");
       __syncthreads();
     }
   }
-  // The last lookups are still on their way into gi0 and gi1, which nothing reads any more: without this wait
-  // their registers would be free for the fragments below while the loads can still write them.
-  if constexpr (WIN) {
+  // The last lookup is still on its way into gi, which nothing reads any more: without this wait
+  // its register would be free for the fragments below while the load can still write it.
+  if constexpr (COPIES) {
     win_wait(true);
     SLOT_FENCE();
   }
@@ -615,8 +569,7 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
 
   // ---- second product of the last iteration's block (its probabilities are in pa)
   {
-    const int last = ((n_blocks + 1) & ~1) - 1;
-    const lds_ptr vq = opaque(v_rd + vstage(last) * V_STAGE);
+    const lds_ptr vq = opaque(v_rd + v_prev);
 #pragma unroll
     for (int n = 0; n < NPV; ++n)
       o[n & 3] = MFMA(n < LEAD ? vpre[n] : v_frag(vq, n), pa[n >> 2], o[n & 3]);
@@ -663,19 +616,20 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
   }
 }
 
-template <bool WIN, int NWV, bool MIX = false>
+template <int SRC, int NWV, bool MIX = false>
 __global__ __launch_bounds__(64 * NWV, 8 / NWV) void attn_bf16_pipe_kernel(const AttnArgs a,
                                                                             const std::conditional_t<MIX, MixArgs, NoMix> mx) {
-  pipe_item<WIN, NWV, MIX>(a, mx, xcd_item(blockIdx.x, gridDim.x, WIN));
+  pipe_item<SRC, NWV, MIX>(a, mx, xcd_item(blockIdx.x, gridDim.x, SRC != LONG_KEYS));
 }
 
 // Long items and window items of more than 128 rows in one launch.  The last long items of a launch end
 // hundreds of microseconds apart (a core-set item of 591 blocks takes 0.9 ms); the window items, a tenth as
 // long, fill the CUs that have none left instead of waiting for the launch to drain.  (Two argument blocks:
 // one that both branches took would be copied to private memory.)
+template <int SRC>
 __global__ __launch_bounds__(512, 1) void attn_bf16_layer_kernel(const AttnArgs a, const AttnArgs win, int n_long) {
-  if ((int)blockIdx.x < n_long) pipe_item<false, 8, false>(a, NoMix(), blockIdx.x);
-  else pipe_item<true, 8, false>(win, NoMix(), xcd_item(blockIdx.x - n_long, gridDim.x - n_long, true));
+  if ((int)blockIdx.x < n_long) pipe_item<LONG_KEYS, 8, false>(a, NoMix(), blockIdx.x);
+  else pipe_item<SRC, 8, false>(win, NoMix(), xcd_item(blockIdx.x - n_long, gridDim.x - n_long, true));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -689,8 +643,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_layer_kernel(const AttnArgs 
 //   * rings of two stages (KS = 4: K 65 KB, V 68 KB) and two barriers per iteration: K(i+2) is requested
 //     where iteration i begins, into the stage K(i) has left, V(i+1) in its middle, into the stage that
 //     V(i-1) has just left, and each is waited for one and a half iterations later, where its first reader is.
-//   * one launch carries all items of the layer, longest first: the key stream exists twice, for window items
-//     (rows through the index table) and for the others (consecutive rows).
+//   * one launch carries all items of the layer, longest first: the key stream exists once for each source of keys.
 // Bound: the barriers.  The wavefronts of a workgroup reach its two barriers together, and what they do
 // around them (fragment requests, reference check, packing) no matrix instruction covers: about 2,000
 // cycles per 128-key superblock against 1,024 of matrix instructions (2,600 with one barrier, all loads
@@ -724,7 +677,6 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
   const bool unpool = !MIX && w.seg == 1 && a.keep_idx;          // core-set rows straight to their tokens
   uint16_t* O = unpool ? (uint16_t*)a.o0 + a.core_heads[w.head] * a.head_stride0
                        : (uint16_t*)(user ? a.o0 : w.seg == 1 ? a.oc : a.ot) + w.o_off;
-  const int* tok = a.tok_of;                       // of items with a run list (the identity over tile-ordered copies)
   const unsigned row_stride = (unsigned)w.row_stride;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -740,18 +692,21 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
     for (int ks = 0; ks < 8; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qp + 16 * ks));
   }
 
-  const RunList rl(w);
-  int n_keys = 0;
-  for (int r = 0; r < w.n_runs; ++r) n_keys += rl.len(r);
+  const int* row_of = a.row_of;
+  WindowKeys keys(w);
+  keys.keep();
+  const int n_keys = w.listed ? keys.n_keys : w.single_len;
   const int n_sb = (n_keys + SB - 1) / SB;
 
   // ---- staging: a stage is 8 KS groups, wavefront j loads groups j + NWV h (h = 0..3) of K and of V; lane p of a
-  // load fills bytes 16 p .. 16 p + 15 of the group (group layout: see the pipelined kernel, 32-key blocks)
-  const int ld_q = (lane >> 3) & 3, ld_col = 8 * (8 * (lane >> 5) + (lane & 7));
-  auto group_key = [&](int h) {                    // this lane's key of the superblock in group j + NWV h
-    const int group = wave + NWV * h;
-    return 32 * (group >> 3) + (group & 7) + 8 * ld_q;
-  };
+  // load fills bytes 16 p .. 16 p + 15 of the group (group layout and offsets: see the pipelined kernel, 32-key blocks)
+  const int ld_q = lane >> 4;
+  const unsigned ld_col = 8 * (unsigned)((lane & 15) ^ (ld_q & 2 ? 8 : 0));
+  int lane_key;                                    // key of this lane's row, group j + NWV (lane & 3), in superblock 0
+  {
+    const int group = wave + NWV * (lane & 3);
+    lane_key = 32 * (group >> 3) + (group & 7) + 8 * ld_q;
+  }
   const unsigned long long k_pa = (unsigned long long)K, v_pa = (unsigned long long)V;
   const i32x4 rs_k = {__builtin_amdgcn_readfirstlane((int)(unsigned)k_pa), __builtin_amdgcn_readfirstlane((int)((unsigned)(k_pa >> 32) & 0xffffu)), -1, 0x00020000};
   const i32x4 rs_v = {__builtin_amdgcn_readfirstlane((int)(unsigned)v_pa), __builtin_amdgcn_readfirstlane((int)((unsigned)(v_pa >> 32) & 0xffffu)), -1, 0x00020000};
@@ -761,48 +716,20 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
   };
   auto dma_k = [&](int sb, int h, unsigned off) { dma16(rs_k, lds0 + 2u * (unsigned)((sb & 1) * SPLIT_K + (wave + NWV * h) * KG), off); };
   auto dma_v = [&](int sb, int h, unsigned off) { dma16(rs_v, lds0 + 2u * (unsigned)(2 * SPLIT_K + (sb & 1) * SPLIT_V + (wave + NWV * h) * VG), off); };
-  // Index lookups of the superblock under the fetch cursor, which then moves on; past the end of the last run
-  // they repeat its last row.  The loads are invisible to the compiler (see the pipelined kernel): what they
-  // write is not touched until a wait has named it.
-  int fr = 0, fpos = 0, fstart = rl.start(0), flen = rl.len(0);
-  int at_run = 0, at_pos = 0, at_start = 0, at_len = 1;
-  auto note = [&]() {                              // the superblock to look up; scalar work only
-    at_run = fr;
-    at_pos = fpos;
-    at_start = fstart;
-    at_len = flen;
-    fpos += SB;
-    while (fpos >= flen && fr + 1 < w.n_runs) {
-      fpos -= flen;
-      ++fr;
-      fstart = rl.start(fr);
-      flen = rl.len(fr);
-    }
-  };
-  auto lookup = [&](int (&gi)[4]) {
-    int key[4], rows[4];
+  // Offsets of the rows that a wavefront's loads of a superblock fetch, from the row of each lane
+  auto offsets = [&](unsigned row, unsigned (&off)[4]) {
 #pragma unroll
-    for (int h = 0; h < 4; ++h) key[h] = group_key(h);
-    block_rows(rl, at_run, at_pos, at_start, at_len, SB, key, rows);
-    asm volatile("global_load_dword %0, %4, %8\n\tglobal_load_dword %1, %5, %8\n\t"
-                 "global_load_dword %2, %6, %8\n\tglobal_load_dword %3, %7, %8"
-                 : "=&v"(gi[0]), "=&v"(gi[1]), "=&v"(gi[2]), "=&v"(gi[3])
-                 : "v"(rows[0] * 4), "v"(rows[1] * 4), "v"(rows[2] * 4), "v"(rows[3] * 4), "s"(tok)
-                 : "memory");
-  };
-  auto named = [&](int (&gi)[4]) { asm volatile("" : "+v"(gi[0]), "+v"(gi[1]), "+v"(gi[2]), "+v"(gi[3])); };
-  auto offsets = [&](const int (&gi)[4], unsigned (&off)[4]) {
-#pragma unroll
-    for (int h = 0; h < 4; ++h) off[h] = __umul24((unsigned)gi[h], row_stride) + (unsigned)ld_col;
+    for (int h = 0; h < 4; ++h) off[h] = row_bcast(row, h) + ld_col;
   };
   // fragment addresses of the lane in stage 0 of its wavefront's block
   const int t16 = lane & 15, blk = lane >> 4;
-  const lds_ptr k_rd = (lds_ptr)(smem + (8 * kg + (l32 & 7)) * KG + (l32 >> 3) * 64 + 8 * g);
+  const lds_ptr k_rd = (lds_ptr)(smem + (8 * kg + (l32 & 7)) * KG + (l32 >> 3) * 128 + 8 * g + (l32 & 16 ? 64 : 0));
+  const lds_ptr k_rd2 = (lds_ptr)(smem + (8 * kg + (l32 & 7)) * KG + (l32 >> 3) * 128 + 8 * g + (l32 & 16 ? 0 : 64));
   const lds_ptr v_rd = (lds_ptr)(smem + 2 * SPLIT_K + (8 * kg + 4 * g + (t16 >> 2)) * VG + 16 * (blk & 1) + 4 * (t16 & 3));
-  auto k_frag = [&](lds_ptr kq, int ks) { return lds_frag3(kq + 16 * (ks & 3) + 256 * (ks >> 2)); };
+  auto k_frag = [&](lds_ptr kq, lds_ptr kq2, int ks) { return lds_frag3((ks < 4 ? kq : kq2) + 16 * (ks & 3)); };
   auto v_frag = [&](lds_ptr vq, int n) {
-    const lds_ptr ap = vq + 128 * (n >> 2) + 32 * (n & 1) + 256 * ((n & 3) >> 1);
-    return read_vt3(ap, ap + 64);
+    const lds_ptr ap = vq + 256 * (n >> 2) + 32 * ((n & 3) ^ (n >= 4 ? 2 : 0));
+    return read_vt3(ap, ap + 128);
   };
 
   f32x16 o[4], sa, sb;
@@ -822,38 +749,38 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
       if (8 * (v >> 2) + (v & 3) >= nv - 4 * g) t[v] = -INFINITY;
   };
 
-  // The whole key stream.  TABLE: rows through the index table (window items); otherwise the item's keys are
-  // consecutive rows from row 0 and their offsets arithmetic, a tenth of the iteration's instructions less.
-  auto stream = [&](auto table) {
-    constexpr bool TABLE = decltype(table)::value;
-    int gi[4] = {0, 0, 0, 0};                        // indices of superblock i + 2 as iteration i begins
+  // WIN_COPIES: the row of this lane's token of a superblock is looked up; the lookups are invisible to the compiler (see
+  // the pipelined kernel): what they write is not touched until a wait has named it.
+  auto lookup = [&](int sb, int& to) {
+    asm volatile("global_load_dword %0, %1, %2" : "=&v"(to) : "v"(keys.token(lane_key + SB * sb) * 4u), "s"(row_of) : "memory");
+  };
+  // The whole key stream, once for each source of keys.
+  auto stream = [&](auto source) {
+    constexpr int SRC = decltype(source)::value;
+    constexpr bool COPIES = SRC == WIN_COPIES;
+    constexpr int T = COPIES ? 1 : 0;                // lookups of an iteration
+    const unsigned lane_row = (unsigned)lane_key * row_stride, last_row = (unsigned)(n_keys - 1) * row_stride;
+    int gi = 0;                                      // row of this lane's token of superblock i + 2 as iteration i begins
+    auto row_of_sb = [&](int sb) -> unsigned {       // element offset of this lane's row
+      if constexpr (COPIES) return __umul24((unsigned)gi, row_stride);
+      if constexpr (SRC == WIN_TOKENS) return __umul24(keys.token(lane_key + SB * sb), row_stride);
+      return min(lane_row + (unsigned)sb * (SB * row_stride), last_row);
+    };
     unsigned off1[4], off2[4];                       // row offsets of superblocks i + 1 and i + 2
-    unsigned off_key[4], off_last = 0;               // without table: of superblock 0, and the last row's
-    if constexpr (TABLE) {
-      int g0[4], g1[4];
-      note();
-      lookup(g0);
-      note();
-      lookup(g1);
-      note();
-      lookup(gi);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      named(g0);
-      named(g1);
-      named(gi);
+    if constexpr (COPIES) {
+      int g0, g1;
+      lookup(0, g0);
+      lookup(1, g1);
+      lookup(2, gi);
+      asm volatile("s_waitcnt vmcnt(0)" : "+v"(g0), "+v"(g1), "+v"(gi)::"memory");
       // the query rows are here too: let the compiler wait for them now, not behind the row loads
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qf[ks]));
-      offsets(g0, off2);
-      offsets(g1, off1);
+      offsets(__umul24((unsigned)g0, row_stride), off2);
+      offsets(__umul24((unsigned)g1, row_stride), off1);
     } else {
-      off_last = (unsigned)(n_keys - 1) * row_stride + (unsigned)ld_col;
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        off_key[h] = (unsigned)group_key(h) * row_stride + (unsigned)ld_col;
-        off2[h] = min(off_key[h], off_last);
-        off1[h] = min(off_key[h] + SB * row_stride, off_last);
-      }
+      offsets(row_of_sb(0), off2);
+      offsets(row_of_sb(1), off1);
     }
 #pragma unroll
     for (int h = 0; h < 4; ++h) dma_k(0, h, off2[h]);
@@ -865,7 +792,7 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
     __syncthreads();
 
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) sa = MFMA(k_frag(k_rd, ks), qf[ks], sa);
+    for (int ks = 0; ks < 8; ++ks) sa = MFMA(k_frag(k_rd, k_rd2, ks), qf[ks], sa);
     mask_tail(sa, 0);
     __syncthreads();                                 // K(0) is read: the first iteration requests K(2) into its stage
 
@@ -876,13 +803,12 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
       constexpr bool FIRST = decltype(first)::value;
       constexpr int AHEAD = 4;                       // fragments requested ahead of their use
       const lds_ptr vq = opaque(v_rd + ((i + 1) & 1) * SPLIT_V);     // V(i-1)
-      const lds_ptr kq = opaque(k_rd + ((i + 1) & 1) * SPLIT_K);     // K(i+1)
+      const lds_ptr kq = opaque(k_rd + ((i + 1) & 1) * SPLIT_K), kq2 = opaque(k_rd2 + ((i + 1) & 1) * SPLIT_K);     // K(i+1)
       bf16x8 vf[NPV], kf[NS - NPV];
       if (!FIRST) {
 #pragma unroll
         for (int n = 0; n < AHEAD; ++n) vf[n] = v_frag(vq, n);
       }
-      if constexpr (TABLE) note();                   // superblock i+3
       float ps0 = 0.f, ps1 = 0.f;
       float x[NE], ex[NE];
       unsigned u[8];
@@ -891,11 +817,11 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
       for (int n = 0; n < NS; ++n) {
         SLOT_FENCE();
         if (n == NPV) {
-          // K(i+1) was requested one and a half iterations ago; behind it are V(i), the lookups and K(i+2)
-          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TABLE ? 12 : 8) : "memory");
+          // K(i+1) was requested one and a half iterations ago; behind it are V(i), the lookup and K(i+2)
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 + T) : "memory");
           __syncthreads();
 #pragma unroll
-          for (int m = 0; m < AHEAD; ++m) kf[m] = k_frag(kq, m);
+          for (int m = 0; m < AHEAD; ++m) kf[m] = k_frag(kq, kq2, m);
 #pragma unroll
           for (int v = 0; v < 16; ++v) sn[v] = 0.f;
         }
@@ -904,20 +830,14 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
           if (!FIRST && n + AHEAD < NPV) vf[n + AHEAD] = v_frag(vq, n + AHEAD);
         } else {
           sn = MFMA(kf[n - NPV], qf[n - NPV], sn);
-          if (n + AHEAD < NS) kf[n + AHEAD - NPV] = k_frag(kq, n + AHEAD - NPV);
+          if (n + AHEAD < NS) kf[n + AHEAD - NPV] = k_frag(kq, kq2, n + AHEAD - NPV);
         }
-        // staging: the lookups go ahead of the row loads, as the counts of the waits assume
+        // staging: the lookup goes ahead of the row loads, as the counts of the waits assume
         if (n == 0) {
-          if constexpr (TABLE) {
-            named(gi);
-            offsets(gi, off2);
-          } else {
-            const unsigned base = (unsigned)(i + 2) * (SB * row_stride);
-#pragma unroll
-            for (int h = 0; h < 4; ++h) off2[h] = min(off_key[h] + base, off_last);
-          }
+          if constexpr (COPIES) asm volatile("" : "+v"(gi));
+          offsets(row_of_sb(i + 2), off2);
         }
-        if (TABLE && n == 1) lookup(gi);             // superblock i+3
+        if (COPIES && n == 1) lookup(i + 3, gi);
         if (n >= 2 && n < 6) dma_k(i + 2, n - 2, off2[n - 2]);
         if (n > NPV && n <= NPV + 4) {
           dma_v(i + 1, n - NPV - 1, off1[n - NPV - 1]);
@@ -970,8 +890,8 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
       pc[0] = __builtin_bit_cast(bf16x8, make_uint4(u[0], u[1], u[2], u[3]));
       pc[1] = __builtin_bit_cast(bf16x8, make_uint4(u[4], u[5], u[6], u[7]));
       mask_tail(sn, i + 1);
-      // V(i) and the indices of i+3 are here; K(i+2) and V(i+1) may still be on their way
-      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      // V(i) and the lookup of i+3 are here; K(i+2) and V(i+1) may still be on their way
+      asm volatile("s_waitcnt vmcnt(8)" : "+v"(gi)::"memory");
       __syncthreads();
     };
     // The two register sets alternate, so the loop takes superblocks in pairs and the odd one out of those after
@@ -992,8 +912,9 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
     }
 #undef SLOT_FENCE
   };
-  if (w.runs) stream(std::integral_constant<bool, true>());
-  else stream(std::integral_constant<bool, false>());
+  if (!w.listed) stream(std::integral_constant<int, LONG_KEYS>());
+  else if (a.win_gather) stream(std::integral_constant<int, WIN_TOKENS>());
+  else stream(std::integral_constant<int, WIN_COPIES>());
   {                                                // second product of the last superblock
     const lds_ptr vq = opaque(v_rd + ((n_sb - 1) & 1) * SPLIT_V);
 #pragma unroll
@@ -1107,11 +1028,14 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
   static int attr_rc = VORTA_OK;
   std::call_once(once, [] {
     const struct { const void* kernel; const char* name; int lds; } all[] = {
-        {(const void*)attn_bf16_pipe_kernel<false, 8>, "attn_bf16_pipe_kernel<false, 8>", pipe_lds_bytes(8)},
-        {(const void*)attn_bf16_pipe_kernel<false, 8, true>, "attn_bf16_pipe_kernel<false, 8, true>", pipe_lds_bytes(8)},
-        {(const void*)attn_bf16_pipe_kernel<true, 8>, "attn_bf16_pipe_kernel<true, 8>", pipe_lds_bytes(8)},
-        {(const void*)attn_bf16_pipe_kernel<true, 4>, "attn_bf16_pipe_kernel<true, 4>", pipe_lds_bytes(4)},
-        {(const void*)attn_bf16_layer_kernel, "attn_bf16_layer_kernel", pipe_lds_bytes(8)},
+        {(const void*)attn_bf16_pipe_kernel<LONG_KEYS, 8>, "attn_bf16_pipe_kernel<LONG_KEYS, 8>", pipe_lds_bytes(8)},
+        {(const void*)attn_bf16_pipe_kernel<LONG_KEYS, 8, true>, "attn_bf16_pipe_kernel<LONG_KEYS, 8, true>", pipe_lds_bytes(8)},
+        {(const void*)attn_bf16_pipe_kernel<WIN_TOKENS, 8>, "attn_bf16_pipe_kernel<WIN_TOKENS, 8>", pipe_lds_bytes(8)},
+        {(const void*)attn_bf16_pipe_kernel<WIN_COPIES, 8>, "attn_bf16_pipe_kernel<WIN_COPIES, 8>", pipe_lds_bytes(8)},
+        {(const void*)attn_bf16_pipe_kernel<WIN_TOKENS, 4>, "attn_bf16_pipe_kernel<WIN_TOKENS, 4>", pipe_lds_bytes(4)},
+        {(const void*)attn_bf16_pipe_kernel<WIN_COPIES, 4>, "attn_bf16_pipe_kernel<WIN_COPIES, 4>", pipe_lds_bytes(4)},
+        {(const void*)attn_bf16_layer_kernel<WIN_TOKENS>, "attn_bf16_layer_kernel<WIN_TOKENS>", pipe_lds_bytes(8)},
+        {(const void*)attn_bf16_layer_kernel<WIN_COPIES>, "attn_bf16_layer_kernel<WIN_COPIES>", pipe_lds_bytes(8)},
         {(const void*)attn_bf16_split_kernel<4, false>, "attn_bf16_split_kernel<4, false>", split_lds_bytes(4)},
         {(const void*)attn_bf16_split_kernel<4, true>, "attn_bf16_split_kernel<4, true>", split_lds_bytes(4)},
         {(const void*)attn_bf16_split_kernel<2, false>, "attn_bf16_split_kernel<2, false>", split_lds_bytes(2)},
@@ -1141,13 +1065,15 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
     if (int rc = fill_attn_args(p, rl, io, core, BM_LONG, win_text ? WIN_TEXT : WIN_NONE, &a)) return rc;
     if (int rc = fill_attn_args(p, win_rl, io, core, BM_LONG, WIN_TILES, &win, 0)) return rc;
     win.split_from = win.end_tile - form.half_big;
-    hipLaunchKernelGGL(attn_bf16_layer_kernel, dim3(a.end_tile + win.end_tile + form.half_big), dim3(512), pipe_lds_bytes(8), st, a, win, a.end_tile);
+    const dim3 grid(a.end_tile + win.end_tile + form.half_big);
+    if (a.win_gather) hipLaunchKernelGGL((attn_bf16_layer_kernel<WIN_TOKENS>), grid, dim3(512), pipe_lds_bytes(8), st, a, win, a.end_tile);
+    else hipLaunchKernelGGL((attn_bf16_layer_kernel<WIN_COPIES>), grid, dim3(512), pipe_lds_bytes(8), st, a, win, a.end_tile);
   } else if (form.n_long) {
     if (int rc = fill_attn_args(p, rl, io, core, BM_LONG, win_text ? WIN_TEXT : WIN_NONE, &a)) return rc;
     a.split_from = a.end_tile - form.half_long;
     const dim3 grid(a.end_tile + form.half_long);
-    if (mix) hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8, true>), grid, dim3(512), pipe_lds_bytes(8), st, a, *mix);
-    else hipLaunchKernelGGL((attn_bf16_pipe_kernel<false, 8>), grid, dim3(512), pipe_lds_bytes(8), st, a, NoMix());
+    if (mix) hipLaunchKernelGGL((attn_bf16_pipe_kernel<LONG_KEYS, 8, true>), grid, dim3(512), pipe_lds_bytes(8), st, a, *mix);
+    else hipLaunchKernelGGL((attn_bf16_pipe_kernel<LONG_KEYS, 8>), grid, dim3(512), pipe_lds_bytes(8), st, a, NoMix());
   }
   // Window tiles: in 64-row items, or the plan's items of more than 128 rows on the 8-wavefront instance (256 rows,
   // 64-key blocks, one workgroup per CU) and the rest on the 4-wavefront one (128 rows, 32-key blocks, two per CU),
@@ -1161,11 +1087,14 @@ int launch_attention_bf16(vorta_plan* p, const RouteLists& rl, const vorta_attn_
   if (form.n_big && !form.together && !form.win_128) {
     if (int rc = fill_attn_args(p, win_rl, io, core, BM_LONG, WIN_TILES, &a, 0)) return rc;
     a.split_from = a.end_tile - form.half_big;
-    hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 8>), dim3(a.end_tile + form.half_big), dim3(512), pipe_lds_bytes(8), st, a, NoMix());
+    const dim3 grid(a.end_tile + form.half_big);
+    if (a.win_gather) hipLaunchKernelGGL((attn_bf16_pipe_kernel<WIN_TOKENS, 8>), grid, dim3(512), pipe_lds_bytes(8), st, a, NoMix());
+    else hipLaunchKernelGGL((attn_bf16_pipe_kernel<WIN_COPIES, 8>), grid, dim3(512), pipe_lds_bytes(8), st, a, NoMix());
   }
   if (int rc = fill_attn_args(p, win_rl, io, core, BM, WIN_TILES, &a, form.win_128 ? 3 : 1)) return rc;
-  if (a.end_tile > 0)
-    hipLaunchKernelGGL((attn_bf16_pipe_kernel<true, 4>), dim3(a.end_tile), dim3(256), pipe_lds_bytes(4), st, a, NoMix());
+  if (a.end_tile == 0) return launched();
+  if (a.win_gather) hipLaunchKernelGGL((attn_bf16_pipe_kernel<WIN_TOKENS, 4>), dim3(a.end_tile), dim3(256), pipe_lds_bytes(4), st, a, NoMix());
+  else hipLaunchKernelGGL((attn_bf16_pipe_kernel<WIN_COPIES, 4>), dim3(a.end_tile), dim3(256), pipe_lds_bytes(4), st, a, NoMix());
   return launched();
 }
 

@@ -34,9 +34,9 @@ struct AttnArgs {
   const void *qt, *kt, *vt;
   void* ot;
   // route 1 without tile-ordered copies (qt == null, win_gather): rows of the caller's tensors are gathered
-  // through tok_of (tile-order index -> token index); win_heads = head id of each window slot.  With
-  // copies tok_of is the identity.
-  const int* tok_of;                // [N]
+  // through tok_of (tile-order index -> token index; fp32); win_heads = head id of each window slot.
+  // row_of is the inverse.
+  const int *tok_of, *row_of;       // [N]
   const int* tile_row0;             // [n_tiles + 1]: first tile-order row of each tile (edge tiles may be clipped)
   int win_gather;
   const int* runs;                  // [n_tiles][max_runs][2]
@@ -47,7 +47,7 @@ struct AttnArgs {
   // Route 1, bf16: window tiles whose key sets are identical (under the clamped centre rule the first
   // floor(w/2) + 1 tiles of every axis end, under the block rule all tiles of a block) are computed
   // together, their rows cut into blocks across tile borders -- one key stream serves them all.
-  // win_items[i] = {first, n_rows, tile, 0}, the win_count items of every window head; row r of an item
+  // win_items: WIN_ITEM_INTS numbers for each of the win_count items of every window head; row r of an item
   // lies at win_row[first + r] (token, or tile-order row of the copies).  Null (fp32): one item per
   // (tile, q-block), by arithmetic.
   const int* win_items;
@@ -87,6 +87,7 @@ struct WorkItem {
   int seg;                     // 0 dense, 1 core-set, 2 window
   int row0, n_rows;            // query rows row0 .. row0 + n_rows - 1; listed: places of win_row instead of rows
   bool listed;
+  const int* keys;             // listed: what its keys are computed from (WindowKeys)
   int n_runs;
   const int* runs;             // null: the single run {0, single_len}
   int single_len;
@@ -99,6 +100,7 @@ __device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int item) {
   w.n_runs = 1;
   w.head = 0;
   w.listed = false;
+  w.keys = nullptr;
   int half = -1;
   if (item >= a.split_from) {
     half = (item - a.split_from) & 1;
@@ -135,16 +137,15 @@ __device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int item) {
   } else if (a.win_items) {
     item -= a.end_core;
     const int slot = item / a.win_count, i = item - slot * a.win_count;
-    const int* it = a.win_items + 4 * i;
-    const int tile = it[2];
+    const int* it = a.win_items + WIN_ITEM_INTS * i;
     w.seg = 2;
     w.q_off = w.kv_off = w.o_off = a.win_gather ? a.win_heads[slot] * a.head_stride0 : (long)slot * a.N * D;
     w.row_stride = a.win_gather ? a.row_stride0 : D;
     w.row0 = it[0];
     w.n_rows = it[1];
     w.listed = true;
-    w.runs = a.runs + (long)tile * a.max_runs * 2;
-    w.n_runs = a.n_runs[tile];
+    w.keys = it + 2;
+    w.n_runs = 0;
     w.single_len = 0;
   } else {
     item -= a.end_core;
@@ -191,6 +192,36 @@ struct RunList {
       : runs((const_int_ptr)(uintptr_t)w.runs), n_runs(w.n_runs), single_len(w.single_len) {}
   __device__ __forceinline__ int start(int r) const { return runs ? runs[2 * r] : 0; }
   __device__ __forceinline__ int len(int r) const { return runs ? runs[2 * r + 1] : single_len; }
+};
+
+// Keys of a window item: the video tokens of a box of the grid, in raster order, then the text tokens.  The token of
+// a key is computed: a dozen vector instructions a lane and block, two of them products of 32 bits, where the walk
+// through the tile's runs that this replaces took 80 to 150 scalar instructions of every wavefront, which issues one
+// instruction in five cycles whatever it is.  The numbers are the same for every lane and no kernel
+// writes them: constant memory, like the run lists.
+struct WindowKeys {
+  int n_keys, n_box, t0, step, mult_a, shift_a, skip_a, mult_b, shift_b, skip_b, text;
+  __device__ __forceinline__ explicit WindowKeys(const WorkItem& w) {
+    const const_int_ptr at = (const_int_ptr)(uintptr_t)w.keys;
+    int* const field[] = {&n_keys, &n_box, &t0, &step, &mult_a, &shift_a, &skip_a, &mult_b, &shift_b, &skip_b, &text};
+#pragma unroll
+    for (int i = 0; i < 11; ++i) *field[i] = at ? at[i] : 0;
+  }
+  // read once: kept in scalar registers, not read again in every iteration
+  __device__ __forceinline__ void keep() {
+    asm volatile("" : "+s"(n_keys), "+s"(n_box), "+s"(t0), "+s"(step), "+s"(mult_a), "+s"(shift_a), "+s"(skip_a), "+s"(mult_b),
+                      "+s"(shift_b), "+s"(skip_b), "+s"(text));
+  }
+  // token of key k >= 0; past the end, that of the last key
+  __device__ __forceinline__ unsigned token(int k) const {
+    const unsigned key = (unsigned)min(k, n_keys - 1);
+    const unsigned a = __umulhi(key, (unsigned)mult_a) >> shift_a, b = __umulhi(a, (unsigned)mult_b) >> shift_b;
+    const unsigned video = (unsigned)t0 + mul24(key, step) + mul24(a, skip_a) + mul24(b, skip_b);
+    // no branch: the difference is the sign of key - n_box spread over all bits
+    const unsigned in_box = (unsigned)((int)(key - (unsigned)n_box) >> 31), other = key + (unsigned)text;
+    return other ^ ((other ^ video) & in_box);
+  }
+  static __device__ __forceinline__ unsigned mul24(unsigned x, int y) { return (x & 0xffffffu) * ((unsigned)y & 0xffffffu); }
 };
 
 // Rows of the keys k[i] (i < NR, per lane, 0 <= k[i] < bn) of the bn-key block that begins pos keys into run

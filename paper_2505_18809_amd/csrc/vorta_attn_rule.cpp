@@ -238,7 +238,7 @@ AttnForm choose_attention_form(const vorta_plan* p, const RouteLists& rl, bool m
   auto list = [&](int l) {
     Window w;
     w.heads = n_win;
-    w.list = (int)(p->win_list[l].size() / 4);
+    w.list = (int)(p->win_list[l].size() / WIN_ITEM_INTS);
     w.sums = p->win_sums[l].data();
     w.most = p->win_most_blocks[l];
     w.waves = p->win_waves[l];
@@ -322,6 +322,14 @@ int vorta_test_form(const vorta_plan* p, const uint8_t* routes_host, int32_t mix
   const AttnForm f = choose_attention_form(p, rl, mix != 0, true, units);
   const int32_t v[9] = {f.split_all, f.shares, f.split_win, f.together, f.n_long, f.half_long, f.n_big, f.half_big, f.win_128};
   std::copy(v, v + 9, out);
+  return VORTA_OK;
+}
+
+// The window items of list 0 .. 3 (see vorta_plan::win_list): their number, and unless out is null the numbers themselves.
+int vorta_test_window_list(const vorta_plan* p, int32_t list, int32_t* out, int32_t* n_items) {
+  if (!p || list < 0 || list > 3 || !n_items) return fail(VORTA_EINVAL, "list %d", list);
+  *n_items = (int32_t)(p->win_list[list].size() / WIN_ITEM_INTS);
+  if (out) std::copy(p->win_list[list].begin(), p->win_list[list].end(), out);
   return VORTA_OK;
 }
 

@@ -85,6 +85,54 @@ static int window_centre(int q, int n, int w, int mode) {
   return std::min(std::max(q, lo), hi);
 }
 
+// Quotients by d (2 <= d < 2^24) of numbers below 2^31: floor(k / d) = (k * mult >> 32) >> shift.  mult is
+// 2^(32 + shift) / d rounded up, off by less than 1, so k * mult / 2^(32 + shift) is above k / d by less than
+// k / 2^(32 + shift) <= 2^31 / (2^32 d / 2) = 1 / d, and does not reach the next whole number.
+struct Divisor {
+  uint32_t mult;
+  int shift;
+};
+static Divisor divisor(int64_t d) {
+  Divisor r{0, 0};
+  while (((int64_t)2 << r.shift) < d) ++r.shift;           // 2^shift < d <= 2^(shift + 1)
+  r.mult = (uint32_t)((((uint64_t)1 << (32 + r.shift)) + (uint64_t)d - 1) / (uint64_t)d);
+  return r;
+}
+
+// What a window item needs to name its keys (see WIN_ITEM_INTS): the tokens of the box of key tiles that query
+// tile `tile` sees, in raster order, then the text tokens.  Key k of the box is the token
+//   t0 + k s + (k / a) (s_a - a s) + (k / a / b) (s_b - b s_a),
+// a and b being the extents of the box along its two innermost axes and s, s_a, s_b the steps of a token along
+// those and the outermost axis.  Axes along which the box is one token are left out.
+static void window_keys(const vorta_plan* p, int tile, int32_t (&item)[WIN_ITEM_INTS]) {
+  const vorta_layer_desc& d = p->d;
+  const int grid[3] = {d.F, d.H, d.W}, step[3] = {d.H * d.W, d.W, 1};
+  int64_t first = 0, keys = 1, extent[3] = {2, 2, 2}, along[3] = {0, 0, 0};      // innermost first
+  int axes = 0;
+  for (int a = 2; a >= 0; --a) {
+    const int32_t* box = &p->boxes[(size_t)tile * 6 + 2 * a];
+    const int64_t lo = (int64_t)box[0] * d.tile[a], n = std::min<int64_t>((int64_t)(box[1] + 1) * d.tile[a], grid[a]) - lo;
+    first += lo * step[a];
+    keys *= n;
+    if (n == 1) continue;
+    extent[axes] = n;
+    along[axes++] = step[a];
+  }
+  const Divisor by_a = divisor(extent[0]), by_b = divisor(extent[1]);
+  item[2] = (int32_t)(keys + d.n_text);
+  item[3] = (int32_t)keys;
+  item[4] = (int32_t)first;
+  item[5] = (int32_t)along[0];
+  item[6] = (int32_t)by_a.mult;
+  item[7] = by_a.shift;
+  item[8] = axes > 1 ? (int32_t)(along[1] - extent[0] * along[0]) : 0;
+  item[9] = (int32_t)by_b.mult;
+  item[10] = by_b.shift;
+  item[11] = axes > 2 ? (int32_t)(along[2] - extent[1] * along[1]) : 0;
+  item[12] = (int32_t)(p->L - keys);
+  item[13] = item[14] = item[15] = 0;
+}
+
 // Tables of a plan whose description has been checked and clipped.  Allocates: may throw std::bad_alloc.
 static void build_plan(vorta_plan* p) {
   const vorta_layer_desc& d = p->d;
@@ -205,11 +253,13 @@ static void build_plan(vorta_plan* p) {
     if (place[g] == place[g + 1]) continue;      // not the first tile of a group
     const int32_t begin = end;
     for (int32_t i = place[g]; i < place[g + 1]; ++i) end += p->tile_row0[p->win_tiles[i] + 1] - p->tile_row0[p->win_tiles[i]];
-    int64_t keys = 0;
-    for (size_t r = 1; r < run_lists[g].size(); r += 2) keys += run_lists[g][r];
-    const int blocks = (int)((keys + 63) / 64);
+    int32_t item[WIN_ITEM_INTS];
+    window_keys(p, g, item);
+    const int blocks = (item[2] + 63) / 64;
     auto add = [&](int list, int32_t first, int32_t rows) {
-      p->win_list[list].insert(p->win_list[list].end(), {first, rows, g, 0});
+      item[0] = first;
+      item[1] = rows;
+      p->win_list[list].insert(p->win_list[list].end(), item, item + WIN_ITEM_INTS);
       p->win_sums[list].push_back(p->win_sums[list].back() + blocks);
       p->win_most_blocks[list] = std::max(p->win_most_blocks[list], blocks);
       list_waves[list] += (rows + 31) / 32;
@@ -219,7 +269,7 @@ static void build_plan(vorta_plan* p) {
     for (int32_t first = begin; first < end; first += 128) add(3, first, std::min(128, end - first));
   }
   for (int l = 0; l < 4; ++l) {
-    const int64_t n = (int64_t)p->win_list[l].size() / 4;
+    const int64_t n = (int64_t)p->win_list[l].size() / WIN_ITEM_INTS;
     if (n) p->win_waves[l] = (double)list_waves[l] / (double)n;
   }
 

@@ -7,6 +7,10 @@
 
 #include "vorta.h"
 
+namespace vorta {
+constexpr int WIN_ITEM_INTS = 16;   // of an entry of vorta_plan::win_list
+}
+
 struct vorta_plan {
   vorta_layer_desc d;
   int64_t L = 0, N = 0;          // video tokens, all tokens
@@ -28,7 +32,9 @@ struct vorta_plan {
   std::vector<int32_t> slot_base;  // [n_buckets + 1]
   // window work items of the bf16 kernels: the rows of all tiles with one key set are one sequence, cut into
   // blocks whatever the tile borders; win_tiles holds the tiles of these sequences one after the other.
-  // {first, n_rows, tile, 0}: n_rows places of the sequences' rows from `first`, keys as tile `tile` sees them.
+  // An item is WIN_ITEM_INTS numbers: {first, n_rows, ...}, n_rows places of the sequences' rows from `first`, then
+  // what the kernels compute its keys from:
+  //   n_keys, n_box (the video tokens among them), t0, s, mult_a, shift_a, s_a - a s, mult_b, shift_b, s_b - b s_a, L - n_box
   // List 0: blocks of 129 to 256 rows; list 1: what is left of a sequence, at most 128 rows; list 2: the
   // sequences cut into blocks of at most 64 rows instead; list 3: of at most 128 rows.
   std::vector<int32_t> win_tiles;  // [n_tiles]
@@ -58,7 +64,7 @@ struct vorta_plan {
   // which slots a bucket owns depends on its size only, so this is known before any selection
   int32_t* d_slot_bucket = nullptr;
   int32_t* d_tok_of = nullptr;   // [N]: tile-order row -> token (identity for the text rows)
-  int32_t* d_iota = nullptr;     // [N]: 0, 1, 2, ... for tile-ordered copies, whose rows are their own indices
+  int32_t* d_row_of = nullptr;   // [N]: token -> tile-order row, the inverse
   int32_t* d_win_rows = nullptr; // [L]: the tile-order rows of the sequences of win_tiles
   int32_t* d_win_tok = nullptr;  // [L]: their tokens
   int32_t* d_tile_row0 = nullptr;   // [n_tiles + 1]

@@ -45,7 +45,7 @@ static int upload_device_tables(vorta_plan* p, int dev) {
   };
   auto table = [](const auto& v, auto** slot) { return Table{v.data(), v.size() * sizeof(v[0]), (void**)slot, 0}; };
   auto made = [](int64_t n, int32_t** slot) { return Table{nullptr, (size_t)n * sizeof(int32_t), (void**)slot, 0}; };
-  Table tables[] = {made(p->N, &p->d_tok_of), made(p->N, &p->d_iota), made(p->L, &p->d_win_rows), made(p->L, &p->d_win_tok),
+  Table tables[] = {made(p->N, &p->d_tok_of), made(p->N, &p->d_row_of), made(p->L, &p->d_win_rows), made(p->L, &p->d_win_tok),
                     made(2 * p->Lc, &p->d_slot_bucket),
                     table(p->runs, &p->d_runs), table(p->n_runs, &p->d_n_runs), table(p->slot_base, &p->d_slot_base),
                     table(p->tile_row0, &p->d_tile_row0), table(p->win_list[0], &p->d_win_list[0]),
@@ -60,7 +60,7 @@ static int upload_device_tables(vorta_plan* p, int dev) {
   const std::unique_ptr<char[]> image(new (std::nothrow) char[total]);
   if (!image) return fail(VORTA_EHIP, "no host memory for %zu bytes of tables", total);
   auto place = [&](int i) { return (int32_t*)(image.get() + tables[i].at); };
-  int32_t *tok_of = place(0), *iota = place(1), *win_rows = place(2), *win_tok = place(3), *slot_bucket = place(4);
+  int32_t *tok_of = place(0), *row_of = place(1), *win_rows = place(2), *win_tok = place(3), *slot_bucket = place(4);
   // the inverse tile permutation; text rows keep their place
   const vorta_layer_desc& d = p->d;
   int32_t* row = tok_of;
@@ -71,7 +71,7 @@ static int upload_device_tables(vorta_plan* p, int dev) {
           for (int h = h0; h < std::min(h0 + d.tile[1], d.H); ++h)
             for (int w = w0; w < std::min(w0 + d.tile[2], d.W); ++w) *row++ = (f * d.H + h) * d.W + w;
   for (int64_t i = p->L; i < p->N; ++i) tok_of[i] = (int32_t)i;
-  for (int64_t i = 0; i < p->N; ++i) iota[i] = (int32_t)i;
+  for (int64_t i = 0; i < p->N; ++i) row_of[tok_of[i]] = (int32_t)i;
   for (int32_t t : p->win_tiles)
     for (int32_t r = p->tile_row0[t]; r < p->tile_row0[t + 1]; ++r) {
       *win_rows++ = r;

@@ -1,0 +1,78 @@
+"""The numbers from which the bf16 window kernels compute their keys, evaluated here as the kernels do it, against the run
+lists of the tiles: every item sees the tokens of its tiles' runs, each once, and every tile's rows are in
+items that see its keys.  No GPU is needed."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2505_18809_amd as vorta
+
+INTS = 16
+
+
+def window_list(plan, which):
+    lib, n = vorta.load_library(), ctypes.c_int32()
+    assert lib.vorta_test_window_list(plan.handle, ctypes.c_int32(which), None, ctypes.byref(n)) == 0
+    out = np.empty((n.value, INTS), dtype=np.int32)
+    assert lib.vorta_test_window_list(plan.handle, ctypes.c_int32(which), out.ctypes.data_as(ctypes.c_void_p), ctypes.byref(n)) == 0
+    return out
+
+
+def tokens(item, k):
+    """Tokens of the keys k of an item, in the kernels' 32-bit arithmetic."""
+    n_keys, n_box, t0, step, mult_a, shift_a, skip_a, mult_b, shift_b, skip_b, text = (np.uint64(int(x) & 0xffffffff) for x in item[2:13])
+    key = np.minimum(k.astype(np.uint64), n_keys - np.uint64(1))
+    a = (key * mult_a >> np.uint64(32)) >> shift_a
+    b = (a * mult_b >> np.uint64(32)) >> shift_b
+    low = np.uint64(0xffffff)
+    for x in (key, a, b, step, skip_a, skip_b):
+        assert (x <= low).all()                       # factors of 24-bit products
+    video = (t0 + key * step + a * skip_a + b * skip_b) & np.uint64(0xffffffff)
+    return np.where(key < n_box, video, (key + text) & np.uint64(0xffffffff)).astype(np.int64)
+
+
+@pytest.mark.parametrize("grid,tile,window,n_text,mode", [
+    ((21, 30, 52), (3, 6, 4), (3, 3, 3), 0, 0), ((9, 23, 31), (3, 5, 8), (3, 3, 3), 13, 1), ((10, 12, 9), (6, 9, 8), (3, 3, 3), 9, 0),
+    ((8, 9, 10), (2, 3, 3), (3, 3, 3), 6, 2), ((7, 8, 9), (2, 3, 4), (3, 1, 5), 0, 1),
+    ((1, 1, 1), (1, 1, 1), (1, 1, 1), 0, 0), ((1, 1, 1), (1, 1, 1), (1, 1, 1), 5, 0),         # one token
+    ((1, 1, 37), (1, 1, 4), (3, 3, 3), 2, 1), ((1, 37, 1), (1, 4, 1), (1, 3, 1), 0, 1), ((37, 1, 1), (4, 1, 1), (3, 1, 1), 0, 1),
+    ((5, 7, 1), (2, 3, 1), (1, 1, 1), 0, 1), ((5, 1, 7), (2, 1, 3), (1, 1, 1), 3, 1), ((1, 5, 7), (1, 2, 3), (1, 1, 1), 0, 1),
+    ((5, 6, 7), (1, 1, 1), (1, 1, 1), 0, 1), ((5, 6, 7), (2, 1, 1), (1, 1, 1), 1, 1), ((5, 6, 7), (1, 2, 1), (1, 1, 1), 0, 1),
+    ((5, 6, 7), (1, 1, 2), (1, 1, 1), 0, 1), ((6, 8, 8), (2, 2, 2), (2, 4, 99), 0, 1),
+])
+def test_items_see_the_keys_of_their_tiles(grid, tile, window, n_text, mode):
+    plan = vorta.vorta_plan_create(grid, 2, 128, "bf16", tile, window, n_text=n_text, center_mode=mode)
+    token_of = np.argsort(vorta.vorta_tile_permutation(plan))         # the permutation maps a token to its tile-order row
+    row0 = vorta.vorta_tile_row0(plan)
+    runs, n_runs = vorta.vorta_window_runs(plan)
+    want = {}
+    for t in range(plan.n_tiles):
+        rows = np.concatenate([np.arange(s, s + n) for s, n in runs[t, :n_runs[t]]])
+        keys = tuple(sorted(token_of[r] if r < plan.n_video else r for r in rows))
+        want[keys] = want.get(keys, 0) + int(row0[t + 1] - row0[t])
+    most = {0: 256, 1: 128, 2: 64, 3: 128}
+    for lists in ((0, 1), (2,), (3,)):
+        got, places = {}, []
+        for which in lists:
+            for item in window_list(plan, which):
+                assert 0 < item[1] <= most[which] and (which != 0 or item[1] > 128)
+                keys = tokens(item, np.arange(item[2]))
+                assert (np.diff(keys) > 0).all()                      # raster order, then the text tokens
+                assert (tokens(item, np.arange(item[2], item[2] + 300)) == keys[-1]).all()
+                got[tuple(keys)] = got.get(tuple(keys), 0) + int(item[1])
+                places += range(item[0], item[0] + item[1])
+        assert got == want
+        assert sorted(places) == list(range(plan.n_video))
+
+
+@pytest.mark.parametrize("grid", [(1, 3001, 5003), (4093, 1, 4099), (255, 257, 251), (2, 2, 4194303)])
+def test_quotients_are_exact_up_to_the_largest_plan(grid):
+    """One head of nearly 2^24 tokens, all of them keys of every tile."""
+    tile = tuple(-(-g // 2) for g in grid)
+    plan = vorta.vorta_plan_create(grid, 1, 128, "bf16", tile, (99, 99, 99))
+    item = window_list(plan, 3)[0]
+    assert item[2] == plan.n_video
+    for first in range(0, plan.n_video, 1 << 22):
+        k = np.arange(first, min(first + (1 << 22), plan.n_video))
+        assert np.array_equal(tokens(item, k), k)
