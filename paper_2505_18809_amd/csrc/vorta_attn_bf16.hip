@@ -127,7 +127,7 @@ namespace {
 constexpr int KG = 520, VG = 544;        // elements from one four-row group of a K / V stage to the next (1 KiB + pad)
 constexpr int K_RING = 4, V_RING = 5;    // stages
 constexpr int pipe_lds_bytes(int nwv) { return (K_RING * KG + V_RING * VG) * (2 * nwv) * 2; }   // 2 nwv groups per stage
-constexpr int LEAD = 2;                  // slots between a fragment request and its use (2..6 measured alike; 2 needs the fewest registers)
+constexpr int LEAD = 3;                  // slots between a fragment request and its use (2, 3 and 4 measured alike, within 0.3 %; waiting for two fragments at once: 1.1 % slower)
 }  // namespace
 
 __device__ __forceinline__ float elem_of(const f32x16& t0, const f32x16& t1, int e) { return e < 16 ? t0[e] : t1[e - 16]; }
@@ -237,7 +237,7 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
   constexpr int NG = KB / 4;                // four-row groups per stage: group j holds rows j, j + NG, j + 2 NG, j + 3 NG
   constexpr int K_STAGE = NG * KG, V_STAGE = NG * VG;   // elements of a K / V stage
   constexpr int V_BASE = K_RING * K_STAGE;  // the K ring, then the V ring
-  auto after = [](int stage) { return stage == (V_RING - 1) * V_STAGE ? 0 : stage + V_STAGE; };   // V stages, as offsets; K block b: stage b & 3
+  auto after = [](int stage) { return stage == (V_RING - 1) * V_STAGE ? 0 : stage + V_STAGE; };   // offset of the next V stage
   const WorkItem w = decode_item<32 * NWV, D>(a, item);
   const bool user = WIN ? !COPIES : w.seg == 0;     // rows of the caller's tensors
   const uint16_t* Q = (const uint16_t*)(user ? a.q0 : w.seg == 1 ? a.qc : a.qt) + w.q_off;
@@ -272,12 +272,12 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
   // of the group.  Blocks past the end repeat the last row (those copies land in ring stages nobody
   // reads), so the loads need no guard.
   const int ld_q = lane >> 4, ld_chunk = (lane & 15) ^ (KB == 32 && (ld_q & 2) ? 8 : 0);
-  const unsigned ld_col = 8 * ld_chunk;
+  const unsigned ld_col = 16 * ld_chunk, stride2 = 2 * row_stride;      // bytes
   const int lane_key = wave + NWV * (lane & 1) + NG * ld_q;      // key of this lane's row, group wave + NWV (lane & 1), in block 0
-  const unsigned lane_row = (unsigned)lane_key * row_stride, last_row = (unsigned)(n_keys - 1) * row_stride, block_rows = KB * row_stride;
-  auto row_of_block = [&](int b) -> unsigned {  // element offset of this lane's row of block b
-    if constexpr (WIN) return __umul24(keys.token(lane_key + KB * b), row_stride);
-    return min(lane_row + (unsigned)b * block_rows, last_row);
+  auto offset_of = [&](unsigned row) { return WindowKeys::mul24(row, (int)stride2); };
+  auto row_of_block = [&](int b) {  // offset of this lane's row of block b
+    const int key = lane_key + KB * b;
+    return offset_of(WIN ? keys.token(key) : (unsigned)min(key, n_keys - 1));
   };
   // K / V rows come through buffer loads: a scalar resource descriptor per tensor (raw buffer, no
   // range check: offsets are in bounds by construction) plus one 32-bit byte offset per lane.
@@ -292,11 +292,18 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
   const unsigned lds0 = (unsigned)(uintptr_t)(lds_ptr)smem;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   auto dma16 = [&](const i32x4& rs, unsigned lds_addr, unsigned off) {
-    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds_addr), "v"(off * 2u), "s"(rs) : "memory");
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds_addr), "v"(off), "s"(rs) : "memory");
   };
-  // group wave + NWV h of K / V block b (h = 0, 1: this lane's first and second staging row)
-  auto dma_k = [&](int h, int b, unsigned off) { dma16(rs_k, lds0 + 2u * (unsigned)((b & 3) * K_STAGE + (wave_u + NWV * h) * KG), off); };
-  auto dma_v = [&](int h, int stage, unsigned off) { dma16(rs_v, lds0 + 2u * (unsigned)(V_BASE + stage + (wave_u + NWV * h) * VG), off); };
+  // group wave + NWV h (h = 0, 1: this lane's first and second staging row) of the stages that the next block to
+  // request goes to, whose LDS addresses move on with next_stages()
+  const unsigned k_first = lds0 + 2u * (unsigned)(wave_u * KG), v_first = lds0 + 2u * (unsigned)(V_BASE + wave_u * VG);
+  unsigned k_dst = k_first, v_dst = v_first;
+  auto next_stages = [&]() {
+    k_dst = k_dst == k_first + 2u * (K_RING - 1) * K_STAGE ? k_first : k_dst + 2u * K_STAGE;
+    v_dst = v_dst == v_first + 2u * (V_RING - 1) * V_STAGE ? v_first : v_dst + 2u * V_STAGE;
+  };
+  auto dma_k = [&](int h, unsigned off) { dma16(rs_k, k_dst + 2u * (unsigned)(NWV * h * KG), off); };
+  auto dma_v = [&](int h, unsigned off) { dma16(rs_v, v_dst + 2u * (unsigned)(NWV * h * VG), off); };
   // WIN_COPIES: the row of this lane's token of the NEXT block whose rows will be loaded, looked up one block ahead.
   // The lookups are loads the compiler does not see either (it would wait for them with
   // vmcnt(0), which also drains the row loads requested after them): they are requested BEFORE
@@ -311,20 +318,19 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
     if (rows_behind) asm volatile("s_waitcnt vmcnt(4)" : "+v"(gi)::"memory");
     else asm volatile("s_waitcnt vmcnt(0)" : "+v"(gi)::"memory");
   };
-  int v_load = 0, v_prev = 0, v_cur = 0;              // V stages of the block to request, of blocks i - 1 and i
   auto fetch_all = [&](int b, bool first = false) {   // rows of block b into its ring stages
     unsigned row;
     if constexpr (COPIES) {
       win_wait(!first);
-      row = __umul24((unsigned)gi, row_stride);
+      row = offset_of((unsigned)gi);
       win_idx(b + 1);              // of the block after it
     } else {
       row = row_of_block(b);
     }
     const unsigned o0_ = row_bcast(row, 0) + ld_col, o1_ = row_bcast(row, 1) + ld_col;
-    dma_k(0, b, o0_); dma_v(0, v_load, o0_);
-    dma_k(1, b, o1_); dma_v(1, v_load, o1_);
-    v_load = after(v_load);
+    dma_k(0, o0_); dma_v(0, o0_);
+    dma_k(1, o1_); dma_v(1, o1_);
+    next_stages();
   };
   if constexpr (COPIES) win_idx(0);  // prime the index pipeline with block 0
   fetch_all(0, true);              // blocks 0, 1 and 2 into their stages; iteration i requests block i+3
@@ -377,6 +383,7 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
   }
   if (n_keys < KB) mask_tail(sa0, sa1, n_keys);
 
+  int v_prev = 0, v_cur = 0;       // V stages of blocks i - 1 (iteration 0: of block 0) and i
 #define SLOT_FENCE() __builtin_amdgcn_sched_barrier(0)
   // first V^T fragments of the coming iteration, requested before the barrier of this one
   bf16x8 vpre[LEAD];
@@ -466,7 +473,7 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
       if (n == SO) {
         if constexpr (COPIES) {
           win_wait(true);
-          row = __umul24((unsigned)gi, row_stride);
+          row = offset_of((unsigned)gi);
         } else {
           row = row_of_block(i + 3);
         }
@@ -476,12 +483,12 @@ __device__ __forceinline__ void pipe_item(const AttnArgs a, const std::condition
         off0 = row_bcast(row, 0) + ld_col;
         off1 = row_bcast(row, 1) + ld_col;
       }
-      if (n == SL + 1) dma_k(0, i + 3, off0);
-      if (n == SL + 1 + SP) dma_v(0, v_load, off0);
-      if (n == SL + 1 + 2 * SP) dma_k(1, i + 3, off1);
-      if (n == SL + 1 + 3 * SP) dma_v(1, v_load, off1);
+      if (n == SL + 1) dma_k(0, off0);
+      if (n == SL + 1 + SP) dma_v(0, off0);
+      if (n == SL + 1 + 2 * SP) dma_k(1, off1);
+      if (n == SL + 1 + 3 * SP) dma_v(1, off1);
     }
-    v_load = after(v_load);
+    next_stages();
     v_prev = v_cur;
     v_cur = after(v_cur);
     SLOT_FENCE();
@@ -701,7 +708,7 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
   // ---- staging: a stage is 8 KS groups, wavefront j loads groups j + NWV h (h = 0..3) of K and of V; lane p of a
   // load fills bytes 16 p .. 16 p + 15 of the group (group layout and offsets: see the pipelined kernel, 32-key blocks)
   const int ld_q = lane >> 4;
-  const unsigned ld_col = 8 * (unsigned)((lane & 15) ^ (ld_q & 2 ? 8 : 0));
+  const unsigned ld_col = 16 * (unsigned)((lane & 15) ^ (ld_q & 2 ? 8 : 0)), stride2 = 2 * row_stride;      // bytes
   int lane_key;                                    // key of this lane's row, group j + NWV (lane & 3), in superblock 0
   {
     const int group = wave + NWV * (lane & 3);
@@ -712,7 +719,7 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
   const i32x4 rs_v = {__builtin_amdgcn_readfirstlane((int)(unsigned)v_pa), __builtin_amdgcn_readfirstlane((int)((unsigned)(v_pa >> 32) & 0xffffu)), -1, 0x00020000};
   const unsigned lds0 = (unsigned)(uintptr_t)(lds_ptr)smem;
   auto dma16 = [&](const i32x4& rs, unsigned lds_addr, unsigned off) {
-    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds_addr), "v"(off * 2u), "s"(rs) : "memory");
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(lds_addr), "v"(off), "s"(rs) : "memory");
   };
   auto dma_k = [&](int sb, int h, unsigned off) { dma16(rs_k, lds0 + 2u * (unsigned)((sb & 1) * SPLIT_K + (wave + NWV * h) * KG), off); };
   auto dma_v = [&](int sb, int h, unsigned off) { dma16(rs_v, lds0 + 2u * (unsigned)(2 * SPLIT_K + (sb & 1) * SPLIT_V + (wave + NWV * h) * VG), off); };
@@ -759,12 +766,12 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
     constexpr int SRC = decltype(source)::value;
     constexpr bool COPIES = SRC == WIN_COPIES;
     constexpr int T = COPIES ? 1 : 0;                // lookups of an iteration
-    const unsigned lane_row = (unsigned)lane_key * row_stride, last_row = (unsigned)(n_keys - 1) * row_stride;
+    auto offset_of = [&](unsigned row) { return WindowKeys::mul24(row, (int)stride2); };
     int gi = 0;                                      // row of this lane's token of superblock i + 2 as iteration i begins
-    auto row_of_sb = [&](int sb) -> unsigned {       // element offset of this lane's row
-      if constexpr (COPIES) return __umul24((unsigned)gi, row_stride);
-      if constexpr (SRC == WIN_TOKENS) return __umul24(keys.token(lane_key + SB * sb), row_stride);
-      return min(lane_row + (unsigned)sb * (SB * row_stride), last_row);
+    auto row_of_sb = [&](int sb) {                   // offset of this lane's row
+      if constexpr (COPIES) return offset_of((unsigned)gi);
+      const int key = lane_key + SB * sb;
+      return offset_of(SRC == WIN_TOKENS ? keys.token(key) : (unsigned)min(key, n_keys - 1));
     };
     unsigned off1[4], off2[4];                       // row offsets of superblocks i + 1 and i + 2
     if constexpr (COPIES) {
@@ -776,8 +783,8 @@ __global__ __launch_bounds__(128 * KS, 4 / KS) void attn_bf16_split_kernel(const
       // the query rows are here too: let the compiler wait for them now, not behind the row loads
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qf[ks]));
-      offsets(__umul24((unsigned)g0, row_stride), off2);
-      offsets(__umul24((unsigned)g1, row_stride), off1);
+      offsets(offset_of((unsigned)g0), off2);
+      offsets(offset_of((unsigned)g1), off1);
     } else {
       offsets(row_of_sb(0), off2);
       offsets(row_of_sb(1), off1);
