@@ -59,6 +59,8 @@ struct AttnArgs {
   // whose upper wavefronts have no rows runs them as helpers (staging only), which takes about
   // half the time of a full item.  split_from = INT_MAX: no split.
   int split_from;
+  // Split kernel: of the first `round` workgroups the first ones take the last items of that round (see launch_split).
+  int round, round_shift;
   int qb_dense, qb_core, qb_tile, qb_text;   // q-blocks per head / core-set / tile / text part
   int end_text, end_dense, end_core, end_tile;   // cumulative item counts, in grid order; end_tile = all
   float scale;
