@@ -2,7 +2,7 @@
 """Benchmark of the routed attention layer on one MI355X.
 
 A step is one pass of the whole hot path -- core-set selection and pooling, the routed
-attention launches (window rows gathered through the tile permutation, core-set rows written to
+attention launches (window rows read where they lie, core-set rows written to
 the tokens that read them) -- over one seeded synthetic layer, with Q/K/V already resident in HBM.  Prints ONE JSON line.
 
   value       effective TFLOP/s of the whole layer call: FLOPs of the two contractions
@@ -202,8 +202,8 @@ def main():
     q_c, k_c, v_c, o_c = (buf(i, n_lr, plan.n_core_tokens) for i in range(4, 8))
     keep_idx = ws[off[8]: off[8] + n_lr * plan.n_core * 4].view(torch.int32).view(n_lr, plan.n_core)
     assign = ws[off[9]: off[9] + n_lr * plan.n_video * 4].view(torch.int32).view(n_lr, plan.n_video)
-    # what the layer call issues: with bf16 the window kernel gathers rows through the tile
-    # permutation, so there is no reorder pass and no tile-ordered copy
+    # what the layer call issues: with bf16 the window kernel reads rows where they lie,
+    # so there is no reorder pass and no tile-ordered copy
     gather = cfg.dtype == "bf16"
     tiled = {} if gather else dict(q_t=q_t, k_t=k_t, v_t=v_t, o_t=o_t)
     stages = {}
@@ -290,7 +290,7 @@ def main():
     if cfg.dtype == "bf16":
         if counts[0] + counts[2] > 0:
             # (zero operands: off by default, so that a profile of the default command holds launches of one kind)
-            dom = {"kernel": "attn_bf16_pipe_kernel<false, 8>", "flops": per_route[0] + per_route[2],
+            dom = {"kernel": "attn_bf16_pipe_kernel<LONG_KEYS, 8>", "flops": per_route[0] + per_route[2],
                    **heads_alone(routes != 1, zero=args.zero_operands)}
         # the window heads alone (their text rows, if the layer has text tokens, go first in the
         # same launch)
