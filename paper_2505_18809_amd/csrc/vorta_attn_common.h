@@ -65,9 +65,7 @@ struct AttnArgs {
   int qb_dense, qb_core, qb_tile, qb_text;   // q-blocks per head / core-set / tile / text part
   int end_text, end_dense, end_core, end_tile;   // cumulative item counts, in grid order; end_tile = all
   float scale;
-  uint8_t dense_heads[VORTA_MAX_HEADS];
-  uint8_t win_heads[VORTA_MAX_HEADS];
-  uint8_t core_heads[VORTA_MAX_HEADS];
+  HeadIds dense_heads, win_heads, core_heads;
   // [key lists][WIN_KEY_INTS], bf16: never null.  Last: ahead of the numbers above it costs the fp32 kernels' first reads 0.2 us.
   const int* win_keys;
 };
@@ -85,6 +83,10 @@ struct MixArgs {
 };
 struct NoMix {};
 
+// Tables that are the same for every lane and that no kernel writes are read as constant memory: with a wave-uniform index that
+// is a scalar load, whose result lands in a scalar register and whose wait does not include the vector loads in flight.
+typedef const __attribute__((address_space(4))) int* const_int_ptr;
+
 struct WorkItem {
   long q_off, kv_off, o_off;   // element offsets of the head's row 0 in q / k,v / o
   long row_stride;             // elements
@@ -97,6 +99,18 @@ struct WorkItem {
   const int* runs;             // null: the single run {0, single_len}
   int single_len;
 };
+
+// The arguments that finding an item and its rows takes, read all at once.  Read where they are used they are some fifteen
+// scalar loads, each waited for before the branch that needs it, all ahead of an item's first row; with head ids in words
+// (HeadIds) small launches take 0.2 to 0.9 us less: 3 window heads of 3,072 tokens 14.2 -> 13.3 us, 8 heads on all routes 38.0 ->
+// 37.4, two fp32 heads of 256 tokens 16.9 -> 16.7; large ones are level.  (An operand of the statement is a register that holds
+// the argument there; it emits nothing.)
+__device__ __forceinline__ void read_together(const AttnArgs& a) {
+  asm volatile("" ::"s"(a.head_stride0), "s"(a.row_stride0), "s"(a.q0), "s"(a.k0), "s"(a.v0), "s"(a.qc), "s"(a.kc), "s"(a.vc), "s"(a.N),
+               "s"(a.Nc), "s"(a.L), "s"(a.n_text), "s"(a.win_gather), "s"(a.win_items), "s"(a.win_row), "s"(a.win_count),
+               "s"(a.win_keys), "s"(a.split_from), "s"(a.qb_dense), "s"(a.qb_core), "s"(a.qb_text), "s"(a.end_text), "s"(a.end_dense),
+               "s"(a.end_core), "s"(a.scale), "s"(a.round), "s"(a.round_shift), "s"(a.o0));
+}
 
 template <int BM, int D>
 __device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int item) {
@@ -142,7 +156,7 @@ __device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int item) {
   } else if (a.win_items) {
     item -= a.end_core;
     const int slot = item / a.win_count, i = item - slot * a.win_count;
-    const int* it = a.win_items + WIN_ITEM_INTS * i;
+    const const_int_ptr it = (const_int_ptr)(uintptr_t)(a.win_items + WIN_ITEM_INTS * i);
     w.seg = 2;
     w.q_off = w.kv_off = w.o_off = a.win_gather ? a.win_heads[slot] * a.head_stride0 : (long)slot * a.N * D;
     w.row_stride = a.win_gather ? a.row_stride0 : D;
@@ -186,10 +200,7 @@ __device__ __forceinline__ int xcd_item(int block, int n, bool chunked) {
   return xcd * q + min(xcd, r) + loc;
 }
 
-// Run list of a work item.  It is the same for every lane and no kernel writes it, so it is
-// read as constant memory: with a wave-uniform index that is a scalar load, whose result lands
-// in a scalar register and whose wait does not include the vector loads in flight.
-typedef const __attribute__((address_space(4))) int* const_int_ptr;
+// Run list of a work item, read as constant memory.
 struct RunList {
   const_int_ptr runs;      // (start, length) pairs; null: the single run {0, single_len}
   int n_runs, single_len;

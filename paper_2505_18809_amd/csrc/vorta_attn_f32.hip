@@ -53,6 +53,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_f32_kernel(const AttnArg
   constexpr double REF_SLACK = 512.0;        // log2 units a score may exceed the row reference by
   __shared__ double s_ref[NW][BM], s_sum[NW][BM];
   __shared__ f64x4 s_acc[NW / 2][NT][64];
+  read_together(a);
   const WorkItem w = decode_item<BM, D>(a, blockIdx.x);
   if (w.n_rows <= 0) return;       // q-block past the end of a clipped tile
   // window heads without tile-ordered copies: rows of the caller's tensors through the tile permutation

@@ -76,6 +76,17 @@ struct vorta_plan {
 
 namespace vorta {
 
+// Head ids as kernels take them: four to a word.  A byte at a computed index is a vector load from the arguments, ahead of every
+// address that depends on it; a word is a scalar one.
+struct HeadIds {
+  uint32_t word[VORTA_MAX_HEADS / 4];
+  constexpr int operator[](int i) const { return (int)(word[i >> 2] >> (8 * (i & 3)) & 255u); }
+  constexpr void set(int i, int id) {
+    const uint32_t at = 8u * (uint32_t)(i & 3);
+    word[i >> 2] = (word[i >> 2] & ~(255u << at)) | (uint32_t)id << at;
+  }
+};
+
 int fail(int code, const char* fmt, ...);        // records the thread-local message, returns code
 void clear_error();
 

@@ -129,13 +129,13 @@ int ensure_device_tables(vorta_plan* p) {
 
 struct HeadList {
   int n;
-  uint8_t id[VORTA_MAX_HEADS];
+  HeadIds id;
 };
 
 static HeadList head_list(const RouteLists& rl, int route) {
   HeadList h;
   h.n = rl.count[route];
-  for (int i = 0; i < h.n; ++i) h.id[i] = (uint8_t)rl.heads[route][i];
+  for (int i = 0; i < h.n; ++i) h.id.set(i, rl.heads[route][i]);
   return h;
 }
 
@@ -810,7 +810,7 @@ static RopeRows<T> rope_rows_job(const vorta_plan* p, const RouteLists& rl, cons
   job.dst[0] = (T*)r.dst[0]; job.dst[1] = (T*)r.dst[1];
   job.hl.n = 0;
   for (int route = 0; route < 2; ++route)
-    for (int i = 0; i < rl.count[route]; ++i) job.hl.id[job.hl.n++] = (uint8_t)rl.heads[route][i];
+    for (int i = 0; i < rl.count[route]; ++i) job.hl.id.set(job.hl.n++, rl.heads[route][i]);
   const UserTensor ut = user_tensor(p, r.src[0]);
   job.L = (int)p->L; job.N = (int)p->N; job.cshift = chunk_shift(p);
   job.head_stride = ut.head_stride; job.row_stride = ut.row_stride;
