@@ -866,7 +866,13 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
   const Bucket kb = bucket_of(g, b);               // kb.size <= P G: checked on the host
   const int c = lane % CPR, grp = lane / CPR;
 
-  // ---- every load of the wavefront
+  // ---- every load of the wavefront.  With a rotation the pointers of Q and V are made new here: known to be read only, the
+  // compiler moves their loads down to where the rows are merged, a memory round trip behind K's.  (16 heads of 75,600 tokens:
+  // buckets of 27 tokens 433 -> 396 us, of 8 tokens 344 -> 335, of 12 level.  Without a rotation more wavefronts, which the
+  // registers of the early loads cost, hide more: 8 tokens 251 us as it is, 264 that way.)
+  typedef const __attribute__((address_space(1))) T* global_ptr;
+  global_ptr q_now = (global_ptr)q, v_now = (global_ptr)v;
+  if constexpr (ROPE) asm volatile("" : "+s"(q_now), "+s"(v_now));
   const BucketToken centre = bucket_token(g, kb, kb.centre);
   const uint4 craw = Chunk<T>::raw(k + head_off + (long)centre.tok * row_stride + c * CN);
   uint4 rq[P], rk[P], rv[P];
@@ -880,11 +886,12 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
 #pragma unroll
   for (int p = 0; p < P; ++p) rk[p] = Chunk<T>::raw(k + off[p]);
 #pragma unroll
-  for (int p = 0; p < P; ++p) rq[p] = Chunk<T>::raw(q + off[p]);
+  for (int p = 0; p < P; ++p) rq[p] = Chunk<T>::raw((const T*)(q_now + off[p]));
 #pragma unroll
-  for (int p = 0; p < P; ++p) rv[p] = Chunk<T>::raw(v + off[p]);
-  const RopeLane<CN / 2> rl(rope, c * (CN / 2));
+  for (int p = 0; p < P; ++p) rv[p] = Chunk<T>::raw((const T*)(v_now + off[p]));
   const int base_slot = slot_base[b], prune = kb.size - (slot_base[b + 1] - base_slot);
+  if constexpr (ROPE) __builtin_amdgcn_sched_barrier(0);
+  const RopeLane<CN / 2> rl(rope, c * (CN / 2));
 
   // ---- select
   double nc, self, my_dot = 0.0, my_norm = 0.0;
