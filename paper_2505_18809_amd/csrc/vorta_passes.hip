@@ -932,39 +932,65 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
     for (int p = 0; p < P; ++p) rl.load(rope, tok_p[p].f, tok_p[p].h, tok_p[p].w, cs[HOLD ? p : 0]);
   }
   if (ROPE) rl_pair.load(rope, centre.f, centre.h, centre.w, cs_centre);
-  auto pool = [&](const uint4 (&rows)[P], T* dst, auto rotate) {
-    T* out = dst + (long)s * n_core_rows * D + c * CN;
-    double acc[CN];
+  // NT tensors at once: K and Q share the look-ups of their rotation where those are not kept (16 heads of 75,600 tokens, buckets
+  // of 27: 396 -> 360 us, fp32 buckets of 12 9.6 -> 8.8 us for 3 heads of 3,072; where they are kept, the registers of the second
+  // sum cost a wavefront of four: buckets of 12 281 -> 316 us)
+  auto pool = [&](auto tensors, const uint4 (&rows0)[P], T* dst0, const uint4 (&rows1)[P], T* dst1, auto rotate) {
+    constexpr int NT = decltype(tensors)::value;
+    T* const out[2] = {dst0 + (long)s * n_core_rows * D + c * CN, dst1 + (long)s * n_core_rows * D + c * CN};
+    double acc[NT][CN];
 #pragma unroll
-    for (int e = 0; e < CN; ++e) acc[e] = 0.0;
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int e = 0; e < CN; ++e) acc[t][e] = 0.0;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       if (G * p + grp >= kb.size) continue;
       if (slot_p[p] == centre_slot) {
-        double x[CN];
-        Chunk<T>::widen(rows[p], x);
 #pragma unroll
-        for (int e = 0; e < CN; ++e) acc[e] += x[e];
-      } else if constexpr (rotate.value) {
-        double x[CN];
-        Chunk<T>::widen(rows[p], x);
-        if constexpr (!HOLD) rl.load(rope, tok_p[p].f, tok_p[p].h, tok_p[p].w, cs[0]);
-        rl.turn(cs[HOLD ? p : 0], x);
-        *(uint4*)(out + (long)slot_p[p] * D) = pack_chunk<T>(x);
+        for (int t = 0; t < NT; ++t) {
+          double x[CN];
+          Chunk<T>::widen(t ? rows1[p] : rows0[p], x);
+#pragma unroll
+          for (int e = 0; e < CN; ++e) acc[t][e] += x[e];
+        }
       } else {
-        *(uint4*)(out + (long)slot_p[p] * D) = rows[p];
+        if constexpr (rotate.value && !HOLD) rl.load(rope, tok_p[p].f, tok_p[p].h, tok_p[p].w, cs[0]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          uint4 row = t ? rows1[p] : rows0[p];
+          if constexpr (rotate.value) {
+            double x[CN];
+            Chunk<T>::widen(row, x);
+            rl.turn(cs[HOLD ? p : 0], x);
+            row = pack_chunk<T>(x);
+          }
+          *(uint4*)(out[t] + (long)slot_p[p] * D) = row;
+        }
       }
     }
-    double z[2];
-    Merged::sum(acc, z);
 #pragma unroll
-    for (int e = 0; e < 2; ++e) z[e] = div_by(z[e], m, r);
-    if constexpr (rotate.value) rl_pair.turn(cs_centre, z);
-    if (Merged::stores(grp)) store_pair<T>(out + (long)centre_slot * D + 2 * pair, z);
+    for (int t = 0; t < NT; ++t) {
+      double z[2];
+      Merged::sum(acc[t], z);
+#pragma unroll
+      for (int e = 0; e < 2; ++e) z[e] = div_by(z[e], m, r);
+      if constexpr (rotate.value) rl_pair.turn(cs_centre, z);
+      if (Merged::stores(grp)) store_pair<T>(out[t] + (long)centre_slot * D + 2 * pair, z);
+    }
   };
-  pool(rk, kc, std::integral_constant<bool, ROPE>());
-  pool(rq, qc, std::integral_constant<bool, ROPE>());
-  pool(rv, vc, std::integral_constant<bool, false>());
+  const std::integral_constant<int, 1> one;
+  const std::integral_constant<int, 2> two;
+  const std::integral_constant<bool, true> turned;
+  const std::integral_constant<bool, false> as_given;
+  if constexpr (ROPE && !HOLD) {
+    pool(two, rk, kc, rq, qc, turned);
+  } else {
+    const std::integral_constant<bool, ROPE> rotate;
+    pool(one, rk, kc, rk, kc, rotate);
+    pool(one, rq, qc, rq, qc, rotate);
+  }
+  pool(one, rv, vc, rv, vc, as_given);
 }
 
 // True when one of the fused instances holds the plan's buckets: 12, 16 or 32 tokens in rows of 16 chunks,
