@@ -571,8 +571,7 @@ __global__ __launch_bounds__(256) void bcs_index_kernel(const T* __restrict__ fe
   const int c = lane % CPR, grp = lane / CPR;
   const T* base = feat + hl.id[s] * head_stride + c * CN;
   const uint4 craw = Chunk<T>::raw(base + (long)bucket_token(g, k, k.centre).tok * row_stride);
-  double nc, self, my_dot = 0.0, my_norm = 0.0;
-  row_dots<T, CPR>(craw, craw, self, nc);
+  double my_dot = 0.0, my_norm = 0.0;
   // Rows of 32 chunks, two tokens a pass: four passes at a time, so that their loads go out together and their sums
   // run in each other's latency (64-token buckets of 3,072 tokens, 8 heads, 18.7 -> 15.3 us; a large grid 4 to 11 %
   // faster).  With 16 chunks the registers cost more than the latency (75,600 tokens, 94 -> 100 us).
@@ -593,6 +592,7 @@ __global__ __launch_bounds__(256) void bcs_index_kernel(const T* __restrict__ fe
     for (int u = 0; u < U; ++u) take(pass + u, raw[u]);
   }
   for (; pass * G < k.size; ++pass) take(pass, row(pass));
+  const double nc = read_lane(my_norm, k.centre);
   bool kept;
   int centre_slot;
   const int slot = rank_and_assign(k, prune, lane, similarity(my_dot, nc, my_norm), base_slot, kept, centre_slot);
@@ -894,8 +894,7 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
   const RopeLane<CN / 2> rl(rope, c * (CN / 2));
 
   // ---- select
-  double nc, self, my_dot = 0.0, my_norm = 0.0;
-  row_dots<T, CPR>(craw, craw, self, nc);
+  double my_dot = 0.0, my_norm = 0.0;
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     double dot, norm;
@@ -903,6 +902,7 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
     to_token_lane<CPR>(dot, p, lane, my_dot);
     to_token_lane<CPR>(norm, p, lane, my_norm);
   }
+  const double nc = read_lane(my_norm, kb.centre);
   bool kept;
   int centre_slot;
   const int slot_of_lane = rank_and_assign(kb, prune, lane, similarity(my_dot, nc, my_norm), base_slot, kept, centre_slot);
