@@ -834,7 +834,7 @@ static RopeRows<T> rope_rows_job(const vorta_plan* p, const RouteLists& rl, cons
 // that read K a second time as quarter rows, divided in fp64, took 64-bit integer quotients and stored
 // element by element: 397 us and 718 us.
 // ------------------------------------------------------------------------------------------
-template <typename T, int D, int P, bool ROPE>
+template <typename T, int D, int P, bool ROPE, bool APART>
 __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restrict__ q, const T* __restrict__ k,
                                                               const T* __restrict__ v, HeadList hl, Geo g, int n_buckets,
                                                               int bucket_blocks, const int* __restrict__ slot_base,
@@ -844,8 +844,11 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
                                                               Rope rope, int text_blocks, RopeRows<T> rows_job) {
   constexpr int CN = Chunk<T>::N, CPR = D / CN, G = 64 / CPR;
   const int s = blockIdx.y;
+  // APART: a wavefront of its own for K (and the index), Q and V of a bucket
+  const int z = APART ? (int)blockIdx.z : 0;
+  const bool does_k = !APART || z == 0, does_q = !APART || z == 1, does_v = !APART || z == 2;
   if (ROPE && (int)blockIdx.x >= bucket_blocks + text_blocks) {
-    const int block = ((int)blockIdx.x - bucket_blocks - text_blocks) * gridDim.y + s;
+    const int block = (((int)blockIdx.x - bucket_blocks - text_blocks) * (APART ? 3 : 1) + z) * gridDim.y + s;
     if (block < rows_job.blocks * rows_job.tensors) rope_rows_block(rows_job, rope, block);
     return;
   }
@@ -855,9 +858,9 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
     const int t = i / CPR, c = i % CPR;
     if (t >= g.N - g.L) return;
     const long from = head_off + (long)(g.L + t) * row_stride + c * CN, to = ((long)s * n_core_rows + Lc + t) * D + c * CN;
-    *(uint4*)(qc + to) = Chunk<T>::raw(q + from);
-    *(uint4*)(kc + to) = Chunk<T>::raw(k + from);
-    *(uint4*)(vc + to) = Chunk<T>::raw(v + from);
+    if (does_q) *(uint4*)(qc + to) = Chunk<T>::raw(q + from);
+    if (does_k) *(uint4*)(kc + to) = Chunk<T>::raw(k + from);
+    if (does_v) *(uint4*)(vc + to) = Chunk<T>::raw(v + from);
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -885,10 +888,19 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
   }
 #pragma unroll
   for (int p = 0; p < P; ++p) rk[p] = Chunk<T>::raw(k + off[p]);
+  if constexpr (APART) {           // the one tensor that is pooled here, in rq's place
+    if (does_q)
 #pragma unroll
-  for (int p = 0; p < P; ++p) rq[p] = Chunk<T>::raw((const T*)(q_now + off[p]));
+      for (int p = 0; p < P; ++p) rq[p] = Chunk<T>::raw((const T*)(q_now + off[p]));
+    if (does_v)
 #pragma unroll
-  for (int p = 0; p < P; ++p) rv[p] = Chunk<T>::raw((const T*)(v_now + off[p]));
+      for (int p = 0; p < P; ++p) rq[p] = Chunk<T>::raw((const T*)(v_now + off[p]));
+  } else {
+#pragma unroll
+    for (int p = 0; p < P; ++p) rq[p] = Chunk<T>::raw((const T*)(q_now + off[p]));
+#pragma unroll
+    for (int p = 0; p < P; ++p) rv[p] = Chunk<T>::raw((const T*)(v_now + off[p]));
+  }
   const int base_slot = slot_base[b], prune = kb.size - (slot_base[b + 1] - base_slot);
   if constexpr (ROPE) __builtin_amdgcn_sched_barrier(0);
   const RopeLane<CN / 2> rl(rope, c * (CN / 2));
@@ -906,7 +918,7 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
   bool kept;
   int centre_slot;
   const int slot_of_lane = rank_and_assign(kb, prune, lane, similarity(my_dot, nc, my_norm), base_slot, kept, centre_slot);
-  if (lane < kb.size) {
+  if (does_k && lane < kb.size) {
     const int tok = bucket_token(g, kb, lane).tok;
     if (kept) keep_idx[(long)s * Lc + slot_of_lane] = tok;
     assign[(long)s * g.L + tok] = slot_of_lane;
@@ -983,6 +995,13 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
   const std::integral_constant<int, 2> two;
   const std::integral_constant<bool, true> turned;
   const std::integral_constant<bool, false> as_given;
+  if constexpr (APART) {
+    const std::integral_constant<bool, ROPE> rotate;
+    if (does_k) pool(one, rk, kc, rk, kc, rotate);
+    if (does_q) pool(one, rq, qc, rq, qc, rotate);
+    if (does_v) pool(one, rq, vc, rq, vc, as_given);
+    return;
+  }
   if constexpr (ROPE && !HOLD) {
     pool(two, rk, kc, rq, qc, turned);
   } else {
@@ -1015,23 +1034,31 @@ int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, c
   const Geo g = make_geo(p);
   const int rows = (int)(p->Lc + p->d.n_text), fused = fused_tokens(p);
   int turn_blocks = 0;                       // workgroups along x of the rotation
+  // A wavefront for each tensor (APART) while those are no more than the SIMDs, one for all three beyond: the three rank the
+  // bucket each, so what is saved is time only while SIMDs are idle.  32 to 341 (bucket, head) pairs on 256 CUs: 1.13 to 1.2 times
+  // as fast (buckets of 12 of one head of 256 tokens 5.4 -> 4.5 us), 384 to 576 level or up to 4 % slower, 768 9 % slower.  Rotated
+  // buckets of more than 16 tokens, which look the rotation up pass by pass, gain up to 576 (504: 12.6 -> 10.6 us) and not at 600.
+  const long pairs = (long)p->n_buckets * rl.count[2];
+  const int apart = pairs <= (p->rope && fused > 16 ? 9L * p->n_cus / 4 : 4L * p->n_cus / 3) ? 3 : 1;
   const Rope rope = make_rope(p);
   hipStream_t st = (hipStream_t)stream;
-#define VORTA_FUSED(T_, D_, P_, R_)                                                                                     \
+#define VORTA_FUSED(T_, D_, P_, R_, A_)                                                                                     \
   {                                                                                                                     \
     RopeRows<T_> job;                                                                                                   \
     std::memset(&job, 0, sizeof(job));                                                                                  \
     if (R_ && copies) {                                                                                                 \
       job = rope_rows_job<T_>(p, rl, *copies);                                                                          \
-      turn_blocks = (job.blocks * job.tensors + rl.count[2] - 1) / rl.count[2];                                         \
+      turn_blocks = (job.blocks * job.tensors + rl.count[2] * apart - 1) / (rl.count[2] * apart);                       \
     }                                                                                                                   \
-    hipLaunchKernelGGL((bcs_select_pool_kernel<T_, D_, P_, R_>), dim3(bucket_blocks + text_blocks + turn_blocks, rl.count[2]), \
+    hipLaunchKernelGGL((bcs_select_pool_kernel<T_, D_, P_, R_, A_>), dim3(bucket_blocks + text_blocks + turn_blocks, rl.count[2], apart), \
                        dim3(256), 0, st, (const T_*)q, (const T_*)k, (const T_*)v, hl, g, p->n_buckets, bucket_blocks,  \
                        p->d_slot_base, ut.head_stride, ut.row_stride, (int)p->Lc, rows, keep_idx, assign, (T_*)qc,      \
                        (T_*)kc, (T_*)vc, rope, text_blocks, job);                                                       \
   }
 #define VORTA_FUSED_R(T_, D_, P_) \
-  if (p->rope) VORTA_FUSED(T_, D_, P_, true) else VORTA_FUSED(T_, D_, P_, false)
+  if (p->rope) VORTA_FUSED_A(T_, D_, P_, true) else VORTA_FUSED_A(T_, D_, P_, false)
+#define VORTA_FUSED_A(T_, D_, P_, R_) \
+  { if (apart > 1) VORTA_FUSED(T_, D_, P_, R_, true) else VORTA_FUSED(T_, D_, P_, R_, false) }
   if (p->d.dtype == VORTA_BF16) {
     if (fused == 12) { VORTA_FUSED_R(uint16_t, 128, 3); }
     else if (fused == 16) { VORTA_FUSED_R(uint16_t, 128, 4); }
@@ -1045,6 +1072,7 @@ int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, c
     else { VORTA_FUSED_R(float, 128, 8); }
   }
 #undef VORTA_FUSED_R
+#undef VORTA_FUSED_A
 #undef VORTA_FUSED
   return launch_status("bcs_select_pool_kernel");
 }

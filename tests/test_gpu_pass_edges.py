@@ -41,6 +41,25 @@ def test_one_pass_selection_at_the_edges_of_its_instances(bucket, dtype, d, rope
         assert torch.equal(v_c[slot, plan.n_core:], (v[h] if layout == 1 else v[:, h])[cfg.n_video:])
 
 
+@pytest.mark.parametrize("rope", [False, True])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("fp32", 64), ("fp32", 128)])
+@pytest.mark.parametrize("bucket,heads", [((2, 3, 2), 4), ((2, 3, 2), 5), ((4, 2, 2), 5), ((3, 3, 3), 9), ((3, 3, 3), 10), ((3, 3, 3), 16), ((3, 3, 3), 17)])
+def test_one_pass_selection_with_a_wavefront_a_tensor_and_with_one_for_all(bucket, heads, dtype, d, rope):
+    """72 or 36 buckets a head: 288 and 360, 324, 360, 576 and 612 (bucket, head) pairs, on either side of where (256 CUs) the
+    pass gives each tensor a wavefront, with and without a rotation."""
+    dims = ((44, 42, 42) if d == 128 else (16, 24, 24)) if rope else None
+    cfg = LayerConfig("pairs", (5, 18, 7), heads, d, dtype, (1, 1, 1), (1, 1, 1), seed=77, n_text=19, fixed_routes=(2,) * heads,
+                      bucket=bucket, keep_num=2, keep_den=3, rope_dims=dims)
+    print(bucket, heads, dtype, d, rope, flush=True)
+    q, k, v = make_qkv(cfg, DEV, 0)
+    plan = vorta.plan_for(cfg, layout=0)
+    keep_idx, assign, q_c, k_c, v_c = vorta.vorta_bcs_select_pool(plan, q, k, v, cfg.fixed_routes)
+    ki, asg = vorta.vorta_bcs_build_index(plan, k, cfg.fixed_routes)
+    assert torch.equal(keep_idx, ki) and torch.equal(assign, asg)
+    for name, got, src, turn in (("q", q_c, q, True), ("k", k_c, k, True), ("v", v_c, v, False)):
+        assert torch.equal(got, vorta.vorta_bcs_pool(plan, src, cfg.fixed_routes, ki, asg, rotate=turn)), name
+
+
 @pytest.mark.parametrize("dims", [(44, 42, 42), (44, 42, 40), (2, 0, 126), (0, 64, 62), (0, 2, 0)])
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 def test_rotation_with_spans_that_cover_the_head_and_that_do_not(dims, dtype):
