@@ -34,7 +34,7 @@
 // Measured (attention launch and whole layer; the vector-ALU kernel before it in brackets): eight dense
 // heads of 3,072 tokens x 128 run at 57 TFLOP/s, 73 % of the matrix instruction's rate, without the
 // exponentials at 59; the 3,072-token layer with 2 full, 3 window and 3 core-set heads 440 us
-// [1,701 us], two heads of 256 tokens x 64 17 us [140 us, four of its launches reorder passes].
+// [1,701 us], two heads of 256 tokens x 64 16 us [140 us, four of its launches reorder passes].
 #include <hip/hip_runtime.h>
 
 #include "vorta_attn_common.h"
@@ -257,7 +257,7 @@ int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_i
   // NW = 4 lets two workgroups share a CU.  With no more items than CUs the second one is missing and
   // eight wavefronts hide more of the latency, if the key stream is long enough to pay for
   // the longer merge: one head of 2,048 / 3,072 keys 93 -> 88 / 140 -> 129 us, of 770 keys level,
-  // two of 256 keys 22.2 -> 23.3 us.  With more items than CUs NW = 8 costs 8 % (fp32 layer of 3,072 tokens).
+  // two of 256 keys 22.2 -> 23.3 us (fewer than 600 rows 1 to 10 % longer, more than 900 0 to 5 % shorter).  With more items than CUs NW = 8 costs 8 % (fp32 layer of 3,072 tokens).
   const bool few = a.end_tile <= p->n_cus && a.N >= 1024;
   if (p->d.head_dim == 64) {
     if (few) hipLaunchKernelGGL((attn_f32_kernel<64, 8>), grid, dim3(512), 0, st, a);

@@ -468,7 +468,8 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
 // The merged row of a bucket, from every lane's sums over the tokens it has seen (chunk c of its group's tokens): the
 // groups' sums are added so that each group is left with one channel pair of the chunk, which it divides, turns and
 // stores: 18 instead of 112 instructions for eight channels over four groups, and a quarter of the rest.  (Every group
-// with the whole sums, one of them storing: selection of 16 heads of 75,600 tokens 265 -> 253 us, with rotation 326 -> 285.)
+// with the whole sums, one of them storing: selection of 16 heads of 75,600 tokens 265 -> 253 us, with rotation 326 -> 285
+// at that time.)
 template <typename T, int CPR>
 struct MergedRow {
   static constexpr int PAIRS = Chunk<T>::N / 2, G = 64 / CPR;
@@ -497,10 +498,11 @@ template <> __device__ __forceinline__ void store_pair<float>(float* to, const d
   *(float2*)to = make_float2((float)z[0], (float)z[1]);
 }
 
-// ---- shared by the index pass, the pool pass and the two in one.  One wavefront per (bucket, head).  A
-// row is CPR 16-byte chunks (16 or 32) and lies across CPR lanes, lane (c = lane % CPR, group =
-// lane / CPR) holding chunk c of token G pass + group (G = 64 / CPR tokens a pass): every load and store
-// instruction moves whole rows, and index and pool read the bucket in the same form.
+// ---- shared by the index pass, the pool pass and the two in one.  One wavefront per (bucket, head), or three
+// where the one-pass kernel has few of them (its template parameter APART).  A row is CPR 16-byte chunks (16 or
+// 32) and lies across CPR lanes, lane (c = lane % CPR, group = lane / CPR) holding chunk c of token G pass + group
+// (G = 64 / CPR tokens a pass): every load and store instruction moves whole rows, and index and pool read the bucket
+// in the same form.
 
 // Dot product with the centre row (chunk craw) and squared norm of the row whose chunk is xraw, summed over
 // the row's lanes.  fp64; a product of two bf16 (or fp32) values is exact in it, so forming
@@ -820,7 +822,8 @@ static RopeRows<T> rope_rows_job(const vorta_plan* p, const RouteLists& rl, cons
 }
 
 // ------------------------------------------------------------------------------------------
-// Select and pool in one pass (what the layer call runs): one wavefront per (bucket, head) requests the
+// Select and pool in one pass (what the layer call runs): one wavefront per (bucket, head), where there are few of
+// them one for each of its three tensors, requests the
 // bucket's K, Q and V rows before it computes anything, P passes of G tokens each, so one memory round
 // trip covers them all and every row comes from HBM once; then it ranks as bcs_index_kernel does, writes
 // keep_idx / assign, and merges and stores the three tensors as bcs_pool_kernel does (same operations in
@@ -829,8 +832,8 @@ static RopeRows<T> rope_rows_job(const vorta_plan* p, const RouteLists& rl, cons
 // routes 0 and 1 where the layer call asks for that too (a launch of its own costs a small layer 4 us).
 //
 // Bound: HBM.  On 16 heads of 75,600 tokens (1.40 GB with the index) 253 us = 5.5 TB/s, more than a large copy
-// reaches (4.9); with the rotary embedding 285 us, bound by vector instructions (the fp64 turn of every pooled Q and K
-// row and its look-ups).  Buckets of 27 tokens with 2/3 of them kept (1.57 GB) 290 us = 5.4 TB/s.  An earlier form
+// reaches (4.9); with the rotary embedding 281 us, bound by vector instructions (the fp64 turn of every pooled Q and K
+// row and its look-ups).  Buckets of 27 tokens with 2/3 of them kept (1.57 GB) 290 us = 5.4 TB/s, with rotation 360.  An earlier form
 // that read K a second time as quarter rows, divided in fp64, took 64-bit integer quotients and stored
 // element by element: 397 us and 718 us.
 // ------------------------------------------------------------------------------------------
