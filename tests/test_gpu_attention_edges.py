@@ -166,6 +166,16 @@ def test_core_set_rows_written_to_their_tokens_equal_the_staged_unpool(grid, buc
     assert torch.equal(out, staged)
 
 
+@pytest.mark.parametrize("grid,bucket,keep,heads,d,n_text", [
+    ((3, 17, 7), (1, 17, 1), (1, 3), 3, 128, 3),     # 17 tokens a bucket: one more than a turn of the look-ups
+    ((3, 16, 7), (1, 16, 1), (1, 8), 2, 64, 0),      # exactly a turn, nearly all merged
+    ((9, 12, 14), (3, 3, 3), (2, 3), 1, 64, 0),      # eight wavefronts and four pieces of a row
+    ((9, 12, 14), (3, 3, 3), (1, 3), 1, 128, 19),    # eight wavefronts and eight pieces
+])
+def test_fp32_core_set_rows_of_pieces_from_all_wavefronts(grid, bucket, keep, heads, d, n_text):
+    test_core_set_rows_written_to_their_tokens_equal_the_staged_unpool(grid, bucket, keep, heads, "fp32", d, n_text, 1)
+
+
 @pytest.mark.parametrize("n_text,layout,halves", [(0, 1, 0), (0, 1, 128), (77, 0, 131)])
 def test_long_and_window_items_in_one_launch(n_text, layout, halves):
     """A layer large enough for 256-row items on every route: window items follow the long ones in one launch, the last
