@@ -266,7 +266,8 @@ int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_i
   // NW = 4 lets two workgroups share a CU.  With no more items than CUs the second one is missing and
   // eight wavefronts hide more of the latency, if the key stream is long enough to pay for
   // the longer merge: one head of 2,048 / 3,072 keys 93 -> 88 / 140 -> 129 us, of 770 keys level,
-  // two of 256 keys 22.2 -> 23.3 us (fewer than 600 rows 1 to 10 % longer, more than 900 0 to 5 % shorter).  With more items than CUs NW = 8 costs 8 % (fp32 layer of 3,072 tokens).
+  // two of 256 keys 22.2 -> 23.3 us (fewer than 600 rows 1 to 10 % longer, more than 900 0 to 5 % shorter; all with
+  // the merge in a tree).  With more items than CUs NW = 8 costs 8 % (fp32 layer of 3,072 tokens).
   const bool few = a.end_tile <= p->n_cus && a.N >= 1024;
   if (p->d.head_dim == 64) {
     if (few) hipLaunchKernelGGL((attn_f32_kernel<64, 8>), grid, dim3(512), 0, st, a);
