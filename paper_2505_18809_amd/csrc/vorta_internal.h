@@ -77,9 +77,9 @@ struct vorta_plan {
 namespace vorta {
 
 // Head ids as kernels take them: four to a word.  A byte at a computed index is a vector load from the arguments, ahead of every
-// address that depends on it; a word is a scalar one.
+// address that depends on it; a word is a scalar one.  Cleared from the start: set() reads the word that it puts an id into.
 struct HeadIds {
-  uint32_t word[VORTA_MAX_HEADS / 4];
+  uint32_t word[VORTA_MAX_HEADS / 4] = {};
   constexpr int operator[](int i) const { return (int)(word[i >> 2] >> (8 * (i & 3)) & 255u); }
   constexpr void set(int i, int id) {
     const uint32_t at = 8u * (uint32_t)(i & 3);

@@ -1047,8 +1047,7 @@ int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, c
   hipStream_t st = (hipStream_t)stream;
 #define VORTA_FUSED(T_, D_, P_, R_, A_)                                                                                     \
   {                                                                                                                     \
-    RopeRows<T_> job;                                                                                                   \
-    std::memset(&job, 0, sizeof(job));                                                                                  \
+    RopeRows<T_> job{};                                                                                                 \
     if (R_ && copies) {                                                                                                 \
       job = rope_rows_job<T_>(p, rl, *copies);                                                                          \
       turn_blocks = (job.blocks * job.tensors + rl.count[2] * apart - 1) / (rl.count[2] * apart);                       \

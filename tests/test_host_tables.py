@@ -367,6 +367,36 @@ def test_host_code_under_address_and_undefined_behaviour_sanitizers(tmp_path):
     assert "host entry points clean" in run.stdout
 
 
+def test_head_ids_are_whole_words_from_the_start(tmp_path):
+    """An id is put into its word among others, so the word is read first: a constant expression may read no indeterminate
+    value, so this compiles only if the words of a new list are cleared."""
+    import shutil
+    import subprocess
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host compiler")
+    source = tmp_path / "head_ids.cpp"
+    source.write_text("""#include "vorta_internal.h"
+        constexpr vorta::HeadIds ids() {
+          vorta::HeadIds h;
+          for (int i = 0; i < VORTA_MAX_HEADS; i += 3) h.set(i, 255 - i);
+          h.set(3, 7);
+          return h;
+        }
+        constexpr bool right() {
+          const vorta::HeadIds h = ids();
+          for (int i = 0; i < VORTA_MAX_HEADS; ++i)
+            if (h[i] != (i == 3 ? 7 : i % 3 ? 0 : 255 - i)) return false;
+          return true;
+        }
+        static_assert(right());
+    """)
+    cmd = [gxx, "-std=c++17", "-fsyntax-only", "-I", os.path.join(ROOT, "include"),
+           "-I", os.path.join(ROOT, "paper_2505_18809_amd", "csrc"), str(source)]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-3000:]
+
+
 def test_a_plan_that_does_not_fit_in_memory_is_an_error_code():
     """Nothing is thrown through the C ABI: with the address space used up, creating a plan of two million
     one-token tiles returns an error (in a process of its own: the limit stays)."""
