@@ -837,6 +837,7 @@ static RopeRows<T> rope_rows_job(const vorta_plan* p, const RouteLists& rl, cons
 // that read K a second time as quarter rows, divided in fp64, took 64-bit integer quotients and stored
 // element by element: 397 us and 718 us.
 // ------------------------------------------------------------------------------------------
+constexpr int HOLD_PASSES = 4;     // up to so many passes the rotation of a bucket's tokens fits in registers
 template <typename T, int D, int P, bool ROPE, bool APART>
 __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restrict__ q, const T* __restrict__ k,
                                                               const T* __restrict__ v, HeadList hl, Geo g, int n_buckets,
@@ -937,7 +938,7 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
     asm volatile("" : "+v"(rk[p].x), "+v"(rk[p].y), "+v"(rk[p].z), "+v"(rk[p].w));
   }
   // rotation of the bucket's tokens, looked up once for K and Q where it fits in registers
-  constexpr bool HOLD = ROPE && P <= 4;
+  constexpr bool HOLD = ROPE && P <= HOLD_PASSES;
   float2 cs[HOLD ? P : 1][CN / 2], cs_centre[1];
   using Merged = MergedRow<T, CPR>;
   const int pair = Merged::pair_of(grp);
@@ -1024,6 +1025,28 @@ static int fused_tokens(const vorta_plan* p) {
 }
 bool bcs_fused_applies(const vorta_plan* p) { return fused_tokens(p) > 0; }
 
+// How the launch of the selection in one pass is cut.
+struct SelectForm {
+  bool apart;                       // a wavefront for each tensor of a bucket, not one for all three
+  int bucket_blocks, text_blocks;   // workgroups of a head
+};
+
+// A wavefront for each tensor (APART) while those are no more than the SIMDs, one for all three beyond: the three rank the
+// bucket each, so what is saved is time only while SIMDs are idle.  256 CUs, 64 to 336 (bucket, head) pairs: 1.07 to 1.19 times as
+// fast (buckets of 12 of one head of 256 tokens 5.4 -> 4.5 us), 400 to 640 level or up to 4 % slower, 768 9 to 15 % slower.
+// Rotated rows in more than four passes, which look the rotation up pass by pass (HOLD is false), gain up to 512 pairs (400 to 512:
+// buckets of 27 tokens 13.3 -> 11.6 us, 12 and 16 tokens in fp32 rows of 128 channels 9.0 -> 8.3 and 11.0 -> 10.0), are level up to
+// 576 and slower from 600.
+static SelectForm select_form(const vorta_plan* p, const RouteLists& rl, int units) {
+  SelectForm f;
+  f.bucket_blocks = (p->n_buckets + 3) / 4;
+  f.text_blocks = (int)((((long)p->d.n_text << chunk_shift(p)) + 255) / 256);
+  const int passes = (fused_tokens(p) << chunk_shift(p)) / 64;
+  const long pairs = (long)p->n_buckets * rl.count[2];
+  f.apart = pairs <= (p->rope && passes > HOLD_PASSES ? 9L * units / 4 : 4L * units / 3);
+  return f;
+}
+
 // Index on K, then Q, K, V pooled (Q and K rotated if the plan has a rotary embedding) into
 // qc, kc, vc, and the text rows copied behind them.
 int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, const void* k, const void* v,
@@ -1031,18 +1054,12 @@ int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, c
                            void* stream) {
   if (rl.count[2] == 0) return VORTA_OK;
   const UserTensor ut = user_tensor(p, k);
-  const int bucket_blocks = (p->n_buckets + 3) / 4;
-  const int text_blocks = (int)((((long)p->d.n_text << chunk_shift(p)) + 255) / 256);
+  const SelectForm f = select_form(p, rl, p->n_cus);
+  const int bucket_blocks = f.bucket_blocks, text_blocks = f.text_blocks, apart = f.apart ? 3 : 1;
   const HeadList hl = head_list(rl, 2);
   const Geo g = make_geo(p);
   const int rows = (int)(p->Lc + p->d.n_text), fused = fused_tokens(p);
   int turn_blocks = 0;                       // workgroups along x of the rotation
-  // A wavefront for each tensor (APART) while those are no more than the SIMDs, one for all three beyond: the three rank the
-  // bucket each, so what is saved is time only while SIMDs are idle.  32 to 341 (bucket, head) pairs on 256 CUs: 1.13 to 1.2 times
-  // as fast (buckets of 12 of one head of 256 tokens 5.4 -> 4.5 us), 384 to 576 level or up to 4 % slower, 768 9 % slower.  Rotated
-  // buckets of more than 16 tokens, which look the rotation up pass by pass, gain up to 576 (504: 12.6 -> 10.6 us) and not at 600.
-  const long pairs = (long)p->n_buckets * rl.count[2];
-  const int apart = pairs <= (p->rope && fused > 16 ? 9L * p->n_cus / 4 : 4L * p->n_cus / 3) ? 3 : 1;
   const Rope rope = make_rope(p);
   hipStream_t st = (hipStream_t)stream;
 #define VORTA_FUSED(T_, D_, P_, R_, A_)                                                                                     \
@@ -1184,3 +1201,14 @@ int launch_blend3(vorta_plan* p, const void* o0, const void* o1, const void* o2,
 }
 
 }  // namespace vorta
+
+// For the tests, not part of the ABI: how vorta_bcs_select_pool is cut with these routes on a device of `units` CUs:
+// {apart, bucket_blocks, text_blocks}, all 0 where no instance of the one-pass kernel holds the plan's buckets.
+extern "C" int vorta_test_select_form(const vorta_plan* p, const uint8_t* routes_host, int32_t units, int32_t out[3]) {
+  using namespace vorta;
+  RouteLists rl;
+  if (int rc = split_routes(p, routes_host, &rl)) return rc;
+  const SelectForm f = bcs_fused_applies(p) ? select_form(p, rl, units) : SelectForm{};
+  out[0] = f.apart; out[1] = f.bucket_blocks; out[2] = f.text_blocks;
+  return VORTA_OK;
+}

@@ -71,3 +71,12 @@ def window_list(plan, which):
     out = np.empty((n.value, 16), dtype=np.int32)
     assert lib.vorta_test_window_list(plan.handle, ctypes.c_int32(which), out.ctypes.data_as(ctypes.c_void_p), ctypes.byref(n)) == 0
     return out
+
+
+def select_form(plan, routes, units=256):
+    """How the one-pass selection is cut; False where the plan's buckets are selected and pooled in separate passes."""
+    r = np.ascontiguousarray(routes, dtype=np.uint8)
+    out = np.zeros(3, dtype=np.int32)
+    assert vorta.load_library().vorta_test_select_form(plan.handle, r.ctypes.data_as(ctypes.c_void_p), ctypes.c_int32(units),
+                                                       out.ctypes.data_as(ctypes.c_void_p)) == 0
+    return dict(zip(("apart", "bucket_blocks", "text_blocks"), map(int, out))) if out[1] else False
