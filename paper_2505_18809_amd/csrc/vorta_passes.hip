@@ -805,6 +805,8 @@ __device__ __forceinline__ void rope_rows_block(const RopeRows<T>& job, const Ro
   }
 }
 
+static int rope_rows_blocks(const vorta_plan* p) { return (int)((((long)p->N << chunk_shift(p)) + 255) / 256); }
+
 template <typename T>
 static RopeRows<T> rope_rows_job(const vorta_plan* p, const RouteLists& rl, const RopeCopies& r) {
   RopeRows<T> job;
@@ -816,7 +818,7 @@ static RopeRows<T> rope_rows_job(const vorta_plan* p, const RouteLists& rl, cons
   const UserTensor ut = user_tensor(p, r.src[0]);
   job.L = (int)p->L; job.N = (int)p->N; job.cshift = chunk_shift(p);
   job.head_stride = ut.head_stride; job.row_stride = ut.row_stride;
-  job.blocks = (int)((((long)p->N << job.cshift) + 255) / 256);
+  job.blocks = rope_rows_blocks(p);
   job.tensors = r.src[1] ? 2 : 1;
   return job;
 }
@@ -847,24 +849,39 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
                                                               T* __restrict__ qc, T* __restrict__ kc, T* __restrict__ vc,
                                                               Rope rope, int text_blocks, RopeRows<T> rows_job) {
   constexpr int CN = Chunk<T>::N, CPR = D / CN, G = 64 / CPR;
-  const int s = blockIdx.y;
-  // APART: a wavefront of its own for K (and the index), Q and V of a bucket
+  // A head's workgroups: its buckets, its text rows, its share of the rotation.  APART: planes 0, 1 and 2 of the grid are the
+  // buckets' K (and the index), Q and V, and the other workgroups of the launch fill planes behind them.  (Behind each of the
+  // three, where they let Q's and V's start late: 1 core-set head of 4,096 tokens, 16 to a bucket, with 2 heads turned 11.0 us,
+  // one wavefront for all three 9.4, now 8.4.)
   const int z = APART ? (int)blockIdx.z : 0;
   const bool does_k = !APART || z == 0, does_q = !APART || z == 1, does_v = !APART || z == 2;
-  if (ROPE && (int)blockIdx.x >= bucket_blocks + text_blocks) {
-    const int block = (((int)blockIdx.x - bucket_blocks - text_blocks) * (APART ? 3 : 1) + z) * gridDim.y + s;
+  int s = blockIdx.y, x = blockIdx.x;              // x: place among the head's workgroups
+  if constexpr (APART) {
+    if (z >= 3) {
+      const int other = ((z - 3) * (int)gridDim.y + s) * (int)gridDim.x + x, turn = other - text_blocks * (int)gridDim.y;
+      if (turn >= 0) {
+        if constexpr (ROPE)
+          if (turn < rows_job.blocks * rows_job.tensors) rope_rows_block(rows_job, rope, turn);
+        return;
+      }
+      s = other / text_blocks;
+      x = bucket_blocks + other - s * text_blocks;
+    }
+  }
+  if (ROPE && !APART && x >= bucket_blocks + text_blocks) {
+    const int block = (x - bucket_blocks - text_blocks) * gridDim.y + s;
     if (block < rows_job.blocks * rows_job.tensors) rope_rows_block(rows_job, rope, block);
     return;
   }
   const long head_off = hl.id[s] * head_stride;
-  if ((int)blockIdx.x >= bucket_blocks) {          // text rows
-    const int i = ((int)blockIdx.x - bucket_blocks) * 256 + threadIdx.x;
+  if (x >= bucket_blocks) {          // text rows
+    const int i = (x - bucket_blocks) * 256 + threadIdx.x;
     const int t = i / CPR, c = i % CPR;
     if (t >= g.N - g.L) return;
     const long from = head_off + (long)(g.L + t) * row_stride + c * CN, to = ((long)s * n_core_rows + Lc + t) * D + c * CN;
-    if (does_q) *(uint4*)(qc + to) = Chunk<T>::raw(q + from);
-    if (does_k) *(uint4*)(kc + to) = Chunk<T>::raw(k + from);
-    if (does_v) *(uint4*)(vc + to) = Chunk<T>::raw(v + from);
+    *(uint4*)(qc + to) = Chunk<T>::raw(q + from);
+    *(uint4*)(kc + to) = Chunk<T>::raw(k + from);
+    *(uint4*)(vc + to) = Chunk<T>::raw(v + from);
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -1029,6 +1046,7 @@ bool bcs_fused_applies(const vorta_plan* p) { return fused_tokens(p) > 0; }
 struct SelectForm {
   bool apart;                       // a wavefront for each tensor of a bucket, not one for all three
   int bucket_blocks, text_blocks;   // workgroups of a head
+  int turn_blocks;                  // workgroups of the launch that turn rows of the heads on routes 0 and 1
 };
 
 // A wavefront for each tensor (APART) while those are no more than the SIMDs, one for all three beyond: the three rank the
@@ -1037,13 +1055,24 @@ struct SelectForm {
 // Rotated rows in more than four passes, which look the rotation up pass by pass (HOLD is false), gain up to 512 pairs (400 to 512:
 // buckets of 27 tokens 13.3 -> 11.6 us, 12 and 16 tokens in fp32 rows of 128 channels 9.0 -> 8.3 and 11.0 -> 10.0), are level up to
 // 576 and slower from 600.
-static SelectForm select_form(const vorta_plan* p, const RouteLists& rl, int units) {
+// Where the launch turns rows too, the more wavefronts must not delay those: its workgroups (blocks below) are at most 4 a CU, and
+// times the heads that each of the turning ones goes through at most 24 a CU, 64 with rotated buckets in more than four passes,
+// which take longer themselves.  349 such launches of 256 to 9,216 tokens with 1 to 39 turned heads: 0.3 % over the faster form on
+// average, ten by more than 1.5 %, the worst 6 %; by the number of pairs alone, with the order of the workgroups then, 1.0 %, 45 of them slower than
+// one wavefront for all by more than 1 % and up to 20 % (1 core-set head of 3,072 tokens, 24 turned: 15.8 us, 17.6 apart).
+// tensors: that are turned, 0 = none.
+static SelectForm select_form(const vorta_plan* p, const RouteLists& rl, int tensors, int units) {
   SelectForm f;
   f.bucket_blocks = (p->n_buckets + 3) / 4;
   f.text_blocks = (int)((((long)p->d.n_text << chunk_shift(p)) + 255) / 256);
   const int passes = (fused_tokens(p) << chunk_shift(p)) / 64;
+  const bool by_pass = p->rope && passes > HOLD_PASSES;
+  f.turn_blocks = p->rope ? rope_rows_blocks(p) * tensors : 0;
   const long pairs = (long)p->n_buckets * rl.count[2];
-  f.apart = pairs <= (p->rope && passes > HOLD_PASSES ? 9L * units / 4 : 4L * units / 3);
+  const long blocks = (3L * f.bucket_blocks + f.text_blocks) * rl.count[2] + f.turn_blocks;
+  const int turned = f.turn_blocks ? rl.count[0] + rl.count[1] : 0;
+  f.apart = pairs <= (by_pass ? 9L * units / 4 : 4L * units / 3) && blocks <= 4L * units &&
+            blocks * turned <= (by_pass ? 64L : 24L) * units;
   return f;
 }
 
@@ -1054,30 +1083,27 @@ int launch_bcs_select_pool(vorta_plan* p, const RouteLists& rl, const void* q, c
                            void* stream) {
   if (rl.count[2] == 0) return VORTA_OK;
   const UserTensor ut = user_tensor(p, k);
-  const SelectForm f = select_form(p, rl, p->n_cus);
-  const int bucket_blocks = f.bucket_blocks, text_blocks = f.text_blocks, apart = f.apart ? 3 : 1;
+  const SelectForm f = select_form(p, rl, !copies ? 0 : copies->src[1] ? 2 : 1, p->n_cus);
   const HeadList hl = head_list(rl, 2);
   const Geo g = make_geo(p);
   const int rows = (int)(p->Lc + p->d.n_text), fused = fused_tokens(p);
-  int turn_blocks = 0;                       // workgroups along x of the rotation
+  const int n = rl.count[2], per_plane = f.bucket_blocks * n;
+  const dim3 grid = f.apart ? dim3(f.bucket_blocks, n, 3 + (f.text_blocks * n + f.turn_blocks + per_plane - 1) / per_plane)
+                            : dim3(f.bucket_blocks + f.text_blocks + (f.turn_blocks + n - 1) / n, n);
   const Rope rope = make_rope(p);
   hipStream_t st = (hipStream_t)stream;
-#define VORTA_FUSED(T_, D_, P_, R_, A_)                                                                                     \
+#define VORTA_FUSED(T_, D_, P_, R_, A_)                                                                                 \
   {                                                                                                                     \
     RopeRows<T_> job{};                                                                                                 \
-    if (R_ && copies) {                                                                                                 \
-      job = rope_rows_job<T_>(p, rl, *copies);                                                                          \
-      turn_blocks = (job.blocks * job.tensors + rl.count[2] * apart - 1) / (rl.count[2] * apart);                       \
-    }                                                                                                                   \
-    hipLaunchKernelGGL((bcs_select_pool_kernel<T_, D_, P_, R_, A_>), dim3(bucket_blocks + text_blocks + turn_blocks, rl.count[2], apart), \
-                       dim3(256), 0, st, (const T_*)q, (const T_*)k, (const T_*)v, hl, g, p->n_buckets, bucket_blocks,  \
-                       p->d_slot_base, ut.head_stride, ut.row_stride, (int)p->Lc, rows, keep_idx, assign, (T_*)qc,      \
-                       (T_*)kc, (T_*)vc, rope, text_blocks, job);                                                       \
+    if (R_ && copies) job = rope_rows_job<T_>(p, rl, *copies);                                                          \
+    hipLaunchKernelGGL((bcs_select_pool_kernel<T_, D_, P_, R_, A_>), grid, dim3(256), 0, st, (const T_*)q, (const T_*)k, \
+                       (const T_*)v, hl, g, p->n_buckets, f.bucket_blocks, p->d_slot_base, ut.head_stride, ut.row_stride, \
+                       (int)p->Lc, rows, keep_idx, assign, (T_*)qc, (T_*)kc, (T_*)vc, rope, f.text_blocks, job);        \
   }
 #define VORTA_FUSED_R(T_, D_, P_) \
   if (p->rope) VORTA_FUSED_A(T_, D_, P_, true) else VORTA_FUSED_A(T_, D_, P_, false)
 #define VORTA_FUSED_A(T_, D_, P_, R_) \
-  { if (apart > 1) VORTA_FUSED(T_, D_, P_, R_, true) else VORTA_FUSED(T_, D_, P_, R_, false) }
+  { if (f.apart) VORTA_FUSED(T_, D_, P_, R_, true) else VORTA_FUSED(T_, D_, P_, R_, false) }
   if (p->d.dtype == VORTA_BF16) {
     if (fused == 12) { VORTA_FUSED_R(uint16_t, 128, 3); }
     else if (fused == 16) { VORTA_FUSED_R(uint16_t, 128, 4); }
@@ -1202,13 +1228,15 @@ int launch_blend3(vorta_plan* p, const void* o0, const void* o1, const void* o2,
 
 }  // namespace vorta
 
-// For the tests, not part of the ABI: how vorta_bcs_select_pool is cut with these routes on a device of `units` CUs:
-// {apart, bucket_blocks, text_blocks}, all 0 where no instance of the one-pass kernel holds the plan's buckets.
-extern "C" int vorta_test_select_form(const vorta_plan* p, const uint8_t* routes_host, int32_t units, int32_t out[3]) {
+// For the tests, not part of the ABI: how vorta_bcs_select_pool (layer = 0) or the selection launch of a layer call is cut with these
+// routes on a device of `units` CUs: {apart, bucket_blocks, text_blocks, turn_blocks}, all 0 where no instance of the
+// one-pass kernel holds the plan's buckets.
+extern "C" int vorta_test_select_form(const vorta_plan* p, const uint8_t* routes_host, int32_t layer, int32_t units, int32_t out[4]) {
   using namespace vorta;
   RouteLists rl;
   if (int rc = split_routes(p, routes_host, &rl)) return rc;
-  const SelectForm f = bcs_fused_applies(p) ? select_form(p, rl, units) : SelectForm{};
-  out[0] = f.apart; out[1] = f.bucket_blocks; out[2] = f.text_blocks;
+  const int tensors = layer && rl.count[0] + rl.count[1] ? 2 : 0;
+  const SelectForm f = bcs_fused_applies(p) ? select_form(p, rl, tensors, units) : SelectForm{};
+  out[0] = f.apart; out[1] = f.bucket_blocks; out[2] = f.text_blocks; out[3] = f.turn_blocks;
   return VORTA_OK;
 }

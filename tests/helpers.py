@@ -73,10 +73,11 @@ def window_list(plan, which):
     return out
 
 
-def select_form(plan, routes, units=256):
-    """How the one-pass selection is cut; False where the plan's buckets are selected and pooled in separate passes."""
+def select_form(plan, routes, layer=False, units=256):
+    """How the one-pass selection is cut, called alone or in a layer call; False where the plan's buckets are selected and
+    pooled in separate passes."""
     r = np.ascontiguousarray(routes, dtype=np.uint8)
-    out = np.zeros(3, dtype=np.int32)
-    assert vorta.load_library().vorta_test_select_form(plan.handle, r.ctypes.data_as(ctypes.c_void_p), ctypes.c_int32(units),
-                                                       out.ctypes.data_as(ctypes.c_void_p)) == 0
-    return dict(zip(("apart", "bucket_blocks", "text_blocks"), map(int, out))) if out[1] else False
+    out = np.zeros(4, dtype=np.int32)
+    assert vorta.load_library().vorta_test_select_form(plan.handle, r.ctypes.data_as(ctypes.c_void_p), ctypes.c_int32(layer),
+                                                       ctypes.c_int32(units), out.ctypes.data_as(ctypes.c_void_p)) == 0
+    return dict(zip(("apart", "bucket_blocks", "text_blocks", "turn_blocks"), map(int, out))) if out[1] else False

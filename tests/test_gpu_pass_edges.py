@@ -8,7 +8,7 @@ import torch
 import paper_2505_18809_amd as vorta
 from oracle import vorta_oracle as vo
 from synth_inputs import LayerConfig, make_qkv
-from helpers import f64
+from helpers import f64, select_form
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -58,6 +58,37 @@ def test_one_pass_selection_with_a_wavefront_a_tensor_and_with_one_for_all(bucke
     assert torch.equal(keep_idx, ki) and torch.equal(assign, asg)
     for name, got, src, turn in (("q", q_c, q, True), ("k", k_c, k, True), ("v", v_c, v, False)):
         assert torch.equal(got, vorta.vorta_bcs_pool(plan, src, cfg.fixed_routes, ki, asg, rotate=turn)), name
+
+
+@pytest.mark.parametrize("grid,routes,n_text", [((4, 8, 8), (0, 1, 2), 19), ((5, 9, 7), (1, 2, 1, 0, 2, 2, 1), 3), ((4, 8, 8), (1, 2, 2, 2, 2, 2), 0),
+                                                ((3, 6, 2), (0, 1, 2), 70), ((2, 3, 2), (0, 2), 40)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("fp32", 64), ("fp32", 128)])
+@pytest.mark.parametrize("bucket", [(2, 3, 2), (4, 2, 2)])
+def test_text_rows_and_turned_rows_behind_the_planes_of_the_three_tensors(bucket, dtype, d, grid, routes, n_text):
+    """The buffers that a layer call's selection launch leaves in the workspace, against the separate passes bit for bit, where each
+    tensor of a bucket has a wavefront: text and turned rows that fill part of a plane of the grid, one, and several."""
+    dims = (44, 42, 42) if d == 128 else (16, 24, 24)
+    cfg = LayerConfig("planes", grid, len(routes), d, dtype, (1, 1, 1), (1, 1, 1), seed=91, n_text=n_text, fixed_routes=routes,
+                      bucket=bucket, keep_num=1, keep_den=2, rope_dims=dims)
+    print(bucket, dtype, d, grid, routes, n_text, flush=True)
+    q, k, v = make_qkv(cfg, DEV, 0)
+    plan = vorta.plan_for(cfg, layout=0)
+    assert select_form(plan, routes, layer=True)["apart"] == 1
+    workspace = torch.full((vorta.vorta_workspace_bytes(plan, routes),), 0xA5, dtype=torch.uint8, device=DEV)
+    vorta.vorta_routed_attention_layer(plan, q, k, v, routes, workspace=workspace)
+    off = [int(o) for o in vorta.vorta_workspace_layout(plan, routes)]
+
+    def buffer(i, like):
+        return workspace[off[i]:off[i] + like.numel() * like.element_size()].view(like.dtype).view(like.shape)
+    ki, asg = vorta.vorta_bcs_build_index(plan, k, routes)
+    assert torch.equal(buffer(8, ki), ki) and torch.equal(buffer(9, asg), asg)
+    for i, src, turn in ((4, q, True), (5, k, True), (6, v, False)):
+        want = vorta.vorta_bcs_pool(plan, src, routes, ki, asg, rotate=turn)
+        assert torch.equal(buffer(i, want), want), i
+    heads = [h for h, r in enumerate(routes) if r < 2]
+    for i, src in ((10, q), (11, k)):
+        want = vorta.vorta_rope_apply(plan, src, routes)
+        assert torch.equal(buffer(i, want)[:, heads], want[:, heads]), i
 
 
 @pytest.mark.parametrize("dims", [(44, 42, 42), (44, 42, 40), (2, 0, 126), (0, 64, 62), (0, 2, 0)])

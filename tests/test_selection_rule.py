@@ -29,6 +29,32 @@ def test_a_wavefront_for_each_tensor_up_to_so_many_pairs(bucket, dtype, d, rope,
     assert select_form(plan, (2,) * (most // 8), units=128)["apart"] == 0
 
 
+@pytest.mark.parametrize("grid,bucket,routes,rope,alone,layer", [
+    ((8, 16, 16), (2, 3, 2), (0, 8, 1), True, 1, 1),          # 400 workgroups, 8 heads turned
+    ((8, 16, 16), (2, 3, 2), (4, 20, 1), True, 1, 0),         # 24 heads: each turning workgroup is the longest of the launch
+    ((12, 16, 16), (2, 3, 2), (0, 6, 1), True, 1, 1), ((12, 16, 16), (2, 3, 2), (1, 22, 1), True, 1, 0),
+    ((12, 16, 16), (3, 3, 3), (1, 22, 1), True, 1, 1),        # the buckets take longer than 23 heads
+    ((12, 16, 16), (2, 3, 2), (1, 22, 1), False, 1, 1),       # nothing is turned
+    ((16, 16, 16), (4, 2, 2), (0, 2, 1), True, 1, 1), ((16, 16, 16), (4, 2, 2), (2, 10, 1), True, 1, 0),
+    ((16, 24, 24), (3, 3, 3), (0, 8, 1), True, 1, 0),         # 1,440 workgroups
+    ((4, 8, 8), (2, 3, 2), (0, 39, 1), True, 1, 1)])
+def test_turned_rows_in_the_same_launch_count(grid, bucket, routes, rope, alone, layer):
+    heads = sum(routes)
+    plan = plan_of(bucket, heads, rope=rope, grid=grid)
+    r = (0,) * routes[0] + (1,) * routes[1] + (2,) * routes[2]
+    one, whole = select_form(plan, r), select_form(plan, r, layer=True)
+    assert (one["apart"], whole["apart"]) == (alone, layer)
+    rows = grid[0] * grid[1] * grid[2]
+    assert one["turn_blocks"] == 0 and whole["turn_blocks"] == (2 * rows // 16 if rope else 0)
+
+
+def test_text_rows_count_and_core_set_heads_alone_turn_nothing():
+    few, many = (plan_of((2, 3, 2), 1, n_text=n) for n in (77, 20000))
+    assert select_form(few, (2,))["apart"] == 1 and select_form(few, (2,))["text_blocks"] == 5
+    assert select_form(many, (2,))["apart"] == 0
+    assert select_form(plan_of((2, 3, 2), 3, rope=True), (2, 2, 2), layer=True) == {"apart": 1, "bucket_blocks": 2, "text_blocks": 0, "turn_blocks": 0}
+
+
 def test_buckets_that_no_instance_holds_have_no_form():
     assert select_form(plan_of((3, 3, 3), 2, "fp32", 128), (2, 2)) is False
     assert select_form(plan_of((4, 3, 3), 2), (2, 2)) is False
