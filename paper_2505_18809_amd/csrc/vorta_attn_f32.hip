@@ -38,6 +38,8 @@
 // [1,701 us], two heads of 256 tokens x 64 16 us [140 us, four of its launches reorder passes].
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "vorta_attn_common.h"
 
 namespace vorta {
@@ -257,18 +259,28 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_f32_kernel(const AttnArg
   }
 }
 
+// Wavefronts of a workgroup.  Four let two workgroups share a CU; with no more items than CUs the second one is missing, and
+// eight hide more of the latency if the longest item's key stream pays for the longer merge.  340 layers of 196 to 4,056 tokens, 1 to 8
+// heads, each timed both ways: from 32 key blocks on eight are 2 to 11 % faster (3,456 keys 167 -> 135 us, 1,120 keys 56.0 -> 53.4, 588
+// keys level), with fewer 1 to 11 % slower (two heads of 256 tokens 16.9 -> 17.6 us).  They also keep a CU for themselves, where four
+// wavefronts of two items now and then meet on one CU although others are idle (3 heads of 802 tokens 45 us, 69 then).  With
+// more items than CUs four are faster by 5 to 12 % more often than not.  The choice is 0.5 to 1.2 % slower than the faster of the two on average; by
+// the number of rows (1,024 and more, as the tree of additions at the end of an item had it) it was 0.7 to 2.8 %.
+static int f32_wavefronts(const vorta_plan* p, const RouteLists& rl, const AttnArgs& a, int units) {
+  int keys = 0;
+  if (rl.count[0] || (rl.count[1] && a.n_text)) keys = a.N;
+  if (rl.count[1]) keys = std::max(keys, p->win_most_keys);
+  if (rl.count[2]) keys = std::max(keys, a.Nc);
+  return a.end_tile <= units && (keys + 15) / 16 >= 32 ? 8 : 4;
+}
+
 int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_io* io, const CoreIndex* core, void* stream) {
   AttnArgs a;
   if (int rc = fill_attn_args(p, rl, io, core, 16, WIN_ALL, &a)) return rc;
   if (a.end_tile == 0) return VORTA_OK;
   const dim3 grid(a.end_tile);
   hipStream_t st = (hipStream_t)stream;
-  // NW = 4 lets two workgroups share a CU.  With no more items than CUs the second one is missing and
-  // eight wavefronts hide more of the latency, if the key stream is long enough to pay for
-  // the longer merge: one head of 2,048 / 3,072 keys 93 -> 88 / 140 -> 129 us, of 770 keys level,
-  // two of 256 keys 22.2 -> 23.3 us (fewer than 600 rows 1 to 10 % longer, more than 900 0 to 5 % shorter; all with
-  // the merge in a tree).  With more items than CUs NW = 8 costs 8 % (fp32 layer of 3,072 tokens).
-  const bool few = a.end_tile <= p->n_cus && a.N >= 1024;
+  const bool few = f32_wavefronts(p, rl, a, p->n_cus) == 8;
   if (p->d.head_dim == 64) {
     if (few) hipLaunchKernelGGL((attn_f32_kernel<64, 8>), grid, dim3(512), 0, st, a);
     else hipLaunchKernelGGL((attn_f32_kernel<64, 4>), grid, dim3(256), 0, st, a);
@@ -282,3 +294,15 @@ int launch_attention_f32(vorta_plan* p, const RouteLists& rl, const vorta_attn_i
 }
 
 }  // namespace vorta
+
+// For the tests, not part of the ABI: wavefronts of a workgroup of an fp32 layer call with these routes on a device of `units` CUs.
+extern "C" int vorta_test_f32_wavefronts(vorta_plan* p, const uint8_t* routes_host, int32_t units, int32_t* out) {
+  using namespace vorta;
+  RouteLists rl;
+  if (int rc = split_routes(p, routes_host, &rl)) return rc;
+  AttnArgs a;
+  const vorta_attn_io io = {};
+  if (int rc = fill_attn_args(p, rl, &io, nullptr, 16, WIN_ALL, &a)) return rc;
+  *out = f32_wavefronts(p, rl, a, units);
+  return VORTA_OK;
+}

@@ -211,6 +211,9 @@ static void build_plan(vorta_plan* p) {
   for (int t = 0; t < p->n_tiles; ++t) {
     p->n_runs[t] = (int32_t)run_lists[t].size() / 2;
     std::copy(run_lists[t].begin(), run_lists[t].end(), p->runs.begin() + (size_t)t * p->max_runs * 2);
+    int keys = 0;
+    for (size_t r = 1; r < run_lists[t].size(); r += 2) keys += run_lists[t][r];
+    p->win_most_keys = std::max(p->win_most_keys, keys);
   }
 
   // Query tiles with the same box see the same keys (under the clamped centre rule the border tile and its

@@ -20,6 +20,7 @@ struct vorta_plan {
   int n_buckets = 0;
   int64_t Lc = 0;                // core-set slots
   int max_runs = 0;
+  int win_most_keys = 0;         // keys of the query tile that has most, text keys included
   int window_key_tiles = 0;
   int elem_bytes = 0;
   float scale = 0.f;

@@ -81,3 +81,12 @@ def select_form(plan, routes, layer=False, units=256):
     assert vorta.load_library().vorta_test_select_form(plan.handle, r.ctypes.data_as(ctypes.c_void_p), ctypes.c_int32(layer),
                                                        ctypes.c_int32(units), out.ctypes.data_as(ctypes.c_void_p)) == 0
     return dict(zip(("apart", "bucket_blocks", "text_blocks", "turn_blocks"), map(int, out))) if out[1] else False
+
+
+def f32_wavefronts(plan, routes, units=256):
+    """Wavefronts of a workgroup of the fp32 attention launch of a layer call."""
+    r = np.ascontiguousarray(routes, dtype=np.uint8)
+    out = ctypes.c_int32()
+    assert vorta.load_library().vorta_test_f32_wavefronts(plan.handle, r.ctypes.data_as(ctypes.c_void_p), ctypes.c_int32(units),
+                                                          ctypes.byref(out)) == 0
+    return out.value

@@ -10,7 +10,7 @@ import torch
 import paper_2505_18809_amd as vorta
 from oracle import vorta_oracle as vo
 from synth_inputs import LayerConfig, make_qkv
-from helpers import PIPE, f64, force_form, spec_of
+from helpers import PIPE, f32_wavefronts, f64, force_form, spec_of
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -54,6 +54,23 @@ def test_fp32_attention_at_the_edges_of_its_split(grid, tile, n_text, layout, d)
     say(cfg.name)
     q, k, v = make_qkv(cfg, DEV, layout)
     layer_error(cfg, q, k, v, layout, fp32_bar)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("grid,routes,n_text,wavefronts", [
+    ((1, 16, 31), (0,), 0, 4), ((1, 7, 71), (0,), 0, 8),           # 31 whole key blocks; 31 and one key
+    ((2, 16, 32), (2,), 0, 8), ((8, 9, 9), (1,), 0, 8),            # core-set rows, window items of 32 blocks and more
+    ((4, 9, 15), (1, 2), 16, 8),                                   # text rows over 35 blocks, window items of fewer blocks than wavefronts
+])
+def test_fp32_attention_on_either_side_of_its_number_of_wavefronts(grid, routes, n_text, wavefronts, d):
+    cfg = LayerConfig(f"waves{grid}d{d}", grid, len(routes), d, "fp32", (2, 3, 3) if n_text else (3, 3, 3), (1, 1, 1) if n_text else (3, 3, 3),
+                      seed=15, n_text=n_text, fixed_routes=routes, bucket=(2, 1, 1), keep_num=1, keep_den=2)
+    say(cfg.name)
+    assert f32_wavefronts(vorta.plan_for(cfg), routes) == wavefronts
+    q, k, v = make_qkv(cfg, DEV, 1)
+    # pooled rows are rounded to fp32 on their way: 2^-24 of V (up to 4.5), and of each of the 2 d factors of a score, which
+    # moves the weights by scale * 2^-24 * sqrt(2 d) * |q k| (about 1e-7 for the largest): the layer's own bar of 1e-5 holds both
+    layer_error(cfg, q, k, v, 1, (lambda want: 1e-5) if 2 in routes else fp32_bar)
 
 
 def test_fp32_row_reference_follows_scores_far_beyond_its_slack():
