@@ -41,15 +41,26 @@ def test_one_pass_selection_at_the_edges_of_its_instances(bucket, dtype, d, rope
         assert torch.equal(v_c[slot, plan.n_core:], (v[h] if layout == 1 else v[:, h])[cfg.n_video:])
 
 
+@pytest.mark.parametrize("apart", [True, False])
 @pytest.mark.parametrize("rope", [False, True])
-@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("fp32", 64), ("fp32", 128)])
-@pytest.mark.parametrize("bucket,heads", [((2, 3, 2), 4), ((2, 3, 2), 5), ((4, 2, 2), 5), ((3, 3, 3), 9), ((3, 3, 3), 10), ((3, 3, 3), 16), ((3, 3, 3), 17)])
-def test_one_pass_selection_with_a_wavefront_a_tensor_and_with_one_for_all(bucket, heads, dtype, d, rope):
-    """72 or 36 buckets a head: 288 and 360, 324, 360, 576 and 612 (bucket, head) pairs, on either side of where (256 CUs) the
-    pass gives each tensor a wavefront, with and without a rotation."""
+@pytest.mark.parametrize("bucket,dtype,d", [((2, 3, 2), "bf16", 128), ((4, 2, 2), "bf16", 128), ((3, 3, 3), "bf16", 128),
+                                            ((2, 3, 2), "fp32", 64), ((4, 2, 2), "fp32", 64), ((3, 3, 3), "fp32", 64),
+                                            ((2, 3, 2), "fp32", 128), ((4, 2, 2), "fp32", 128)])
+def test_one_pass_selection_with_a_wavefront_a_tensor_and_with_one_for_all(bucket, dtype, d, rope, apart):
+    """Every instance of the one-pass kernel in both its forms: as many heads as still give each tensor of a bucket a wavefront on
+    this device, and one more.  36 or 72 buckets a head, the last of each axis clipped."""
     dims = ((44, 42, 42) if d == 128 else (16, 24, 24)) if rope else None
-    cfg = LayerConfig("pairs", (5, 18, 7), heads, d, dtype, (1, 1, 1), (1, 1, 1), seed=77, n_text=19, fixed_routes=(2,) * heads,
-                      bucket=bucket, keep_num=2, keep_den=3, rope_dims=dims)
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+
+    def config(heads):
+        return LayerConfig("pairs", (5, 18, 7), heads, d, dtype, (1, 1, 1), (1, 1, 1), seed=77, n_text=19, fixed_routes=(2,) * heads,
+                           bucket=bucket, keep_num=2, keep_den=3, rope_dims=dims)
+
+    def form(heads):
+        return select_form(vorta.plan_for(config(heads), layout=0), (2,) * heads, units=units)["apart"] == 1
+    heads = next(h for h in range(1, 128) if form(h) and not form(h + 1)) + (not apart)
+    assert form(heads) == apart
+    cfg = config(heads)
     print(bucket, heads, dtype, d, rope, flush=True)
     q, k, v = make_qkv(cfg, DEV, 0)
     plan = vorta.plan_for(cfg, layout=0)
