@@ -194,6 +194,26 @@ def test_first_scores_of_the_split_kernel_wait_for_no_later_rows(kernels):
         assert streams == 3, (name, streams)       # consecutive rows, tokens of a window, copies
 
 
+def test_pipelined_iterations_begin_without_a_wait_for_fragments(kernels):
+    """The fragments of an iteration's first three matrix instructions are requested ahead of the barrier of the one before and have
+    arrived with it; those of the first iteration are waited for ahead of the loop.  Anything else in flight on the way into the
+    loop makes the compiler wait at its head, in every iteration."""
+    checked = 0
+    for name, (code, labels) in kernels.items():
+        if "split" in name:
+            continue
+        for i, (op, rest) in enumerate(code):
+            head = labels.get(rest.strip("<>"), i) if op.startswith(("s_branch", "s_cbranch")) else i
+            products = [k for k in range(head, i) if code[k][0].startswith("v_mfma")]
+            # two iterations of 16 or 32 matrix instructions and a barrier each: the main loop, and no span of other code around it
+            if len(products) not in (32, 64) or [op for op, _ in code[head:i]].count("s_barrier") != 2:
+                continue
+            late = [rest for op, rest in code[head:products[2]] if op == "s_waitcnt" and "lgkmcnt" in rest]
+            assert not late, (name, late)
+            checked += 1
+    assert checked >= 8, checked
+
+
 def test_window_blocks_that_outweigh_the_row_are_not_redone(kernels):
     """A block of window keys that weighs more than twice all before it has its sum taken of the rounded probabilities (v_dot2).
     Peaked scores have many such blocks: the way there from the matrix instructions of the iteration leads past the
