@@ -14,9 +14,9 @@ namespace vorta {
 //
 // Item costs are microseconds, fixed + per 64-key block, fitted to 2,098 measured layers (256 to 80,000 tokens, 1 to 40
 // heads, every route alone and mixed, with and without text, every form timed on each) with the kernels of that time: before
-// window keys were computed, and before the query rows of the split kernel came by direct loads.  With the kernels as they are
-// the form chosen for 1,260 others is 1.2 % slower than the fastest on average, 30 of them by more than 10 %, one by
-// 39 % (profiles/attention_forms.txt); most of those are window heads alone whose items fill the chip once or twice.  Costs
+// window keys were computed, query rows of the split kernel came by direct loads and arguments in one batch, and key shares were merged
+// in two barriers.  With the kernels as they are the form chosen for 1,260 others is 1.1 % slower than the fastest on average, 32 of
+// them by more than 10 %, one by 37 % (profiles/attention_forms.txt); most of those are window heads alone whose items fill the chip once or twice.  Costs
 // fitted to earlier versions of the kernels were 2.6 % off on average, 71 of 798 by more than 10 % and up to 55 %, and
 // without items of 128 rows a layer of 768 tokens, 24 window heads and 32-token tiles took 20.2 us instead of 17.1.
 // ------------------------------------------------------------------------------------------

@@ -833,6 +833,10 @@ static RopeRows<T> rope_rows_job(const vorta_plan* p, const RouteLists& rl, cons
 // head copy its text rows behind the pooled ones, and the last ones turn the rows of the heads on
 // routes 0 and 1 where the layer call asks for that too (a launch of its own costs a small layer 4 us).
 //
+// Rows of 12 tokens in bf16 without rotation take 74 vector registers, six wavefronts a SIMD (72 and seven while head ids were single bytes):
+// 3 heads of 32,760 tokens 21.6 to 22.3 us then, 22.1 to 22.7 now, 16 of 75,600 level.  32-bit offsets of the output rows bring 72 back and up to
+// 1.5 % there, but cost launches of less than 10 us 1 to 3 % and the 16-token instance a wavefront; a launch bound spills (8 to 12 % slower).
+//
 // Bound: HBM.  On 16 heads of 75,600 tokens (1.40 GB with the index) 253 us = 5.5 TB/s, more than a large copy
 // reaches (4.9); with the rotary embedding 281 us, bound by vector instructions (the fp64 turn of every pooled Q and K
 // row and its look-ups).  Buckets of 27 tokens with 2/3 of them kept (1.57 GB) 290 us = 5.4 TB/s, with rotation 360.  An earlier form
@@ -954,7 +958,8 @@ __global__ __launch_bounds__(256) void bcs_select_pool_kernel(const T* __restric
     // widen K again below instead of keeping its fp64 form in registers across the ranking
     asm volatile("" : "+v"(rk[p].x), "+v"(rk[p].y), "+v"(rk[p].z), "+v"(rk[p].w));
   }
-  // rotation of the bucket's tokens, looked up once for K and Q where it fits in registers
+  // rotation of the bucket's tokens, looked up once for K and Q where it fits in registers (V's wavefront looks it up too where it has one
+  // of its own: pooling V ahead of that is level to 3 % slower)
   constexpr bool HOLD = ROPE && P <= HOLD_PASSES;
   float2 cs[HOLD ? P : 1][CN / 2], cs_centre[1];
   using Merged = MergedRow<T, CPR>;
