@@ -101,13 +101,13 @@ struct WorkItem {
 };
 
 // The arguments that finding an item and its rows takes, read all at once.  Read where they are used they are some fifteen
-// scalar loads, each waited for before the branch that needs it, all ahead of an item's first row; with head ids in words
-// (HeadIds) small launches take 0.2 to 0.9 us less: 3 window heads of 3,072 tokens 14.2 -> 13.3 us, 8 heads on all routes 38.0 ->
-// 37.4, two fp32 heads of 256 tokens 16.9 -> 16.7; large ones are level, but for layers whose end is set by a few text rows of long
-// streams beside thousands of short window items, which start sooner and press harder on the memory that those wait for (6 window heads of
-// 61,017 tokens with 20 text rows 461 -> 477 us).  The fp32 kernels read five arguments here that they have no use for: without
-// those, and with six that they do use in their place, 21 layers of 128 to 3,072 tokens are level.  (An operand of the statement is
-// a register that holds the argument there; it emits nothing.)
+// scalar loads, each waited for before the branch that needs it, all ahead of an item's first row.  13 layers, 11 of them small: 1.7 %
+// (3 window heads of 3,072 tokens 15.3 -> 14.4 us, 4 dense ones of 1,024 13.4 -> 13.1), and head ids in words (HeadIds) another 0.5 %; two fp32
+// heads of 256 tokens 16.9 -> 16.7; large layers are level, but where a few text rows of long streams beside thousands of short window
+// items set the end: those start sooner and press harder on the memory that the streams wait for (16 window heads of 35,712 tokens with
+// 20 text rows 605 -> 621 us).  The fp32 kernels read five arguments here that they have no use for: without those, and with
+// six that they do use in their place, 21 layers of 128 to 3,072 tokens are level.  (An operand of the statement is a register that
+// holds the argument there; it emits nothing.)
 __device__ __forceinline__ void read_together(const AttnArgs& a) {
   asm volatile("" ::"s"(a.head_stride0), "s"(a.row_stride0), "s"(a.q0), "s"(a.k0), "s"(a.v0), "s"(a.qc), "s"(a.kc), "s"(a.vc), "s"(a.N),
                "s"(a.Nc), "s"(a.L), "s"(a.n_text), "s"(a.win_gather), "s"(a.win_items), "s"(a.win_row), "s"(a.win_count),
