@@ -238,8 +238,8 @@ int vorta_bcs_pool(vorta_plan* plan, const void* src, const uint8_t* routes_host
                    const int32_t* keep_idx, const int32_t* assign, int32_t rotate, void* dst, void* stream);
 
 /* vorta_bcs_build_index on K followed by vorta_bcs_pool of Q, K (rotate = 1) and V, as ONE pass
- * over the data where the plan allows it (buckets of at most 16 tokens, rows of 256 bytes: the
- * paper's (2,3,2) bucket in bf16) -- K is then read from memory once and all rows of a bucket are
+ * over the data where the plan allows it (buckets of at most 32 tokens in rows of 256 bytes, of at most 16 in
+ * rows of 512: the paper's (2,3,2) bucket among them) -- K is then read from memory once and all rows of a bucket are
  * requested together; otherwise the four separate passes.  The results are those of the separate
  * calls, bit for bit.  This is the form the layer call runs (section 3.2: selection and merging
  * are both O(L), appendix complexity paragraph). */
